@@ -5,6 +5,7 @@
 //   device_tables.hpp   extents, tensor descriptors, chunk table
 //   kernels_tensor.hpp  single-tensor kernels (quantise-and-pack, decode-and-sum, update)
 //   kernels_sparse.hpp  sparse form of a packed stream
+//   decode_tile.hpp     decode-and-sum of one tile, all workers
 //   kernels_probe.hpp   bare streaming kernel (measurement aid)
 //   kernels_fused.hpp   passes over a layer list: fused compressed pass, passes on 32-bit gradients
 //   kernels_static.hpp  tables built on the device for the entry point that allocates nothing
@@ -16,10 +17,10 @@
 // the 32-bit-word layout in cdsgd.h).  A tensor is cut into "chunks" of 1024
 // quads (4096 elements, 1 KiB of a packed stream); the chunk table of a plan
 // lists (tensor, chunk) pairs, and only a tensor's last chunk can be ragged.
-//   * The kernels over a layer list work on "pieces" of a chunk, one quad per
-//     lane: 256-lane workgroups for the compressed pass (the peers' codes
-//     come in through LDS, 128 bits per lane and 16 peers per instruction),
-//     single waves for the passes on 32-bit gradients.
+//   * The kernels over a layer list work on parts of a chunk, one quad per
+//     lane: "tiles" of 256 lanes for the compressed pass (the peers' codes are
+//     decoded word by word, decode_tile.hpp), "pieces" of one wave for the
+//     passes on 32-bit gradients.
 //   * Of the single-tensor kernels, decode-and-sum gives a chunk to a
 //     workgroup of kBlock lanes, lane `tid` taking quads j*kBlock + tid;
 //     quantise-and-pack and the update work in single-wave pieces.
@@ -46,6 +47,7 @@
 #include "device_tables.hpp"
 #include "kernels_tensor.hpp"
 #include "kernels_sparse.hpp"
+#include "decode_tile.hpp"
 #include "kernels_probe.hpp"
 #include "kernels_fused.hpp"
 #include "kernels_static.hpp"
@@ -68,8 +70,7 @@ namespace {
 //   quantise-and-pack               6.71 / 6.72 / - / 6.83 / - / 6.88 / 6.09 / 5.10
 //   update, both rules              6.36 / 6.34 / - / 6.55 / - / 6.50 / 6.55 / 6.18
 //   correction pass, sum in kernel  6.19 / 6.39-6.41 / 6.35 / 6.24 / - / 5.97
-// eq. 11 alone and the compressed pass (whose workgroups already hold 4-16 KiB of staged codes) lose with
-// any bound and get none.  The same bound stated to the compiler instead (amdgpu_waves_per_eu with a maximum of
+// eq. 11 alone loses with any bound and gets none; the compressed pass has a rule of its own (compressed_launch).  The same bound stated to the compiler instead (amdgpu_waves_per_eu with a maximum of
 // 5) gives 6.55 and 6.45 TB/s on the first and the third line: most of the gain, not all of it.  While a
 // pass launched this way runs it holds the compute units' LDS, so a kernel of another stream that needs
 // LDS waits for it; a pass with a workgroup limit (cdsgd_plan_set_max_workgroups), which is meant to run
@@ -150,6 +151,9 @@ inline bool is_pow2_threshold(float t)
     return m == 0.5f && e > -100 && e < 100;
 }
 
+// A threshold whose half may not be exact (the chain form's multipliers are 2, see chain_word).
+inline bool is_tiny_threshold(float t) { return t < 0x1p-125f; }
+
 inline bool good_threshold(float t) { return std::isfinite(t) && t > 0.0f; }
 
 inline bool good_step_params(long step, int k, float threshold, float lr_local, float lr_global)
@@ -170,8 +174,8 @@ inline int launch_status()
 struct PlanTables {
     TensorDesc *tensors = nullptr;
     ChunkRef *chunks = nullptr;
-    const uint8_t **peers = nullptr;    // [num_tensors][num_workers - 1]
-    const void **peer_grads = nullptr;  // same shape, or null: correction passes read agg_full
+    const uint8_t **rows = nullptr;     // [num_tensors][row_entries(num_workers)], null where nothing is loaded
+    const void **peer_grads = nullptr;  // [num_tensors][num_workers - 1], or null: correction passes read agg_full
     int num_tensors = 0;
     int num_workers = 0;
     int self = 0;
@@ -181,6 +185,7 @@ struct PlanTables {
     int grad_type = kGradF32;          // element type of grad and of the bound peer gradients
     bool own_thresholds = false;       // every tensor carries its own threshold
     bool own_thresholds_pow2 = false;  // ... and all of them are powers of two
+    bool own_thresholds_tiny = false;  // ... and the half of some may not be exact
     unsigned max_workgroups = 0;       // > 0: launch at most this many workgroups (they take several chunks each)
     bool peers_sparse = false;         // the peers' streams are in the sparse form (cdsgd_plan_set_peer_format)
 
@@ -446,12 +451,13 @@ int cdsgd_plan_create_typed(const cdsgd_tensor *tensors, int num_tensors, const 
     bool all_agg = true;
     const int rc = check_layer_list(tensors, num_tensors, peers, num_workers, self, grad_dtype, &total_chunks, &all_agg);
     if (rc != CDSGD_OK) return rc;
-    const int num_peers = num_workers - 1;
+    const unsigned row = row_entries(num_workers);
 
     // host image of the device block
     const size_t bytes_t = sizeof(TensorDesc) * (size_t)num_tensors;
     const size_t bytes_c = sizeof(ChunkRef) * (size_t)total_chunks;
-    const size_t bytes_p = sizeof(const uint8_t *) * (size_t)num_tensors * (size_t)(num_peers > 0 ? num_peers : 1);
+    // (a batch of pointers past the last row: a kernel for any number of workers reads a short row that far)
+    const size_t bytes_p = sizeof(const uint8_t *) * ((size_t)num_tensors * row + CDSGD_MAX_WORKERS);
     const size_t off_c = (bytes_t + 255) & ~(size_t)255;
     const size_t off_p = (off_c + bytes_c + 255) & ~(size_t)255;
     const size_t total = off_p + bytes_p;
@@ -471,12 +477,8 @@ int cdsgd_plan_create_typed(const cdsgd_tensor *tensors, int num_tensors, const 
             hc[ci].chunk = c;
             ++ci;
         }
-        int slot = 0;
-        for (int j = 0; j < num_workers; ++j) {
-            if (j == self) continue;
-            hp[(size_t)i * (size_t)num_peers + (size_t)slot] = reinterpret_cast<const uint8_t *>(peers[j][i]);
-            ++slot;
-        }
+        for (int j = 0; j < num_workers; ++j)
+            if (j != self) hp[(size_t)i * row + (size_t)j] = reinterpret_cast<const uint8_t *>(peers[j][i]);
     }
 
     cdsgd_plan *plan = new (std::nothrow) cdsgd_plan;
@@ -495,7 +497,7 @@ int cdsgd_plan_create_typed(const cdsgd_tensor *tensors, int num_tensors, const 
     unsigned char *base = static_cast<unsigned char *>(plan->device_block);
     plan->tensors = reinterpret_cast<TensorDesc *>(base);
     plan->chunks = reinterpret_cast<ChunkRef *>(base + off_c);
-    plan->peers = reinterpret_cast<const uint8_t **>(base + off_p);
+    plan->rows = reinterpret_cast<const uint8_t **>(base + off_p);
     plan->num_tensors = num_tensors;
     plan->num_workers = num_workers;
     plan->self = self;
@@ -526,6 +528,44 @@ int cdsgd_plan_destroy(cdsgd_plan *plan)
 
 namespace {
 
+// Launch shape of a compressed pass: waves per group, and the LDS a group asks for in all (0: what it uses).
+//
+// The passes are bound by HBM, and HBM serves a mix of reads and writes best when the streams' requests in flight
+// stay close together: groups are dispatched in order, so the number of groups resident bounds how far apart they
+// are, and the LDS that a group asks for bounds that number (160 KiB per compute unit).  Short lists fit the
+// memory-side cache in part and end before such an order matters: there every resident group helps.  Measured, time
+// of the whole pass against the former kernels (one 128-bit load for 16 peers, bytes staged through LDS), N = 16:
+//   groups per compute unit     all      4      3
+//   VGG-16-shaped, t = 0.5     0.91   0.98   1.02     (0.602 ms against 0.612)
+//   VGG-16-shaped, t = 0.3     0.94   1.00   0.97
+//   25 M elements, t = 0.5     1.00   1.02   1.01     (the same with t = 0.3: 1.01 / 1.00 / 0.95)
+//   4 M elements, t = 0.5      1.05   1.02   0.99
+// The chain form's decode is longer and wants one group more.  Up to 8 workers on lists of 16 to 48 M elements, and
+// up to 4 on longer ones, one-wave groups (a quarter of a tile, 22 groups per compute unit) are 1-2 % faster than
+// groups of four waves; elsewhere those are (8 workers: 4 M elements 1.06 against 1.03, VGG-16 1.02-1.05 against
+// 1.00).  Above 16 workers: VGG-16-shaped, N = 32, t = 0.5 0.722 ms before, 0.745 with all groups, 0.714 with
+// 32 KiB each; t = 0.3 0.749, 0.735, 0.703 with 38 KiB (N = 64: 1.155, 0.922, 0.915).  Sparse peers, N = 16: 0.581
+// with all groups, 0.594 with 32 KiB each when one code in 256 is sent (0.597 before), 0.673 and 0.653 when one in 4
+// is (0.645 before); above 16 workers all groups (N = 32: 0.643, 0.690; 0.733 before).
+struct CompressedLaunch {
+    unsigned waves, lds;
+};
+
+CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int form, bool sparse)
+{
+    const unsigned tiles = num_chunks * kTilesPerChunk;  // of 1024 elements
+    const bool long_list = tiles > 28u * 1024u;
+    if (sparse) return {4u, long_list && num_workers <= kUpTo16 ? 32768u : 0u};
+    if (num_workers <= kUpTo8 && form != kChainTiny) {
+        if (tiles <= 16u * 1024u) return {4u, 0u};
+        if (num_workers > 4 && tiles > 48u * 1024u) return {4u, 49152u};
+        return {1u, 7168u};
+    }
+    if (num_workers <= kUpTo16 && form == kCount) return {4u, long_list ? 49152u : (tiles > 6u * 1024u ? 32768u : 0u)};
+    if (num_workers <= kUpTo16 || form == kCount) return {4u, long_list ? 32768u : 0u};
+    return {4u, long_list ? 38912u : 0u};
+}
+
 // One pass of FormalTraining's loop; with_local = false leaves eq. 11 out (split form).
 int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold, float lr_local, float lr_global,
                        bool with_local, void *hip_stream)
@@ -537,51 +577,45 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
         return launch_full_pass(plan, with_local ? kLocalRule : kLocalNone, lr_local, lr_global, hip_stream);
     const float scale = lr_global / (float)plan->num_workers;
     hipStream_t s = (hipStream_t)hip_stream;
-    const int num_peers = plan->num_workers - 1;
-    const unsigned waves = num_peers <= kFewPeers ? 1u : kPieceWavesMany;
-    const bool many = num_peers > 16;  // count form: the kernel compiled for more waves per SIMD
-    const unsigned long long num_pieces = (unsigned long long)plan->num_chunks * (kChunkQuads / (64u * waves));
-    const dim3 grid(plan->grid_size(num_pieces, 64u * waves)), block(64u * waves);
-#define CDSGD_LAUNCH_COMPRESSED_S(W, POW2, LOCAL, GT, SPARSE)                                                  \
-    hipLaunchKernelGGL((k_fused_compressed<W, POW2, LOCAL, GT, SPARSE>), grid, block, 0, s, plan->tensors,      \
-                       plan->chunk_table(), num_pieces, plan->peers, num_peers, plan->self, threshold, lr_local, \
-                       scale)
-#define CDSGD_LAUNCH_COMPRESSED_M(LOCAL, GT, SPARSE)                                                           \
-    hipLaunchKernelGGL((k_fused_compressed_many<LOCAL, GT, SPARSE>), grid, block, 0, s, plan->tensors,          \
-                       plan->chunk_table(), num_pieces, plan->peers, num_peers, plan->self, threshold, lr_local, \
-                       scale)
-#define CDSGD_LAUNCH_COMPRESSED_W(W, POW2, LOCAL, GT)                                                          \
-    do {                                                                                                       \
-        if (POW2 && many) {                                                                                    \
-            if (plan->peers_sparse) CDSGD_LAUNCH_COMPRESSED_M(LOCAL, GT, true);                                 \
-            else CDSGD_LAUNCH_COMPRESSED_M(LOCAL, GT, false);                                                   \
-        } else if (plan->peers_sparse) CDSGD_LAUNCH_COMPRESSED_S(W, POW2, LOCAL, GT, true);                     \
-        else CDSGD_LAUNCH_COMPRESSED_S(W, POW2, LOCAL, GT, false);                                              \
-    } while (0)
-#define CDSGD_LAUNCH_COMPRESSED_T(POW2, LOCAL, GT)                                                            \
-    do {                                                                                                       \
-        if (waves == 1u) CDSGD_LAUNCH_COMPRESSED_W(1u, POW2, LOCAL, GT);                                        \
-        else CDSGD_LAUNCH_COMPRESSED_W(kPieceWavesMany, POW2, LOCAL, GT);                                       \
-    } while (0)
-#define CDSGD_LAUNCH_COMPRESSED(POW2, LOCAL)                                                                  \
-    do {                                                                                                       \
-        if (plan->grad_type == kGradBF16) CDSGD_LAUNCH_COMPRESSED_T(POW2, LOCAL, kGradBF16);                   \
-        else if (plan->grad_type == kGradF16) CDSGD_LAUNCH_COMPRESSED_T(POW2, LOCAL, kGradF16);                \
-        else CDSGD_LAUNCH_COMPRESSED_T(POW2, LOCAL, kGradF32);                                                 \
-    } while (0)
-    // the count form of the decode needs every threshold in use to be a power of two
+    const int N = plan->num_workers;
+    // the count form of the decode needs every threshold in use to be a power of two; the chain form's multipliers
+    // need half of each to be exact
     const bool pow2 = plan->own_thresholds ? plan->own_thresholds_pow2 : is_pow2_threshold(threshold);
-    if (pow2) {
-        if (with_local) CDSGD_LAUNCH_COMPRESSED(true, true);
-        else CDSGD_LAUNCH_COMPRESSED(true, false);
-    } else {
-        if (with_local) CDSGD_LAUNCH_COMPRESSED(false, true);
-        else CDSGD_LAUNCH_COMPRESSED(false, false);
-    }
+    const bool tiny = plan->own_thresholds ? plan->own_thresholds_tiny : is_tiny_threshold(threshold);
+    const int form = pow2 ? kCount : (tiny ? kChainTiny : kChain);
+    const CompressedLaunch shape = compressed_launch(plan->num_chunks, N, form, plan->peers_sparse);
+    const unsigned num_tiles = plan->num_chunks * (kChunkQuads / (64u * shape.waves));
+    const unsigned grid = plan->grid_size(num_tiles, 64u * shape.waves);
+    // (a pass with a workgroup limit is meant to share the GPU with other kernels: it leaves the LDS to them)
+    const auto bound = [&](unsigned used) { return plan->max_workgroups || shape.lds <= used ? 0u : shape.lds - used; };
+#define CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, GT, SPARSE)                                                 \
+    hipLaunchKernelGGL((k_fused_compressed<SZ, WAVES, FORM, GT, SPARSE>), dim3(grid), dim3(64 * WAVES),         \
+                       bound(kTileLds<SZ, FORM, WAVES>), s, plan->tensors, plan->chunk_table(), plan->rows,      \
+                       num_tiles, grid, N, plan->self, threshold, lr_local, scale, with_local ? 1 : 0)
+#define CDSGD_LAUNCH_COMPRESSED_G(SZ, WAVES, FORM, SPARSE)                                                     \
+    do {                                                                                                       \
+        if (plan->grad_type == kGradBF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradBF16, SPARSE);        \
+        else if (plan->grad_type == kGradF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF16, SPARSE);     \
+        else CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF32, SPARSE);                                      \
+    } while (0)
+#define CDSGD_LAUNCH_COMPRESSED_F(SZ, FORM)                                                                    \
+    do {                                                                                                       \
+        if (plan->peers_sparse) CDSGD_LAUNCH_COMPRESSED_G(SZ, 4, FORM, true);                                   \
+        else CDSGD_LAUNCH_COMPRESSED_G(SZ, 4, FORM, false);                                                     \
+    } while (0)
+#define CDSGD_LAUNCH_COMPRESSED(FORM)                                                                          \
+    do {                                                                                                       \
+        if (shape.waves == 1u) CDSGD_LAUNCH_COMPRESSED_G(kUpTo8, 1, FORM, false);                               \
+        else if (N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED_F(kUpTo8, FORM);                                          \
+        else if (N <= kUpTo16) CDSGD_LAUNCH_COMPRESSED_F(kUpTo16, FORM);                                        \
+        else CDSGD_LAUNCH_COMPRESSED_F(kAnyWorkers, FORM);                                                      \
+    } while (0)
+    if (form == kCount) CDSGD_LAUNCH_COMPRESSED(kCount);
+    else if (form == kChain) CDSGD_LAUNCH_COMPRESSED(kChain);
+    else CDSGD_LAUNCH_COMPRESSED_F(kAnyWorkers, kChainTiny);
 #undef CDSGD_LAUNCH_COMPRESSED
-#undef CDSGD_LAUNCH_COMPRESSED_T
-#undef CDSGD_LAUNCH_COMPRESSED_W
-#undef CDSGD_LAUNCH_COMPRESSED_M
+#undef CDSGD_LAUNCH_COMPRESSED_F
+#undef CDSGD_LAUNCH_COMPRESSED_G
 #undef CDSGD_LAUNCH_COMPRESSED_S
     return launch_status();
 }
@@ -701,11 +735,12 @@ int cdsgd_plan_bind_full_grads(cdsgd_plan *plan, const float *const *const *peer
 int cdsgd_plan_set_thresholds(cdsgd_plan *plan, const float *thresholds)
 {
     if (!plan) return CDSGD_ERR_NULL;
-    bool all_pow2 = true;
+    bool all_pow2 = true, any_tiny = false;
     if (thresholds)
         for (int i = 0; i < plan->num_tensors; ++i) {
             if (!good_threshold(thresholds[i])) return CDSGD_ERR_PARAM;
             all_pow2 = all_pow2 && is_pow2_threshold(thresholds[i]);
+            any_tiny = any_tiny || is_tiny_threshold(thresholds[i]);
         }
     std::vector<TensorDesc> next = plan->host_tensors;
     for (int i = 0; i < plan->num_tensors; ++i) next[(size_t)i].threshold = thresholds ? thresholds[i] : 0.0f;
@@ -716,6 +751,7 @@ int cdsgd_plan_set_thresholds(cdsgd_plan *plan, const float *thresholds)
     plan->host_tensors.swap(next);
     plan->own_thresholds = thresholds != nullptr;
     plan->own_thresholds_pow2 = thresholds != nullptr && all_pow2;
+    plan->own_thresholds_tiny = any_tiny;
     return CDSGD_OK;
 }
 
@@ -980,7 +1016,6 @@ extern "C" int cdsgd_step_fused_static(const cdsgd_tensor *tensors, int num_tens
     rc = static_scratch(&base);
     if (rc != CDSGD_OK) return rc;
     hipStream_t s = (hipStream_t)hip_stream;
-    const int num_peers = num_workers - 1;
 
     // descriptor table
     StaticWriter w(s, base + kStaticOffDesc);
@@ -998,13 +1033,14 @@ extern "C" int cdsgd_step_fused_static(const cdsgd_tensor *tensors, int num_tens
     }
     w.put(&start, sizeof(start));
     w.flush();
-    // peers' streams, [tensor][peer], the own row left out (compressed passes only)
-    if (compressed && num_peers > 0) {
+    // the workers' streams, a row per tensor (compressed passes only)
+    if (compressed) {
         w.dst = base + kStaticOffPeers;
+        const int row = (int)row_entries(num_workers);
         for (int i = 0; i < num_tensors; ++i)
-            for (int j = 0; j < num_workers; ++j) {
-                if (j == self) continue;
-                const uint8_t *ptr = reinterpret_cast<const uint8_t *>(peers[j][i]);
+            for (int j = 0; j < row; ++j) {
+                const uint8_t *ptr = nullptr;
+                if (j < num_workers && j != self) ptr = reinterpret_cast<const uint8_t *>(peers[j][i]);
                 w.put(&ptr, sizeof(ptr));
             }
         w.flush();
@@ -1020,7 +1056,7 @@ extern "C" int cdsgd_step_fused_static(const cdsgd_tensor *tensors, int num_tens
     PlanTables pt;
     pt.tensors = reinterpret_cast<TensorDesc *>(base + kStaticOffDesc);
     pt.chunks = reinterpret_cast<ChunkRef *>(base + kStaticOffChunks);
-    pt.peers = reinterpret_cast<const uint8_t **>(base + kStaticOffPeers);
+    pt.rows = reinterpret_cast<const uint8_t **>(base + kStaticOffPeers);
     pt.num_tensors = num_tensors;
     pt.num_workers = num_workers;
     pt.self = self;

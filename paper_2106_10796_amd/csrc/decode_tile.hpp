@@ -1,0 +1,346 @@
+// Decode-and-sum of the workers' packed streams for one tile (a4: Sec. 3.2.1; the sum of eq. 10).
+#pragma once
+
+namespace {
+
+// A tile is 1024 elements of a tensor, the work of a group of four waves: 4 KiB of every fp32 stream, one quad per
+// lane (quad 64 v + l for lane l of wave v), and 256 bytes of every packed stream, two whole 128-byte lines, 64
+// words.  The group decodes words, sixteen consecutive elements each, not the bytes of a lane's own quad.
+constexpr unsigned kTileQuads = 256, kTileWords = 64, kTileBytes = kTileQuads;
+constexpr unsigned kTilesPerChunk = kChunkQuads / kTileQuads;
+static_assert(kChunkQuads % kTileQuads == 0, "tiles tile a chunk");
+
+// How a kernel is compiled for the number of workers.  The waves share the workers out: wave v takes
+// kWordsPerWave<SZ> of every row, lane l its word l of each, and all of a group's loads are in flight at once.
+constexpr int kUpTo8 = 8, kUpTo16 = 16, kAnyWorkers = 0;
+template <int SZ>
+constexpr int kMaxRows = SZ == kAnyWorkers ? CDSGD_MAX_WORKERS : SZ;
+template <int SZ>
+constexpr int kWordsPerWave = kMaxRows<SZ> / 4;
+
+// A row of stream pointers: one entry per worker, in worker order, null where there is nothing to load (the own
+// entry, and the entries past the last worker up to a whole batch).
+inline constexpr unsigned row_entries(int num_workers)
+{
+    return num_workers <= kUpTo8 ? 8u : ((unsigned)num_workers + 15u) / 16u * 16u;
+}
+
+// Decode forms.  kCount: thresholds that are powers of two, where every partial sum is exact and the sum is
+// count x t bit for bit.  kChain: one rounded add per worker and element, in worker order.  kChainTiny: the same
+// for thresholds below 2^-125, whose half is not exact (kAnyWorkers kernels only).
+constexpr int kCount = 0, kChain = 1, kChainTiny = 2;
+
+// One word of a buffer of `bytes` bytes at byte offset `off`; 0 past the end (the buffer's own range check), which
+// is what the lanes behind a ragged end and the absent workers (bytes == 0: nothing is read) want.
+__device__ __forceinline__ unsigned ld_word(const uint8_t *base, unsigned bytes, unsigned off)
+{
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(base), 0, (int)bytes, 0x00027000);
+    return __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)off, 0, 0);
+}
+
+// Where the streams of a tile are.
+struct TileStreams {
+    const uint8_t *const *row;  // row_entries(num_workers) pointers
+    int num_workers;
+    unsigned stream_bytes;      // packed form: bytes of a stream, and where the tile starts in it
+    unsigned tile_at;
+    size_t segment_at;          // sparse form: the chunk's segment, and the tile's number in the chunk
+    unsigned tile;
+};
+
+// The worker whose word a wave holds in slot i: four neighbours out of every sixteen (two out of eight), so that
+// the slots of a wave fill up evenly with the number of workers.
+template <int SZ>
+__device__ __forceinline__ constexpr int worker_of(int wave, int i)
+{
+    return SZ == kUpTo8 ? 2 * wave + i : 16 * (i / 4) + 4 * wave + i % 4;
+}
+
+// This lane's words of the workers that its wave takes; 0 where there is nothing to load.
+template <int SZ>
+__device__ __forceinline__ void load_packed(unsigned (&w)[kWordsPerWave<SZ>], const TileStreams &s, int wave, unsigned lane)
+{
+#pragma unroll
+    for (int i = 0; i < kWordsPerWave<SZ>; ++i) {
+        const int j = worker_of<SZ>(wave, i);
+        w[i] = 0u;
+        if (SZ != kAnyWorkers || 16 * (i / 4) < s.num_workers) {
+            const uint8_t *p = s.row[j];
+            if (SZ == kAnyWorkers && j >= s.num_workers) p = nullptr;
+            w[i] = ld_word(p, p ? s.stream_bytes : 0u, s.tile_at + 4u * lane);
+        }
+    }
+}
+
+// The same from streams in the sparse form (segment of 8 bitmap words and the non-zero words, see kernels_sparse.hpp).
+// Lane 4 i + m fetches bitmap words 2 m and 2 m + 1 of the worker in slot i; a tile's 64 words are one such pair, so
+// its bitmap, and the number of words in front of it, are wave-uniform, and a lane's word lies at the rank of its bit.
+template <int SZ>
+__device__ __forceinline__ void load_sparse(unsigned (&w)[kWordsPerWave<SZ>], const TileStreams &s, int wave, unsigned lane)
+{
+    const int slot = (int)(lane >> 2);
+    const unsigned m = lane & 3u;
+    u2 bm = {0u, 0u};
+    if (slot < kWordsPerWave<SZ>) {
+        const int j = worker_of<SZ>(wave, slot);
+        if (SZ != kAnyWorkers || j < s.num_workers) {
+            const uint8_t *p = s.row[j];
+            typedef unsigned u2a __attribute__((ext_vector_type(2), aligned(4)));
+            if (p) bm = *(const CDSGD_GLOBAL u2a *)(p + s.segment_at + 8u * m);
+        }
+    }
+    // words in front of the tile's own: summed over the worker's four lanes
+    int before = m < s.tile ? __builtin_popcount(bm.x) + __builtin_popcount(bm.y) : 0;
+    before += __builtin_amdgcn_mov_dpp(before, 0xB1, 0xF, 0xF, true);  // quad_perm [1, 0, 3, 2]
+    before += __builtin_amdgcn_mov_dpp(before, 0x4E, 0xF, 0xF, true);  // quad_perm [2, 3, 0, 1]
+#pragma unroll
+    for (int i = 0; i < kWordsPerWave<SZ>; ++i) {
+        w[i] = 0u;
+        if (SZ != kAnyWorkers || 16 * (i / 4) < s.num_workers) {
+            const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)bm.x, 4 * i + (int)s.tile);
+            const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)bm.y, 4 * i + (int)s.tile);
+            const unsigned at = 8u + (unsigned)__builtin_amdgcn_readlane(before, 4 * i);
+            const uint8_t *p = s.row[worker_of<SZ>(wave, i)];
+            if (SZ == kAnyWorkers && worker_of<SZ>(wave, i) >= s.num_workers) p = nullptr;
+            const unsigned rank = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+            const bool sent = __builtin_amdgcn_inverse_ballot_w64(((unsigned long long)hi << 32) | lo);
+            // a lane whose word is zero asks past the end of the segment and gets 0 without a read
+            w[i] = ld_word(p + s.segment_at, p ? 4u * kSegStride : 0u, sent ? 4u * (at + rank) : 4u * kSegStride);
+        }
+    }
+}
+
+// Groups of one wave: a quarter of a tile, 16 words of every stream; lanes 16 v .. 16 v + 15 take what wave v takes
+// in a group of four (packed form, up to eight workers).
+__device__ __forceinline__ void load_packed_quarter(unsigned (&w)[kWordsPerWave<kUpTo8>], const TileStreams &s, unsigned lane)
+{
+    const unsigned off = s.tile_at + 4u * (lane & 15u);
+#pragma unroll
+    for (int i = 0; i < kWordsPerWave<kUpTo8>; ++i) {
+        const uint8_t *p = s.row[2u * (lane >> 4) + (unsigned)i];
+        w[i] = 0u;
+        if (p && off < s.stream_bytes) w[i] = *global_ptr(reinterpret_cast<const unsigned *>(p + off));
+    }
+}
+
+template <int SZ, int WAVES, bool SPARSE>
+__device__ __forceinline__ void load_words(unsigned (&w)[kWordsPerWave<SZ>], const TileStreams &s, int wave, unsigned lane)
+{
+    if constexpr (WAVES == 1) {
+        static_assert(SZ == kUpTo8 && !SPARSE, "one wave: up to eight packed streams");
+        load_packed_quarter(w, s, lane);
+    } else if constexpr (SPARSE) load_sparse<SZ>(w, s, wave, lane);
+    else load_packed<SZ>(w, s, wave, lane);
+}
+
+// ---- count form -------------------------------------------------------------
+// Bit-sliced counting.  The value of a code is (low bit) - (high bit), also for the field that is never written
+// (11 reads as nothing), so it is enough to count the set bits of the words position by position: a carry-save
+// adder is two vector operations (three-input logic) on 32 positions.  Each wave counts its own workers' words, the
+// four waves' counts meet in LDS as bytes.  One operation per worker and element, and a byte read from LDS per worker
+// and quad, become a tenth of that; with 64 workers that was what bounded the pass (25 M elements: 0.191 ms before,
+// 0.169 now, 6.0 TB/s).
+__device__ __forceinline__ void csa(unsigned &carry, unsigned &sum, unsigned a, unsigned b, unsigned c)
+{
+    const unsigned s = __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);  // a ^ b ^ c
+    carry = __builtin_amdgcn_bitop3_b32(a, b, c, 0xE8);             // at least two of the three
+    sum = s;
+}
+
+template <int PLANES>
+struct BitCounts {
+    unsigned p[PLANES];  // p[i]: bit i of the count of every position
+
+    // Count W words (W = 2, 4 or 16; at most 2^PLANES - 1 at a time can be held).
+    template <int W>
+    __device__ __forceinline__ void count(const unsigned (&w)[W])
+    {
+        if constexpr (W == 2) {
+            p[0] = w[0] ^ w[1];
+            p[1] = w[0] & w[1];
+        } else {
+            static_assert(W % 4 == 0, "words in groups of four");
+#pragma unroll
+            for (int i = 0; i < PLANES; ++i) p[i] = 0u;
+#pragma unroll
+            for (int i = 0; i < W; i += 4) {
+                unsigned t0, t1, e;
+                csa(t0, p[0], p[0], w[i], w[i + 1]);
+                csa(t1, p[0], p[0], w[i + 2], w[i + 3]);
+                csa(e, p[1], p[1], t0, t1);
+#pragma unroll
+                for (int k = 2; k < PLANES; ++k) {
+                    const unsigned both = p[k] & e;
+                    p[k] ^= e;
+                    e = both;
+                }
+            }
+        }
+    }
+
+    // Byte j of out[c] = (2^PLANES - 1) + sum of the values of element 4 j + c of the lane's word.
+    __device__ __forceinline__ void to_bytes(unsigned (&out)[4]) const
+    {
+        static_assert(PLANES <= 5, "four groups' fields, 2^PLANES - 1 plus a count each, add up in a byte");
+#pragma unroll
+        for (int i0 = 0; i0 < PLANES; i0 += 3) {
+            unsigned even = 0u, odd = 0u;  // nibbles: elements 0, 2, 4, ... and 1, 3, 5, ...; three planes: at most 14
+#pragma unroll
+            for (int i = i0; i < i0 + 3 && i < PLANES; ++i) {
+                // 1 + (low bit) - (high bit) of every position pair, in the pair's two bits
+                const unsigned h = p[i] >> 1;
+                const unsigned same = __builtin_amdgcn_bitop3_b32(p[i], h, 0x55555555u, 0x82);  // ~(p ^ h) & mask
+                const unsigned plus = __builtin_amdgcn_bitop3_b32(p[i], h, 0x55555555u, 0x20);  // p & ~h & mask
+                const unsigned z = (plus << 1) | same;
+                even += (z & 0x33333333u) << (i - i0);
+                odd += ((z >> 2) & 0x33333333u) << (i - i0);
+            }
+            const unsigned b0 = even & 0x0F0F0F0Fu, b2 = (even >> 4) & 0x0F0F0F0Fu;
+            const unsigned b1 = odd & 0x0F0F0F0Fu, b3 = (odd >> 4) & 0x0F0F0F0Fu;
+            out[0] = i0 == 0 ? b0 : out[0] + (b0 << i0);
+            out[1] = i0 == 0 ? b1 : out[1] + (b1 << i0);
+            out[2] = i0 == 0 ? b2 : out[2] + (b2 << i0);
+            out[3] = i0 == 0 ? b3 : out[3] + (b3 << i0);
+        }
+    }
+};
+
+// planes a wave needs: counts up to 2, 4 and 16
+template <int SZ>
+constexpr int kPlanes = SZ == kUpTo8 ? 2 : (SZ == kUpTo16 ? 3 : 5);
+
+// ---- chain form -------------------------------------------------------------
+// One rounded add of +t, -t or 0 per worker and element: a fused multiply-add whose multiplier is a 16-bit float
+// read from half a register.  The top two bits of a 16-bit float are its sign and the top bit of its exponent:
+// 01 is +2, 11 is -2 and 00 is 0, which is the two's-complement form of a code's value.  So a word's codes become
+// multipliers with one shift and one mask for two elements, and the products are exact with t / 2.
+// A bit more than 2 vector operations per worker and element, against 4.25 with a bit-field extract, a convert and a
+// multiply-add per element of every byte (25 M elements, N = 64, bf16 gradients: 0.226 ms before, 0.164 now).
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+
+// Two of a word's eight pairs: elements i and i + 8, i + 1 and i + 9, from the word's signed fields; shift = 14 - 2 i.
+template <bool TINY>
+__device__ __forceinline__ void chain_pairs(float (&acc)[4], unsigned fields, unsigned shift, float t)
+{
+    const float factor = TINY ? t : 0.5f * t;
+    const float unit = TINY ? 0.5f : 1.0f;
+    const h2 a = __builtin_bit_cast(h2, (fields << shift) & 0xC000C000u);
+    const h2 b = __builtin_bit_cast(h2, (fields << (shift - 2u)) & 0xC000C000u);
+    acc[0] = __builtin_fmaf(unit * (float)a.x, factor, acc[0]);
+    acc[1] = __builtin_fmaf(unit * (float)b.x, factor, acc[1]);
+    acc[2] = __builtin_fmaf(unit * (float)a.y, factor, acc[2]);
+    acc[3] = __builtin_fmaf(unit * (float)b.y, factor, acc[3]);
+}
+
+// A quad's four codes, from the byte of signed fields.
+__device__ __forceinline__ void chain_byte(f4 &acc, unsigned byte, float t)
+{
+    const float factor = 0.5f * t;
+    const unsigned y = (byte << 12) | (byte << 24);
+    const h2 a = __builtin_bit_cast(h2, (y << 2) & 0xC000C000u);  // elements 0 and 2
+    const h2 b = __builtin_bit_cast(h2, y & 0xC000C000u);         // elements 1 and 3
+    acc[0] = __builtin_fmaf((float)a.x, factor, acc[0]);
+    acc[1] = __builtin_fmaf((float)b.x, factor, acc[1]);
+    acc[2] = __builtin_fmaf((float)a.y, factor, acc[2]);
+    acc[3] = __builtin_fmaf((float)b.y, factor, acc[3]);
+}
+
+// ---- a tile's sums ------------------------------------------------------------
+// LDS of a group: the four waves' partial counts, or the workers' words as signed fields and the sums on their way
+// from words to quads.
+template <int SZ, int FORM, int WAVES>
+constexpr unsigned kTileLds = (FORM == kCount ? 4u * 4u * kTileQuads
+                                              : (unsigned)kMaxRows<SZ> * kTileBytes + (SZ == kAnyWorkers ? 16u * kTileQuads : 0u)) *
+                              WAVES / 4;
+
+template <int WAVES>
+__device__ __forceinline__ void group_sync()
+{
+    if (WAVES == 1) {
+        // one wave's LDS operations run in order, only the compiler has to keep them so
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+        __syncthreads();
+    }
+}
+
+// The sums of this lane's quad of a tile over all workers.  `w` holds the wave's words (load_words); the own codes
+// come as this lane's packed byte and as the values it stands for, own_at is their place in the order (-1: none).
+// Everything a group has written to LDS before has been read when it calls this again (a barrier of the caller's).
+template <int SZ, int FORM, int WAVES>
+__device__ __forceinline__ f4 tile_sums(const unsigned (&w)[kWordsPerWave<SZ>], unsigned own_code, f4 own_value,
+                                        int own_at, int num_workers, float t, uint8_t *lds)
+{
+    // a group of four waves: wave v holds words of its workers, word l in lane l; a group of one: lanes 16 v ..
+    constexpr unsigned kQuads = 64u * WAVES, kWords = 16u * WAVES, kBytes = kQuads;
+    const unsigned tid = threadIdx.x, lane = tid & (kWords - 1u);
+    const int wave = WAVES == 4 ? __builtin_amdgcn_readfirstlane((int)(tid >> 6)) : (int)(tid >> 4);
+    f4 agg;
+    if (FORM == kCount) {
+        constexpr int P = kPlanes<SZ>;
+        BitCounts<P> counts;
+        counts.count(w);
+        unsigned a[4];
+        counts.to_bytes(a);
+        // a[c] byte j -> dword j byte c: one dword per quad of this lane's word
+        const unsigned x0 = __builtin_amdgcn_perm(a[1], a[0], 0x05010400u), x1 = __builtin_amdgcn_perm(a[1], a[0], 0x07030602u);
+        const unsigned y0 = __builtin_amdgcn_perm(a[3], a[2], 0x05010400u), y1 = __builtin_amdgcn_perm(a[3], a[2], 0x07030602u);
+        u4 q;
+        q[0] = __builtin_amdgcn_perm(y0, x0, 0x05040100u);
+        q[1] = __builtin_amdgcn_perm(y0, x0, 0x07060302u);
+        q[2] = __builtin_amdgcn_perm(y1, x1, 0x05040100u);
+        q[3] = __builtin_amdgcn_perm(y1, x1, 0x07060302u);
+        reinterpret_cast<u4 *>(lds)[tid] = q;  // [wave][word][quad]
+        group_sync<WAVES>();
+        unsigned v = 0u;
+#pragma unroll
+        for (unsigned k = 0; k < 4; ++k) v += reinterpret_cast<const unsigned *>(lds)[kQuads * k + tid];
+        const float bias_t = -(float)(4 * ((1 << P) - 1)) * t;
+#pragma unroll
+        for (unsigned c = 0; c < 4; ++c) agg[c] = __builtin_fmaf((float)((v >> (8u * c)) & 0xFFu), t, bias_t);
+        agg = agg + own_value;
+    } else {
+        // rows of signed fields, worker by worker; the rows up to the next multiple of four are zero
+        unsigned *rows = reinterpret_cast<unsigned *>(lds);
+#pragma unroll
+        for (int i = 0; i < kWordsPerWave<SZ>; ++i) {
+            const int j = worker_of<SZ>(wave, i);
+            if (j != own_at && (SZ != kAnyWorkers || 16 * (i / 4) < num_workers)) rows[kWords * (unsigned)j + lane] = signed_fields(w[i]);
+        }
+        if (own_at >= 0) lds[kBytes * (unsigned)own_at + tid] = (uint8_t)signed_fields(own_code);
+        group_sync<WAVES>();
+        if constexpr (SZ != kAnyWorkers) {
+            // every lane adds up its own quad, a byte of every row: one operation more per worker than by words, no exchange
+            agg = f4{0.0f, 0.0f, 0.0f, 0.0f};
+            unsigned code[SZ];
+#pragma unroll
+            for (int j = 0; j < SZ; ++j) code[j] = lds[kBytes * (unsigned)j + tid];
+#pragma unroll
+            for (int j0 = 0; j0 < SZ; j0 += 4)
+                if (j0 < num_workers) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) chain_byte(agg, code[j0 + k], t);
+                }
+        } else {
+            float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            const unsigned shift = 14u - 4u * (unsigned)wave;
+            for (int j0 = 0; j0 < num_workers; j0 += 4) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) chain_pairs<FORM == kChainTiny>(acc, rows[kTileWords * (j0 + k) + lane], shift, t);
+            }
+            // elements 2 v, 2 v + 1 and 2 v + 8, 2 v + 9 of word l -> quads
+            typedef float f2 __attribute__((ext_vector_type(2)));
+            float *sums = reinterpret_cast<float *>(lds + (unsigned)kMaxRows<SZ> * kTileBytes);
+            *reinterpret_cast<f2 *>(sums + 16u * lane + 2u * (unsigned)wave) = f2{acc[0], acc[1]};
+            *reinterpret_cast<f2 *>(sums + 16u * lane + 2u * (unsigned)wave + 8u) = f2{acc[2], acc[3]};
+            group_sync<WAVES>();
+            agg = reinterpret_cast<const f4 *>(sums)[tid];
+        }
+    }
+    return agg;
+}
+
+}  // namespace

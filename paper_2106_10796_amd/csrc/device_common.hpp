@@ -16,9 +16,19 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 // ---------------------------------------------------------------------------
 // 128-bit loads / stores, with the ragged end of a tensor handled per element
 // ---------------------------------------------------------------------------
+// Pointers that a kernel reads from a table are generic to the compiler, and it would access them with flat
+// instructions, which count as LDS operations too: every wait for LDS, and every wait for some of the loads in
+// flight, then becomes a wait for all of them.  All data buffers are global memory, and are accessed as that.
+#define CDSGD_GLOBAL __attribute__((address_space(1)))
+template <typename T>
+__device__ __forceinline__ CDSGD_GLOBAL T *global_ptr(T *p)
+{
+    return (CDSGD_GLOBAL T *)p;
+}
+
 __device__ __forceinline__ f4 ld4(const float *base, unsigned qi)
 {
-    const f4 *p = reinterpret_cast<const f4 *>(base) + qi;
+    const CDSGD_GLOBAL f4 *p = global_ptr(reinterpret_cast<const f4 *>(base)) + qi;
 #if CDSGD_NT_LOAD
     return __builtin_nontemporal_load(p);
 #else
@@ -28,7 +38,7 @@ __device__ __forceinline__ f4 ld4(const float *base, unsigned qi)
 
 __device__ __forceinline__ void st4(float *base, unsigned qi, f4 v)
 {
-    f4 *p = reinterpret_cast<f4 *>(base) + qi;
+    CDSGD_GLOBAL f4 *p = global_ptr(reinterpret_cast<f4 *>(base)) + qi;
 #if CDSGD_NT_STORE
     __builtin_nontemporal_store(v, p);
 #else
@@ -42,7 +52,7 @@ __device__ __forceinline__ f4 ld4g(const float *base, unsigned qi, int cnt)
 {
     if (!G || cnt == 4) return ld4(base, qi);
     f4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-    const float *p = base + 4u * qi;
+    const CDSGD_GLOBAL float *p = global_ptr(base) + 4u * qi;
     if (cnt > 0) v.x = p[0];
     if (cnt > 1) v.y = p[1];
     if (cnt > 2) v.z = p[2];
@@ -56,7 +66,7 @@ __device__ __forceinline__ void st4g(float *base, unsigned qi, int cnt, f4 v)
         st4(base, qi, v);
         return;
     }
-    float *p = base + 4u * qi;
+    CDSGD_GLOBAL float *p = global_ptr(base) + 4u * qi;
     if (cnt > 0) p[0] = v.x;
     if (cnt > 1) p[1] = v.y;
     if (cnt > 2) p[2] = v.z;
@@ -87,7 +97,7 @@ __device__ __forceinline__ f4 ldgrad(const void *base, unsigned qi, int cnt)
 {
     if (GT == kGradF32) return ld4g<G>(static_cast<const float *>(base), qi, cnt);
     if (!G || cnt == 4) {
-        const u2 *p = static_cast<const u2 *>(base) + qi;
+        const CDSGD_GLOBAL u2 *p = global_ptr(static_cast<const u2 *>(base)) + qi;
 #if CDSGD_NT_LOAD
         const u2 v = __builtin_nontemporal_load(p);
 #else
@@ -97,7 +107,7 @@ __device__ __forceinline__ f4 ldgrad(const void *base, unsigned qi, int cnt)
                   widen16<GT>(v.y >> 16)};
     }
     f4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-    const unsigned short *p = static_cast<const unsigned short *>(base) + 4u * qi;
+    const CDSGD_GLOBAL unsigned short *p = global_ptr(static_cast<const unsigned short *>(base)) + 4u * qi;
     if (cnt > 0) v.x = widen16<GT>(p[0]);
     if (cnt > 1) v.y = widen16<GT>(p[1]);
     if (cnt > 2) v.z = widen16<GT>(p[2]);

@@ -3,257 +3,117 @@
 
 namespace {
 
-// Piece-granular kernels: which piece workgroup b takes.  Workgroup b runs on XCD b % 8.  Within
-// a block of 8 chunks' worth of workgroups, XCD k takes every piece of chunk k, so that the two
-// halves of a 128-byte line of a peer's codes, and the pieces' reads of the chunk's table
-// entries, meet in one L2 (measured on the ResNet-50-shaped list: 6.1 -> 6.8 TB/s).  The last,
-// incomplete block keeps the plain order.  A bijection on [0, num_pieces) for any grid size.
-template <bool XCD>
-__device__ __forceinline__ unsigned long long piece_of_workgroup(unsigned long long b, unsigned per_chunk,
-                                                                 unsigned long long num_pieces)
+// Which part (tile or piece) of the chunk table workgroup b takes.  Workgroup b runs on XCD b % 8.  Within
+// a block of 8 chunks' worth of workgroups, XCD k takes every part of chunk k, so that the parts' reads of
+// the chunk's table entries and of shared 128-byte lines of a peer's codes meet in one L2 (compressed pass on
+// 1 GiB buckets, N = 16: 1.150 ms against 1.25 in the plain order).  The last, incomplete block keeps the
+// plain order.  A bijection on [0, num_pieces) for any grid size.
+template <bool XCD, typename T>
+__device__ __forceinline__ T piece_of_workgroup(T b, unsigned per_chunk, T num_pieces)
 {
     if (!XCD) return b;
 #if CDSGD_XCD_PIECES
-    const unsigned long long group = 8ull * per_chunk;
-    const unsigned long long blk = b / group, within = b % group;
+    const T group = (T)8 * per_chunk;
+    const T blk = b / group, within = b % group;
     if ((blk + 1) * group <= num_pieces) return (blk * 8 + within % 8) * per_chunk + within / 8;
 #endif
     return b;
 }
 
 // ---------------------------------------------------------------------------
-// Fused compressed step (a1-a6), one workgroup per piece of a chunk
+// Fused compressed step (a1-a6), one group of waves per tile of a chunk
 // ---------------------------------------------------------------------------
-// A piece is 256 quads (1024 elements): 4 KiB of every fp32 stream and 256 bytes, two whole
-// 128-byte lines, of every packed stream.  Its workgroup has 256 lanes (four waves), one quad
-// and therefore one packed byte per lane.
-//
-// The peers' codes of a piece are fetched with ONE 128-bit load instruction per 16 peers: lane L
-// takes bytes [16 (L % 16), +16) of peer L / 16, the workgroup writes them to LDS as
-// [peer][byte], and every lane then reads its own byte of each peer back (LDS staging instead
-// of one byte-wide global load per peer and lane).  No load of a peer's codes depends on
-// another, so a workgroup's life is one round trip to memory however many workers there are,
-// and the memory system sees the packed streams as whole lines.
-//
-// Measured on the VGG-16-shaped list (N = 16, count form): 6.3-6.4 TB/s, where 512-lane
-// workgroups that took a whole chunk, two quads per lane and a byte load per peer, reached
-// 6.0 TB/s; with one wave per piece (64 bytes per peer, half a line) 5.8-6.0 TB/s.
-// Waves per piece: four for many workers (two whole lines of every packed stream per workgroup),
-// one for few (N <= 9: the fp32 streams dominate, and they run best in single-wave workgroups).
-constexpr unsigned kPieceWavesMany = CDSGD_PIECE_WAVES;
-constexpr int kFewPeers = CDSGD_FEW_PEERS;
-constexpr unsigned kPeerSlots = 64;  // LDS rows: peers rounded up to a multiple of 16 (63 peers at most)
-static_assert(CDSGD_MAX_WORKERS - 1 <= kPeerSlots, "an LDS row for every peer");
-static_assert(kChunkQuads % (64 * kPieceWavesMany) == 0, "pieces tile a chunk");
+// Bound by HBM (24 + N / 4 bytes per element): every load of a group is in flight at once, so a group's life is the
+// table lookups (chunk, then descriptor and stream pointers), one round trip to memory, the decode and the stores.
+// A persistent grid whose groups fetch the next tile before they finish one is 15 % slower: its groups drift apart,
+// and the streams' requests in flight with them (2^26 elements, N = 16: 0.366 ms against 0.293).
+// Whether the local weights, which do not wait for the sums, are stored before the decode or beside the global ones:
+// before, where the decode is long enough to hide the store and the list of workers short enough for it to matter
+// (1 GiB buckets, t = 0.05, N = 16: 1.161 ms against 1.25; count form 1.194 against 1.150 at their best residencies).
+template <int SZ, int FORM>
+constexpr bool kLocalFirst = SZ == kUpTo16 && FORM != kCount;
 
-template <unsigned kPieceWaves, bool G, bool POW2, bool WRITE_LOCAL, int GT, bool SPARSE>
-__device__ __forceinline__ void fused_piece(const TensorDesc &d, const uint8_t *const *__restrict__ peers,
-                                            int num_peers, int self, size_t quad0, unsigned piece,
-                                            unsigned rem_elems, unsigned rem_bytes, float t, float lr_local,
-                                            float scale, uint8_t *lds)
+template <bool G, int SZ, int WAVES, int FORM, int GT, bool SPARSE>
+__device__ __forceinline__ void fused_tile(const TensorDesc &d, const uint8_t *const *__restrict__ row, int num_workers,
+                                           int self, unsigned chunk, unsigned tile, unsigned rem_elems,
+                                           unsigned rem_bytes, float t, float lr_local, float scale, bool write_local,
+                                           uint8_t *lds)
 {
-    constexpr unsigned kPieceQuads = 64 * kPieceWaves;  // lanes per workgroup, one quad each
-    const unsigned lane = threadIdx.x;
-    const unsigned qi = piece * kPieceQuads + lane;  // quad of the chunk = byte of the chunk's packed streams
+    const unsigned tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const size_t quad0 = (size_t)chunk * kChunkQuads + tile * (64u * WAVES);
     const void *__restrict__ grad = grad_at<GT>(d.grad, quad0);
     float *__restrict__ resid = d.residual + 4 * quad0;
     float *__restrict__ wg = d.w_global + 4 * quad0;
     float *__restrict__ wl = d.w_local + 4 * quad0;
-    uint8_t *__restrict__ pself = d.packed_self + quad0;
-    const int cnt = quad_count<G>(rem_elems, qi);
+    CDSGD_GLOBAL uint8_t *pself = global_ptr(d.packed_self + quad0);
+    const int cnt = quad_count<G>(rem_elems, tid);
 
-    // the peers' bytes of this piece: 16 peers per load instruction
-    constexpr unsigned kParts = kPieceQuads / 16;        // 16-byte parts of a peer's bytes of one piece
-    const unsigned part = lane % kParts;                 // which of them this lane fetches
-    const unsigned first = piece * kPieceQuads + 16u * part;  // its first byte within the chunk
-    const int groups = (num_peers + 15) >> 4;
-    uint32_t *bitmaps = reinterpret_cast<uint32_t *>(lds + kPeerSlots * kPieceQuads);  // [peer][8], sparse form only
-    if (SPARSE) {
-        // the segments' bitmaps first (8 words per peer, one word per lane), through LDS to every lane
-        for (unsigned e = lane; e < 8u * 16u * (unsigned)groups; e += kPieceQuads) {
-            const int p = (int)(e >> 3);
-            bitmaps[e] = p < num_peers ? (reinterpret_cast<const uint32_t *>(peers[p]) +
-                                          (quad0 / kChunkQuads) * kSegStride)[e & 7u]
-                                       : 0u;
-        }
-        if (kPieceWaves == 1) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        } else {
-            __syncthreads();
-        }
-    }
-    u4 cw[kPeerSlots / 16];
-#pragma unroll
-    for (int gI = 0; gI < (int)(kPeerSlots / 16); ++gI) {
-        cw[gI] = u4{0u, 0u, 0u, 0u};
-        const int p = 16 * gI + (int)(lane / kParts);
-        if (SPARSE) {
-            // the peer's stream is in the sparse form: rebuild the lane's four packed words from the
-            // segment of this chunk (pad words past the end of the stream have no bit set)
-            if (gI < groups && p < num_peers)
-                cw[gI] = sparse_words4(reinterpret_cast<const uint32_t *>(peers[p]) + (quad0 / kChunkQuads) * kSegStride,
-                                       bitmaps + (16u * gI + lane / kParts) * 8u, first >> 2);
-        } else if (gI < groups && p < num_peers) {
-            const uint8_t *src = peers[p] + quad0 + first;
-            if (!G || first + 16u <= rem_bytes) {
-                typedef unsigned u4a __attribute__((ext_vector_type(4), aligned(4)));
-                cw[gI] = *reinterpret_cast<const u4a *>(src);
-            } else {
-                // ragged end of the stream (a whole number of 32-bit words): word by word
-#pragma unroll
-                for (unsigned i = 0; i < 4; ++i)
-                    if (first + 4u * i < rem_bytes) cw[gI][i] = *reinterpret_cast<const unsigned *>(src + 4u * i);
-            }
-        }
-    }
-
-    f4 g = ldgrad<G, GT>(grad, qi, cnt);
-    f4 r = ld4g<G>(resid, qi, cnt);
-    const f4 w = ld4g<G>(wg, qi, cnt);
+    TileStreams s;
+    s.row = row;
+    s.num_workers = num_workers;
+    s.stream_bytes = d.ext.full_chunks * kChunkQuads + d.ext.tail_bytes;
+    s.tile_at = (unsigned)quad0;
+    s.segment_at = (size_t)chunk * (4u * kSegStride);
+    s.tile = tile;
+    unsigned words[kWordsPerWave<SZ>];
+    load_words<SZ, WAVES, SPARSE>(words, s, wave, tid & 63u);
+    const f4 g = ldgrad<G, GT>(grad, tid, cnt);
+    f4 r = ld4g<G>(resid, tid, cnt);
+    const f4 w = ld4g<G>(wg, tid, cnt);
 
     // own codes: quantise, keep the residual, write what would be pushed
     f4 sent;
     const unsigned own = quantize_quad(g, r, t, sent);
-    st4g<G>(resid, qi, cnt, r);
-    if (!G || qi < rem_bytes) pself[qi] = (uint8_t)own;
-
-    // stage the peers' bytes: row p of the LDS block holds peer p's bytes of this piece
-#pragma unroll
-    for (int gI = 0; gI < (int)(kPeerSlots / 16); ++gI)
-        if (gI < groups) *reinterpret_cast<u4 *>(lds + (16u * gI + lane / kParts) * kPieceQuads + 16u * part) = cw[gI];
-    if (kPieceWaves == 1) {
-        // one wave per workgroup: a wave-level release / acquire pair orders its LDS writes before its reads
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    } else {
-        __syncthreads();
-    }
-
-    f4 agg = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (POW2) {
-        // count form: four workers' bytes side by side in one register; field k of acc[c] collects
-        // 2 + value for element c of the workers in byte position k
-        unsigned acc[4] = {0u, 0u, 0u, 0u};
-        auto add4 = [&](unsigned w4) {
-            const unsigned z = ((w4 & 0x55555555u) | 0xAAAAAAAAu) - ((w4 >> 1) & 0x55555555u);
-            acc[0] += z & 0x03030303u;
-            acc[1] += (z >> 2) & 0x03030303u;
-            acc[2] += (z >> 4) & 0x03030303u;
-            acc[3] += (z >> 6) & 0x03030303u;
-        };
-        add4(own);  // the own byte and three empty positions
-        const int words = (num_peers + 3) >> 2;
-        for (int q = 0; q < words; ++q) {
-            const uint8_t *row = lds + (4u * q) * kPieceQuads + lane;
-            const unsigned w4 = (unsigned)row[0] | ((unsigned)row[kPieceQuads] << 8) |
-                                ((unsigned)row[2 * kPieceQuads] << 16) | ((unsigned)row[3 * kPieceQuads] << 24);
-            add4(w4);
-        }
-        // every position added 2 whether a worker stood there or not
-        const float bias_t = -(2.0f * (float)(4 * words + 4)) * t;
-#pragma unroll
-        for (unsigned c = 0; c < 4; ++c) {
-            const unsigned a = acc[c];
-            const unsigned sum = (a & 0xFFu) + ((a >> 8) & 0xFFu) + ((a >> 16) & 0xFFu) + (a >> 24);
-            agg[c] = __builtin_fmaf((float)sum, t, bias_t);
-        }
-    } else {
-        // literal chain: one rounded add per worker and element, worker order, own codes at `self`
-        auto chain = [&](unsigned b) {
-            const unsigned sf = signed_fields(b);
-#pragma unroll
-            for (unsigned c = 0; c < 4; ++c) {
-                const int m = ((int)(sf << (30u - 2u * c))) >> 30;
-                agg[c] = __builtin_fmaf((float)m, t, agg[c]);
-            }
-        };
-        for (int p = 0; p < self; ++p) chain(lds[(unsigned)p * kPieceQuads + lane]);
-        agg = agg + sent;
-        for (int p = self; p < num_peers; ++p) chain(lds[(unsigned)p * kPieceQuads + lane]);
-    }
+    st4g<G>(resid, tid, cnt, r);
+    if (!G || tid < rem_bytes) pself[tid] = (uint8_t)own;
 
     // eq. 11 and eq. 10 from the same loaded weight
     f4 vl, vg;
 #pragma unroll
-    for (unsigned c = 0; c < 4; ++c) {
-        vl[c] = __builtin_fmaf(-lr_local, g[c], w[c]);
-        vg[c] = __builtin_fmaf(-scale, agg[c], w[c]);
-    }
-    if (WRITE_LOCAL) st4g<G>(wl, qi, cnt, vl);
-    st4g<G>(wg, qi, cnt, vg);
-    // the next piece of this workgroup overwrites the LDS block: keep its writes behind these reads
-    if (kPieceWaves == 1) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    } else {
-        __syncthreads();
-    }
+    for (unsigned c = 0; c < 4; ++c) vl[c] = __builtin_fmaf(-lr_local, g[c], w[c]);
+    if (kLocalFirst<SZ, FORM> && write_local) st4g<G>(wl, tid, cnt, vl);
+
+    const f4 agg = tile_sums<SZ, FORM, WAVES>(words, own, sent, self, num_workers, t, lds);
+#pragma unroll
+    for (unsigned c = 0; c < 4; ++c) vg[c] = __builtin_fmaf(-scale, agg[c], w[c]);
+    if (!kLocalFirst<SZ, FORM> && write_local) st4g<G>(wl, tid, cnt, vl);
+    st4g<G>(wg, tid, cnt, vg);
 }
 
-// The compressed pass over the pieces a workgroup takes (the body of the two kernels below).
-template <unsigned kPieceWaves, bool POW2, bool WRITE_LOCAL, int GT, bool SPARSE>
-__device__ __forceinline__ void compressed_pass(const TensorDesc *__restrict__ tensors,
-                                                const ChunkRef *__restrict__ chunks, unsigned long long num_pieces,
-                                                const uint8_t *const *__restrict__ peers, int num_peers, int self,
-                                                float t_call, float lr_local, float scale)
+// write_local: eq. 11 as well (false: the global half of a split step)
+template <int SZ, int WAVES, int FORM, int GT, bool SPARSE>
+__global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDesc *__restrict__ tensors,
+                                                                 const ChunkRef *__restrict__ chunks,
+                                                                 const uint8_t *const *__restrict__ rows,
+                                                                 unsigned num_tiles, unsigned grid, int num_workers,
+                                                                 int self, float t_call, float lr_local, float scale,
+                                                                 int write_local)
 {
-    constexpr unsigned kPieceQuads = 64 * kPieceWaves;
-    constexpr unsigned kPerChunk = kChunkQuads / kPieceQuads;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[kPeerSlots * kPieceQuads + (SPARSE ? kPeerSlots * 32 : 0)];
-    for (unsigned long long b = blockIdx.x; b < num_pieces; b += gridDim.x) {
-        const unsigned long long x = piece_of_workgroup<true>(b, kPerChunk, num_pieces);
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kTileLds<SZ, FORM, WAVES>];
+    constexpr unsigned kQuads = 64u * WAVES, kPerChunk = kChunkQuads / kQuads;
+    for (unsigned b = blockIdx.x;;) {
+        const unsigned x = piece_of_workgroup<true>(b, kPerChunk, num_tiles);
         const ChunkRef cr = chunks[x / kPerChunk];
         const TensorDesc d = tensors[cr.tensor];
-        const size_t quad0 = (size_t)cr.chunk * kChunkQuads;
-        const unsigned piece = (unsigned)(x % kPerChunk);
-        const uint8_t *const *tp = peers + (size_t)cr.tensor * (size_t)num_peers;
+        const unsigned tile = x % kPerChunk;
+        const uint8_t *const *row = rows + (size_t)cr.tensor * row_entries(num_workers);
         const float t = d.threshold > 0.0f ? d.threshold : t_call;
         if (cr.chunk < d.ext.full_chunks) {
-            fused_piece<kPieceWaves, false, POW2, WRITE_LOCAL, GT, SPARSE>(d, tp, num_peers, self, quad0, piece, kChunkElems,
-                                                                   kChunkQuads, t, lr_local, scale, lds);
-        } else if (piece * kPieceQuads < d.ext.tail_bytes) {
-            // (the packed bytes of the ragged end cover its elements: pieces past them have nothing to do)
-            fused_piece<kPieceWaves, true, POW2, WRITE_LOCAL, GT, SPARSE>(d, tp, num_peers, self, quad0, piece,
-                                                                  d.ext.tail_elems, d.ext.tail_bytes, t, lr_local,
-                                                                  scale, lds);
+            fused_tile<false, SZ, WAVES, FORM, GT, SPARSE>(d, row, num_workers, self, cr.chunk, tile, kQuads * 4u, kQuads,
+                                                    t, lr_local, scale, write_local != 0, lds);
+        } else if (tile * kQuads < d.ext.tail_bytes) {
+            // (the packed bytes of the ragged end cover its elements: tiles past them have nothing to do)
+            const unsigned elems0 = tile * kQuads * 4u;
+            fused_tile<true, SZ, WAVES, FORM, GT, SPARSE>(d, row, num_workers, self, cr.chunk, tile,
+                                                   d.ext.tail_elems > elems0 ? d.ext.tail_elems - elems0 : 0u,
+                                                   d.ext.tail_bytes - tile * kQuads, t, lr_local, scale,
+                                                   write_local != 0, lds);
         }
+        if (num_tiles - b <= grid) break;
+        b += grid;
+        group_sync<WAVES>();  // the next tile overwrites the LDS block
     }
-}
-
-// Waves per SIMD.  With up to 16 peers the count form is left to what its registers allow (5 for packed
-// peers, 6 for sparse ones: forcing 4, 6, 7 or 8 on the packed form is 0-4 % slower, forcing 5 on the
-// sparse one 6 %); the literal chain has three times the arithmetic per worker and runs 3 % faster with
-// the registers squeezed for 6 (4 GiB bucket: 4.70 against 4.84 ms).
-template <unsigned kPieceWaves, bool POW2, bool WRITE_LOCAL, int GT, bool SPARSE>
-__attribute__((amdgpu_waves_per_eu(POW2 ? 1 : 6, POW2 ? 8 : 6)))
-__global__ __launch_bounds__(64 * kPieceWaves) void k_fused_compressed(const TensorDesc *__restrict__ tensors,
-                                                                       const ChunkRef *__restrict__ chunks,
-                                                                       unsigned long long num_pieces,
-                                                                       const uint8_t *const *__restrict__ peers,
-                                                                       int num_peers, int self, float t_call,
-                                                                       float lr_local, float scale)
-{
-    compressed_pass<kPieceWaves, POW2, WRITE_LOCAL, GT, SPARSE>(tensors, chunks, num_pieces, peers, num_peers, self,
-                                                                t_call, lr_local, scale);
-}
-
-// The count form for more than 16 peers: the decode's arithmetic grows with the workers, and the same
-// squeeze to 6 waves per SIMD pays (VGG-16-shaped list, N = 24 / 32 / 48 / 64: 0.745 / 0.747 / 0.687 / 0.648
-// of peak as the kernel above, 0.779 / 0.777 / 0.732 / 0.705 as this one).
-template <bool WRITE_LOCAL, int GT, bool SPARSE>
-__attribute__((amdgpu_waves_per_eu(6, 6)))
-__global__ __launch_bounds__(64 * kPieceWavesMany) void k_fused_compressed_many(const TensorDesc *__restrict__ tensors,
-                                                                                const ChunkRef *__restrict__ chunks,
-                                                                                unsigned long long num_pieces,
-                                                                                const uint8_t *const *__restrict__ peers,
-                                                                                int num_peers, int self, float t_call,
-                                                                                float lr_local, float scale)
-{
-    compressed_pass<kPieceWavesMany, true, WRITE_LOCAL, GT, SPARSE>(tensors, chunks, num_pieces, peers, num_peers, self,
-                                                                    t_call, lr_local, scale);
 }
 
 // Passes that use the workers' 32-bit gradients (Alg. 1: WARMUP passes and the

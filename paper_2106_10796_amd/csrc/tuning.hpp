@@ -25,12 +25,6 @@
 #ifndef CDSGD_XCD_FULL
 #define CDSGD_XCD_FULL 0
 #endif
-#ifndef CDSGD_PIECE_WAVES
-#define CDSGD_PIECE_WAVES 4
-#endif
-#ifndef CDSGD_FEW_PEERS
-#define CDSGD_FEW_PEERS 8
-#endif
 #ifndef CDSGD_XCD_PIECES
 #define CDSGD_XCD_PIECES 1
 #endif
