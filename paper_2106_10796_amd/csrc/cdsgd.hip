@@ -21,9 +21,8 @@
 //     lane: "tiles" of 256 lanes for the compressed pass (the peers' codes are
 //     decoded word by word, decode_tile.hpp), "pieces" of one wave for the
 //     passes on 32-bit gradients.
-//   * Of the single-tensor kernels, decode-and-sum gives a chunk to a
-//     workgroup of kBlock lanes, lane `tid` taking quads j*kBlock + tid;
-//     quantise-and-pack and the update work in single-wave pieces.
+//   * Of the single-tensor kernels, decode-and-sum works in the same tiles,
+//     quantise-and-pack and the update in single-wave pieces.
 // Either way every wave instruction on an fp32 buffer touches one contiguous
 // 1 KiB span: all traffic is fully coalesced.
 //
@@ -135,13 +134,9 @@ inline Extent extent_of_units(size_t n, unsigned unit_quads)
 constexpr unsigned long long kMaxGrid = 0xFFFFFFFFull / 1024;
 constexpr unsigned kQuantLanes = 64;   // lanes = quads of a piece of k_quantize_pack
 constexpr unsigned kUpdateLanes = 64;  // ... and of k_update
-// lanes of k_decode_sum's workgroup (one chunk): measured on 2^27 elements, N = 16, count form 6.03 TB/s with
-// 512 lanes and 5.78 with 256; literal chain 4.66 with 512 and 5.40 with 256 (more workgroups resident to
-// hide its arithmetic)
-constexpr unsigned kDecodeLanesCount = 512, kDecodeLanesChain = 256;
-// ... and of k_decode_sum_sparse's: 256 either way (count form, nothing sent / every word sent: 4.15 / 5.66 TB/s of
-// the bytes moved against 3.76 / 4.53 with 512)
-constexpr unsigned kSparseLanes = 256;
+// Tensors and lists of more tiles (1024 elements each) than this are long: their streams pass the 256 MB
+// memory-side cache by far, and the order in which they are read and written decides.
+constexpr unsigned kLongListTiles = 28u * 1024u;
 
 // A threshold 2^e (moderate e): every multiple m*t, |m| <= 2*CDSGD_MAX_WORKERS, is exact.
 inline bool is_pow2_threshold(float t)
@@ -327,6 +322,33 @@ int launch_full_pass(const PlanTables *plan, int local_mode, float lr_local, flo
     return launch_status();
 }
 
+// a4 for one tensor on checked arguments.
+template <bool SPARSE>
+int launch_decode_sum(const uint32_t *const *streams, int num_workers, float *agg, size_t n, float threshold, void *hip_stream)
+{
+    StreamTable tab;
+    std::memset(&tab, 0, sizeof(tab));
+    for (int j = 0; j < num_workers; ++j) tab.p[j] = reinterpret_cast<const uint8_t *>(streams[j]);
+    const unsigned tiles = (unsigned)units_of(n, kTileQuads);
+    const Extent ext = extent_of(n);
+    const int xcd = SPARSE || tiles > kLongListTiles ? 1 : 0;
+#define CDSGD_LAUNCH_DECODE(SZ, FORM)                                                                          \
+    hipLaunchKernelGGL((k_decode_sum<SZ, FORM, SPARSE>), dim3(tiles), dim3(kTileQuads), 0, (hipStream_t)hip_stream, \
+                       tab, num_workers, agg, ext, tiles, xcd, threshold)
+#define CDSGD_LAUNCH_DECODE_N(FORM)                                                                            \
+    do {                                                                                                       \
+        if (num_workers <= kUpTo8) CDSGD_LAUNCH_DECODE(kUpTo8, FORM);                                           \
+        else if (num_workers <= kUpTo16) CDSGD_LAUNCH_DECODE(kUpTo16, FORM);                                    \
+        else CDSGD_LAUNCH_DECODE(kAnyWorkers, FORM);                                                            \
+    } while (0)
+    if (is_pow2_threshold(threshold)) CDSGD_LAUNCH_DECODE_N(kCount);
+    else if (!is_tiny_threshold(threshold)) CDSGD_LAUNCH_DECODE_N(kChain);
+    else CDSGD_LAUNCH_DECODE(kAnyWorkers, kChainTiny);
+#undef CDSGD_LAUNCH_DECODE_N
+#undef CDSGD_LAUNCH_DECODE
+    return launch_status();
+}
+
 }  // namespace
 
 #ifndef CDSGD_BUILD_ID_HEX
@@ -392,18 +414,7 @@ int cdsgd_decode_sum(const uint32_t *const *packed, int num_workers, float *agg,
         if (!aligned(packed[j], 4)) return CDSGD_ERR_ALIGN;
     for (int j = 0; j < num_workers; ++j)
         if (overlap2(packed[j], (size_t)packed_bytes_of(n), agg, n * sizeof(float))) return CDSGD_ERR_ALIAS;
-    StreamTable tab;
-    std::memset(&tab, 0, sizeof(tab));
-    for (int j = 0; j < num_workers; ++j) tab.p[j] = reinterpret_cast<const uint8_t *>(packed[j]);
-    const float bias_t = -(2.0f * (float)num_workers) * threshold;
-    const unsigned grid = (unsigned)chunks_of(n);
-    if (is_pow2_threshold(threshold))
-        hipLaunchKernelGGL((k_decode_sum<true, kDecodeLanesCount>), dim3(grid), dim3(kDecodeLanesCount), 0, (hipStream_t)hip_stream, tab,
-                           num_workers, agg, extent_of(n), threshold, bias_t);
-    else
-        hipLaunchKernelGGL((k_decode_sum<false, kDecodeLanesChain>), dim3(grid), dim3(kDecodeLanesChain), 0, (hipStream_t)hip_stream, tab,
-                           num_workers, agg, extent_of(n), threshold, bias_t);
-    return launch_status();
+    return launch_decode_sum<false>(packed, num_workers, agg, n, threshold, hip_stream);
 }
 
 int cdsgd_update(float *w_global, float *w_local, const float *grad_local, const float *agg, size_t n,
@@ -554,7 +565,7 @@ struct CompressedLaunch {
 CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int form, bool sparse)
 {
     const unsigned tiles = num_chunks * kTilesPerChunk;  // of 1024 elements
-    const bool long_list = tiles > 28u * 1024u;
+    const bool long_list = tiles > kLongListTiles;
     if (sparse) return {4u, long_list && num_workers <= kUpTo16 ? 32768u : 0u};
     if (num_workers <= kUpTo8 && form != kChainTiny) {
         if (tiles <= 16u * 1024u) return {4u, 0u};
@@ -788,18 +799,7 @@ int cdsgd_decode_sum_sparse(const uint32_t *const *sparse, int num_workers, floa
         if (!aligned(sparse[j], 4)) return CDSGD_ERR_ALIGN;
     for (int j = 0; j < num_workers; ++j)
         if (overlap2(sparse[j], cdsgd_sparse_words(n) * 4, agg, n * sizeof(float))) return CDSGD_ERR_ALIAS;
-    StreamTable tab;
-    std::memset(&tab, 0, sizeof(tab));
-    for (int j = 0; j < num_workers; ++j) tab.p[j] = reinterpret_cast<const uint8_t *>(sparse[j]);
-    const unsigned grid = (unsigned)chunks_of(n);
-    const float bias_t = -(2.0f * (float)num_workers) * threshold;
-    if (is_pow2_threshold(threshold))
-        hipLaunchKernelGGL((k_decode_sum_sparse<true, kSparseLanes>), dim3(grid), dim3(kSparseLanes), 0, (hipStream_t)hip_stream, tab,
-                           num_workers, agg, extent_of(n), threshold, bias_t);
-    else
-        hipLaunchKernelGGL((k_decode_sum_sparse<false, kSparseLanes>), dim3(grid), dim3(kSparseLanes), 0, (hipStream_t)hip_stream, tab,
-                           num_workers, agg, extent_of(n), threshold, bias_t);
-    return launch_status();
+    return launch_decode_sum<true>(sparse, num_workers, agg, n, threshold, hip_stream);
 }
 
 int cdsgd_plan_set_peer_format(cdsgd_plan *plan, int format)

@@ -18,6 +18,16 @@ constexpr int kMaxRows = SZ == kAnyWorkers ? CDSGD_MAX_WORKERS : SZ;
 template <int SZ>
 constexpr int kWordsPerWave = kMaxRows<SZ> / 4;
 
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+
+// values of the codes of a register, as 2-bit two's-complement fields (01 -> +1, 10 -> -1, else 0)
+__device__ __forceinline__ unsigned signed_fields(unsigned w)
+{
+    const unsigned x = w & 0x55555555u;
+    const unsigned y = (w >> 1) & 0x55555555u;
+    return (x ^ y) | ((y & ~x) << 1);
+}
+
 // A row of stream pointers: one entry per worker, in worker order, null where there is nothing to load (the own
 // entry, and the entries past the last worker up to a whole batch).
 inline constexpr unsigned row_entries(int num_workers)
@@ -341,6 +351,48 @@ __device__ __forceinline__ f4 tile_sums(const unsigned (&w)[kWordsPerWave<SZ>], 
         }
     }
     return agg;
+}
+
+// ---------------------------------------------------------------------------
+// a4 for one tensor, packed or sparse streams: a tile per group of four waves
+// ---------------------------------------------------------------------------
+// Bound by HBM (4 + N / 4 bytes per element).  Measured, this kernel with the global update behind it, against the
+// former one (a chunk per workgroup, bytes staged through LDS): 2^24 elements, N = 32, t = 0.1 86.0 -> 72 us, t = 0.5
+// 73 -> 69; N = 64 128 -> 98 and 101 -> 94; N = 8 48.5 -> 47.2; sparse N = 32 75.6 -> 74.8; 2^27 elements, N = 16 as
+// before.  A bound on the resident groups never helps here (2^24, N = 32, t = 0.1: 83 us with 5 per compute unit).
+// xcd: which order the tiles are dealt in.  The chunk-wise order pays where the tiles of a chunk share its segment
+// (sparse streams), and on long tensors (2^27 elements, N = 16: 421 against 428 us); on shorter ones the plain order
+// is 1 % faster (2^24: 71.5 against 72.5).
+// The workers' stream pointers of a single-tensor call; they travel in the kernel arguments.
+struct StreamTable {
+    const uint8_t *p[CDSGD_MAX_WORKERS];  // null past the last worker
+};
+
+template <int SZ, int FORM, bool SPARSE>
+__global__ __launch_bounds__(kTileQuads) void k_decode_sum(StreamTable tab, int num_workers, float *__restrict__ agg_out,
+                                                           Extent ext, unsigned num_tiles, int xcd, float t)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kTileLds<SZ, FORM, 4>];
+    const unsigned tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const unsigned x = xcd ? piece_of_workgroup<true>(blockIdx.x, kTilesPerChunk, num_tiles) : blockIdx.x;
+    const unsigned chunk = x / kTilesPerChunk;
+    TileStreams s;
+    s.row = tab.p;
+    s.num_workers = num_workers;
+    s.stream_bytes = ext.full_chunks * kChunkQuads + ext.tail_bytes;
+    s.tile_at = x * kTileBytes;
+    s.segment_at = (size_t)chunk * (4u * kSegStride);
+    s.tile = x % kTilesPerChunk;
+    unsigned words[kWordsPerWave<SZ>];
+    load_words<SZ, 4, SPARSE>(words, s, wave, tid & 63u);
+    const f4 agg = tile_sums<SZ, FORM, 4>(words, 0u, f4{0.0f, 0.0f, 0.0f, 0.0f}, -1, num_workers, t, lds);
+    float *out = agg_out + (size_t)x * (4u * kTileQuads);
+    if (chunk < ext.full_chunks) st4(out, tid, agg);
+    else {
+        const unsigned e0 = s.tile * 4u * kTileQuads;
+        st4g<true>(out, tid, quad_count<true>(ext.tail_elems > e0 ? ext.tail_elems - e0 : 0u, tid), agg);
+    }
 }
 
 }  // namespace

@@ -40,6 +40,23 @@ struct ChunkRef {
 // in steps of the grid size.  Normally the grid has one workgroup per piece and the loop runs
 // once; a plan with a workgroup limit (cdsgd_plan_set_max_workgroups) launches fewer
 // workgroups, which then take several pieces each and leave compute units free for other
-// kernels.  How pieces are dealt to the 8 XCDs is piece_of_workgroup's business.
+// kernels.  How pieces are dealt to the 8 XCDs is piece_of_workgroup's business:
+
+// Which part (tile or piece) of the chunk table workgroup b takes.  Workgroup b runs on XCD b % 8.  Within
+// a block of 8 chunks' worth of workgroups, XCD k takes every part of chunk k, so that the parts' reads of
+// the chunk's table entries and of shared 128-byte lines of a peer's codes meet in one L2 (compressed pass on
+// 1 GiB buckets, N = 16: 1.150 ms against 1.25 in the plain order).  The last, incomplete block keeps the
+// plain order.  A bijection on [0, num_pieces) for any grid size.
+template <bool XCD, typename T>
+__device__ __forceinline__ T piece_of_workgroup(T b, unsigned per_chunk, T num_pieces)
+{
+    if (!XCD) return b;
+#if CDSGD_XCD_PIECES
+    const T group = (T)8 * per_chunk;
+    const T blk = b / group, within = b % group;
+    if ((blk + 1) * group <= num_pieces) return (blk * 8 + within % 8) * per_chunk + within / 8;
+#endif
+    return b;
+}
 
 }  // namespace

@@ -3,23 +3,6 @@
 
 namespace {
 
-// Which part (tile or piece) of the chunk table workgroup b takes.  Workgroup b runs on XCD b % 8.  Within
-// a block of 8 chunks' worth of workgroups, XCD k takes every part of chunk k, so that the parts' reads of
-// the chunk's table entries and of shared 128-byte lines of a peer's codes meet in one L2 (compressed pass on
-// 1 GiB buckets, N = 16: 1.150 ms against 1.25 in the plain order).  The last, incomplete block keeps the
-// plain order.  A bijection on [0, num_pieces) for any grid size.
-template <bool XCD, typename T>
-__device__ __forceinline__ T piece_of_workgroup(T b, unsigned per_chunk, T num_pieces)
-{
-    if (!XCD) return b;
-#if CDSGD_XCD_PIECES
-    const T group = (T)8 * per_chunk;
-    const T blk = b / group, within = b % group;
-    if ((blk + 1) * group <= num_pieces) return (blk * 8 + within % 8) * per_chunk + within / 8;
-#endif
-    return b;
-}
-
 // ---------------------------------------------------------------------------
 // Fused compressed step (a1-a6), one group of waves per tile of a chunk
 // ---------------------------------------------------------------------------

@@ -50,8 +50,6 @@ constexpr size_t kStaticOffPeers = round256(kStaticOffStart + sizeof(unsigned) *
 constexpr size_t kStaticOffChunks =
     round256(kStaticOffPeers + sizeof(void *) * ((size_t)kStaticMaxTensors * row_entries(CDSGD_MAX_WORKERS) + CDSGD_MAX_WORKERS) + 16);
 constexpr size_t kStaticBytes = kStaticOffChunks + sizeof(ChunkRef) * (size_t)kStaticMaxChunks;
-#if CDSGD_BLOCK == 512 && CDSGD_QPL == 2
 static_assert(kChunkElems == CDSGD_STATIC_CHUNK_ELEMS, "the header states the chunk size the limit is counted in");
-#endif
 
 }  // namespace

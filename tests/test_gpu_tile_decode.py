@@ -65,6 +65,13 @@ def test_compressed_pass_at_tile_and_batch_edges(B, oracle, N, t, sparse):
         for key, ref in zip(("residual", "packed_self", "w_global", "w_local"), want[i]):
             ref = ref.view(np.int32) if key == "packed_self" else ref
             assert_bits_equal(layers[i][key].cpu().numpy(), ref, "%s N=%d self=%d n=%d t=%g" % (key, N, self_rank, n, t))
+        # the same streams through the single-tensor call
+        full = torch.full((n + 8,), 9.0, device="cuda")
+        decode = B.cdsgd_decode_sum_sparse if sparse else B.cdsgd_decode_sum
+        decode([on_gpu(streams[j][i], n) for j in range(N)], full[:n], t)
+        agg = oracle.decode_sum([streams[j][i] for j in range(N)], n, t)
+        assert_bits_equal(full[:n].cpu().numpy(), agg, "agg N=%d n=%d t=%g" % (N, n, t))
+        assert bool((full[n:] == 9.0).all())
     plan.destroy()
 
 
