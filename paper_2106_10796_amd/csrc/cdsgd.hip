@@ -68,13 +68,14 @@ namespace {
 //   correction pass with agg_full   6.42-6.45 / 6.40 / 6.51 / 6.66-6.67 / 6.55 / 6.55-6.60 / 6.41 / 5.88
 //   quantise-and-pack               6.71 / 6.72 / - / 6.83 / - / 6.88 / 6.09 / 5.10
 //   update, both rules              6.36 / 6.34 / - / 6.55 / - / 6.50 / 6.55 / 6.18
-//   correction pass, sum in kernel  6.19 / 6.39-6.41 / 6.35 / 6.24 / - / 5.97
+//   correction pass, sum in kernel  6.19 / 6.39-6.41 / 6.35 / 6.24 / - / 5.97   (by size and type: lds_of_kernel_sum)
 // eq. 11 alone loses with any bound and gets none; the compressed pass has a rule of its own (compressed_launch).  The same bound stated to the compiler instead (amdgpu_waves_per_eu with a maximum of
 // 5) gives 6.55 and 6.45 TB/s on the first and the third line: most of the gain, not all of it.  While a
 // pass launched this way runs it holds the compute units' LDS, so a kernel of another stream that needs
 // LDS waits for it; a pass with a workgroup limit (cdsgd_plan_set_max_workgroups), which is meant to run
 // beside other kernels, is launched without the bound.
 constexpr unsigned kLdsFor20Waves = 8192;
+constexpr unsigned kLdsFor22Waves = 7168;
 constexpr unsigned kLdsFor26Waves = 6144;
 
 inline bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
@@ -285,6 +286,23 @@ TensorDesc make_desc(const cdsgd_tensor &t)
     return d;
 }
 
+// LDS bound of a pass that sums the workers' gradients in the kernel.  Measured, time of the pass with 26 waves per
+// compute unit over its time with 0 (32 waves) / 6 / 7 / 8 KiB (26, 22 and 20 waves):
+//   32-bit   VGG-16-shaped, N = 4 / 8 / 16   0.99 0.99 0.97 / 1.00 1.00 1.00 / 1.02 1.02 1.02 / 1.04 1.05 1.00
+//            25 M elements, N = 8 / 16       0.99 0.99 / 1.00 1.01 / 1.01 1.02 / 1.00 1.00
+//            4 M elements, N = 8 / 16        1.01 1.01 / 1.01 1.01 / 0.95 0.94 / 0.97 0.98
+//   16-bit   VGG-16-shaped, N = 8 / 16       0.99 1.05 / 1.00 1.07 / 1.01 1.08 / 1.02 1.07
+//   (pairs)  25 M elements, N = 8 / 16       1.04 1.08 / 1.04 1.08 / 1.03 1.07 / 1.02 1.05;  N = 2 0.98 / 1.00 / 1.00 / 1.00
+//            4 M elements, N = 8             1.13 / 1.10 / 1.02 / 1.02
+unsigned lds_of_kernel_sum(unsigned num_chunks, int num_workers, int grad_type)
+{
+    const unsigned tiles = num_chunks * kTilesPerChunk;
+    const bool short_list = tiles <= 6u * 1024u, long_list = tiles > kLongListTiles;
+    if (grad_type != kGradF32) return short_list ? 0u : (long_list ? kLdsFor22Waves : kLdsFor26Waves);
+    if (short_list) return kLdsFor26Waves;
+    return long_list && num_workers <= 8 ? kLdsFor20Waves : kLdsFor22Waves;
+}
+
 // Launch one full-gradient pass (see k_fused_full) for a plan.
 int launch_full_pass(const PlanTables *plan, int local_mode, float lr_local, float lr_global, void *hip_stream)
 {
@@ -297,7 +315,7 @@ int launch_full_pass(const PlanTables *plan, int local_mode, float lr_local, flo
     const int np = plan->num_workers - 1;
     // a pass with a workgroup limit is meant to share the GPU with other kernels: it leaves the LDS to them
     const unsigned lds_plain = plan->max_workgroups ? 0u : kLdsFor20Waves;
-    const unsigned lds_sum = plan->max_workgroups ? 0u : kLdsFor26Waves;
+    const unsigned lds_sum = plan->max_workgroups ? 0u : lds_of_kernel_sum(plan->num_chunks, plan->num_workers, plan->grad_type);
 #define CDSGD_LAUNCH_FULL_T(SUM, LOCAL, GT)                                                                    \
     hipLaunchKernelGGL((k_fused_full<SUM, LOCAL, GT>), grid, block, (SUM ? lds_sum : lds_plain), s,              \
                        plan->tensors, plan->chunk_table(),                                                      \

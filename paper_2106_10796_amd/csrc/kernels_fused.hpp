@@ -120,7 +120,10 @@ constexpr int kLocalOnly = 3;  // eq. 11 alone: w_local = W - lr_local * g, the 
 // the requests in flight chip-wide fall on one or two streams at a time instead of all N.
 // On the VGG-16-shaped list with 16 workers the sum runs at 6.2-6.3 TB/s that way; with 15
 // loads in flight per wave it ran at 5.6 TB/s, and with 512-lane workgroups, two quads per lane
-// and 8 loads in flight at 5.6-5.7 TB/s.
+// and 8 loads in flight at 5.6-5.7 TB/s.  Two at a time and fewer waves (13 per compute unit) give the
+// same with 32-bit gradients (8 workers 0.942 ms against 0.947; 25 M elements 0.180 against 0.182) and are
+// better with 16-bit ones, whose loads are half as large (25 M elements, N = 16: 0.186 ms against 0.190,
+// and 0.203 with one at a time and 26 waves; 4 M elements, N = 8: 20.5 us against 21.1 and 23.1).
 constexpr unsigned kFullBlock = CDSGD_FULL_BLOCK;            // lanes per workgroup = quads per piece
 constexpr unsigned kPiecesPerChunk = kChunkQuads / kFullBlock;
 static_assert(kChunkQuads % kFullBlock == 0 && kFullBlock % 64 == 0, "pieces tile a chunk, whole waves");
@@ -148,10 +151,21 @@ __device__ __forceinline__ void full_piece(const TensorDesc &d, const void *cons
     }
     if (!SUM) a = ld4g<G>(d.agg_full + 4 * quad0, qi, cnt);
     if (SUM) {
-        // one gradient at a time, each add waiting for its load: see the note on the launch shape
-        for (int p = 0; p < self; ++p) a = a + ldgrad<G, GT>(grad_at<GT>(pg[p], quad0), qi, cnt);
+        // 32-bit gradients one at a time, each add waiting for its load, 16-bit ones (half the bytes a load) in pairs:
+        // see the note on the launch shape
+        const auto add = [&](int p, int end) {
+            if (GT != kGradF32)
+                for (; p + 1 < end; p += 2) {
+                    const f4 u = ldgrad<G, GT>(grad_at<GT>(pg[p], quad0), qi, cnt);
+                    const f4 v = ldgrad<G, GT>(grad_at<GT>(pg[p + 1], quad0), qi, cnt);
+                    a = a + u;
+                    a = a + v;
+                }
+            for (; p < end; ++p) a = a + ldgrad<G, GT>(grad_at<GT>(pg[p], quad0), qi, cnt);
+        };
+        add(0, self);
         a = a + g;
-        for (int p = self; p < num_peers; ++p) a = a + ldgrad<G, GT>(grad_at<GT>(pg[p], quad0), qi, cnt);
+        add(self, num_peers);
     }
     f4 vg, vl;
 #pragma unroll
