@@ -979,40 +979,98 @@ int static_scratch(unsigned char **out)
     return CDSGD_OK;
 }
 
-// Streams host bytes into a region of the static array through kernel arguments:
-// no host-to-device copy call, no staging memory, nothing a graph capture could not record.
-struct StaticWriter {
-    hipStream_t stream;
-    unsigned char *dst;  // device address the next flush writes to
-    StorePayload buf;
-    unsigned fill = 0;
-    bool ok = true;
+// The offset, in 16 elements, of tensor i's buffers from tensor 0's if every one of them is that far (agg_full
+// everywhere or nowhere), -1 if not.
+long long arena_offset16(const cdsgd_tensor *tensors, int i, const uint32_t *const *const *peers, int num_workers,
+                         int self, unsigned grad_bytes)
+{
+    const cdsgd_tensor &z = tensors[0], &t = tensors[i];
+    const auto diff = [](const void *a, const void *b) {
+        return (long long)(reinterpret_cast<uintptr_t>(a) - reinterpret_cast<uintptr_t>(b));
+    };
+    const long long bytes = diff(t.w_global, z.w_global);
+    if (bytes < 0 || bytes % 64 != 0 || bytes / 64 > 0xFFFFFFFFll) return -1;
+    const long long off = bytes / 64;
+    if (diff(t.w_local, z.w_local) != bytes || diff(t.residual, z.residual) != bytes ||
+        diff(t.grad, z.grad) != off * 16 * (long long)grad_bytes || diff(t.packed_self, z.packed_self) != off * 4)
+        return -1;
+    if ((t.agg_full == nullptr) != (z.agg_full == nullptr) || (t.agg_full && diff(t.agg_full, z.agg_full) != bytes))
+        return -1;
+    for (int j = 0; j < num_workers; ++j)
+        if (j != self && diff(peers[j][i], peers[j][0]) != off * 4) return -1;
+    return off;
+}
 
-    StaticWriter(hipStream_t s, unsigned char *d) : stream(s), dst(d) {}
+template <typename Payload>
+int launch_static_build(const StaticTarget &to, const Payload &p, hipStream_t s)
+{
+    const unsigned work = to.slots > to.count * to.row ? to.slots : to.count * to.row;
+    const unsigned blocks = (work + 255u) / 256u;
+    hipLaunchKernelGGL((k_static_build<Payload>), dim3(blocks < 1024u ? blocks : 1024u), dim3(256), 0, s, to, p);
+    return launch_status();
+}
 
-    void flush()
-    {
-        if (fill == 0) return;
-        while (fill % 16u) reinterpret_cast<unsigned char *>(&buf)[fill++] = 0;
-        hipLaunchKernelGGL(k_static_store, dim3(1), dim3(256), 0, stream, buf, reinterpret_cast<uint4 *>(dst), fill / 16u);
-        ok = ok && hipGetLastError() == hipSuccess;
-        dst += fill;
-        fill = 0;
+// Write the tables of a checked layer list into the static array at `base`.
+int build_static_tables(unsigned char *base, const cdsgd_tensor *tensors, int num_tensors,
+                        const uint32_t *const *const *peers, int num_workers, int self, int grad_dtype, bool with_rows,
+                        hipStream_t s)
+{
+    const unsigned grad_bytes = grad_dtype == CDSGD_GRAD_F32 ? 4u : 2u;
+    StaticTarget to;
+    to.desc = reinterpret_cast<TensorDesc *>(base + kStaticOffDesc);
+    to.chunks = reinterpret_cast<ChunkRef *>(base + kStaticOffChunks);
+    to.rows = reinterpret_cast<const uint8_t **>(base + kStaticOffPeers);
+    to.row = with_rows ? row_entries(num_workers) : 0u;
+    to.workers = with_rows ? (unsigned)num_workers : 0u;
+    to.self = (unsigned)self;
+    to.grad_bytes = grad_bytes;
+    to.slot0 = 0;
+    const int streams = (int)to.workers;
+    const auto bits = [](const void *p) { return (unsigned long long)reinterpret_cast<uintptr_t>(p); };
+    bool arenas = true;
+    for (int i = 1; i < num_tensors && arenas; ++i)
+        arenas = arena_offset16(tensors, i, peers, streams, self, grad_bytes) >= 0;
+    StaticArenas flat;
+    StaticPointers any;
+    if (arenas) {
+        std::memset(&flat, 0, sizeof(flat));
+        const cdsgd_tensor &z = tensors[0];
+        const void *const role[kStaticRoles] = {z.w_global, z.w_local, z.residual, z.grad, z.packed_self, z.agg_full};
+        for (int r = 0; r < kStaticRoles; ++r) flat.role[r] = bits(role[r]);
+        for (int j = 0; j < streams; ++j)
+            if (j != self) flat.stream[j] = bits(peers[j][0]);
+    } else {
+        std::memset(&any, 0, sizeof(any));
     }
-
-    void put(const void *src, unsigned bytes)
-    {
-        const unsigned char *p = static_cast<const unsigned char *>(src);
-        while (bytes) {
-            const unsigned take = bytes < kStorePayload - fill ? bytes : kStorePayload - fill;
-            std::memcpy(reinterpret_cast<unsigned char *>(&buf) + fill, p, take);
-            fill += take;
-            p += take;
-            bytes -= take;
-            if (fill == kStorePayload) flush();
+    const unsigned stride = StaticPointers::stride(to.workers);
+    const unsigned part = arenas ? StaticArenas::kTensors : StaticPointers::kWords / stride;
+    for (int first = 0; first < num_tensors; first += (int)part) {
+        const unsigned left = (unsigned)(num_tensors - first);
+        to.first = (unsigned)first;
+        to.count = left < part ? left : part;
+        to.slots = 0;
+        for (unsigned k = 0; k < to.count; ++k) {
+            const int i = first + (int)k;
+            const cdsgd_tensor &t = tensors[i];
+            if (arenas) {
+                flat.t[k].off16 = i == 0 ? 0u : (unsigned)arena_offset16(tensors, i, peers, streams, self, grad_bytes);
+                flat.t[k].n = (unsigned)t.n;
+                flat.t[k].slot = to.slots;
+            } else {
+                unsigned long long *w = any.w + (size_t)k * stride;
+                const void *const role[kStaticRoles] = {t.w_global, t.w_local, t.residual, t.grad, t.packed_self, t.agg_full};
+                *w++ = (unsigned long long)t.n | (unsigned long long)to.slots << 32;
+                for (int r = 0; r < kStaticRoles; ++r) *w++ = bits(role[r]);
+                for (int j = 0; j < streams; ++j) *w++ = j == self ? 0ull : bits(peers[j][i]);
+            }
+            to.slots += (unsigned)chunks_of(t.n);
         }
+        const int rc = arenas ? launch_static_build(to, flat, s) : launch_static_build(to, any, s);
+        if (rc != CDSGD_OK) return rc;
+        to.slot0 += to.slots;
     }
-};
+    return CDSGD_OK;
+}
 
 }  // namespace
 
@@ -1035,41 +1093,8 @@ extern "C" int cdsgd_step_fused_static(const cdsgd_tensor *tensors, int num_tens
     if (rc != CDSGD_OK) return rc;
     hipStream_t s = (hipStream_t)hip_stream;
 
-    // descriptor table
-    StaticWriter w(s, base + kStaticOffDesc);
-    for (int i = 0; i < num_tensors; ++i) {
-        const TensorDesc d = make_desc(tensors[i]);
-        w.put(&d, sizeof(d));
-    }
-    w.flush();
-    // chunk_start: running count of chunks, num_tensors + 1 entries
-    w.dst = base + kStaticOffStart;
-    unsigned start = 0;
-    for (int i = 0; i < num_tensors; ++i) {
-        w.put(&start, sizeof(start));
-        start += (unsigned)chunks_of(tensors[i].n);
-    }
-    w.put(&start, sizeof(start));
-    w.flush();
-    // the workers' streams, a row per tensor (compressed passes only)
-    if (compressed) {
-        w.dst = base + kStaticOffPeers;
-        const int row = (int)row_entries(num_workers);
-        for (int i = 0; i < num_tensors; ++i)
-            for (int j = 0; j < row; ++j) {
-                const uint8_t *ptr = nullptr;
-                if (j < num_workers && j != self) ptr = reinterpret_cast<const uint8_t *>(peers[j][i]);
-                w.put(&ptr, sizeof(ptr));
-            }
-        w.flush();
-    }
-    if (!w.ok) return CDSGD_ERR_DEVICE;
-    // chunk table, on the device
-    const unsigned total = (unsigned)total_chunks;
-    hipLaunchKernelGGL(k_static_chunks, dim3((total + 255u) / 256u), dim3(256), 0, s,
-                       reinterpret_cast<const unsigned *>(base + kStaticOffStart), num_tensors,
-                       reinterpret_cast<ChunkRef *>(base + kStaticOffChunks), total);
-    if (hipGetLastError() != hipSuccess) return CDSGD_ERR_DEVICE;
+    rc = build_static_tables(base, tensors, num_tensors, peers, num_workers, self, grad_dtype, compressed, s);
+    if (rc != CDSGD_OK) return rc;
 
     PlanTables pt;
     pt.tensors = reinterpret_cast<TensorDesc *>(base + kStaticOffDesc);
@@ -1078,7 +1103,7 @@ extern "C" int cdsgd_step_fused_static(const cdsgd_tensor *tensors, int num_tens
     pt.num_tensors = num_tensors;
     pt.num_workers = num_workers;
     pt.self = self;
-    pt.num_chunks = total;
+    pt.num_chunks = (unsigned)total_chunks;
     pt.has_agg_full = all_agg;
     pt.grad_type = grad_dtype;
     return launch_formal_pass(&pt, step, k, threshold, lr_local, lr_global, true, hip_stream);

@@ -6,49 +6,122 @@ namespace {
 // ---------------------------------------------------------------------------
 // tables built on the device, for the entry point that allocates nothing
 // ---------------------------------------------------------------------------
-// Up to kStorePayload bytes travel in the kernel arguments and are written to dst.
-constexpr unsigned kStorePayload = 3072;
-struct StorePayload {
-    uint4 q[kStorePayload / 16];
+// The layer list travels in the arguments of one or more launches of k_static_build, each of which writes the
+// descriptors, the rows of stream pointers and the chunk table entries of the tensors it carries.  Bound by launches
+// (2-4 us each) and nothing else, so what matters is how many tensors fit the 4 KiB that a kernel's arguments may
+// take.  Lists whose buffers lie in arenas, every buffer of tensor i at the same element offset from tensor 0's (what
+// a program with flat gradient buckets has), need an offset per tensor: 256 tensors a launch.  Any other list needs
+// its pointers: 464 / (7 + workers) tensors a launch.  (ResNet-50-shaped list, N = 8, fp16 gradients: 9 launches of
+// 3 KiB of finished tables and one for the chunk table took 22 us of the call's 113; one launch takes 4.5 of 100.)
+constexpr int kStaticRoles = 6;  // w_global, w_local, residual, grad, packed_self, agg_full
+
+struct StaticTarget {
+    TensorDesc *desc;
+    ChunkRef *chunks;
+    const uint8_t **rows;
+    unsigned first, count;   // tensors [first, first + count) of the list
+    unsigned slot0, slots;   // their entries of the chunk table
+    unsigned row;            // entries of a row of stream pointers; 0: the pass reads none
+    unsigned workers, self, grad_bytes;
 };
 
-__global__ __launch_bounds__(256) void k_static_store(StorePayload p, uint4 *__restrict__ dst, unsigned count16)
-{
-    const unsigned i = threadIdx.x;
-    if (i < count16) dst[i] = p.q[i];
-}
+struct StaticArenas {
+    static constexpr unsigned kTensors = 256;
+    unsigned long long role[kStaticRoles];            // tensor 0's buffers (0: none)
+    unsigned long long stream[CDSGD_MAX_WORKERS];     // tensor 0's stream of every worker
+    struct {
+        unsigned off16, n, slot;  // offset in 16 elements, elements, first chunk table entry (counted from slot0)
+    } t[kTensors];
 
-// chunk_start[i] = number of chunks of tensors 0..i-1 (num_tensors + 1 entries, the last one
-// the total).  Slot s of the chunk table belongs to the tensor i with
-// chunk_start[i] <= s < chunk_start[i + 1].
-__global__ __launch_bounds__(256) void k_static_chunks(const unsigned *__restrict__ chunk_start, int num_tensors,
-                                                       ChunkRef *__restrict__ chunks, unsigned total)
-{
-    const unsigned slot = blockIdx.x * 256u + threadIdx.x;
-    if (slot >= total) return;
-    int lo = 0, hi = num_tensors;  // invariant: chunk_start[lo] <= slot < chunk_start[hi]
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (chunk_start[mid] <= slot) lo = mid;
-        else hi = mid;
+    __device__ unsigned n(unsigned i, unsigned) const { return t[i].n; }
+    __device__ unsigned slot(unsigned i, unsigned) const { return t[i].slot; }
+    __device__ unsigned long long buffer(unsigned i, int r, unsigned grad_bytes, unsigned) const
+    {
+        if (role[r] == 0ull) return 0ull;
+        const unsigned long long off = (unsigned long long)t[i].off16;
+        return role[r] + (r == 4 ? off * 4u : off * 16u * (r == 3 ? grad_bytes : 4u));
     }
-    ChunkRef cr;
-    cr.tensor = (unsigned)lo;
-    cr.chunk = slot - chunk_start[lo];
-    chunks[slot] = cr;
+    __device__ unsigned long long of_worker(unsigned i, unsigned j, unsigned) const
+    {
+        return stream[j] + (unsigned long long)t[i].off16 * 4u;
+    }
+};
+
+struct StaticPointers {
+    static constexpr unsigned kWords = 464;
+    // per tensor: elements and first chunk table entry, the buffers, the workers' streams
+    unsigned long long w[kWords];
+
+    __device__ __host__ static constexpr unsigned stride(unsigned workers) { return 1u + kStaticRoles + workers; }
+    __device__ unsigned n(unsigned i, unsigned workers) const { return (unsigned)w[i * stride(workers)]; }
+    __device__ unsigned slot(unsigned i, unsigned workers) const { return (unsigned)(w[i * stride(workers)] >> 32); }
+    __device__ unsigned long long buffer(unsigned i, int r, unsigned, unsigned workers) const
+    {
+        return w[i * stride(workers) + 1u + (unsigned)r];
+    }
+    __device__ unsigned long long of_worker(unsigned i, unsigned j, unsigned workers) const
+    {
+        return w[i * stride(workers) + 1u + kStaticRoles + j];
+    }
+};
+
+constexpr unsigned kStaticMaxPart = StaticArenas::kTensors;  // most tensors of one launch
+
+template <typename Payload>
+__global__ __launch_bounds__(256) void k_static_build(StaticTarget to, Payload p)
+{
+    __shared__ unsigned starts[kStaticMaxPart];
+    for (unsigned i = threadIdx.x; i < to.count; i += 256u) starts[i] = p.slot(i, to.workers);
+    __syncthreads();
+    const unsigned id = blockIdx.x * 256u + threadIdx.x, step = gridDim.x * 256u;
+    for (unsigned i = id; i < to.count; i += step) {
+        const unsigned n = p.n(i, to.workers);
+        TensorDesc d;
+        d.w_global = reinterpret_cast<float *>(p.buffer(i, 0, to.grad_bytes, to.workers));
+        d.w_local = reinterpret_cast<float *>(p.buffer(i, 1, to.grad_bytes, to.workers));
+        d.residual = reinterpret_cast<float *>(p.buffer(i, 2, to.grad_bytes, to.workers));
+        d.grad = reinterpret_cast<const void *>(p.buffer(i, 3, to.grad_bytes, to.workers));
+        d.packed_self = reinterpret_cast<uint8_t *>(p.buffer(i, 4, to.grad_bytes, to.workers));
+        d.agg_full = reinterpret_cast<const float *>(p.buffer(i, 5, to.grad_bytes, to.workers));
+        d.ext.full_chunks = n / kChunkElems;
+        d.ext.tail_elems = n % kChunkElems;
+        d.ext.tail_bytes = (d.ext.tail_elems + 15u) / 16u * 4u;
+        d.ext.pad_ = 0u;
+        d.threshold = 0.0f;
+        d.pad_ = 0u;
+        to.desc[to.first + i] = d;
+    }
+    for (unsigned e = id; e < to.count * to.row; e += step) {
+        const unsigned i = e / to.row, j = e % to.row;
+        to.rows[to.first * to.row + e] =
+            j < to.workers && j != to.self ? reinterpret_cast<const uint8_t *>(p.of_worker(i, j, to.workers)) : nullptr;
+    }
+    for (unsigned s = id; s < to.slots; s += step) {
+        unsigned lo = 0, hi = to.count;  // invariant: starts[lo] <= s < starts[hi] (the total behind the last one)
+        while (hi - lo > 1) {
+            const unsigned mid = (lo + hi) >> 1;
+            if (starts[mid] <= s) lo = mid;
+            else hi = mid;
+        }
+        ChunkRef cr;
+        cr.tensor = to.first + lo;
+        cr.chunk = s - starts[lo];
+        to.chunks[to.slot0 + s] = cr;
+    }
 }
 
-// Layout of the static device array: descriptor table, chunk_start, peers' pointer table,
-// chunk table; every region starts on a 256-byte boundary and has room for the 16-byte
-// granularity of k_static_store.
+static_assert(sizeof(StaticTarget) + sizeof(StaticArenas) <= 3840 && sizeof(StaticTarget) + sizeof(StaticPointers) <= 3840,
+              "4 KiB of arguments, 256 bytes of which the runtime fills in");
+
+// Layout of the static device array: descriptor table, rows of stream pointers, chunk table; every
+// region starts on a 256-byte boundary.
 constexpr size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr int kStaticMaxTensors = CDSGD_STATIC_MAX_TENSORS;
 constexpr unsigned kStaticMaxChunks = CDSGD_STATIC_MAX_CHUNKS;
 constexpr size_t kStaticOffDesc = 0;
-constexpr size_t kStaticOffStart = round256(sizeof(TensorDesc) * kStaticMaxTensors + 16);
-constexpr size_t kStaticOffPeers = round256(kStaticOffStart + sizeof(unsigned) * (kStaticMaxTensors + 1) + 16);
+constexpr size_t kStaticOffPeers = round256(sizeof(TensorDesc) * kStaticMaxTensors);
 constexpr size_t kStaticOffChunks =
-    round256(kStaticOffPeers + sizeof(void *) * ((size_t)kStaticMaxTensors * row_entries(CDSGD_MAX_WORKERS) + CDSGD_MAX_WORKERS) + 16);
+    round256(kStaticOffPeers + sizeof(void *) * ((size_t)kStaticMaxTensors * row_entries(CDSGD_MAX_WORKERS) + CDSGD_MAX_WORKERS));
 constexpr size_t kStaticBytes = kStaticOffChunks + sizeof(ChunkRef) * (size_t)kStaticMaxChunks;
 static_assert(kChunkElems == CDSGD_STATIC_CHUNK_ELEMS, "the header states the chunk size the limit is counted in");
 
