@@ -570,9 +570,9 @@ namespace {
 //   25 M elements, t = 0.5     1.00   1.02   1.01     (the same with t = 0.3: 1.01 / 1.00 / 0.95)
 //   4 M elements, t = 0.5      1.05   1.02   0.99
 // The chain form's decode is longer and wants one group more.  Up to 8 workers on lists of 16 to 48 M elements, and
-// up to 4 on longer ones, one-wave groups (a quarter of a tile, 22 groups per compute unit) are 1-2 % faster than
-// groups of four waves; elsewhere those are (8 workers: 4 M elements 1.06 against 1.03, VGG-16 1.02-1.05 against
-// 1.00).  Above 16 workers: VGG-16-shaped, N = 32, t = 0.5 0.722 ms before, 0.745 with all groups, 0.714 with
+// up to 4 on longer ones, one-wave groups (a quarter of a tile, 22 groups per compute unit, 26 with 16-bit gradients:
+// 40 M elements, N = 8, fp16 143.7 us, 148.6 with 22, 147.4 before) are 1-2 % faster than groups of four waves;
+// elsewhere those are (8 workers: 4 M elements 1.06 against 1.03, VGG-16 1.02-1.05 against 1.00).  Above 16 workers: VGG-16-shaped, N = 32, t = 0.5 0.722 ms before, 0.745 with all groups, 0.714 with
 // 32 KiB each; t = 0.3 0.749, 0.735, 0.703 with 38 KiB (N = 64: 1.155, 0.922, 0.915).  Sparse peers, N = 16: 0.581
 // with all groups, 0.594 with 32 KiB each when one code in 256 is sent (0.597 before), 0.673 and 0.653 when one in 4
 // is (0.645 before); above 16 workers all groups (N = 32: 0.643, 0.690; 0.733 before).
@@ -580,7 +580,7 @@ struct CompressedLaunch {
     unsigned waves, lds;
 };
 
-CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int form, bool sparse)
+CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int form, bool sparse, int grad_type)
 {
     const unsigned tiles = num_chunks * kTilesPerChunk;  // of 1024 elements
     const bool long_list = tiles > kLongListTiles;
@@ -588,7 +588,7 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
     if (num_workers <= kUpTo8 && form != kChainTiny) {
         if (tiles <= 16u * 1024u) return {4u, 0u};
         if (num_workers > 4 && tiles > 48u * 1024u) return {4u, 49152u};
-        return {1u, 7168u};
+        return {1u, grad_type == kGradF32 ? 7168u : 6144u};
     }
     if (num_workers <= kUpTo16 && form == kCount) return {4u, long_list ? 49152u : (tiles > 6u * 1024u ? 32768u : 0u)};
     if (num_workers <= kUpTo16 || form == kCount) return {4u, long_list ? 32768u : 0u};
@@ -612,7 +612,7 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
     const bool pow2 = plan->own_thresholds ? plan->own_thresholds_pow2 : is_pow2_threshold(threshold);
     const bool tiny = plan->own_thresholds ? plan->own_thresholds_tiny : is_tiny_threshold(threshold);
     const int form = pow2 ? kCount : (tiny ? kChainTiny : kChain);
-    const CompressedLaunch shape = compressed_launch(plan->num_chunks, N, form, plan->peers_sparse);
+    const CompressedLaunch shape = compressed_launch(plan->num_chunks, N, form, plan->peers_sparse, plan->grad_type);
     const unsigned num_tiles = plan->num_chunks * (kChunkQuads / (64u * shape.waves));
     const unsigned grid = plan->grid_size(num_tiles, 64u * shape.waves);
     // (a pass with a workgroup limit is meant to share the GPU with other kernels: it leaves the LDS to them)
