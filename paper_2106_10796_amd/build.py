@@ -20,6 +20,9 @@ HIPCC_FLAGS = [
     "-ffp-contract=off", "-fno-fast-math",
     # no packed-fp32 instructions from the auto-vectoriser
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # a kernel's first 14 words of arguments arrive in registers: one trip to memory less before its first load
+    # (layer ranges of a million elements: 10.3 -> 9.9 us a launch)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wno-unused-command-line-argument",
 ]
 
