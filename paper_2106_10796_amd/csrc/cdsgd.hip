@@ -147,7 +147,7 @@ inline bool is_pow2_threshold(float t)
     return m == 0.5f && e > -100 && e < 100;
 }
 
-// A threshold whose half may not be exact (the chain form's multipliers are 2, see chain_word).
+// A threshold whose half may not be exact (the chain form's multipliers are 2, see chain_pairs).
 inline bool is_tiny_threshold(float t) { return t < 0x1p-125f; }
 
 inline bool good_threshold(float t) { return std::isfinite(t) && t > 0.0f; }
@@ -572,10 +572,14 @@ namespace {
 // The chain form's decode is longer and wants one group more.  Up to 8 workers on lists of 16 to 48 M elements, and
 // up to 4 on longer ones, one-wave groups (a quarter of a tile, 22 groups per compute unit, 26 with 16-bit gradients:
 // 40 M elements, N = 8, fp16 143.7 us, 148.6 with 22, 147.4 before) are 1-2 % faster than groups of four waves;
-// elsewhere those are (8 workers: 4 M elements 1.06 against 1.03, VGG-16 1.02-1.05 against 1.00).  Above 16 workers: VGG-16-shaped, N = 32, t = 0.5 0.722 ms before, 0.745 with all groups, 0.714 with
-// 32 KiB each; t = 0.3 0.749, 0.735, 0.703 with 38 KiB (N = 64: 1.155, 0.922, 0.915).  Sparse peers, N = 16: 0.581
+// elsewhere those are (8 workers: 4 M elements 1.06 against 1.03, VGG-16 1.02-1.05 against 1.00).  Above 16
+// workers: VGG-16-shaped, N = 32, t = 0.5 0.722 ms before, 0.745 with all groups, 0.714 with 32 KiB each; t = 0.3 0.749, 0.735, 0.703 with 38 KiB (N = 64: 1.155, 0.922, 0.915).  Sparse peers, N = 16: 0.581
 // with all groups, 0.594 with 32 KiB each when one code in 256 is sent (0.597 before), 0.673 and 0.653 when one in 4
 // is (0.645 before); above 16 workers all groups (N = 32: 0.643, 0.690; 0.733 before).
+// Count form, 9 to 16 workers, between: 10 M elements 42.5 us with 24 KiB each, 45.4 with 32; from kLateWordsTiles on
+// (see launch_formal_pass) 32 KiB with 32-bit gradients (25 M elements 111.1 us, 113.0 with 24) and 24 with 16-bit
+// ones (103.1, 106.7 with 32).
+constexpr unsigned kLateWordsTiles = 16u * 1024u;
 struct CompressedLaunch {
     unsigned waves, lds;
 };
@@ -590,7 +594,11 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
         if (num_workers > 4 && tiles > 48u * 1024u) return {4u, 49152u};
         return {1u, grad_type == kGradF32 ? 7168u : 6144u};
     }
-    if (num_workers <= kUpTo16 && form == kCount) return {4u, long_list ? 49152u : (tiles > 6u * 1024u ? 32768u : 0u)};
+    if (num_workers <= kUpTo16 && form == kCount) {
+        if (long_list) return {4u, 49152u};
+        if (tiles <= 6u * 1024u) return {4u, 0u};
+        return {4u, tiles > kLateWordsTiles && grad_type == kGradF32 ? 32768u : 24576u};
+    }
     if (num_workers <= kUpTo16 || form == kCount) return {4u, long_list ? 32768u : 0u};
     return {4u, long_list ? 38912u : 0u};
 }
@@ -615,31 +623,37 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
     const CompressedLaunch shape = compressed_launch(plan->num_chunks, N, form, plan->peers_sparse, plan->grad_type);
     const unsigned num_tiles = plan->num_chunks * (kChunkQuads / (64u * shape.waves));
     const unsigned grid = plan->grid_size(num_tiles, 64u * shape.waves);
+    // The workers' words are asked for first, so that the decode has them soonest (ResNet-50-shaped list in ranges of
+    // a million elements, N = 16: 166.5 us against 169.3), but behind the tile's own streams in the count form of a
+    // longer list, where the order of the requests at HBM counts (VGG-16-shaped, N = 16: 597 us against 603).
+    const bool late = form == kCount && N > kUpTo8 && N <= kUpTo16 && !plan->peers_sparse &&
+                      plan->num_chunks * kTilesPerChunk > kLateWordsTiles;
     // (a pass with a workgroup limit is meant to share the GPU with other kernels: it leaves the LDS to them)
     const auto bound = [&](unsigned used) { return plan->max_workgroups || shape.lds <= used ? 0u : shape.lds - used; };
-#define CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, GT, SPARSE)                                                 \
-    hipLaunchKernelGGL((k_fused_compressed<SZ, WAVES, FORM, GT, SPARSE>), dim3(grid), dim3(64 * WAVES),         \
+#define CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, GT, SPARSE, LATE)                                                 \
+    hipLaunchKernelGGL((k_fused_compressed<SZ, WAVES, FORM, GT, SPARSE, LATE>), dim3(grid), dim3(64 * WAVES),         \
                        bound(kTileLds<SZ, FORM, WAVES>), s, plan->tensors, plan->chunk_table(), plan->rows,      \
                        num_tiles, grid, N, plan->self, threshold, lr_local, scale, with_local ? 1 : 0)
-#define CDSGD_LAUNCH_COMPRESSED_G(SZ, WAVES, FORM, SPARSE)                                                     \
+#define CDSGD_LAUNCH_COMPRESSED_G(SZ, WAVES, FORM, SPARSE, LATE)                                                     \
     do {                                                                                                       \
-        if (plan->grad_type == kGradBF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradBF16, SPARSE);        \
-        else if (plan->grad_type == kGradF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF16, SPARSE);     \
-        else CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF32, SPARSE);                                      \
+        if (plan->grad_type == kGradBF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradBF16, SPARSE, LATE);        \
+        else if (plan->grad_type == kGradF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF16, SPARSE, LATE);     \
+        else CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF32, SPARSE, LATE);                                      \
     } while (0)
 #define CDSGD_LAUNCH_COMPRESSED_F(SZ, FORM)                                                                    \
     do {                                                                                                       \
-        if (plan->peers_sparse) CDSGD_LAUNCH_COMPRESSED_G(SZ, 4, FORM, true);                                   \
-        else CDSGD_LAUNCH_COMPRESSED_G(SZ, 4, FORM, false);                                                     \
+        if (plan->peers_sparse) CDSGD_LAUNCH_COMPRESSED_G(SZ, 4, FORM, true, false);                                   \
+        else CDSGD_LAUNCH_COMPRESSED_G(SZ, 4, FORM, false, false);                                                     \
     } while (0)
 #define CDSGD_LAUNCH_COMPRESSED(FORM)                                                                          \
     do {                                                                                                       \
-        if (shape.waves == 1u) CDSGD_LAUNCH_COMPRESSED_G(kUpTo8, 1, FORM, false);                               \
+        if (shape.waves == 1u) CDSGD_LAUNCH_COMPRESSED_G(kUpTo8, 1, FORM, false, false);                               \
         else if (N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED_F(kUpTo8, FORM);                                          \
         else if (N <= kUpTo16) CDSGD_LAUNCH_COMPRESSED_F(kUpTo16, FORM);                                        \
         else CDSGD_LAUNCH_COMPRESSED_F(kAnyWorkers, FORM);                                                      \
     } while (0)
-    if (form == kCount) CDSGD_LAUNCH_COMPRESSED(kCount);
+    if (late) CDSGD_LAUNCH_COMPRESSED_G(kUpTo16, 4, kCount, false, true);
+    else if (form == kCount) CDSGD_LAUNCH_COMPRESSED(kCount);
     else if (form == kChain) CDSGD_LAUNCH_COMPRESSED(kChain);
     else CDSGD_LAUNCH_COMPRESSED_F(kAnyWorkers, kChainTiny);
 #undef CDSGD_LAUNCH_COMPRESSED

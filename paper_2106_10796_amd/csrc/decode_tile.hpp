@@ -51,7 +51,6 @@ __device__ __forceinline__ unsigned ld_word(const uint8_t *base, unsigned bytes,
 
 // Where the streams of a tile are.
 struct TileStreams {
-    const uint8_t *const *row;  // row_entries(num_workers) pointers
     int num_workers;
     unsigned stream_bytes;      // packed form: bytes of a stream, and where the tile starts in it
     unsigned tile_at;
@@ -67,19 +66,55 @@ __device__ __forceinline__ constexpr int worker_of(int wave, int i)
     return SZ == kUpTo8 ? 2 * wave + i : 16 * (i / 4) + 4 * wave + i % 4;
 }
 
+// The streams of the workers that a wave takes (a group of one wave: that the lane takes); null: nothing to load.
+// They are fetched in one piece and before anything waits: a load that stands inside the test for its worker is
+// fetched, waited for and used before the next, which cost the kernels for more than 16 workers up to 16 trips to
+// the scalar cache in a row, and behind the descriptor of the tensor it costs every group one trip.
+template <int SZ, int WAVES, bool SPARSE>
+struct StreamPointers {
+    const uint8_t *p[kWordsPerWave<SZ>];
+    const uint8_t *bitmap;  // sparse form: the stream of the worker whose bitmap words the lane fetches
+
+    // `row` has row_entries(num_workers) entries, and kMaxRows<SZ> can be read.
+    __device__ __forceinline__ void load(const uint8_t *const *__restrict__ row, int num_workers, int wave, unsigned lane)
+    {
+        bitmap = nullptr;
+        if constexpr (WAVES == 1) {
+            static_assert(SZ == kUpTo8 && !SPARSE, "one wave: up to eight packed streams");
+#pragma unroll
+            for (int i = 0; i < kWordsPerWave<SZ>; ++i) p[i] = row[2u * (lane >> 4) + (unsigned)i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < kWordsPerWave<SZ>; ++i) p[i] = row[worker_of<SZ>(wave, i)];
+            if constexpr (SPARSE) {
+                const int slot = (int)(lane >> 2);
+                if (slot < kWordsPerWave<SZ>) {
+                    const int j = worker_of<SZ>(wave, slot);
+                    if (SZ != kAnyWorkers || j < num_workers) bitmap = row[j];
+                }
+            }
+        }
+    }
+
+    // Keeps the compiler from moving the loads to where their pointers are used.
+    __device__ __forceinline__ void pin()
+    {
+        if constexpr (WAVES != 1) {
+#pragma unroll
+            for (int i = 0; i < kWordsPerWave<SZ>; ++i) asm volatile("" : "+s"(p[i]));
+        }
+    }
+};
+
 // This lane's words of the workers that its wave takes; 0 where there is nothing to load.
 template <int SZ>
-__device__ __forceinline__ void load_packed(unsigned (&w)[kWordsPerWave<SZ>], const TileStreams &s, int wave, unsigned lane)
+__device__ __forceinline__ void load_packed(unsigned (&w)[kWordsPerWave<SZ>], const uint8_t *const (&p)[kWordsPerWave<SZ>],
+                                            const TileStreams &s, int wave, unsigned lane)
 {
 #pragma unroll
     for (int i = 0; i < kWordsPerWave<SZ>; ++i) {
-        const int j = worker_of<SZ>(wave, i);
-        w[i] = 0u;
-        if (SZ != kAnyWorkers || 16 * (i / 4) < s.num_workers) {
-            const uint8_t *p = s.row[j];
-            if (SZ == kAnyWorkers && j >= s.num_workers) p = nullptr;
-            w[i] = ld_word(p, p ? s.stream_bytes : 0u, s.tile_at + 4u * lane);
-        }
+        const bool there = p[i] && (SZ != kAnyWorkers || worker_of<SZ>(wave, i) < s.num_workers);
+        w[i] = ld_word(p[i], there ? s.stream_bytes : 0u, s.tile_at + 4u * lane);
     }
 }
 
@@ -87,19 +122,13 @@ __device__ __forceinline__ void load_packed(unsigned (&w)[kWordsPerWave<SZ>], co
 // Lane 4 i + m fetches bitmap words 2 m and 2 m + 1 of the worker in slot i; a tile's 64 words are one such pair, so
 // its bitmap, and the number of words in front of it, are wave-uniform, and a lane's word lies at the rank of its bit.
 template <int SZ>
-__device__ __forceinline__ void load_sparse(unsigned (&w)[kWordsPerWave<SZ>], const TileStreams &s, int wave, unsigned lane)
+__device__ __forceinline__ void load_sparse(unsigned (&w)[kWordsPerWave<SZ>], const StreamPointers<SZ, 4, true> &from,
+                                            const TileStreams &s, int wave, unsigned lane)
 {
-    const int slot = (int)(lane >> 2);
     const unsigned m = lane & 3u;
     u2 bm = {0u, 0u};
-    if (slot < kWordsPerWave<SZ>) {
-        const int j = worker_of<SZ>(wave, slot);
-        if (SZ != kAnyWorkers || j < s.num_workers) {
-            const uint8_t *p = s.row[j];
-            typedef unsigned u2a __attribute__((ext_vector_type(2), aligned(4)));
-            if (p) bm = *(const CDSGD_GLOBAL u2a *)(p + s.segment_at + 8u * m);
-        }
-    }
+    typedef unsigned u2a __attribute__((ext_vector_type(2), aligned(4)));
+    if (from.bitmap) bm = *(const CDSGD_GLOBAL u2a *)(from.bitmap + s.segment_at + 8u * m);
     // words in front of the tile's own: summed over the worker's four lanes
     int before = m < s.tile ? __builtin_popcount(bm.x) + __builtin_popcount(bm.y) : 0;
     before += __builtin_amdgcn_mov_dpp(before, 0xB1, 0xF, 0xF, true);  // quad_perm [1, 0, 3, 2]
@@ -111,37 +140,37 @@ __device__ __forceinline__ void load_sparse(unsigned (&w)[kWordsPerWave<SZ>], co
             const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)bm.x, 4 * i + (int)s.tile);
             const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)bm.y, 4 * i + (int)s.tile);
             const unsigned at = 8u + (unsigned)__builtin_amdgcn_readlane(before, 4 * i);
-            const uint8_t *p = s.row[worker_of<SZ>(wave, i)];
-            if (SZ == kAnyWorkers && worker_of<SZ>(wave, i) >= s.num_workers) p = nullptr;
+            const uint8_t *p = from.p[i];
             const unsigned rank = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
             const bool sent = __builtin_amdgcn_inverse_ballot_w64(((unsigned long long)hi << 32) | lo);
             // a lane whose word is zero asks past the end of the segment and gets 0 without a read
-            w[i] = ld_word(p + s.segment_at, p ? 4u * kSegStride : 0u, sent ? 4u * (at + rank) : 4u * kSegStride);
+            const bool there = p && (SZ != kAnyWorkers || worker_of<SZ>(wave, i) < s.num_workers);
+            w[i] = ld_word(p + s.segment_at, there ? 4u * kSegStride : 0u, sent ? 4u * (at + rank) : 4u * kSegStride);
         }
     }
 }
 
 // Groups of one wave: a quarter of a tile, 16 words of every stream; lanes 16 v .. 16 v + 15 take what wave v takes
 // in a group of four (packed form, up to eight workers).
-__device__ __forceinline__ void load_packed_quarter(unsigned (&w)[kWordsPerWave<kUpTo8>], const TileStreams &s, unsigned lane)
+__device__ __forceinline__ void load_packed_quarter(unsigned (&w)[kWordsPerWave<kUpTo8>],
+                                                    const uint8_t *const (&p)[kWordsPerWave<kUpTo8>],
+                                                    const TileStreams &s, unsigned lane)
 {
     const unsigned off = s.tile_at + 4u * (lane & 15u);
 #pragma unroll
     for (int i = 0; i < kWordsPerWave<kUpTo8>; ++i) {
-        const uint8_t *p = s.row[2u * (lane >> 4) + (unsigned)i];
         w[i] = 0u;
-        if (p && off < s.stream_bytes) w[i] = *global_ptr(reinterpret_cast<const unsigned *>(p + off));
+        if (p[i] && off < s.stream_bytes) w[i] = *global_ptr(reinterpret_cast<const unsigned *>(p[i] + off));
     }
 }
 
 template <int SZ, int WAVES, bool SPARSE>
-__device__ __forceinline__ void load_words(unsigned (&w)[kWordsPerWave<SZ>], const TileStreams &s, int wave, unsigned lane)
+__device__ __forceinline__ void load_words(unsigned (&w)[kWordsPerWave<SZ>], const StreamPointers<SZ, WAVES, SPARSE> &from,
+                                           const TileStreams &s, int wave, unsigned lane)
 {
-    if constexpr (WAVES == 1) {
-        static_assert(SZ == kUpTo8 && !SPARSE, "one wave: up to eight packed streams");
-        load_packed_quarter(w, s, lane);
-    } else if constexpr (SPARSE) load_sparse<SZ>(w, s, wave, lane);
-    else load_packed<SZ>(w, s, wave, lane);
+    if constexpr (WAVES == 1) load_packed_quarter(w, from.p, s, lane);
+    else if constexpr (SPARSE) load_sparse<SZ>(w, from, s, wave, lane);
+    else load_packed<SZ>(w, from.p, s, wave, lane);
 }
 
 // ---- count form -------------------------------------------------------------
@@ -377,15 +406,17 @@ __global__ __launch_bounds__(kTileQuads) void k_decode_sum(StreamTable tab, int 
     const int wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const unsigned x = xcd ? piece_of_workgroup<true>(blockIdx.x, kTilesPerChunk, num_tiles) : blockIdx.x;
     const unsigned chunk = x / kTilesPerChunk;
+    StreamPointers<SZ, 4, SPARSE> from;
+    from.load(tab.p, num_workers, wave, tid & 63u);
+    from.pin();
     TileStreams s;
-    s.row = tab.p;
     s.num_workers = num_workers;
     s.stream_bytes = ext.full_chunks * kChunkQuads + ext.tail_bytes;
     s.tile_at = x * kTileBytes;
     s.segment_at = (size_t)chunk * (4u * kSegStride);
     s.tile = x % kTilesPerChunk;
     unsigned words[kWordsPerWave<SZ>];
-    load_words<SZ, 4, SPARSE>(words, s, wave, tid & 63u);
+    load_words<SZ, 4, SPARSE>(words, from, s, wave, tid & 63u);
     const f4 agg = tile_sums<SZ, FORM, 4>(words, 0u, f4{0.0f, 0.0f, 0.0f, 0.0f}, -1, num_workers, t, lds);
     float *out = agg_out + (size_t)x * (4u * kTileQuads);
     if (chunk < ext.full_chunks) st4(out, tid, agg);

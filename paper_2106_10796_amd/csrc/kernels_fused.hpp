@@ -7,7 +7,10 @@ namespace {
 // Fused compressed step (a1-a6), one group of waves per tile of a chunk
 // ---------------------------------------------------------------------------
 // Bound by HBM (24 + N / 4 bytes per element): every load of a group is in flight at once, so a group's life is the
-// table lookups (chunk, then descriptor and stream pointers), one round trip to memory, the decode and the stores.
+// table lookups (chunk, then descriptor and stream pointers together), one round trip to memory, the decode and the
+// stores.  (Stream pointers fetched behind the descriptor, one worker after the other above 16 workers: layer ranges of
+// a million elements, N = 16 169.3 us for 17 launches, 166.5 now; 300 k elements, N = 64 6.3 us, 6.1; 1 M elements
+// decoded and updated, N = 64 29.6 us, 28.6.  Longer lists are bound by HBM and gain nothing.)
 // A persistent grid whose groups fetch the next tile before they finish one is 15 % slower: its groups drift apart,
 // and the streams' requests in flight with them (2^26 elements, N = 16: 0.366 ms against 0.293).
 // Whether the local weights, which do not wait for the sums, are stored before the decode or beside the global ones:
@@ -16,8 +19,9 @@ namespace {
 template <int SZ, int FORM>
 constexpr bool kLocalFirst = SZ == kUpTo16 && FORM != kCount;
 
-template <bool G, int SZ, int WAVES, int FORM, int GT, bool SPARSE>
-__device__ __forceinline__ void fused_tile(const TensorDesc &d, const uint8_t *const *__restrict__ row, int num_workers,
+// LATE: the workers' words are asked for behind the tile's own streams instead of in front of them.
+template <bool G, int SZ, int WAVES, int FORM, int GT, bool SPARSE, bool LATE>
+__device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPointers<SZ, WAVES, SPARSE> &from, int num_workers,
                                            int self, unsigned chunk, unsigned tile, unsigned rem_elems,
                                            unsigned rem_bytes, float t, float lr_local, float scale, bool write_local,
                                            uint8_t *lds)
@@ -33,17 +37,20 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const uint8_t *c
     const int cnt = quad_count<G>(rem_elems, tid);
 
     TileStreams s;
-    s.row = row;
     s.num_workers = num_workers;
     s.stream_bytes = d.ext.full_chunks * kChunkQuads + d.ext.tail_bytes;
     s.tile_at = (unsigned)quad0;
     s.segment_at = (size_t)chunk * (4u * kSegStride);
     s.tile = tile;
     unsigned words[kWordsPerWave<SZ>];
-    load_words<SZ, WAVES, SPARSE>(words, s, wave, tid & 63u);
+    if (!LATE) load_words<SZ, WAVES, SPARSE>(words, from, s, wave, tid & 63u);
     const f4 g = ldgrad<G, GT>(grad, tid, cnt);
     f4 r = ld4g<G>(resid, tid, cnt);
     const f4 w = ld4g<G>(wg, tid, cnt);
+    if (LATE) {
+        __builtin_amdgcn_sched_barrier(0);
+        load_words<SZ, WAVES, SPARSE>(words, from, s, wave, tid & 63u);
+    }
 
     // own codes: quantise, keep the residual, write what would be pushed
     f4 sent;
@@ -65,7 +72,7 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const uint8_t *c
 }
 
 // write_local: eq. 11 as well (false: the global half of a split step)
-template <int SZ, int WAVES, int FORM, int GT, bool SPARSE>
+template <int SZ, int WAVES, int FORM, int GT, bool SPARSE, bool LATE>
 __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDesc *__restrict__ tensors,
                                                                  const ChunkRef *__restrict__ chunks,
                                                                  const uint8_t *const *__restrict__ rows,
@@ -75,20 +82,23 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[kTileLds<SZ, FORM, WAVES>];
     constexpr unsigned kQuads = 64u * WAVES, kPerChunk = kChunkQuads / kQuads;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     for (unsigned b = blockIdx.x;;) {
         const unsigned x = piece_of_workgroup<true>(b, kPerChunk, num_tiles);
         const ChunkRef cr = chunks[x / kPerChunk];
+        StreamPointers<SZ, WAVES, SPARSE> from;
+        from.load(rows + (size_t)cr.tensor * row_entries(num_workers), num_workers, wave, threadIdx.x & 63u);
         const TensorDesc d = tensors[cr.tensor];
+        from.pin();
         const unsigned tile = x % kPerChunk;
-        const uint8_t *const *row = rows + (size_t)cr.tensor * row_entries(num_workers);
         const float t = d.threshold > 0.0f ? d.threshold : t_call;
         if (cr.chunk < d.ext.full_chunks) {
-            fused_tile<false, SZ, WAVES, FORM, GT, SPARSE>(d, row, num_workers, self, cr.chunk, tile, kQuads * 4u, kQuads,
+            fused_tile<false, SZ, WAVES, FORM, GT, SPARSE, LATE>(d, from, num_workers, self, cr.chunk, tile, kQuads * 4u, kQuads,
                                                     t, lr_local, scale, write_local != 0, lds);
         } else if (tile * kQuads < d.ext.tail_bytes) {
             // (the packed bytes of the ragged end cover its elements: tiles past them have nothing to do)
             const unsigned elems0 = tile * kQuads * 4u;
-            fused_tile<true, SZ, WAVES, FORM, GT, SPARSE>(d, row, num_workers, self, cr.chunk, tile,
+            fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, LATE>(d, from, num_workers, self, cr.chunk, tile,
                                                    d.ext.tail_elems > elems0 ? d.ext.tail_elems - elems0 : 0u,
                                                    d.ext.tail_bytes - tile * kQuads, t, lr_local, scale,
                                                    write_local != 0, lds);

@@ -76,9 +76,10 @@ def test_compressed_pass_at_tile_and_batch_edges(B, oracle, N, t, sparse):
 
 
 @pytest.mark.parametrize("t", [0.5, 0.3])
-@pytest.mark.parametrize("N", [4, 8])
+@pytest.mark.parametrize("N", [4, 8, 12])
 def test_long_list_of_few_workers(B, N, t):
-    """A list long enough for the one-wave groups (more than 2^24 elements), against the single-tensor calls."""
+    """A list long enough for the one-wave groups, and for the workers' words behind the tile's own streams (more than
+    2^24 elements), against the single-tensor calls."""
     n = (1 << 24) + 4096 * 3 + 277
     gen = torch.Generator(device="cuda").manual_seed(5 + N)
     rand = lambda s: torch.empty(n, device="cuda").normal_(0, s, generator=gen)
