@@ -412,9 +412,14 @@ int cdsgd_quantize_pack(const float *grad, float *residual, uint32_t *packed, si
         overlap2(packed, (size_t)packed_bytes_of(n), grad, n * sizeof(float)) ||
         overlap2(packed, (size_t)packed_bytes_of(n), residual, n * sizeof(float)))
         return CDSGD_ERR_ALIAS;
-    hipLaunchKernelGGL(k_quantize_pack<kQuantLanes>, dim3((unsigned)units_of(n, kQuantLanes)), dim3(kQuantLanes), kLdsFor20Waves,
-                       (hipStream_t)hip_stream, grad, residual, reinterpret_cast<uint8_t *>(packed),
-                       extent_of_units(n, kQuantLanes), threshold);
+    const dim3 grid((unsigned)units_of(n, kQuantLanes)), block(kQuantLanes);
+    const Extent pieces = extent_of_units(n, kQuantLanes);
+    hipStream_t s = (hipStream_t)hip_stream;
+    uint8_t *codes = reinterpret_cast<uint8_t *>(packed);
+    if (n <= kKeepElems)
+        hipLaunchKernelGGL((k_quantize_pack<kQuantLanes, true>), grid, block, kLdsFor20Waves, s, grad, residual, codes, pieces, threshold);
+    else
+        hipLaunchKernelGGL((k_quantize_pack<kQuantLanes, false>), grid, block, kLdsFor20Waves, s, grad, residual, codes, pieces, threshold);
     return launch_status();
 }
 
@@ -456,12 +461,16 @@ int cdsgd_update(float *w_global, float *w_local, const float *grad_local, const
     hipStream_t s = (hipStream_t)hip_stream;
     const dim3 grid((unsigned)units_of(n, kUpdateLanes)), block(kUpdateLanes);
     const Extent pieces = extent_of_units(n, kUpdateLanes);
-    if (local && global)
-        hipLaunchKernelGGL((k_update<true, true>), grid, block, kLdsFor20Waves, s, w_global, w_local, grad_local, agg, pieces, lr_local, scale);
-    else if (local)
-        hipLaunchKernelGGL((k_update<true, false>), grid, block, 0, s, w_global, w_local, grad_local, agg, pieces, lr_local, scale);
-    else
-        hipLaunchKernelGGL((k_update<false, true>), grid, block, 0, s, w_global, w_local, grad_local, agg, pieces, lr_local, scale);
+#define CDSGD_LAUNCH_UPDATE(LOCAL, GLOBAL, KEEP, LDS)                                                          \
+    hipLaunchKernelGGL((k_update<LOCAL, GLOBAL, KEEP>), grid, block, LDS, s, w_global, w_local, grad_local, agg, \
+                       pieces, lr_local, scale)
+    const bool keep = n <= kKeepElems;
+    if (local && global && keep) CDSGD_LAUNCH_UPDATE(true, true, true, kLdsFor20Waves);
+    else if (local && global) CDSGD_LAUNCH_UPDATE(true, true, false, kLdsFor20Waves);
+    else if (local && keep) CDSGD_LAUNCH_UPDATE(true, false, true, 0);
+    else if (local) CDSGD_LAUNCH_UPDATE(true, false, false, 0);
+    else CDSGD_LAUNCH_UPDATE(false, true, false, 0);
+#undef CDSGD_LAUNCH_UPDATE
     return launch_status();
 }
 

@@ -33,6 +33,12 @@ __device__ __forceinline__ f4 ld4(const float *base, unsigned qi)
 #endif
 }
 
+// The same with the default cache policy: for what the next call reads again.
+__device__ __forceinline__ f4 ld4_kept(const float *base, unsigned qi)
+{
+    return *(global_ptr(reinterpret_cast<const f4 *>(base)) + qi);
+}
+
 __device__ __forceinline__ void st4(float *base, unsigned qi, f4 v)
 {
     CDSGD_GLOBAL f4 *p = global_ptr(reinterpret_cast<f4 *>(base)) + qi;

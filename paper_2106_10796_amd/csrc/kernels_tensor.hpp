@@ -3,10 +3,17 @@
 
 namespace {
 
+// The gradient of a worker's own tensor is read twice, by the update and by the quantiser (KEEP): up to kKeepElems
+// elements its loads take the default cache policy, and the second pass finds it in the 256 MB memory-side cache.
+// Update and quantise-and-pack one after the other, non-temporal / default policy: 4 M elements 18.2 / 16.9 us, 9 M
+// 38.2 / 36.4, 16 M 65.1 / 62.3, 32 M 123.9 / 123.1, 64 M 241 / 241, 100 M 375 / 383.  (The aggregate between
+// decode-and-sum and the update is better off non-temporal: 16 M elements, N = 8 46.9 us, 51 with the default policy.)
+constexpr size_t kKeepElems = (size_t)24 << 20;
+
 // a5 + a6 (eq. 10, eq. 11) for one tensor, both from the weight that was loaded, in single-wave pieces of
 // 64 quads (`ext` in pieces, as for k_quantize_pack; measured on 2^27 elements: 6.29 TB/s against 6.02 TB/s
 // for 512-lane workgroups with two quads per lane).
-template <bool G, bool LOCAL, bool GLOBAL>
+template <bool G, bool LOCAL, bool GLOBAL, bool KEEP>
 __device__ __forceinline__ void update_piece(float *__restrict__ wg, float *__restrict__ wl,
                                              const float *__restrict__ grad, const float *__restrict__ agg,
                                              unsigned rem_elems, float lr_local, float scale)
@@ -15,7 +22,7 @@ __device__ __forceinline__ void update_piece(float *__restrict__ wg, float *__re
     const int cnt = quad_count<G>(rem_elems, lane);
     const f4 w = ld4g<G>(wg, lane, cnt);
     f4 g = {0.0f, 0.0f, 0.0f, 0.0f}, a = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (LOCAL) g = ld4g<G>(grad, lane, cnt);
+    if (LOCAL) g = KEEP && (!G || cnt == 4) ? ld4_kept(grad, lane) : ld4g<G>(grad, lane, cnt);
     if (GLOBAL) a = ld4g<G>(agg, lane, cnt);
     if (LOCAL) {
         f4 v;
@@ -31,7 +38,7 @@ __device__ __forceinline__ void update_piece(float *__restrict__ wg, float *__re
     }
 }
 
-template <bool LOCAL, bool GLOBAL>
+template <bool LOCAL, bool GLOBAL, bool KEEP>
 __global__ __launch_bounds__(64) void k_update(float *__restrict__ wg, float *__restrict__ wl,
                                                      const float *__restrict__ grad, const float *__restrict__ agg,
                                                      Extent ext, float lr_local, float scale)
@@ -44,16 +51,14 @@ __global__ __launch_bounds__(64) void k_update(float *__restrict__ wg, float *__
         grad += 4 * quad0;
     }
     if (GLOBAL) agg += 4 * quad0;
-    if (piece < ext.full_chunks) update_piece<false, LOCAL, GLOBAL>(wg, wl, grad, agg, 256u, lr_local, scale);
-    else update_piece<true, LOCAL, GLOBAL>(wg, wl, grad, agg, ext.tail_elems, lr_local, scale);
+    if (piece < ext.full_chunks) update_piece<false, LOCAL, GLOBAL, KEEP>(wg, wl, grad, agg, 256u, lr_local, scale);
+    else update_piece<true, LOCAL, GLOBAL, KEEP>(wg, wl, grad, agg, ext.tail_elems, lr_local, scale);
 }
 
 // a1-a3 for one tensor, one wave per piece of L = 64 quads (measured: 6.68 TB/s against 6.41 TB/s for
-// 512-lane workgroups with two quads per lane; decode-and-sum is faster in that shape and keeps it: in
-// pieces, with the workers' bytes staged through LDS as in the fused pass, it reached 4.1-5.4 TB/s against
-// 5.8 TB/s, a piece of it having too little else to do).  `ext` describes the tensor in pieces: full_chunks whole pieces, then at most one
+// 512-lane workgroups with two quads per lane).  `ext` describes the tensor in pieces: full_chunks whole pieces, then at most one
 // ragged piece of tail_elems elements and tail_bytes packed bytes.
-template <unsigned L>
+template <unsigned L, bool KEEP>
 __global__ __launch_bounds__(L) void k_quantize_pack(const float *__restrict__ grad, float *__restrict__ resid,
                                                        uint8_t *__restrict__ packed, Extent ext, float t)
 {
@@ -64,7 +69,7 @@ __global__ __launch_bounds__(L) void k_quantize_pack(const float *__restrict__ g
     packed += quad0;
     f4 sent;
     if (piece < ext.full_chunks) {
-        const f4 g = ld4(grad, lane);
+        const f4 g = KEEP ? ld4_kept(grad, lane) : ld4(grad, lane);
         f4 r = ld4(resid, lane);
         const unsigned b = quantize_quad(g, r, t, sent);
         st4(resid, lane, r);

@@ -98,3 +98,25 @@ def test_long_list_of_few_workers(B, N, t):
     for key, ref in (("packed_self", own), ("residual", r), ("w_global", w), ("w_local", wl)):
         assert torch.equal(layer[key].view(torch.int32), ref.view(torch.int32)), "%s N=%d t=%g" % (key, N, t)
     plan.destroy()
+
+
+@pytest.mark.parametrize("n", [(24 << 20) - 3, 24 << 20, (24 << 20) + 5])
+def test_single_tensor_calls_at_the_kept_gradient_limit(B, n):
+    """Quantise-and-pack and the update (eq. 11 alone, both rules) on the two sides of the length up to which the
+    gradient's loads keep it cached, against the pass over a list of that one tensor, N = 1."""
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    rand = lambda s: torch.empty(n, device="cuda").normal_(0, s, generator=gen)
+    g, r, w = rand(0.3), rand(0.2), rand(1.0)
+    layer = dict(w_global=w.clone(), w_local=torch.zeros_like(w), residual=r.clone(), grad=g, packed_self=B.new_packed(n))
+    plan = B.Plan([layer], None, 1, 0)
+    plan.step(1, 4, 0.3, 0.4, 0.7)
+    own, agg, wl, wl2 = B.new_packed(n), torch.empty_like(w), torch.zeros_like(w), torch.zeros_like(w)
+    B.cdsgd_update(w, wl, g, None, 0.4, 0.7, 1)
+    B.cdsgd_quantize_pack(g, r, own, 0.3)
+    B.cdsgd_decode_sum([own], agg, 0.3)
+    B.cdsgd_update(w, wl2, g, agg, 0.4, 0.7, 1)
+    torch.cuda.synchronize()
+    for what, a, b in (("packed", layer["packed_self"], own), ("residual", layer["residual"], r), ("w_global", layer["w_global"], w),
+                       ("w_local", layer["w_local"], wl), ("w_local, both rules", layer["w_local"], wl2)):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32)), "%s n=%d" % (what, n)
+    plan.destroy()
