@@ -3,9 +3,9 @@
 //   tuning.hpp          build-time knobs (launch shapes, cache policy)
 //   device_common.hpp   chunk geometry, 128-bit loads / stores, 16-bit widening, the quantiser
 //   device_tables.hpp   extents, tensor descriptors, chunk table
-//   kernels_tensor.hpp  single-tensor kernels (quantise-and-pack, decode-and-sum, update)
+//   kernels_tensor.hpp  single-tensor kernels (quantise-and-pack, update)
 //   kernels_sparse.hpp  sparse form of a packed stream
-//   decode_tile.hpp     decode-and-sum of one tile, all workers
+//   decode_tile.hpp     decode-and-sum of one tile, all workers; decode-and-sum of one tensor
 //   kernels_probe.hpp   bare streaming kernel (measurement aid)
 //   kernels_fused.hpp   passes over a layer list: fused compressed pass, passes on 32-bit gradients
 //   kernels_static.hpp  tables built on the device for the entry point that allocates nothing
@@ -22,7 +22,8 @@
 //     decoded word by word, decode_tile.hpp), "pieces" of one wave for the
 //     passes on 32-bit gradients.
 //   * Of the single-tensor kernels, decode-and-sum works in the same tiles,
-//     quantise-and-pack and the update in single-wave pieces.
+//     one to four to a group, quantise-and-pack and the update in single-wave
+//     pieces.
 // Either way every wave instruction on an fp32 buffer touches one contiguous
 // 1 KiB span: all traffic is fully coalesced.
 //
@@ -138,6 +139,7 @@ constexpr unsigned kUpdateLanes = 64;  // ... and of k_update
 // Tensors and lists of more tiles (1024 elements each) than this are long: their streams pass the 256 MB
 // memory-side cache by far, and the order in which they are read and written decides.
 constexpr unsigned kLongListTiles = 28u * 1024u;
+constexpr unsigned kMidListTiles = 16u * 1024u;  // half of that: where the residency of some passes begins to matter
 
 // A threshold 2^e (moderate e): every multiple m*t, |m| <= 2*CDSGD_MAX_WORKERS, is exact.
 inline bool is_pow2_threshold(float t)
@@ -341,6 +343,17 @@ int launch_full_pass(const PlanTables *plan, int local_mode, float lr_local, flo
 }
 
 // a4 for one tensor on checked arguments.
+//
+// Tiles of a group: 4 up to 16 workers; above that the loads of a wave are enough with one tile of packed streams
+// (N = 32, 2^27 elements, t = 0.5: 0.268 ms, 0.277 with 2 tiles) and want two of sparse ones (N = 24, one code in 256:
+// 0.277 ms with one, 0.230 with 2), except in the chain form above 32 workers, where a tile's rows and sums take 20 KiB
+// (N = 64: 0.65 ms, 0.70 with 2).
+// LDS that a group asks for in all, which bounds the groups resident (kLdsFor20Waves): with more than 4 packed streams
+// the mix of reads and writes is served better with 5 groups in the count form (N = 8, 2^27 elements: 133 us with all
+// groups, 127 with 5) and 6 in the chain form (N = 9: 140 with all, 136 with 6, 144 with 5), above 8 workers from 16 M
+// elements on (N = 16: 9 M 17.8 us with all, 18.4 with 6; 25 M 40.0 and 39.5); 4 streams and fewer write mostly and
+// lose with any bound (N = 2: 96 us, 113 with 5); sparse streams gain in the count form (N = 12, one code in 4: 173 us,
+// 169 with 6) and lose in the chain form.
 template <bool SPARSE>
 int launch_decode_sum(const uint32_t *const *streams, int num_workers, float *agg, size_t n, float threshold, void *hip_stream)
 {
@@ -350,19 +363,33 @@ int launch_decode_sum(const uint32_t *const *streams, int num_workers, float *ag
     const unsigned tiles = (unsigned)units_of(n, kTileQuads);
     const Extent ext = extent_of(n);
     const int xcd = SPARSE || tiles > kLongListTiles ? 1 : 0;
-#define CDSGD_LAUNCH_DECODE(SZ, FORM)                                                                          \
-    hipLaunchKernelGGL((k_decode_sum<SZ, FORM, SPARSE>), dim3(tiles), dim3(kTileQuads), 0, (hipStream_t)hip_stream, \
-                       tab, num_workers, agg, ext, tiles, xcd, threshold)
-#define CDSGD_LAUNCH_DECODE_N(FORM)                                                                            \
+    hipStream_t s = (hipStream_t)hip_stream;
+#define CDSGD_LAUNCH_DECODE(SZ, FORM, TILES, LDS)                                                              \
     do {                                                                                                       \
-        if (num_workers <= kUpTo8) CDSGD_LAUNCH_DECODE(kUpTo8, FORM);                                           \
-        else if (num_workers <= kUpTo16) CDSGD_LAUNCH_DECODE(kUpTo16, FORM);                                    \
-        else CDSGD_LAUNCH_DECODE(kAnyWorkers, FORM);                                                            \
+        const unsigned groups = (tiles + TILES - 1u) / TILES, used = kTileLds<SZ, FORM, 4> * TILES, want = LDS; \
+        hipLaunchKernelGGL((k_decode_sum<SZ, FORM, SPARSE, TILES>), dim3(groups), dim3(kTileQuads),             \
+                           want > used ? want - used : 0u, s, tab, num_workers, agg, ext, groups, xcd, threshold); \
     } while (0)
-    if (is_pow2_threshold(threshold)) CDSGD_LAUNCH_DECODE_N(kCount);
-    else if (!is_tiny_threshold(threshold)) CDSGD_LAUNCH_DECODE_N(kChain);
-    else CDSGD_LAUNCH_DECODE(kAnyWorkers, kChainTiny);
-#undef CDSGD_LAUNCH_DECODE_N
+    const bool count = is_pow2_threshold(threshold);
+    constexpr unsigned kLdsCount = SPARSE ? 24576u : 32768u, kLdsChain = SPARSE ? 0u : 24576u;
+    constexpr int kTilesMany = SPARSE ? 2 : 1;
+    if (!count && is_tiny_threshold(threshold)) CDSGD_LAUNCH_DECODE(kAnyWorkers, kChainTiny, 1, 0u);
+    else if (num_workers <= kUpTo4) {
+        if (count) CDSGD_LAUNCH_DECODE(kUpTo4, kCount, 4, 0u);
+        else CDSGD_LAUNCH_DECODE(kUpTo4, kChain, 4, 0u);
+    } else if (num_workers <= kUpTo8) {
+        if (count) CDSGD_LAUNCH_DECODE(kUpTo8, kCount, 4, kLdsCount);
+        else CDSGD_LAUNCH_DECODE(kUpTo8, kChain, 4, kLdsChain);
+    } else if (num_workers <= kUpTo16) {
+        if (count) CDSGD_LAUNCH_DECODE(kUpTo16, kCount, 4, kLdsCount);
+        else CDSGD_LAUNCH_DECODE(kUpTo16, kChain, 4, (tiles > kMidListTiles ? kLdsChain : 0u));
+    } else if (num_workers <= kUpTo32) {
+        if (count) CDSGD_LAUNCH_DECODE(kUpTo32, kCount, kTilesMany, 0u);
+        else CDSGD_LAUNCH_DECODE(kUpTo32, kChain, kTilesMany, 0u);
+    } else {
+        if (count) CDSGD_LAUNCH_DECODE(kAnyWorkers, kCount, kTilesMany, 0u);
+        else CDSGD_LAUNCH_DECODE(kAnyWorkers, kChain, 1, 0u);
+    }
 #undef CDSGD_LAUNCH_DECODE
     return launch_status();
 }
@@ -585,10 +612,9 @@ namespace {
 // workers: VGG-16-shaped, N = 32, t = 0.5 0.722 ms before, 0.745 with all groups, 0.714 with 32 KiB each; t = 0.3 0.749, 0.735, 0.703 with 38 KiB (N = 64: 1.155, 0.922, 0.915).  Sparse peers, N = 16: 0.581
 // with all groups, 0.594 with 32 KiB each when one code in 256 is sent (0.597 before), 0.673 and 0.653 when one in 4
 // is (0.645 before); above 16 workers all groups (N = 32: 0.643, 0.690; 0.733 before).
-// Count form, 9 to 16 workers, between: 10 M elements 42.5 us with 24 KiB each, 45.4 with 32; from kLateWordsTiles on
+// Count form, 9 to 16 workers, between: 10 M elements 42.5 us with 24 KiB each, 45.4 with 32; from kMidListTiles on
 // (see launch_formal_pass) 32 KiB with 32-bit gradients (25 M elements 111.1 us, 113.0 with 24) and 24 with 16-bit
 // ones (103.1, 106.7 with 32).
-constexpr unsigned kLateWordsTiles = 16u * 1024u;
 struct CompressedLaunch {
     unsigned waves, lds;
 };
@@ -599,14 +625,14 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
     const bool long_list = tiles > kLongListTiles;
     if (sparse) return {4u, long_list && num_workers <= kUpTo16 ? 32768u : 0u};
     if (num_workers <= kUpTo8 && form != kChainTiny) {
-        if (tiles <= 16u * 1024u) return {4u, 0u};
+        if (tiles <= kMidListTiles) return {4u, 0u};
         if (num_workers > 4 && tiles > 48u * 1024u) return {4u, 49152u};
         return {1u, grad_type == kGradF32 ? 7168u : 6144u};
     }
     if (num_workers <= kUpTo16 && form == kCount) {
         if (long_list) return {4u, 49152u};
         if (tiles <= 6u * 1024u) return {4u, 0u};
-        return {4u, tiles > kLateWordsTiles && grad_type == kGradF32 ? 32768u : 24576u};
+        return {4u, tiles > kMidListTiles && grad_type == kGradF32 ? 32768u : 24576u};
     }
     if (num_workers <= kUpTo16 || form == kCount) return {4u, long_list ? 32768u : 0u};
     return {4u, long_list ? 38912u : 0u};
@@ -636,7 +662,7 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
     // a million elements, N = 16: 166.5 us against 169.3), but behind the tile's own streams in the count form of a
     // longer list, where the order of the requests at HBM counts (VGG-16-shaped, N = 16: 597 us against 603).
     const bool late = form == kCount && N > kUpTo8 && N <= kUpTo16 && !plan->peers_sparse &&
-                      plan->num_chunks * kTilesPerChunk > kLateWordsTiles;
+                      plan->num_chunks * kTilesPerChunk > kMidListTiles;
     // (a pass with a workgroup limit is meant to share the GPU with other kernels: it leaves the LDS to them)
     const auto bound = [&](unsigned used) { return plan->max_workgroups || shape.lds <= used ? 0u : shape.lds - used; };
 #define CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, GT, SPARSE, LATE)                                                 \

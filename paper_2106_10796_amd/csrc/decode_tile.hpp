@@ -12,7 +12,7 @@ static_assert(kChunkQuads % kTileQuads == 0, "tiles tile a chunk");
 
 // How a kernel is compiled for the number of workers.  The waves share the workers out: wave v takes
 // kWordsPerWave<SZ> of every row, lane l its word l of each, and all of a group's loads are in flight at once.
-constexpr int kUpTo8 = 8, kUpTo16 = 16, kAnyWorkers = 0;
+constexpr int kUpTo4 = 4, kUpTo8 = 8, kUpTo16 = 16, kUpTo32 = 32, kAnyWorkers = 0;
 template <int SZ>
 constexpr int kMaxRows = SZ == kAnyWorkers ? CDSGD_MAX_WORKERS : SZ;
 template <int SZ>
@@ -58,12 +58,12 @@ struct TileStreams {
     unsigned tile;
 };
 
-// The worker whose word a wave holds in slot i: four neighbours out of every sixteen (two out of eight), so that
-// the slots of a wave fill up evenly with the number of workers.
+// The worker whose word a wave holds in slot i: four neighbours out of every sixteen (two out of eight, one out of
+// four), so that the slots of a wave fill up evenly with the number of workers.
 template <int SZ>
 __device__ __forceinline__ constexpr int worker_of(int wave, int i)
 {
-    return SZ == kUpTo8 ? 2 * wave + i : 16 * (i / 4) + 4 * wave + i % 4;
+    return SZ == kUpTo4 ? wave : (SZ == kUpTo8 ? 2 * wave + i : 16 * (i / 4) + 4 * wave + i % 4);
 }
 
 // The streams of the workers that a wave takes (a group of one wave: that the lane takes); null: nothing to load.
@@ -75,7 +75,11 @@ struct StreamPointers {
     const uint8_t *p[kWordsPerWave<SZ>];
     const uint8_t *bitmap;  // sparse form: the stream of the worker whose bitmap words the lane fetches
 
-    // `row` has row_entries(num_workers) entries, and kMaxRows<SZ> can be read.
+    // `row` has row_entries(num_workers) entries, and kMaxRows<SZ> can be read.  SELECT: the lanes pick the bitmap's
+    // stream from the wave's pointers instead of reading it from the row, which is a trip to memory of its own where
+    // the row is in the kernel's arguments (decode-and-sum of 2^27 elements, sparse, N = 4 and 8, one code in 256:
+    // 1.09 and 1.07 against 0.97 and 1.00 of the time of a kernel that stages the bitmaps through LDS).
+    template <bool SELECT>
     __device__ __forceinline__ void load(const uint8_t *const *__restrict__ row, int num_workers, int wave, unsigned lane)
     {
         bitmap = nullptr;
@@ -88,7 +92,11 @@ struct StreamPointers {
             for (int i = 0; i < kWordsPerWave<SZ>; ++i) p[i] = row[worker_of<SZ>(wave, i)];
             if constexpr (SPARSE) {
                 const int slot = (int)(lane >> 2);
-                if (slot < kWordsPerWave<SZ>) {
+                if constexpr (SELECT && SZ != kAnyWorkers) {
+#pragma unroll
+                    for (int i = 0; i < kWordsPerWave<SZ>; ++i)
+                        if (slot == i) bitmap = p[i];
+                } else if (slot < kWordsPerWave<SZ>) {
                     const int j = worker_of<SZ>(wave, slot);
                     if (SZ != kAnyWorkers || j < num_workers) bitmap = row[j];
                 }
@@ -121,14 +129,20 @@ __device__ __forceinline__ void load_packed(unsigned (&w)[kWordsPerWave<SZ>], co
 // The same from streams in the sparse form (segment of 8 bitmap words and the non-zero words, see kernels_sparse.hpp).
 // Lane 4 i + m fetches bitmap words 2 m and 2 m + 1 of the worker in slot i; a tile's 64 words are one such pair, so
 // its bitmap, and the number of words in front of it, are wave-uniform, and a lane's word lies at the rank of its bit.
-template <int SZ>
-__device__ __forceinline__ void load_sparse(unsigned (&w)[kWordsPerWave<SZ>], const StreamPointers<SZ, 4, true> &from,
-                                            const TileStreams &s, int wave, unsigned lane)
+// The bitmap words are the chunk's, the same for each of its tiles.
+__device__ __forceinline__ u2 load_bitmap(const uint8_t *stream, const TileStreams &s, unsigned lane)
 {
-    const unsigned m = lane & 3u;
     u2 bm = {0u, 0u};
     typedef unsigned u2a __attribute__((ext_vector_type(2), aligned(4)));
-    if (from.bitmap) bm = *(const CDSGD_GLOBAL u2a *)(from.bitmap + s.segment_at + 8u * m);
+    if (stream) bm = *(const CDSGD_GLOBAL u2a *)(stream + s.segment_at + 8u * (lane & 3u));
+    return bm;
+}
+
+template <int SZ>
+__device__ __forceinline__ void load_sparse(unsigned (&w)[kWordsPerWave<SZ>], const StreamPointers<SZ, 4, true> &from,
+                                            u2 bm, const TileStreams &s, int wave, unsigned lane)
+{
+    const unsigned m = lane & 3u;
     // words in front of the tile's own: summed over the worker's four lanes
     int before = m < s.tile ? __builtin_popcount(bm.x) + __builtin_popcount(bm.y) : 0;
     before += __builtin_amdgcn_mov_dpp(before, 0xB1, 0xF, 0xF, true);  // quad_perm [1, 0, 3, 2]
@@ -169,7 +183,7 @@ __device__ __forceinline__ void load_words(unsigned (&w)[kWordsPerWave<SZ>], con
                                            const TileStreams &s, int wave, unsigned lane)
 {
     if constexpr (WAVES == 1) load_packed_quarter(w, from.p, s, lane);
-    else if constexpr (SPARSE) load_sparse<SZ>(w, from, s, wave, lane);
+    else if constexpr (SPARSE) load_sparse<SZ>(w, from, load_bitmap(from.bitmap, s, lane), s, wave, lane);
     else load_packed<SZ>(w, from.p, s, wave, lane);
 }
 
@@ -191,11 +205,13 @@ template <int PLANES>
 struct BitCounts {
     unsigned p[PLANES];  // p[i]: bit i of the count of every position
 
-    // Count W words (W = 2, 4 or 16; at most 2^PLANES - 1 at a time can be held).
+    // Count W words (W = 1, 2, 4, 8 or 16; at most 2^PLANES - 1 at a time can be held).
     template <int W>
     __device__ __forceinline__ void count(const unsigned (&w)[W])
     {
-        if constexpr (W == 2) {
+        if constexpr (W == 1) {
+            p[0] = w[0];
+        } else if constexpr (W == 2) {
             p[0] = w[0] ^ w[1];
             p[1] = w[0] & w[1];
         } else {
@@ -245,9 +261,9 @@ struct BitCounts {
     }
 };
 
-// planes a wave needs: counts up to 2, 4 and 16
+// planes a wave needs: counts up to 1, 2, 4, 8 and 16
 template <int SZ>
-constexpr int kPlanes = SZ == kUpTo8 ? 2 : (SZ == kUpTo16 ? 3 : 5);
+constexpr int kPlanes = SZ == kUpTo4 ? 1 : (SZ == kUpTo8 ? 2 : (SZ == kUpTo16 ? 3 : (SZ == kUpTo32 ? 4 : 5)));
 
 // ---- chain form -------------------------------------------------------------
 // One rounded add of +t, -t or 0 per worker and element: a fused multiply-add whose multiplier is a 16-bit float
@@ -288,9 +304,13 @@ __device__ __forceinline__ void chain_byte(f4 &acc, unsigned byte, float t)
 // ---- a tile's sums ------------------------------------------------------------
 // LDS of a group: the four waves' partial counts, or the workers' words as signed fields and the sums on their way
 // from words to quads.
+// Chain form: up to 16 workers every lane adds up the bytes of its own quad, above that the lanes add up words and
+// exchange the sums (decode-and-sum of 2^27 elements, N = 32: 0.270 ms by words, 0.298 by bytes).
+template <int SZ>
+constexpr bool kByBytes = SZ != kAnyWorkers && SZ <= kUpTo16;
 template <int SZ, int FORM, int WAVES>
 constexpr unsigned kTileLds = (FORM == kCount ? 4u * 4u * kTileQuads
-                                              : (unsigned)kMaxRows<SZ> * kTileBytes + (SZ == kAnyWorkers ? 16u * kTileQuads : 0u)) *
+                                              : (unsigned)kMaxRows<SZ> * kTileBytes + (kByBytes<SZ> ? 0u : 16u * kTileQuads)) *
                               WAVES / 4;
 
 template <int WAVES>
@@ -306,18 +326,31 @@ __device__ __forceinline__ void group_sync()
     }
 }
 
+// A lane's place in its group.  A group of four waves: wave v holds words of its workers, word l in lane l; a group of
+// one: lanes 16 v ..
+template <int WAVES>
+struct TilePlace {
+    unsigned tid, lane;
+    int wave;
+    __device__ __forceinline__ TilePlace()
+    {
+        tid = threadIdx.x;
+        lane = tid & (16u * WAVES - 1u);
+        wave = WAVES == 4 ? __builtin_amdgcn_readfirstlane((int)(tid >> 6)) : (int)(tid >> 4);
+    }
+};
+
 // The sums of this lane's quad of a tile over all workers.  `w` holds the wave's words (load_words); the own codes
 // come as this lane's packed byte and as the values it stands for, own_at is their place in the order (-1: none).
-// Everything a group has written to LDS before has been read when it calls this again (a barrier of the caller's).
+// In two halves, with a barrier between them: the first leaves in LDS what the waves know of their workers, the second
+// reads it.  Everything a group has written to LDS before has been read when it starts over (a barrier of the caller's).
 template <int SZ, int FORM, int WAVES>
-__device__ __forceinline__ f4 tile_sums(const unsigned (&w)[kWordsPerWave<SZ>], unsigned own_code, f4 own_value,
-                                        int own_at, int num_workers, float t, uint8_t *lds)
+__device__ __forceinline__ void tile_put(const unsigned (&w)[kWordsPerWave<SZ>], unsigned own_code, int own_at,
+                                         int num_workers, uint8_t *lds, TilePlace<WAVES> at)
 {
-    // a group of four waves: wave v holds words of its workers, word l in lane l; a group of one: lanes 16 v ..
-    constexpr unsigned kQuads = 64u * WAVES, kWords = 16u * WAVES, kBytes = kQuads;
-    const unsigned tid = threadIdx.x, lane = tid & (kWords - 1u);
-    const int wave = WAVES == 4 ? __builtin_amdgcn_readfirstlane((int)(tid >> 6)) : (int)(tid >> 4);
-    f4 agg;
+    constexpr unsigned kWords = 16u * WAVES, kBytes = 64u * WAVES;
+    const unsigned tid = at.tid, lane = at.lane;
+    const int wave = at.wave;
     if (FORM == kCount) {
         constexpr int P = kPlanes<SZ>;
         BitCounts<P> counts;
@@ -333,14 +366,6 @@ __device__ __forceinline__ f4 tile_sums(const unsigned (&w)[kWordsPerWave<SZ>], 
         q[2] = __builtin_amdgcn_perm(y1, x1, 0x05040100u);
         q[3] = __builtin_amdgcn_perm(y1, x1, 0x07060302u);
         reinterpret_cast<u4 *>(lds)[tid] = q;  // [wave][word][quad]
-        group_sync<WAVES>();
-        unsigned v = 0u;
-#pragma unroll
-        for (unsigned k = 0; k < 4; ++k) v += reinterpret_cast<const unsigned *>(lds)[kQuads * k + tid];
-        const float bias_t = -(float)(4 * ((1 << P) - 1)) * t;
-#pragma unroll
-        for (unsigned c = 0; c < 4; ++c) agg[c] = __builtin_fmaf((float)((v >> (8u * c)) & 0xFFu), t, bias_t);
-        agg = agg + own_value;
     } else {
         // rows of signed fields, worker by worker; the rows up to the next multiple of four are zero
         unsigned *rows = reinterpret_cast<unsigned *>(lds);
@@ -350,8 +375,28 @@ __device__ __forceinline__ f4 tile_sums(const unsigned (&w)[kWordsPerWave<SZ>], 
             if (j != own_at && (SZ != kAnyWorkers || 16 * (i / 4) < num_workers)) rows[kWords * (unsigned)j + lane] = signed_fields(w[i]);
         }
         if (own_at >= 0) lds[kBytes * (unsigned)own_at + tid] = (uint8_t)signed_fields(own_code);
-        group_sync<WAVES>();
-        if constexpr (SZ != kAnyWorkers) {
+    }
+}
+
+template <int SZ, int FORM, int WAVES>
+__device__ __forceinline__ f4 tile_get(f4 own_value, int num_workers, float t, uint8_t *lds, TilePlace<WAVES> at)
+{
+    constexpr unsigned kQuads = 64u * WAVES, kBytes = kQuads;
+    const unsigned tid = at.tid, lane = at.lane;
+    const int wave = at.wave;
+    f4 agg;
+    if (FORM == kCount) {
+        constexpr int P = kPlanes<SZ>;
+        unsigned v = 0u;
+#pragma unroll
+        for (unsigned k = 0; k < 4; ++k) v += reinterpret_cast<const unsigned *>(lds)[kQuads * k + tid];
+        const float bias_t = -(float)(4 * ((1 << P) - 1)) * t;
+#pragma unroll
+        for (unsigned c = 0; c < 4; ++c) agg[c] = __builtin_fmaf((float)((v >> (8u * c)) & 0xFFu), t, bias_t);
+        agg = agg + own_value;
+    } else {
+        const unsigned *rows = reinterpret_cast<const unsigned *>(lds);
+        if constexpr (kByBytes<SZ>) {
             // every lane adds up its own quad, a byte of every row: one operation more per worker than by words, no exchange
             agg = f4{0.0f, 0.0f, 0.0f, 0.0f};
             unsigned code[SZ];
@@ -382,47 +427,79 @@ __device__ __forceinline__ f4 tile_sums(const unsigned (&w)[kWordsPerWave<SZ>], 
     return agg;
 }
 
+template <int SZ, int FORM, int WAVES>
+__device__ __forceinline__ f4 tile_sums(const unsigned (&w)[kWordsPerWave<SZ>], unsigned own_code, f4 own_value,
+                                        int own_at, int num_workers, float t, uint8_t *lds)
+{
+    const TilePlace<WAVES> at;
+    tile_put<SZ, FORM, WAVES>(w, own_code, own_at, num_workers, lds, at);
+    group_sync<WAVES>();
+    return tile_get<SZ, FORM, WAVES>(own_value, num_workers, t, lds, at);
+}
+
 // ---------------------------------------------------------------------------
-// a4 for one tensor, packed or sparse streams: a tile per group of four waves
+// a4 for one tensor, packed or sparse streams: TILES tiles of a chunk per group of four waves
 // ---------------------------------------------------------------------------
-// Bound by HBM (4 + N / 4 bytes per element).  Measured, this kernel with the global update behind it, against the
-// former one (a chunk per workgroup, bytes staged through LDS): 2^24 elements, N = 32, t = 0.1 86.0 -> 72 us, t = 0.5
-// 73 -> 69; N = 64 128 -> 98 and 101 -> 94; N = 8 48.5 -> 47.2; sparse N = 32 75.6 -> 74.8; 2^27 elements, N = 16 as
-// before.  A bound on the resident groups never helps here (2^24, N = 32, t = 0.1: 83 us with 5 per compute unit).
+// Bound by HBM (4 + N / 4 bytes per element), as long as a group has enough to load and store: with few workers one
+// tile a group is too little (each group lives for one or two round trips, the sparse form's bitmaps in front of its
+// words), so the loads of TILES tiles are in flight together and one barrier serves them all; a chunk's bitmaps are
+// fetched once.  Time of the call, 2^27 elements, several sets of buffers in turn, us: a kernel that takes a chunk per
+// group and stages bytes through LDS / one tile a group / now (the TILES of launch_decode_sum):
+//   packed   N = 2 108 / 133 / 96;  4 106 / 138 / 110;  8 128 / 139 / 126;  17, t = 0.3 212 / 227 / 201
+//   sparse, one code in 4     N = 4 112 / 238 / 114;  8 139 / 237 / 142;  16 194 / 242 / 201;  17 216 / 280 / 209
+//   sparse, one code in 256   N = 4 103 / 183 / 100;  8 146 / 248 / 146;  16 194 / 267 / 184;  17 221 / 292 / 209
+// With many workers it is the word-wise decode that pays (2^24 elements, N = 32 and 64, t = 0.3: 55 and 100 us with
+// the chunk-wise kernel, 40 and 65 now).
 // xcd: which order the tiles are dealt in.  The chunk-wise order pays where the tiles of a chunk share its segment
 // (sparse streams), and on long tensors (2^27 elements, N = 16: 421 against 428 us); on shorter ones the plain order
-// is 1 % faster (2^24: 71.5 against 72.5).
+// is 1 % faster (2^24: 71.5 against 72.5; both with the global update behind it).
 // The workers' stream pointers of a single-tensor call; they travel in the kernel arguments.
 struct StreamTable {
     const uint8_t *p[CDSGD_MAX_WORKERS];  // null past the last worker
 };
 
-template <int SZ, int FORM, bool SPARSE>
+template <int SZ, int FORM, bool SPARSE, int TILES>
 __global__ __launch_bounds__(kTileQuads) void k_decode_sum(StreamTable tab, int num_workers, float *__restrict__ agg_out,
-                                                           Extent ext, unsigned num_tiles, int xcd, float t)
+                                                           Extent ext, unsigned num_groups, int xcd, float t)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[kTileLds<SZ, FORM, 4>];
+    static_assert(kTilesPerChunk % TILES == 0, "the tiles of a group lie in one chunk");
+    constexpr unsigned kPerChunk = kTilesPerChunk / TILES, kLds = kTileLds<SZ, FORM, 4>;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kLds * TILES];
     const unsigned tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
-    const unsigned x = xcd ? piece_of_workgroup<true>(blockIdx.x, kTilesPerChunk, num_tiles) : blockIdx.x;
-    const unsigned chunk = x / kTilesPerChunk;
+    const unsigned x = xcd ? piece_of_workgroup<true>(blockIdx.x, kPerChunk, num_groups) : blockIdx.x;
+    const unsigned chunk = x / kPerChunk;
     StreamPointers<SZ, 4, SPARSE> from;
-    from.load(tab.p, num_workers, wave, tid & 63u);
+    from.template load<true>(tab.p, num_workers, wave, tid & 63u);
     from.pin();
     TileStreams s;
     s.num_workers = num_workers;
     s.stream_bytes = ext.full_chunks * kChunkQuads + ext.tail_bytes;
-    s.tile_at = x * kTileBytes;
     s.segment_at = (size_t)chunk * (4u * kSegStride);
-    s.tile = x % kTilesPerChunk;
-    unsigned words[kWordsPerWave<SZ>];
-    load_words<SZ, 4, SPARSE>(words, from, s, wave, tid & 63u);
-    const f4 agg = tile_sums<SZ, FORM, 4>(words, 0u, f4{0.0f, 0.0f, 0.0f, 0.0f}, -1, num_workers, t, lds);
-    float *out = agg_out + (size_t)x * (4u * kTileQuads);
-    if (chunk < ext.full_chunks) st4(out, tid, agg);
-    else {
-        const unsigned e0 = s.tile * 4u * kTileQuads;
-        st4g<true>(out, tid, quad_count<true>(ext.tail_elems > e0 ? ext.tail_elems - e0 : 0u, tid), agg);
+    u2 bitmap = {0u, 0u};
+    if constexpr (SPARSE) bitmap = load_bitmap(from.bitmap, s, tid & 63u);
+    const TilePlace<4> at;
+    unsigned words[TILES][kWordsPerWave<SZ>];
+#pragma unroll
+    for (unsigned k = 0; k < TILES; ++k) {
+        s.tile_at = (x * TILES + k) * kTileBytes;
+        s.tile = x % kPerChunk * TILES + k;
+        if constexpr (SPARSE) load_sparse<SZ>(words[k], from, bitmap, s, wave, tid & 63u);
+        else load_packed<SZ>(words[k], from.p, s, wave, tid & 63u);
+    }
+#pragma unroll
+    for (unsigned k = 0; k < TILES; ++k) tile_put<SZ, FORM, 4>(words[k], 0u, -1, num_workers, lds + kLds * k, at);
+    group_sync<4>();
+    float *out = agg_out + (size_t)x * (4u * kTileQuads * TILES);
+#pragma unroll
+    for (unsigned k = 0; k < TILES; ++k) {
+        const f4 agg = tile_get<SZ, FORM, 4>(f4{0.0f, 0.0f, 0.0f, 0.0f}, num_workers, t, lds + kLds * k, at);
+        const unsigned qi = kTileQuads * k + tid;
+        if (chunk < ext.full_chunks) st4(out, qi, agg);
+        else {
+            const unsigned e0 = x % kPerChunk * (4u * kTileQuads * TILES);
+            st4g<true>(out, qi, quad_count<true>(ext.tail_elems > e0 ? ext.tail_elems - e0 : 0u, qi), agg);
+        }
     }
 }
 

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
         const unsigned x = piece_of_workgroup<true>(b, kPerChunk, num_tiles);
         const ChunkRef cr = chunks[x / kPerChunk];
         StreamPointers<SZ, WAVES, SPARSE> from;
-        from.load(rows + (size_t)cr.tensor * row_entries(num_workers), num_workers, wave, threadIdx.x & 63u);
+        from.template load<false>(rows + (size_t)cr.tensor * row_entries(num_workers), num_workers, wave, threadIdx.x & 63u);
         const TensorDesc d = tensors[cr.tensor];
         from.pin();
         const unsigned tile = x % kPerChunk;
