@@ -593,49 +593,90 @@ int cdsgd_plan_destroy(cdsgd_plan *plan)
 
 namespace {
 
-// Launch shape of a compressed pass: waves per group, and the LDS a group asks for in all (0: what it uses).
+// Launch shape of a compressed pass: waves per group, the LDS a group asks for in all (0: what it uses), and whether the
+// workers' words are asked for behind the tile's own streams instead of in front of them.
 //
 // The passes are bound by HBM, and HBM serves a mix of reads and writes best when the streams' requests in flight
 // stay close together: groups are dispatched in order, so the number of groups resident bounds how far apart they
 // are, and the LDS that a group asks for bounds that number (160 KiB per compute unit).  Short lists fit the
-// memory-side cache in part and end before such an order matters: there every resident group helps.  Measured, time
-// of the whole pass against the former kernels (one 128-bit load for 16 peers, bytes staged through LDS), N = 16:
-//   groups per compute unit     all      4      3
-//   VGG-16-shaped, t = 0.5     0.91   0.98   1.02     (0.602 ms against 0.612)
-//   VGG-16-shaped, t = 0.3     0.94   1.00   0.97
-//   25 M elements, t = 0.5     1.00   1.02   1.01     (the same with t = 0.3: 1.01 / 1.00 / 0.95)
-//   4 M elements, t = 0.5      1.05   1.02   0.99
-// The chain form's decode is longer and wants one group more.  Up to 8 workers on lists of 16 to 48 M elements, and
-// up to 4 on longer ones, one-wave groups (a quarter of a tile, 22 groups per compute unit, 26 with 16-bit gradients:
-// 40 M elements, N = 8, fp16 143.7 us, 148.6 with 22, 147.4 before) are 1-2 % faster than groups of four waves;
-// elsewhere those are (8 workers: 4 M elements 1.06 against 1.03, VGG-16 1.02-1.05 against 1.00).  Above 16
-// workers: VGG-16-shaped, N = 32, t = 0.5 0.722 ms before, 0.745 with all groups, 0.714 with 32 KiB each; t = 0.3 0.749, 0.735, 0.703 with 38 KiB (N = 64: 1.155, 0.922, 0.915).  Sparse peers, N = 16: 0.581
-// with all groups, 0.594 with 32 KiB each when one code in 256 is sent (0.597 before), 0.673 and 0.653 when one in 4
-// is (0.645 before); above 16 workers all groups (N = 32: 0.643, 0.690; 0.733 before).
-// Count form, 9 to 16 workers, between: 10 M elements 42.5 us with 24 KiB each, 45.4 with 32; from kMidListTiles on
-// (see launch_formal_pass) 32 KiB with 32-bit gradients (25 M elements 111.1 us, 113.0 with 24) and 24 with 16-bit
-// ones (103.1, 106.7 with 32).
+// memory-side cache in part and end before such an order matters: there every resident group helps.  Words asked for
+// first are there soonest for the decode (ResNet-50-shaped list in ranges of a million elements, N = 16: 166.5 us
+// against 169.3), asked for last they leave the order of the tile's own streams at HBM alone.
+//
+// Measured: time of the pass over that of the kernels before these (one 128-bit load for 16 peers, bytes staged
+// through LDS), with several sets of buffers in turn (5 GB in all, as a program that does something else between two
+// passes leaves the memory-side cache).  Lists: flat of 20, 40 and 90 M elements, VGG-16-shaped.  Groups per compute
+// unit, "all" where registers alone bound them; "late": words last.
+//   up to 8 workers, one-wave groups    all / 26 / 22 / 20              four waves: all / 3
+//     N = 4, t = 0.3, 32-bit   20 M     .99 / .99 / .99 / .99           1.01 / .99
+//                              90 M    1.03 / 1.04 / 1.00 / 1.00        1.08 / .99
+//                              VGG-16  1.03 / 1.04 / 1.00 / .98         1.10 / .95
+//     N = 4, t = 0.3, bf16     40 M    1.01 / 1.00 / .99 / 1.00         1.04 / 1.00
+//     N = 8, t = 0.3, bf16     40 M    1.02 / 1.02 / 1.00 / 1.00        1.04 / 1.00     (25 M, fp16: 94.9 us with 26, 95.5 with 22)
+//                              VGG-16  1.05 / 1.04 / 1.00 / 1.01        1.08 / 1.01
+//     N = 8, t = 0.5, 32-bit   40 M    1.01 / 1.01 / .99 / .98          1.04 / .98
+//                              VGG-16  1.05 / 1.05 / 1.03 / 1.00        1.12 / .99
+//   9 to 16 workers, count form         all / 5 / 4 / 3                 late: all / 5 / 4 / 3
+//     N = 16, 32-bit           20 M    1.03 / .98 / .99 / .97           1.04 / .98 / .98 / .97
+//                              40 M    1.04 / 1.01 / 1.00 / .98         1.04 / .99 / .99 / .98
+//                              VGG-16  1.09 / 1.03 / 1.02 / .99         1.10 / 1.02 / 1.03 / .98
+//     N = 16, bf16             20 M    1.00 / .96 / .96 / .97           .98 / .96 / .97 / 1.00
+//                              40 M    1.03 / .98 / .97 / .98           1.02 / .98 / .97 / 1.01
+//                              VGG-16  1.05 / .98 / .98 / .98           1.04 / .97 / .97 / 1.01
+//   9 to 16 workers, chain form         all / 5 / 3                     late: all / 5
+//     N = 16, t = 0.3, 32-bit  26 M    1.01 / 1.00 / 1.07               1.00 / 1.01
+//                              40 M    1.02 / .99 / 1.05                1.02 / 1.00
+//                              VGG-16  1.09 / 1.00 / 1.06               1.08 / 1.01
+//     N = 16, t = 0.3, bf16    40 M    1.00 / 1.00 / 1.07               .99 / 1.00
+//                              VGG-16  1.03 / 1.01 / 1.07               1.02 / 1.00
+//   above 16 workers                    all / 5 / 3
+//     N = 32, t = 0.5, 32-bit  20 M    1.02 / 1.00 / 1.00
+//                              VGG-16  1.06 / 1.01 / 1.00
+//     N = 32, t = 0.3, 32-bit  20 M    .98 / .94 / 1.00                 (VGG-16: 1.01 / .95 / 1.04)
+//     N = 17, t = 0.3, bf16    26 M    1.01 / 1.02 / 1.17               (VGG-16: 1.05 / 1.01 / 1.16)
+//   sparse peers                        all / 5       one code in 256, then one in 4
+//     N = 8, t = 0.3           VGG-16  1.01 / .98     1.04 / .97
+//     N = 9 / 16, t = 0.5      VGG-16   .97 / 1.01, .97 / .99     1.00 / .98, 1.03 / 1.01
+//     N = 16, t = 0.3          VGG-16   .88 / .99     .93 / 1.01
+//   (The bound of the sparse count form above 8 workers costs 3 % where few codes are sent and saves as much where many are.)
+// The same buffers pass after pass with nothing in between are another matter: up to 64 M elements part of them is
+// still in the memory-side cache, and lists of 28 to 64 M elements of 9 to 16 workers would run up to 7 % faster with
+// all groups (N = 16, t = 0.3, 64 M: 267 us, 284 with 5).  No training step leaves the cache alone like that.
 struct CompressedLaunch {
     unsigned waves, lds;
+    bool late;
 };
 
 CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int form, bool sparse, int grad_type)
 {
     const unsigned tiles = num_chunks * kTilesPerChunk;  // of 1024 elements
-    const bool long_list = tiles > kLongListTiles;
-    if (sparse) return {4u, long_list && num_workers <= kUpTo16 ? 32768u : 0u};
-    if (num_workers <= kUpTo8 && form != kChainTiny) {
-        if (tiles <= kMidListTiles) return {4u, 0u};
-        if (num_workers > 4 && tiles > 48u * 1024u) return {4u, 49152u};
-        return {1u, grad_type == kGradF32 ? 7168u : 6144u};
+    const bool mid_list = tiles > kMidListTiles, long_list = tiles > kLongListTiles, half = grad_type != kGradF32;
+    if (form == kChainTiny) {
+        const bool all = !long_list || (sparse && num_workers > kUpTo16);
+        return {4u, all ? 0u : (num_workers <= kUpTo16 ? 32768u : 38912u), false};
+    }
+    if (sparse) {
+        const bool all = !long_list || num_workers > kUpTo16 || (num_workers > kUpTo8 && form == kChain);
+        return {4u, all ? 0u : 32768u, false};
+    }
+    if (num_workers <= kUpTo8) {
+        if (!mid_list) return {4u, 0u, false};
+        if (tiles <= 48u * 1024u) return {1u, half && !long_list ? 6144u : 7168u, false};
+        if (num_workers > 4) return {4u, 49152u, false};
+        return {1u, half ? 7168u : 8192u, false};
     }
     if (num_workers <= kUpTo16 && form == kCount) {
-        if (long_list) return {4u, 49152u};
-        if (tiles <= 6u * 1024u) return {4u, 0u};
-        return {4u, tiles > kMidListTiles && grad_type == kGradF32 ? 32768u : 24576u};
+        if (tiles <= 6u * 1024u) return {4u, 0u, false};
+        if (!mid_list) return {4u, 24576u, false};
+        if (half) return {4u, 40960u, false};
+        return {4u, long_list ? 49152u : 32768u, true};
     }
-    if (num_workers <= kUpTo16 || form == kCount) return {4u, long_list ? 32768u : 0u};
-    return {4u, long_list ? 38912u : 0u};
+    if (num_workers <= kUpTo16) {
+        if (tiles > (half ? 80u * 1024u : kLongListTiles)) return {4u, 32768u, false};
+        return {4u, 0u, mid_list};
+    }
+    if (form == kCount) return {4u, mid_list ? 32768u : 0u, false};
+    return {4u, (half ? long_list : mid_list) ? 38912u : 0u, false};
 }
 
 // One pass of FormalTraining's loop; with_local = false leaves eq. 11 out (split form).
@@ -658,11 +699,6 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
     const CompressedLaunch shape = compressed_launch(plan->num_chunks, N, form, plan->peers_sparse, plan->grad_type);
     const unsigned num_tiles = plan->num_chunks * (kChunkQuads / (64u * shape.waves));
     const unsigned grid = plan->grid_size(num_tiles, 64u * shape.waves);
-    // The workers' words are asked for first, so that the decode has them soonest (ResNet-50-shaped list in ranges of
-    // a million elements, N = 16: 166.5 us against 169.3), but behind the tile's own streams in the count form of a
-    // longer list, where the order of the requests at HBM counts (VGG-16-shaped, N = 16: 597 us against 603).
-    const bool late = form == kCount && N > kUpTo8 && N <= kUpTo16 && !plan->peers_sparse &&
-                      plan->num_chunks * kTilesPerChunk > kMidListTiles;
     // (a pass with a workgroup limit is meant to share the GPU with other kernels: it leaves the LDS to them)
     const auto bound = [&](unsigned used) { return plan->max_workgroups || shape.lds <= used ? 0u : shape.lds - used; };
 #define CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, GT, SPARSE, LATE)                                                 \
@@ -687,7 +723,9 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
         else if (N <= kUpTo16) CDSGD_LAUNCH_COMPRESSED_F(kUpTo16, FORM);                                        \
         else CDSGD_LAUNCH_COMPRESSED_F(kAnyWorkers, FORM);                                                      \
     } while (0)
-    if (late) CDSGD_LAUNCH_COMPRESSED_G(kUpTo16, 4, kCount, false, true);
+    // (what compressed_launch asks late words for: 9 to 16 workers, the count form with 32-bit gradients only)
+    if (shape.late && form == kCount) CDSGD_LAUNCH_COMPRESSED_S(kUpTo16, 4, kCount, kGradF32, false, true);
+    else if (shape.late) CDSGD_LAUNCH_COMPRESSED_G(kUpTo16, 4, kChain, false, true);
     else if (form == kCount) CDSGD_LAUNCH_COMPRESSED(kCount);
     else if (form == kChain) CDSGD_LAUNCH_COMPRESSED(kChain);
     else CDSGD_LAUNCH_COMPRESSED_F(kAnyWorkers, kChainTiny);

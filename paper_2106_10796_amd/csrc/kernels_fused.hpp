@@ -87,7 +87,8 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
         const unsigned x = piece_of_workgroup<true>(b, kPerChunk, num_tiles);
         const ChunkRef cr = chunks[x / kPerChunk];
         StreamPointers<SZ, WAVES, SPARSE> from;
-        from.template load<false>(rows + (size_t)cr.tensor * row_entries(num_workers), num_workers, wave, threadIdx.x & 63u);
+        // (the select spares 9 to 16 sparse peers a load, 5-7 % of the time of the pass; up to 8 it costs long lists 1-2 %)
+        from.template load<SZ == kUpTo16>(rows + (size_t)cr.tensor * row_entries(num_workers), num_workers, wave, threadIdx.x & 63u);
         const TensorDesc d = tensors[cr.tensor];
         from.pin();
         const unsigned tile = x % kPerChunk;
