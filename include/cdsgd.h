@@ -272,9 +272,11 @@ int cdsgd_plan_set_peer_format(cdsgd_plan *plan, int format);
 /*
  * Bound the number of workgroups that the passes of this plan launch (Sec. 3.2.2: the rest of
  * the step should not stand in the way of the next iteration's computation).  By default a
- * pass launches one workgroup per 4096-element chunk of the layer list and fills the GPU; with
- * a limit it launches at most max_workgroups workgroups, each walking several chunks, so that
- * a pass enqueued on a second stream leaves compute units to kernels that run beside it.  The
+ * pass launches a workgroup for every 256 to 1024 elements of the layer list and fills the GPU;
+ * with a limit it launches at most max_workgroups workgroups of at most 256 threads, each walking
+ * the list in steps, so that a pass enqueued on a second stream leaves compute units to kernels
+ * that run beside it.  (A compressed pass over more than 16 M elements launches no more than 768
+ * for any limit below a sixth of its 1024-element tiles: more of them are slower.)  The
  * results are bit for bit the same for every limit.  0 removes the limit; negative values are
  * CDSGD_ERR_PARAM.  Host-side setting only: it applies to passes enqueued after the call.
  */

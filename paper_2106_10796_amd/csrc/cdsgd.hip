@@ -642,41 +642,69 @@ namespace {
 // The same buffers pass after pass with nothing in between are another matter: up to 64 M elements part of them is
 // still in the memory-side cache, and lists of 28 to 64 M elements of 9 to 16 workers would run up to 7 % faster with
 // all groups (N = 16, t = 0.3, 64 M: 267 us, 284 with 5).  No training step leaves the cache alone like that.
+//
+// With a workgroup limit the groups walk the list, and drift apart as they go: the more of them, the farther apart the
+// streams' requests.  Three to a compute unit keep HBM busy, so above 16 M elements a larger limit is not used up;
+// groups of four waves whatever the length, so that a limit means the same everywhere; 32 KiB each, which leaves 64 of
+// a compute unit's 160 to kernels that run beside (the former kernels held 16 KiB for each of up to five groups) and
+// keeps a kernel that fills the chip from starving the pass.  VGG-16-shaped, us: the former kernels / as many groups
+// as the limit allows, none bounded / now:
+//   alone, N = 16, t = 0.5     limit 1024 711 / 789 / 712;  2048 748 / 801 / 712;  4096 777 / 855 / 712
+//   alone, N = 16, t = 0.3     1024 717 / 775 / 693;  4096 776 / 839 / 693
+//   alone, N = 32, t = 0.5     1024 831 / 909 / 839;  4096 825 / 987 / 839
+//   alone, N = 4, t = 0.5      512 1942 / 1671 / 549 (one-wave groups before);  4096 632 / 640 / 566
+//   the other half of the split step in a stream beside 48 small products, N = 16: 2048 1282 / 1406 / 1275;
+//   N = 8: 4096 1135 / 1340 / 1175;  beside one product that fills the chip, N = 16: 2048 1706 / 1732 / 1742 (1906
+//   without the LDS);  N = 8: 4096 1656 / 1705 / 1665
+// The exceptions: a limit of more than a sixth of the tiles hardly limits, and the pass has the LDS that it has without
+// one (N = 16, limit 60000: 687 us with no bound, 668); sparse streams drift less and use the limit up (N = 16, t = 0.3,
+// 25 M elements, 8192: 112 us, 122 with 768 groups), but for the long lists of the count form (4096: 673 and 650).
+// The words are asked for last where that is better: 16-bit gradients (N = 16, limit 700: 647 us, 708 with the words
+// first), 32-bit ones up to 512 groups (25 M elements 117 and 121; 768 groups, VGG-16-shaped, 757 and 712).
+constexpr unsigned kWalkingGroups = 768;
 struct CompressedLaunch {
     unsigned waves, lds;
     bool late;
+    unsigned groups;  // launch at most this many (0: no bound)
 };
 
-CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int form, bool sparse, int grad_type)
+CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int form, bool sparse, int grad_type,
+                                   unsigned max_workgroups)
 {
     const unsigned tiles = num_chunks * kTilesPerChunk;  // of 1024 elements
     const bool mid_list = tiles > kMidListTiles, long_list = tiles > kLongListTiles, half = grad_type != kGradF32;
+    if (max_workgroups != 0) {
+        const bool walk = max_workgroups <= tiles / 6u, count16 = form == kCount && num_workers > kUpTo8 && num_workers <= kUpTo16;
+        if (!mid_list || (sparse && !(walk && long_list && count16))) return {4u, 0u, false, 0u};
+        if (walk) return {4u, 32768u, !sparse && count16 && (half || max_workgroups <= 512u), kWalkingGroups};
+        if (num_workers <= kUpTo8) return {4u, 49152u, false, 0u};
+    }
     if (form == kChainTiny) {
         const bool all = !long_list || (sparse && num_workers > kUpTo16);
-        return {4u, all ? 0u : (num_workers <= kUpTo16 ? 32768u : 38912u), false};
+        return {4u, all ? 0u : (num_workers <= kUpTo16 ? 32768u : 38912u), false, 0u};
     }
     if (sparse) {
         const bool all = !long_list || num_workers > kUpTo16 || (num_workers > kUpTo8 && form == kChain);
-        return {4u, all ? 0u : 32768u, false};
+        return {4u, all ? 0u : 32768u, false, 0u};
     }
     if (num_workers <= kUpTo8) {
-        if (!mid_list) return {4u, 0u, false};
-        if (tiles <= 48u * 1024u) return {1u, half && !long_list ? 6144u : 7168u, false};
-        if (num_workers > 4) return {4u, 49152u, false};
-        return {1u, half ? 7168u : 8192u, false};
+        if (!mid_list) return {4u, 0u, false, 0u};
+        if (tiles <= 48u * 1024u) return {1u, half && !long_list ? 6144u : 7168u, false, 0u};
+        if (num_workers > 4) return {4u, 49152u, false, 0u};
+        return {1u, half ? 7168u : 8192u, false, 0u};
     }
     if (num_workers <= kUpTo16 && form == kCount) {
-        if (tiles <= 6u * 1024u) return {4u, 0u, false};
-        if (!mid_list) return {4u, 24576u, false};
-        if (half) return {4u, 40960u, false};
-        return {4u, long_list ? 49152u : 32768u, true};
+        if (tiles <= 6u * 1024u) return {4u, 0u, false, 0u};
+        if (!mid_list) return {4u, 24576u, false, 0u};
+        if (half) return {4u, 40960u, false, 0u};
+        return {4u, long_list ? 49152u : 32768u, true, 0u};
     }
     if (num_workers <= kUpTo16) {
-        if (tiles > (half ? 80u * 1024u : kLongListTiles)) return {4u, 32768u, false};
-        return {4u, 0u, mid_list};
+        if (tiles > (half ? 80u * 1024u : kLongListTiles)) return {4u, 32768u, false, 0u};
+        return {4u, 0u, mid_list, 0u};
     }
-    if (form == kCount) return {4u, mid_list ? 32768u : 0u, false};
-    return {4u, (half ? long_list : mid_list) ? 38912u : 0u, false};
+    if (form == kCount) return {4u, mid_list ? 32768u : 0u, false, 0u};
+    return {4u, (half ? long_list : mid_list) ? 38912u : 0u, false, 0u};
 }
 
 // One pass of FormalTraining's loop; with_local = false leaves eq. 11 out (split form).
@@ -696,11 +724,12 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
     const bool pow2 = plan->own_thresholds ? plan->own_thresholds_pow2 : is_pow2_threshold(threshold);
     const bool tiny = plan->own_thresholds ? plan->own_thresholds_tiny : is_tiny_threshold(threshold);
     const int form = pow2 ? kCount : (tiny ? kChainTiny : kChain);
-    const CompressedLaunch shape = compressed_launch(plan->num_chunks, N, form, plan->peers_sparse, plan->grad_type);
+    const CompressedLaunch shape = compressed_launch(plan->num_chunks, N, form, plan->peers_sparse, plan->grad_type,
+                                                     plan->max_workgroups);
     const unsigned num_tiles = plan->num_chunks * (kChunkQuads / (64u * shape.waves));
-    const unsigned grid = plan->grid_size(num_tiles, 64u * shape.waves);
-    // (a pass with a workgroup limit is meant to share the GPU with other kernels: it leaves the LDS to them)
-    const auto bound = [&](unsigned used) { return plan->max_workgroups || shape.lds <= used ? 0u : shape.lds - used; };
+    unsigned grid = plan->grid_size(num_tiles, 64u * shape.waves);
+    if (shape.groups != 0 && grid > shape.groups) grid = shape.groups;
+    const auto bound = [&](unsigned used) { return shape.lds <= used ? 0u : shape.lds - used; };
 #define CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, GT, SPARSE, LATE)                                                 \
     hipLaunchKernelGGL((k_fused_compressed<SZ, WAVES, FORM, GT, SPARSE, LATE>), dim3(grid), dim3(64 * WAVES),         \
                        bound(kTileLds<SZ, FORM, WAVES>), s, plan->tensors, plan->chunk_table(), plan->rows,      \
@@ -723,8 +752,8 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
         else if (N <= kUpTo16) CDSGD_LAUNCH_COMPRESSED_F(kUpTo16, FORM);                                        \
         else CDSGD_LAUNCH_COMPRESSED_F(kAnyWorkers, FORM);                                                      \
     } while (0)
-    // (what compressed_launch asks late words for: 9 to 16 workers, the count form with 32-bit gradients only)
-    if (shape.late && form == kCount) CDSGD_LAUNCH_COMPRESSED_S(kUpTo16, 4, kCount, kGradF32, false, true);
+    // (late words: 9 to 16 workers' packed streams only)
+    if (shape.late && form == kCount) CDSGD_LAUNCH_COMPRESSED_G(kUpTo16, 4, kCount, false, true);
     else if (shape.late) CDSGD_LAUNCH_COMPRESSED_G(kUpTo16, 4, kChain, false, true);
     else if (form == kCount) CDSGD_LAUNCH_COMPRESSED(kCount);
     else if (form == kChain) CDSGD_LAUNCH_COMPRESSED(kChain);
