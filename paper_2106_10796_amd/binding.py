@@ -145,7 +145,7 @@ def _stream():
 
     Asked for without building a torch.cuda.Stream object (0.2 us instead of 2.9, of the 7 us that a call on a
     small layer list took)."""
-    if _raw_stream is not None and torch.cuda.is_initialized():
+    if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
         return _raw_stream(_current_device())
     return torch.cuda.current_stream().cuda_stream
 
