@@ -276,7 +276,13 @@ int cdsgd_plan_set_peer_format(cdsgd_plan *plan, int format);
  * with a limit it launches at most max_workgroups workgroups of at most 256 threads, each walking
  * the list in steps, so that a pass enqueued on a second stream leaves compute units to kernels
  * that run beside it.  (A compressed pass over more than 16 M elements launches no more than 768
- * for any limit below a sixth of its 1024-element tiles: more of them are slower.)  The
+ * for any limit below a sixth of its 1024-element tiles: more of them are slower.)
+ * LDS left to other streams, of 160 KiB per compute unit: without a limit, compressed passes over
+ * more than 6 M elements and full-gradient passes of any length may ask for LDS to bound the
+ * workgroups resident, 120 to 160 KiB in all (three groups of 48 KiB, or one-wave groups of 6 to
+ * 8 KiB), so a kernel of another stream that needs more than the rest waits until groups end.  With
+ * a limit a full-gradient pass asks for none, and a compressed pass at most for 32 KiB in each of three
+ * groups, as long as the limit is below that sixth.  The
  * results are bit for bit the same for every limit.  0 removes the limit; negative values are
  * CDSGD_ERR_PARAM.  Host-side setting only: it applies to passes enqueued after the call.
  */

@@ -70,11 +70,12 @@ namespace {
 //   quantise-and-pack               6.71 / 6.72 / - / 6.83 / - / 6.88 / 6.09 / 5.10
 //   update, both rules              6.36 / 6.34 / - / 6.55 / - / 6.50 / 6.55 / 6.18
 //   correction pass, sum in kernel  6.19 / 6.39-6.41 / 6.35 / 6.24 / - / 5.97   (by size and type: lds_of_kernel_sum)
-// eq. 11 alone loses with any bound and gets none; the compressed pass has a rule of its own (compressed_launch).  The same bound stated to the compiler instead (amdgpu_waves_per_eu with a maximum of
-// 5) gives 6.55 and 6.45 TB/s on the first and the third line: most of the gain, not all of it.  While a
-// pass launched this way runs it holds the compute units' LDS, so a kernel of another stream that needs
-// LDS waits for it; a pass with a workgroup limit (cdsgd_plan_set_max_workgroups), which is meant to run
-// beside other kernels, is launched without the bound.
+// eq. 11 alone loses with any bound and gets none; the compressed pass has a rule of its own (compressed_launch).
+// The same bound stated to the compiler instead (amdgpu_waves_per_eu with a maximum of 5) gives 6.55 and 6.45 TB/s on
+// the first and the third line: most of the gain, not all of it.  While a pass launched this way runs it holds the
+// compute units' LDS, so a kernel of another stream that needs LDS waits for it; a full-gradient pass with a
+// workgroup limit (cdsgd_plan_set_max_workgroups), which is meant to run beside other kernels, is launched without
+// the bound, a compressed one with a smaller one (compressed_launch).
 constexpr unsigned kLdsFor20Waves = 8192;
 constexpr unsigned kLdsFor22Waves = 7168;
 constexpr unsigned kLdsFor26Waves = 6144;
@@ -139,7 +140,7 @@ constexpr unsigned kUpdateLanes = 64;  // ... and of k_update
 // Tensors and lists of more tiles (1024 elements each) than this are long: their streams pass the 256 MB
 // memory-side cache by far, and the order in which they are read and written decides.
 constexpr unsigned kLongListTiles = 28u * 1024u;
-constexpr unsigned kMidListTiles = 16u * 1024u;  // half of that: where the residency of some passes begins to matter
+constexpr unsigned kMidListTiles = 16u * 1024u;  // where the residency of most compressed passes begins to matter
 
 // A threshold 2^e (moderate e): every multiple m*t, |m| <= 2*CDSGD_MAX_WORKERS, is exact.
 inline bool is_pow2_threshold(float t)
@@ -653,6 +654,9 @@ namespace {
 //   alone, N = 16, t = 0.3     1024 717 / 775 / 693;  4096 776 / 839 / 693
 //   alone, N = 32, t = 0.5     1024 831 / 909 / 839;  4096 825 / 987 / 839
 //   alone, N = 4, t = 0.5      512 1942 / 1671 / 549 (one-wave groups before);  4096 632 / 640 / 566
+//   the other half of the split step alone, N = 16: 1024 576 / 659 / 617;  2048 607 / 665 / 613;  t = 0.3, 1024
+//   606 / 624 / 567  (behind the former kernels at t = 0.5 and limits near 1024: two groups per compute unit take
+//   520 us alone, but beside the small products below 1620 us against 1250, so three stay)
 //   the other half of the split step in a stream beside 48 small products, N = 16: 2048 1282 / 1406 / 1275;
 //   N = 8: 4096 1135 / 1340 / 1175;  beside one product that fills the chip, N = 16: 2048 1706 / 1732 / 1742 (1906
 //   without the LDS);  N = 8: 4096 1656 / 1705 / 1665

@@ -126,15 +126,15 @@ constexpr int kLocalOnly = 3;  // eq. 11 alone: w_local = W - lr_local * g, the 
 // Launch shape of these passes, chosen by measurement: a workgroup is ONE wave that takes one
 // quad per lane (a "piece" of 64 quads = 1 KiB of every stream; 16 pieces to a chunk), and the
 // N-way sum loads the workers' gradients one after the other, each add waiting for its load.
-// Memory-level parallelism comes from the number of waves (32 per compute unit), not from
+// Memory-level parallelism comes from the number of waves (20 to 32 per compute unit), not from
 // loads in flight per wave: waves that start together then walk the N streams together, so
 // the requests in flight chip-wide fall on one or two streams at a time instead of all N.
 // On the VGG-16-shaped list with 16 workers the sum runs at 6.2-6.3 TB/s that way; with 15
 // loads in flight per wave it ran at 5.6 TB/s, and with 512-lane workgroups, two quads per lane
-// and 8 loads in flight at 5.6-5.7 TB/s.  Two at a time and fewer waves (13 per compute unit) give the
-// same with 32-bit gradients (8 workers 0.942 ms against 0.947; 25 M elements 0.180 against 0.182) and are
-// better with 16-bit ones, whose loads are half as large (25 M elements, N = 16: 0.186 ms against 0.190,
-// and 0.203 with one at a time and 26 waves; 4 M elements, N = 8: 20.5 us against 21.1 and 23.1).
+// and 8 loads in flight at 5.6-5.7 TB/s.  Two at a time, at the residencies launched (lds_of_kernel_sum), are
+// worse with 32-bit gradients (VGG-16-shaped, N = 8 / 16: 0.967 / 1.731 ms, 0.918 / 1.631 one at a time; 25 M
+// elements, N = 16: 327 and 309 us) and better with 16-bit ones, whose loads are half as large (VGG-16-shaped,
+// N = 16: 0.929 ms, 1.148 one at a time; 25 M elements, N = 16: 183 and 204 us; 4 M, N = 8: 20.7 and 21.4 us).
 constexpr unsigned kFullBlock = CDSGD_FULL_BLOCK;            // lanes per workgroup = quads per piece
 constexpr unsigned kPiecesPerChunk = kChunkQuads / kFullBlock;
 static_assert(kChunkQuads % kFullBlock == 0 && kFullBlock % 64 == 0, "pieces tile a chunk, whole waves");

@@ -251,8 +251,8 @@ int main(int argc, char **argv)
     HIP_OK(hipSetDevice(0));
     std::printf("library build %s\n", cdsgd_build_id());
     int bad = 0;
-    bad |= run(seed + 1, 4, 1, 2, 3, 0.25f, false);   // count form of the decode, one-wave pieces
-    bad |= run(seed + 2, 16, 15, 0, 4, 0.3f, false);  // chain form, four-wave pieces, no warm-up pass before the copy
+    bad |= run(seed + 1, 4, 1, 2, 3, 0.25f, false);   // count form of the decode
+    bad |= run(seed + 2, 16, 15, 0, 4, 0.3f, false);  // chain form, no warm-up pass before the copy
     bad |= run(seed + 3, 1, 0, 1, 2, 0.5f, false);    // a single worker
     bad |= run(seed + 4, 9, 4, 1, 3, 0.05f, true);    // ranges, own stream
     if (bad) {
