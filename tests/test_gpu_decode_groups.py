@@ -1,6 +1,7 @@
 """GPU parity of decode-and-sum at the edges of its groups (4, 2 or 1 tiles of 1024 elements, by the number of workers)
-and of the batches of workers it is compiled for (4, 8, 16, 32), packed and sparse streams, count and chain form: bit
-for bit against the oracle, and on tensors long enough for the chunk-wise order against the call on their parts."""
+and of the batches of workers it is compiled for (4, 8, 16, 32), packed and sparse streams, count and chain form and the
+chain of thresholds whose half is not exact: bit for bit against the oracle, and on tensors long enough for the
+chunk-wise order against the call on their parts."""
 import numpy as np
 import pytest
 import torch
@@ -22,7 +23,7 @@ def B():
 
 
 @pytest.mark.parametrize("sparse", [False, True])
-@pytest.mark.parametrize("t", [0.25, 0.3])
+@pytest.mark.parametrize("t", [0.25, 0.3, 1.1e-38])
 @pytest.mark.parametrize("N", [1, 3, 4, 5, 8, 9, 16, 17, 20, 31, 32, 33, 64])
 def test_decode_sum_at_group_and_batch_edges(B, oracle, N, t, sparse):
     rng = np.random.default_rng(41 * N + int(sparse))
