@@ -354,7 +354,13 @@ int launch_full_pass(const PlanTables *plan, int local_mode, float lr_local, flo
 // groups, 127 with 5) and 6 in the chain form (N = 9: 140 with all, 136 with 6, 144 with 5), above 8 workers from 16 M
 // elements on (N = 16: 9 M 17.8 us with all, 18.4 with 6; 25 M 40.0 and 39.5); 4 streams and fewer write mostly and
 // lose with any bound (N = 2: 96 us, 113 with 5); sparse streams gain in the count form (N = 12, one code in 4: 173 us,
-// 169 with 6) and lose in the chain form.
+// 169 with 6) and lose in the chain form; above 32 workers the count form gains from 16 M elements on (N = 64, 60 M:
+// decode-and-sum and update 288 us with all, 283 with 5).
+// Packed streams are read non-temporally when they are more than the caches between the workers' data and the compute
+// units hold on to: above 28 MB, and above 56 MB up to 8 workers, whose sums write more than they read (decode-and-sum
+// and update, default policy / non-temporal, us: N = 4, 25 M 62 / 63, 60 M 145 / 143;  N = 8, 25 M 66 / 67, 60 M 159 /
+// 154;  N = 16, 4 M 16.7 / 16.9, 9 M 32.1 / 31.6, 60 M 181 / 173;  N = 17, 4 M 16.7 / 17.5;  N = 32, 4 M 20.0 / 19.7,
+// 16 M 67 / 63;  N = 64, 1 M the same, 4 M 27.9 / 27.2, 60 M 327 / 313).
 template <bool SPARSE>
 int launch_decode_sum(const uint32_t *const *streams, int num_workers, float *agg, size_t n, float threshold, void *hip_stream)
 {
@@ -364,12 +370,18 @@ int launch_decode_sum(const uint32_t *const *streams, int num_workers, float *ag
     const unsigned tiles = (unsigned)units_of(n, kTileQuads);
     const Extent ext = extent_of(n);
     const int xcd = SPARSE || tiles > kLongListTiles ? 1 : 0;
+    const bool nt = !SPARSE && (unsigned long long)num_workers * packed_bytes_of(n) > (num_workers > kUpTo8 ? 28000000ull : 56000000ull);
     hipStream_t s = (hipStream_t)hip_stream;
 #define CDSGD_LAUNCH_DECODE(SZ, FORM, TILES, LDS)                                                              \
     do {                                                                                                       \
         const unsigned groups = (tiles + TILES - 1u) / TILES, used = kTileLds<SZ, FORM, 4> * TILES, want = LDS; \
-        hipLaunchKernelGGL((k_decode_sum<SZ, FORM, SPARSE, TILES>), dim3(groups), dim3(kTileQuads),             \
-                           want > used ? want - used : 0u, s, tab, num_workers, agg, ext, groups, xcd, threshold); \
+        const unsigned more = want > used ? want - used : 0u;                                                   \
+        if (!SPARSE && nt)                                                                                      \
+            hipLaunchKernelGGL((k_decode_sum<SZ, FORM, SPARSE, TILES, !SPARSE>), dim3(groups), dim3(kTileQuads), \
+                               more, s, tab, num_workers, agg, ext, groups, xcd, threshold);                    \
+        else                                                                                                    \
+            hipLaunchKernelGGL((k_decode_sum<SZ, FORM, SPARSE, TILES, false>), dim3(groups), dim3(kTileQuads),  \
+                               more, s, tab, num_workers, agg, ext, groups, xcd, threshold);                    \
     } while (0)
     const bool count = is_pow2_threshold(threshold);
     constexpr unsigned kLdsCount = SPARSE ? 24576u : 32768u, kLdsChain = SPARSE ? 0u : 24576u;
@@ -396,7 +408,7 @@ int launch_decode_sum(const uint32_t *const *streams, int num_workers, float *ag
         else if (tiny && !SPARSE) CDSGD_LAUNCH_DECODE(kAnyWorkers, kChainTiny, 1, 0u);
         else CDSGD_LAUNCH_DECODE_CHAIN(kUpTo32, kTilesMany, 0u);
     } else {
-        if (count) CDSGD_LAUNCH_DECODE(kAnyWorkers, kCount, kTilesMany, 0u);
+        if (count) CDSGD_LAUNCH_DECODE(kAnyWorkers, kCount, kTilesMany, (!SPARSE && tiles > kMidListTiles ? kLdsCount : 0u));
         else CDSGD_LAUNCH_DECODE_CHAIN(kAnyWorkers, 1, 0u);
     }
 #undef CDSGD_LAUNCH_DECODE_CHAIN

@@ -42,11 +42,13 @@ constexpr int kCount = 0, kChain = 1, kChainTiny = 2;
 
 // One word of a buffer of `bytes` bytes at byte offset `off`; 0 past the end (the buffer's own range check), which
 // is what the lanes behind a ragged end and the absent workers (bytes == 0: nothing is read) want.
+// POLICY: 0, or kStream where the streams are more than the caches hold (load_packed).
+template <int POLICY>
 __device__ __forceinline__ unsigned ld_word(const uint8_t *base, unsigned bytes, unsigned off)
 {
     const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(base), 0, (int)bytes, 0x00027000);
-    return __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)off, 0, 0);
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(base), 0, (int)bytes, kBufferFlags);
+    return __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)off, 0, POLICY);
 }
 
 // Where the streams of a tile are.
@@ -119,14 +121,15 @@ struct StreamPointers {
 };
 
 // This lane's words of the workers that its wave takes; 0 where there is nothing to load.
-template <int SZ>
+// NT: non-temporal.  A bare read of 32 streams of 4 MB beside one written: 38.7 us at the default policy, 33.6 so.
+template <int SZ, bool NT>
 __device__ __forceinline__ void load_packed(unsigned (&w)[kWordsPerWave<SZ>], const uint8_t *const (&p)[kWordsPerWave<SZ>],
                                             const TileStreams &s, int wave, unsigned lane)
 {
 #pragma unroll
     for (int i = 0; i < kWordsPerWave<SZ>; ++i) {
         const bool there = p[i] && (SZ != kAnyWorkers || worker_of<SZ>(wave, i) < s.num_workers);
-        w[i] = ld_word(p[i], there ? s.stream_bytes : 0u, s.tile_at + 4u * lane);
+        w[i] = ld_word<NT ? kStream : 0>(p[i], there ? s.stream_bytes : 0u, s.tile_at + 4u * lane);
     }
 }
 
@@ -163,7 +166,7 @@ __device__ __forceinline__ void load_sparse(unsigned (&w)[kWordsPerWave<SZ>], co
             const bool sent = __builtin_amdgcn_inverse_ballot_w64(((unsigned long long)hi << 32) | lo);
             // a lane whose word is zero asks past the end of the segment and gets 0 without a read
             const bool there = p && (SZ != kAnyWorkers || worker_of<SZ>(wave, i) < s.num_workers);
-            w[i] = ld_word(p + s.segment_at, there ? 4u * kSegStride : 0u, sent ? 4u * (at + rank) : 4u * kSegStride);
+            w[i] = ld_word<0>(p + s.segment_at, there ? 4u * kSegStride : 0u, sent ? 4u * (at + rank) : 4u * kSegStride);
         }
     }
 }
@@ -188,7 +191,7 @@ __device__ __forceinline__ void load_words(unsigned (&w)[kWordsPerWave<SZ>], con
 {
     if constexpr (WAVES == 1) load_packed_quarter(w, from.p, s, lane);
     else if constexpr (SPARSE) load_sparse<SZ>(w, from, load_bitmap(from.bitmap, s, lane), s, wave, lane);
-    else load_packed<SZ>(w, from.p, s, wave, lane);
+    else load_packed<SZ, false>(w, from.p, s, wave, lane);
 }
 
 // ---- count form -------------------------------------------------------------
@@ -457,12 +460,15 @@ __device__ __forceinline__ f4 tile_sums(const unsigned (&w)[kWordsPerWave<SZ>], 
 // xcd: which order the tiles are dealt in.  The chunk-wise order pays where the tiles of a chunk share its segment
 // (sparse streams), and on long tensors (2^27 elements, N = 16: 421 against 428 us); on shorter ones the plain order
 // is 1 % faster (2^24: 71.5 against 72.5; both with the global update behind it).
+// The aggregate is written through and stays in the memory-side cache, where the global update that follows finds it
+// (decode-and-sum and update, non-temporal store / now, us: N = 16, 50 M 162 / 150; N = 32, 16 M 70 / 66; N = 4, 4 M
+// 13.0 / 12.5; at the default policy the flush of the L2s at the end of the kernel costs what the update gains).
 // The workers' stream pointers of a single-tensor call; they travel in the kernel arguments.
 struct StreamTable {
     const uint8_t *p[CDSGD_MAX_WORKERS];  // null past the last worker
 };
 
-template <int SZ, int FORM, bool SPARSE, int TILES>
+template <int SZ, int FORM, bool SPARSE, int TILES, bool NT>
 __global__ __launch_bounds__(kTileQuads) void k_decode_sum(StreamTable tab, int num_workers, float *__restrict__ agg_out,
                                                            Extent ext, unsigned num_groups, int xcd, float t)
 {
@@ -489,7 +495,7 @@ __global__ __launch_bounds__(kTileQuads) void k_decode_sum(StreamTable tab, int 
         s.tile_at = (x * TILES + k) * kTileBytes;
         s.tile = x % kPerChunk * TILES + k;
         if constexpr (SPARSE) load_sparse<SZ>(words[k], from, bitmap, s, wave, tid & 63u);
-        else load_packed<SZ>(words[k], from.p, s, wave, tid & 63u);
+        else load_packed<SZ, NT>(words[k], from.p, s, wave, tid & 63u);
     }
 #pragma unroll
     for (unsigned k = 0; k < TILES; ++k) tile_put<SZ, FORM, 4>(words[k], 0u, -1, num_workers, lds + kLds * k, at);
@@ -499,10 +505,10 @@ __global__ __launch_bounds__(kTileQuads) void k_decode_sum(StreamTable tab, int 
     for (unsigned k = 0; k < TILES; ++k) {
         const f4 agg = tile_get<SZ, FORM, 4>(f4{0.0f, 0.0f, 0.0f, 0.0f}, num_workers, t, lds + kLds * k, at);
         const unsigned qi = kTileQuads * k + tid;
-        if (chunk < ext.full_chunks) st4(out, qi, agg);
+        if (chunk < ext.full_chunks) st4p<kThrough>(out, qi, agg);
         else {
             const unsigned e0 = x % kPerChunk * (4u * kTileQuads * TILES);
-            st4g<true>(out, qi, quad_count<true>(ext.tail_elems > e0 ? ext.tail_elems - e0 : 0u, qi), agg);
+            st4g<true, kThrough>(out, qi, quad_count<true>(ext.tail_elems > e0 ? ext.tail_elems - e0 : 0u, qi), agg);
         }
     }
 }

@@ -49,6 +49,30 @@ __device__ __forceinline__ void st4(float *base, unsigned qi, f4 v)
 #endif
 }
 
+// Stores that are written through the L2 of the compute die to memory, so that no dirty line is left for the flush at
+// the end of the kernel (2.2 us after a kernel that writes at the default policy; non-temporal stores leave some).
+//   kThrough        the lines stay in the 256 MB memory-side cache: for what the next call reads
+//   kThroughStream  they do not: for what is read again a training step later
+// Policies of a buffer instruction: 1 and 16 are the scope bits sc0 and sc1, 2 is nt.
+constexpr int kStream = 2, kThrough = 17, kThroughStream = 19;
+
+constexpr unsigned kBufferFlags = 0x00027000;  // raw buffer, range checked in bytes
+
+// A quad at most a chunk behind `base`, which is the same in all lanes.
+template <int POLICY>
+__device__ __forceinline__ void st4p(float *base, unsigned qi, f4 v)
+{
+    static_assert(POLICY == kStream || POLICY == kThrough || POLICY == kThroughStream, "policies in use");
+    if constexpr (POLICY == kStream) {
+        st4(base, qi, v);
+    } else {
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        const __amdgpu_buffer_rsrc_t rsrc =
+            __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)(kChunkElems * sizeof(float)), kBufferFlags);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), rsrc, (int)(qi * 16u), 0, POLICY);
+    }
+}
+
 // cnt = number of elements of this quad that exist (4 in the interior).
 template <bool G>
 __device__ __forceinline__ f4 ld4g(const float *base, unsigned qi, int cnt)
@@ -62,11 +86,11 @@ __device__ __forceinline__ f4 ld4g(const float *base, unsigned qi, int cnt)
     return v;
 }
 
-template <bool G>
+template <bool G, int POLICY = kStream>
 __device__ __forceinline__ void st4g(float *base, unsigned qi, int cnt, f4 v)
 {
     if (!G || cnt == 4) {
-        st4(base, qi, v);
+        st4p<POLICY>(base, qi, v);
         return;
     }
     CDSGD_GLOBAL float *p = global_ptr(base) + 4u * qi;
