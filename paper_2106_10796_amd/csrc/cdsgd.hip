@@ -465,10 +465,12 @@ int cdsgd_quantize_pack(const float *grad, float *residual, uint32_t *packed, si
     const Extent pieces = extent_of_units(n, kQuantLanes);
     hipStream_t s = (hipStream_t)hip_stream;
     uint8_t *codes = reinterpret_cast<uint8_t *>(packed);
-    if (n <= kKeepElems)
-        hipLaunchKernelGGL((k_quantize_pack<kQuantLanes, true>), grid, block, kLdsFor20Waves, s, grad, residual, codes, pieces, threshold);
-    else
-        hipLaunchKernelGGL((k_quantize_pack<kQuantLanes, false>), grid, block, kLdsFor20Waves, s, grad, residual, codes, pieces, threshold);
+#define CDSGD_LAUNCH_QUANT(LEN, LDS)                                                                           \
+    hipLaunchKernelGGL((k_quantize_pack<kQuantLanes, LEN>), grid, block, LDS, s, grad, residual, codes, pieces, threshold)
+    if (n <= kSmallElems) CDSGD_LAUNCH_QUANT(kSmallTensor, 0);
+    else if (n <= kKeepElems) CDSGD_LAUNCH_QUANT(kMidTensor, kLdsFor26Waves);
+    else CDSGD_LAUNCH_QUANT(kLargeTensor, kLdsFor20Waves);
+#undef CDSGD_LAUNCH_QUANT
     return launch_status();
 }
 
@@ -510,15 +512,22 @@ int cdsgd_update(float *w_global, float *w_local, const float *grad_local, const
     hipStream_t s = (hipStream_t)hip_stream;
     const dim3 grid((unsigned)units_of(n, kUpdateLanes)), block(kUpdateLanes);
     const Extent pieces = extent_of_units(n, kUpdateLanes);
-#define CDSGD_LAUNCH_UPDATE(LOCAL, GLOBAL, KEEP, LDS)                                                          \
-    hipLaunchKernelGGL((k_update<LOCAL, GLOBAL, KEEP>), grid, block, LDS, s, w_global, w_local, grad_local, agg, \
+#define CDSGD_LAUNCH_UPDATE(LOCAL, GLOBAL, LEN, LDS)                                                           \
+    hipLaunchKernelGGL((k_update<LOCAL, GLOBAL, LEN>), grid, block, LDS, s, w_global, w_local, grad_local, agg, \
                        pieces, lr_local, scale)
-    const bool keep = n <= kKeepElems;
-    if (local && global && keep) CDSGD_LAUNCH_UPDATE(true, true, true, kLdsFor20Waves);
-    else if (local && global) CDSGD_LAUNCH_UPDATE(true, true, false, kLdsFor20Waves);
-    else if (local && keep) CDSGD_LAUNCH_UPDATE(true, false, true, 0);
-    else if (local) CDSGD_LAUNCH_UPDATE(true, false, false, 0);
-    else CDSGD_LAUNCH_UPDATE(false, true, false, 0);
+    const bool small = n <= kSmallElems, mid = n <= kKeepElems;
+    if (local && global) {
+        if (small) CDSGD_LAUNCH_UPDATE(true, true, kSmallTensor, 0);
+        else if (mid) CDSGD_LAUNCH_UPDATE(true, true, kMidTensor, kLdsFor20Waves);
+        else CDSGD_LAUNCH_UPDATE(true, true, kLargeTensor, kLdsFor20Waves);
+    } else if (local) {
+        if (small) CDSGD_LAUNCH_UPDATE(true, false, kSmallTensor, 0);
+        else if (mid) CDSGD_LAUNCH_UPDATE(true, false, kMidTensor, kLdsFor26Waves);
+        else CDSGD_LAUNCH_UPDATE(true, false, kLargeTensor, kLdsFor20Waves);
+    } else {
+        if (small) CDSGD_LAUNCH_UPDATE(false, true, kSmallTensor, 0);
+        else CDSGD_LAUNCH_UPDATE(false, true, kMidTensor, 0);
+    }
 #undef CDSGD_LAUNCH_UPDATE
     return launch_status();
 }

@@ -1,7 +1,11 @@
-"""GPU parity of decode-and-sum on either side of the sizes where the cache policy of its loads changes, and behind a ragged
-end there: bit for bit against the call on parts that are short enough for the other policy."""
+"""GPU parity of the single-tensor calls on either side of the sizes where the cache policy of their loads and stores
+changes, and of the lanes behind a ragged end there: bit for bit against the oracle (update, quantise-and-pack) and,
+for decode-and-sum, against the call on parts that are short enough for the other policy."""
+import numpy as np
 import pytest
 import torch
+
+from helpers import assert_bits_equal
 
 pytestmark = pytest.mark.gpu
 
@@ -13,6 +17,50 @@ def B():
     binding.lib()
     assert torch.cuda.is_available()
     return binding
+
+
+SMALL, KEEP = 3 << 19, 24 << 20
+
+
+def _floats(rng, n, scale):
+    return rng.standard_normal(n, dtype=np.float32) * np.float32(scale)
+
+
+@pytest.mark.parametrize("n", [SMALL, SMALL + 3, KEEP, KEEP + 1])
+@pytest.mark.parametrize("mode", ["local", "global", "both"])
+def test_update_at_the_edges_of_its_lengths(B, oracle, n, mode):
+    rng = np.random.default_rng(n + len(mode))
+    w, g, a = (_floats(rng, n, s) for s in (1.0, 0.1, 3.0))
+    host = {"w": w, "l": np.full(n, 7.0, np.float32), "g": g if mode != "global" else None, "a": a if mode != "local" else None}
+    want_w, want_l = w.copy(), (host["l"].copy() if mode != "global" else None)
+    oracle.update(want_w, want_l, host["g"], host["a"], 0.05, 0.1, 5)
+    pad = {k: torch.full((n + 8,), 9.0, device="cuda") for k in ("w", "l")}
+    for k in pad:
+        pad[k][:n] = torch.from_numpy(host[k]).cuda()
+    dev = {k: None if host[k] is None else torch.from_numpy(host[k]).cuda() for k in ("g", "a")}
+    B.cdsgd_update(pad["w"][:n], pad["l"][:n] if mode != "global" else None, dev["g"], dev["a"], 0.05, 0.1, 5)
+    torch.cuda.synchronize()
+    assert_bits_equal(pad["w"][:n].cpu().numpy(), want_w, "w_global")
+    if mode != "global":
+        assert_bits_equal(pad["l"][:n].cpu().numpy(), want_l, "w_local")
+    assert all(bool((x[n:] == 9.0).all()) for x in pad.values()), "written past the end"
+
+
+@pytest.mark.parametrize("n", [SMALL, SMALL + 3, KEEP, KEEP + 1])
+def test_quantize_pack_at_the_edges_of_its_lengths(B, oracle, n):
+    rng = np.random.default_rng(n)
+    t = 0.3
+    g, r = _floats(rng, n, 0.3), _floats(rng, n, 0.2)
+    want_r = r.copy()
+    want_p = oracle.quantize_pack(g, want_r, t)
+    pad = torch.full((n + 8,), 9.0, device="cuda")
+    pad[:n] = torch.from_numpy(r).cuda()
+    packed = torch.full((B.packed_words(n) + 4,), 5, dtype=torch.int32, device="cuda")
+    B.cdsgd_quantize_pack(torch.from_numpy(g).cuda(), pad[:n], packed[:B.packed_words(n)], t)
+    torch.cuda.synchronize()
+    assert_bits_equal(pad[:n].cpu().numpy(), want_r, "residual")
+    assert_bits_equal(packed[:B.packed_words(n)].cpu().numpy().view(np.uint32), want_p, "packed")
+    assert bool((pad[n:] == 9.0).all()) and bool((packed[B.packed_words(n):] == 5).all()), "written past the end"
 
 
 # elements x workers / 4 bytes of streams: above 28 MB (56 MB up to eight workers) they are read non-temporally
