@@ -306,6 +306,21 @@ unsigned lds_of_kernel_sum(unsigned num_chunks, int num_workers, int grad_type)
     return long_list && num_workers <= 8 ? kLdsFor20Waves : kLdsFor22Waves;
 }
 
+// Whether a pass on 32-bit gradients writes its results through, and leaves them in the memory-side cache, instead of
+// non-temporally.  Measured with both rules, time over that of non-temporal stores, 32-bit / bf16:
+//   sum, N = 2    2 M .94 / .78, 4 M 1.00 / .97, 8 M .97 / .97, 16 M 1.03 / 1.04, 80 M 1.01 / .98, VGG-16 1.02 / .99
+//        N = 4    2 M .95 / .87, 4 M .99 / 1.01, 8 M .94 / .94, 16 M 1.02 / 1.02, 80 M 1.01 / .99, VGG-16 1.01 / .99
+//        N = 8    2 M .99 / .91, 4 M 1.00 / 1.01, 8 M .97 / .95, 16 M 1.01 / 1.02, 80 M .99 / .99, VGG-16 .98 / .99
+//        N = 16   2 M .98 / .96, 3 M 1.02 / 1.13, 8 M .99 / .98, 16 M 1.01 / 1.03, 80 M .99 / .98, VGG-16 .98 / .98
+//   agg_full      1 M 1.00 / 1.00, 4 M .99 / 1.01, 12 M .97 / .97, 25 M 1.01 / 1.01, VGG-16 1.02 / .98
+// (not staying, as the compressed pass stores: 4 M 1.03-1.09, VGG-16 .99-1.01)
+bool keeps_results(unsigned num_chunks, int num_workers, bool sum)
+{
+    const unsigned tiles = num_chunks * kTilesPerChunk;
+    const bool many = sum && num_workers > 4;
+    return tiles <= 2u * 1024u || (many ? tiles > 72u * 1024u : tiles <= 14u * 1024u);
+}
+
 // Launch one full-gradient pass (see k_fused_full) for a plan.
 int launch_full_pass(const PlanTables *plan, int local_mode, float lr_local, float lr_global, void *hip_stream)
 {
@@ -319,24 +334,27 @@ int launch_full_pass(const PlanTables *plan, int local_mode, float lr_local, flo
     // a pass with a workgroup limit is meant to share the GPU with other kernels: it leaves the LDS to them
     const unsigned lds_plain = plan->max_workgroups ? 0u : kLdsFor20Waves;
     const unsigned lds_sum = plan->max_workgroups ? 0u : lds_of_kernel_sum(plan->num_chunks, plan->num_workers, plan->grad_type);
-#define CDSGD_LAUNCH_FULL_T(SUM, LOCAL, GT)                                                                    \
-    hipLaunchKernelGGL((k_fused_full<SUM, LOCAL, GT>), grid, block, (SUM ? lds_sum : lds_plain), s,              \
+#define CDSGD_LAUNCH_FULL_T(SUM, LOCAL, GT, STORE)                                                             \
+    hipLaunchKernelGGL((k_fused_full<SUM, LOCAL, GT, STORE>), grid, block, (SUM ? lds_sum : lds_plain), s,              \
                        plan->tensors, plan->chunk_table(),                                                      \
                        num_pieces, plan->peer_grads, np, plan->self, lr_local, scale)
-#define CDSGD_LAUNCH_FULL(SUM, LOCAL)                                                                          \
+#define CDSGD_LAUNCH_FULL(SUM, LOCAL, STORE)                                                                   \
     do {                                                                                                       \
-        if (plan->grad_type == kGradBF16) CDSGD_LAUNCH_FULL_T(SUM, LOCAL, kGradBF16);                          \
-        else if (plan->grad_type == kGradF16) CDSGD_LAUNCH_FULL_T(SUM, LOCAL, kGradF16);                       \
-        else CDSGD_LAUNCH_FULL_T(SUM, LOCAL, kGradF32);                                                        \
+        if (plan->grad_type == kGradBF16) CDSGD_LAUNCH_FULL_T(SUM, LOCAL, kGradBF16, STORE);                   \
+        else if (plan->grad_type == kGradF16) CDSGD_LAUNCH_FULL_T(SUM, LOCAL, kGradF16, STORE);                \
+        else CDSGD_LAUNCH_FULL_T(SUM, LOCAL, kGradF32, STORE);                                                 \
     } while (0)
+    const bool keep = plan->max_workgroups == 0 && keeps_results(plan->num_chunks, plan->num_workers, sum);
     if (sum) {
-        if (local_mode == kLocalNone) CDSGD_LAUNCH_FULL(true, kLocalNone);
-        else if (local_mode == kLocalCopy) CDSGD_LAUNCH_FULL(true, kLocalCopy);
-        else CDSGD_LAUNCH_FULL(true, kLocalRule);
+        if (local_mode == kLocalNone) CDSGD_LAUNCH_FULL(true, kLocalNone, kStream);
+        else if (local_mode == kLocalCopy) CDSGD_LAUNCH_FULL(true, kLocalCopy, kStream);
+        else if (keep) CDSGD_LAUNCH_FULL(true, kLocalRule, kThrough);
+        else CDSGD_LAUNCH_FULL(true, kLocalRule, kStream);
     } else {
-        if (local_mode == kLocalNone) CDSGD_LAUNCH_FULL(false, kLocalNone);
-        else if (local_mode == kLocalCopy) CDSGD_LAUNCH_FULL(false, kLocalCopy);
-        else CDSGD_LAUNCH_FULL(false, kLocalRule);
+        if (local_mode == kLocalNone) CDSGD_LAUNCH_FULL(false, kLocalNone, kStream);
+        else if (local_mode == kLocalCopy) CDSGD_LAUNCH_FULL(false, kLocalCopy, kStream);
+        else if (keep) CDSGD_LAUNCH_FULL(false, kLocalRule, kThrough);
+        else CDSGD_LAUNCH_FULL(false, kLocalRule, kStream);
     }
 #undef CDSGD_LAUNCH_FULL
 #undef CDSGD_LAUNCH_FULL_T
@@ -696,9 +714,23 @@ namespace {
 // The words are asked for last where that is better: 16-bit gradients (N = 16, limit 700: 647 us, 708 with the words
 // first), 32-bit ones up to 512 groups (25 M elements 117 and 121; 768 groups, VGG-16-shaped, 757 and 712).
 constexpr unsigned kWalkingGroups = 768;
+
+// Stores and the loads of the words.  Non-temporal stores leave dirty lines in the L2s of the compute dies, the packed
+// codes' at the default policy all of them, for the flush at the end of the kernel; written through they leave none.
+// Time of the pass with results written through over that without:
+//   9 to 16 workers   N = 9 / 12 / 16 count, 16 chain, 16 chain bf16   2 M .99 / - / .99 / .99 / .97;  12 M - / .99 / - /
+//                     .99 / .98;  18 M 1.00 / - / .98 / 1.00 / .99;  25 M - / .99 / .97 / .97 / .98;  40 M .98 / - / .98 /
+//                     .99 / .98;  VGG-16 - / .99 / .99 / 1.00 / .98;  90 M 1.04 / - / .99 / 1.01 / .99;  260 M .99 / - /
+//                     .99 / 1.00 / .98   (long 32-bit chains gain nothing and 1 GiB buckets at t = 0.05 lose 1 %)
+//   up to 8 workers   N = 4, t = 0.3  4 M 1.03, 12 M .99, 25 M 1.00, VGG-16 1.06;  N = 8 1.02 / 1.00 / 1.01 / 1.00
+//   above 16          N = 17 / 32, t = 0.3  4 M 1.02 / 1.01;  25 M 1.00 / 1.00;  VGG-16 .98 / .99;  t = 0.5 .99 / 1.01
+// Words read non-temporally, as in decode-and-sum, and 5 groups, over the default policy at its own residency:
+//   N = 33   8 M 1.07-1.08, 20 M .97-1.00, 50 M .96;  N = 48  8 M 1.06, 10 M .96;  N = 64  6 M 1.04, 8 M .95, 25 M .96-.98,
+//   VGG-16 .94-.99   (N = 17: 25 M .99-1.03, VGG-16 1.00-1.04;  N = 32: 25 M .98-.99, VGG-16 1.02-1.04;  N = 16 25 M 1.04)
+constexpr unsigned long long kStreamWordsBytes = 112000000;
 struct CompressedLaunch {
     unsigned waves, lds;
-    bool late;
+    int how;          // kLate, kWrittenOut, kStreamWords
     unsigned groups;  // launch at most this many (0: no bound)
 };
 
@@ -709,36 +741,38 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
     const bool mid_list = tiles > kMidListTiles, long_list = tiles > kLongListTiles, half = grad_type != kGradF32;
     if (max_workgroups != 0) {
         const bool walk = max_workgroups <= tiles / 6u, count16 = form == kCount && num_workers > kUpTo8 && num_workers <= kUpTo16;
-        if (!mid_list || (sparse && !(walk && long_list && count16))) return {4u, 0u, false, 0u};
-        if (walk) return {4u, 32768u, !sparse && count16 && (half || max_workgroups <= 512u), kWalkingGroups};
-        if (num_workers <= kUpTo8) return {4u, 49152u, false, 0u};
+        if (!mid_list || (sparse && !(walk && long_list && count16))) return {4u, 0u, 0, 0u};
+        if (walk) return {4u, 32768u, !sparse && count16 && (half || max_workgroups <= 512u) ? kLate : 0, kWalkingGroups};
+        if (num_workers <= kUpTo8) return {4u, 49152u, 0, 0u};
     }
     if (form == kChainTiny) {
         const bool all = !long_list || (sparse && num_workers > kUpTo16);
-        return {4u, all ? 0u : (num_workers <= kUpTo16 ? 32768u : 38912u), false, 0u};
+        return {4u, all ? 0u : (num_workers <= kUpTo16 ? 32768u : 38912u), 0, 0u};
     }
     if (sparse) {
         const bool all = !long_list || num_workers > kUpTo16 || (num_workers > kUpTo8 && form == kChain);
-        return {4u, all ? 0u : 32768u, false, 0u};
+        return {4u, all ? 0u : 32768u, 0, 0u};
     }
     if (num_workers <= kUpTo8) {
-        if (!mid_list) return {4u, 0u, false, 0u};
-        if (tiles <= 48u * 1024u) return {1u, half && !long_list ? 6144u : 7168u, false, 0u};
-        if (num_workers > 4) return {4u, 49152u, false, 0u};
-        return {1u, half ? 7168u : 8192u, false, 0u};
+        if (!mid_list) return {4u, 0u, 0, 0u};
+        if (tiles <= 48u * 1024u) return {1u, half && !long_list ? 6144u : 7168u, 0, 0u};
+        if (num_workers > 4) return {4u, 49152u, 0, 0u};
+        return {1u, half ? 7168u : 8192u, 0, 0u};
     }
     if (num_workers <= kUpTo16 && form == kCount) {
-        if (tiles <= 6u * 1024u) return {4u, 0u, false, 0u};
-        if (!mid_list) return {4u, 24576u, false, 0u};
-        if (half) return {4u, 40960u, false, 0u};
-        return {4u, long_list ? 49152u : 32768u, true, 0u};
+        if (tiles <= 6u * 1024u) return {4u, 0u, kWrittenOut, 0u};
+        if (!mid_list) return {4u, 24576u, kWrittenOut, 0u};
+        if (half) return {4u, 40960u, kWrittenOut, 0u};
+        return {4u, long_list ? 49152u : 32768u, kWrittenOut | kLate, 0u};
     }
     if (num_workers <= kUpTo16) {
-        if (tiles > (half ? 80u * 1024u : kLongListTiles)) return {4u, 32768u, false, 0u};
-        return {4u, 0u, mid_list, 0u};
+        if (tiles > (half ? 80u * 1024u : kLongListTiles)) return {4u, 32768u, half || tiles <= 48u * 1024u ? kWrittenOut : 0, 0u};
+        return {4u, 0u, kWrittenOut | (mid_list ? kLate : 0), 0u};
     }
-    if (form == kCount) return {4u, mid_list ? 32768u : 0u, false, 0u};
-    return {4u, (half ? long_list : mid_list) ? 38912u : 0u, false, 0u};
+    if (num_workers > kUpTo32 && (unsigned long long)num_workers * tiles * kTileBytes > kStreamWordsBytes)
+        return {4u, 32768u, kStreamWords, 0u};
+    if (form == kCount) return {4u, mid_list ? 32768u : 0u, 0, 0u};
+    return {4u, (half ? long_list : mid_list) ? 38912u : 0u, 0, 0u};
 }
 
 // One pass of FormalTraining's loop; with_local = false leaves eq. 11 out (split form).
@@ -764,37 +798,36 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
     unsigned grid = plan->grid_size(num_tiles, 64u * shape.waves);
     if (shape.groups != 0 && grid > shape.groups) grid = shape.groups;
     const auto bound = [&](unsigned used) { return shape.lds <= used ? 0u : shape.lds - used; };
-#define CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, GT, SPARSE, LATE)                                                 \
-    hipLaunchKernelGGL((k_fused_compressed<SZ, WAVES, FORM, GT, SPARSE, LATE>), dim3(grid), dim3(64 * WAVES),         \
-                       bound(kTileLds<SZ, FORM, WAVES>), s, plan->tensors, plan->chunk_table(), plan->rows,      \
+#define CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, GT, SPARSE, HOW)                                            \
+    hipLaunchKernelGGL((k_fused_compressed<SZ, WAVES, FORM, GT, SPARSE, HOW>), dim3(grid), dim3(64 * WAVES),   \
+                       bound(kTileLds<SZ, FORM, WAVES>), s, plan->tensors, plan->chunk_table(), plan->rows,    \
                        num_tiles, grid, N, plan->self, threshold, lr_local, scale, with_local ? 1 : 0)
-#define CDSGD_LAUNCH_COMPRESSED_G(SZ, WAVES, FORM, SPARSE, LATE)                                                     \
+#define CDSGD_LAUNCH_COMPRESSED(SZ, WAVES, FORM, SPARSE, HOW)                                                  \
     do {                                                                                                       \
-        if (plan->grad_type == kGradBF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradBF16, SPARSE, LATE);        \
-        else if (plan->grad_type == kGradF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF16, SPARSE, LATE);     \
-        else CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF32, SPARSE, LATE);                                      \
+        if (plan->grad_type == kGradBF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradBF16, SPARSE, HOW);  \
+        else if (plan->grad_type == kGradF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF16, SPARSE, HOW); \
+        else CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF32, SPARSE, HOW);                                \
     } while (0)
-#define CDSGD_LAUNCH_COMPRESSED_F(SZ, FORM)                                                                    \
+#define CDSGD_LAUNCH_COMPRESSED_F(FORM)                                                                        \
     do {                                                                                                       \
-        if (plan->peers_sparse) CDSGD_LAUNCH_COMPRESSED_G(SZ, 4, FORM, true, false);                                   \
-        else CDSGD_LAUNCH_COMPRESSED_G(SZ, 4, FORM, false, false);                                                     \
+        if (plan->peers_sparse && N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, true, 0);              \
+        else if (plan->peers_sparse && N <= kUpTo16) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, true, 0);       \
+        else if (plan->peers_sparse) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, true, 0);                   \
+        else if (shape.waves == 1u) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 1, FORM, false, 0);                        \
+        else if (N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, false, 0);                              \
+        else if (N > kUpTo16 && (shape.how & kStreamWords)) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, false, kStreamWords); \
+        else if (N > kUpTo16) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, false, 0);                         \
+        else if (shape.how == (kWrittenOut | kLate)) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kWrittenOut | kLate); \
+        else if (shape.how == kWrittenOut) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kWrittenOut);      \
+        else CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, 0);                                              \
     } while (0)
-#define CDSGD_LAUNCH_COMPRESSED(FORM)                                                                          \
-    do {                                                                                                       \
-        if (shape.waves == 1u) CDSGD_LAUNCH_COMPRESSED_G(kUpTo8, 1, FORM, false, false);                               \
-        else if (N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED_F(kUpTo8, FORM);                                          \
-        else if (N <= kUpTo16) CDSGD_LAUNCH_COMPRESSED_F(kUpTo16, FORM);                                        \
-        else CDSGD_LAUNCH_COMPRESSED_F(kAnyWorkers, FORM);                                                      \
-    } while (0)
-    // (late words: 9 to 16 workers' packed streams only)
-    if (shape.late && form == kCount) CDSGD_LAUNCH_COMPRESSED_G(kUpTo16, 4, kCount, false, true);
-    else if (shape.late) CDSGD_LAUNCH_COMPRESSED_G(kUpTo16, 4, kChain, false, true);
-    else if (form == kCount) CDSGD_LAUNCH_COMPRESSED(kCount);
-    else if (form == kChain) CDSGD_LAUNCH_COMPRESSED(kChain);
-    else CDSGD_LAUNCH_COMPRESSED_F(kAnyWorkers, kChainTiny);
+    if (form == kCount && shape.how == kLate) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, kCount, false, kLate);  // walking groups
+    else if (form == kCount) CDSGD_LAUNCH_COMPRESSED_F(kCount);
+    else if (form == kChain) CDSGD_LAUNCH_COMPRESSED_F(kChain);
+    else if (plan->peers_sparse) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, kChainTiny, true, 0);
+    else CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, kChainTiny, false, 0);
 #undef CDSGD_LAUNCH_COMPRESSED
 #undef CDSGD_LAUNCH_COMPRESSED_F
-#undef CDSGD_LAUNCH_COMPRESSED_G
 #undef CDSGD_LAUNCH_COMPRESSED_S
     return launch_status();
 }
@@ -818,7 +851,7 @@ int launch_local_pass(const PlanTables *plan, float lr_local, void *hip_stream)
     const dim3 grid(plan->grid_size(num_pieces, kFullBlock)), block(kFullBlock);
     hipStream_t s = (hipStream_t)hip_stream;
 #define CDSGD_LAUNCH_LOCAL(GT)                                                                                 \
-    hipLaunchKernelGGL((k_fused_full<false, kLocalOnly, GT>), grid, block, 0, s, plan->tensors,                  \
+    hipLaunchKernelGGL((k_fused_full<false, kLocalOnly, GT, kStream>), grid, block, 0, s, plan->tensors,                  \
                        plan->chunk_table(), num_pieces, (const void *const *)nullptr, 0, plan->self, lr_local,   \
                        0.0f)
     if (plan->grad_type == kGradBF16) CDSGD_LAUNCH_LOCAL(kGradBF16);

@@ -185,13 +185,13 @@ __device__ __forceinline__ void load_packed_quarter(unsigned (&w)[kWordsPerWave<
     }
 }
 
-template <int SZ, int WAVES, bool SPARSE>
+template <int SZ, int WAVES, bool SPARSE, bool NT>
 __device__ __forceinline__ void load_words(unsigned (&w)[kWordsPerWave<SZ>], const StreamPointers<SZ, WAVES, SPARSE> &from,
                                            const TileStreams &s, int wave, unsigned lane)
 {
     if constexpr (WAVES == 1) load_packed_quarter(w, from.p, s, lane);
     else if constexpr (SPARSE) load_sparse<SZ>(w, from, load_bitmap(from.bitmap, s, lane), s, wave, lane);
-    else load_packed<SZ, false>(w, from.p, s, wave, lane);
+    else load_packed<SZ, NT>(w, from.p, s, wave, lane);
 }
 
 // ---- count form -------------------------------------------------------------

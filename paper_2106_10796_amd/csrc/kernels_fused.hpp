@@ -19,13 +19,20 @@ namespace {
 template <int SZ, int FORM>
 constexpr bool kLocalFirst = SZ == kUpTo16 && FORM != kCount;
 
-// LATE: the workers' words are asked for behind the tile's own streams instead of in front of them.
-template <bool G, int SZ, int WAVES, int FORM, int GT, bool SPARSE, bool LATE>
+// How a pass is compiled beside its sizes (compressed_launch says which and why).
+//   kLate        the workers' words are asked for behind the tile's own streams instead of in front of them
+//   kWrittenOut  results are written through the L2 of the compute die (kThroughStream)
+//   kStreamWords the workers' words are read non-temporally
+constexpr int kLate = 1, kWrittenOut = 2, kStreamWords = 4;
+
+template <bool G, int SZ, int WAVES, int FORM, int GT, bool SPARSE, int HOW>
 __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPointers<SZ, WAVES, SPARSE> &from, int num_workers,
                                            int self, unsigned chunk, unsigned tile, unsigned rem_elems,
                                            unsigned rem_bytes, float t, float lr_local, float scale, bool write_local,
                                            uint8_t *lds)
 {
+    constexpr bool LATE = (HOW & kLate) != 0, OUT = (HOW & kWrittenOut) != 0, NT = (HOW & kStreamWords) != 0;
+    constexpr int kStore = OUT ? kThroughStream : kStream;
     const unsigned tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const size_t quad0 = (size_t)chunk * kChunkQuads + tile * (64u * WAVES);
@@ -33,7 +40,7 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
     float *__restrict__ resid = d.residual + 4 * quad0;
     float *__restrict__ wg = d.w_global + 4 * quad0;
     float *__restrict__ wl = d.w_local + 4 * quad0;
-    CDSGD_GLOBAL uint8_t *pself = global_ptr(d.packed_self + quad0);
+    uint8_t *pself = d.packed_self + quad0;
     const int cnt = quad_count<G>(rem_elems, tid);
 
     TileStreams s;
@@ -43,36 +50,36 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
     s.segment_at = (size_t)chunk * (4u * kSegStride);
     s.tile = tile;
     unsigned words[kWordsPerWave<SZ>];
-    if (!LATE) load_words<SZ, WAVES, SPARSE>(words, from, s, wave, tid & 63u);
+    if (!LATE) load_words<SZ, WAVES, SPARSE, NT>(words, from, s, wave, tid & 63u);
     const f4 g = ldgrad<G, GT>(grad, tid, cnt);
     f4 r = ld4g<G>(resid, tid, cnt);
     const f4 w = ld4g<G>(wg, tid, cnt);
     if (LATE) {
         __builtin_amdgcn_sched_barrier(0);
-        load_words<SZ, WAVES, SPARSE>(words, from, s, wave, tid & 63u);
+        load_words<SZ, WAVES, SPARSE, NT>(words, from, s, wave, tid & 63u);
     }
 
     // own codes: quantise, keep the residual, write what would be pushed
     f4 sent;
     const unsigned own = quantize_quad(g, r, t, sent);
-    st4g<G>(resid, tid, cnt, r);
-    if (!G || tid < rem_bytes) pself[tid] = (uint8_t)own;
+    st4g<G, kStore>(resid, tid, cnt, r);
+    if (!G || tid < rem_bytes) st_code<OUT>(pself, tid, own);
 
     // eq. 11 and eq. 10 from the same loaded weight
     f4 vl, vg;
 #pragma unroll
     for (unsigned c = 0; c < 4; ++c) vl[c] = __builtin_fmaf(-lr_local, g[c], w[c]);
-    if (kLocalFirst<SZ, FORM> && write_local) st4g<G>(wl, tid, cnt, vl);
+    if (kLocalFirst<SZ, FORM> && write_local) st4g<G, kStore>(wl, tid, cnt, vl);
 
     const f4 agg = tile_sums<SZ, FORM, WAVES>(words, own, sent, self, num_workers, t, lds);
 #pragma unroll
     for (unsigned c = 0; c < 4; ++c) vg[c] = __builtin_fmaf(-scale, agg[c], w[c]);
-    if (!kLocalFirst<SZ, FORM> && write_local) st4g<G>(wl, tid, cnt, vl);
-    st4g<G>(wg, tid, cnt, vg);
+    if (!kLocalFirst<SZ, FORM> && write_local) st4g<G, kStore>(wl, tid, cnt, vl);
+    st4g<G, kStore>(wg, tid, cnt, vg);
 }
 
 // write_local: eq. 11 as well (false: the global half of a split step)
-template <int SZ, int WAVES, int FORM, int GT, bool SPARSE, bool LATE>
+template <int SZ, int WAVES, int FORM, int GT, bool SPARSE, int HOW>
 __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDesc *__restrict__ tensors,
                                                                  const ChunkRef *__restrict__ chunks,
                                                                  const uint8_t *const *__restrict__ rows,
@@ -94,12 +101,12 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
         const unsigned tile = x % kPerChunk;
         const float t = d.threshold > 0.0f ? d.threshold : t_call;
         if (cr.chunk < d.ext.full_chunks) {
-            fused_tile<false, SZ, WAVES, FORM, GT, SPARSE, LATE>(d, from, num_workers, self, cr.chunk, tile, kQuads * 4u, kQuads,
+            fused_tile<false, SZ, WAVES, FORM, GT, SPARSE, HOW>(d, from, num_workers, self, cr.chunk, tile, kQuads * 4u, kQuads,
                                                     t, lr_local, scale, write_local != 0, lds);
         } else if (tile * kQuads < d.ext.tail_bytes) {
             // (the packed bytes of the ragged end cover its elements: tiles past them have nothing to do)
             const unsigned elems0 = tile * kQuads * 4u;
-            fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, LATE>(d, from, num_workers, self, cr.chunk, tile,
+            fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, HOW>(d, from, num_workers, self, cr.chunk, tile,
                                                    d.ext.tail_elems > elems0 ? d.ext.tail_elems - elems0 : 0u,
                                                    d.ext.tail_bytes - tile * kQuads, t, lr_local, scale,
                                                    write_local != 0, lds);
@@ -140,7 +147,7 @@ constexpr unsigned kPiecesPerChunk = kChunkQuads / kFullBlock;
 static_assert(kChunkQuads % kFullBlock == 0 && kFullBlock % 64 == 0, "pieces tile a chunk, whole waves");
 
 // One piece of one chunk: quad qi of the chunk for this lane, cnt of its elements exist.
-template <bool G, bool SUM, int LOCAL, int GT>
+template <bool G, bool SUM, int LOCAL, int GT, int STORE>
 __device__ __forceinline__ void full_piece(const TensorDesc &d, const void *const *__restrict__ pg,
                                            int num_peers, int self, size_t quad0, unsigned qi,
                                            unsigned rem_elems, float lr_local, float scale)
@@ -157,7 +164,7 @@ __device__ __forceinline__ void full_piece(const TensorDesc &d, const void *cons
         f4 vl;
 #pragma unroll
         for (unsigned c = 0; c < 4; ++c) vl[c] = __builtin_fmaf(-lr_local, g[c], w[c]);
-        st4g<G>(wl, qi, cnt, vl);
+        st4g<G, STORE>(wl, qi, cnt, vl);
         return;
     }
     if (!SUM) a = ld4g<G>(d.agg_full + 4 * quad0, qi, cnt);
@@ -184,13 +191,13 @@ __device__ __forceinline__ void full_piece(const TensorDesc &d, const void *cons
         vg[c] = __builtin_fmaf(-scale, a[c], w[c]);
         vl[c] = LOCAL == kLocalRule ? __builtin_fmaf(-lr_local, g[c], w[c]) : vg[c];
     }
-    if (LOCAL != kLocalNone) st4g<G>(wl, qi, cnt, vl);
-    st4g<G>(wg, qi, cnt, vg);
+    if (LOCAL != kLocalNone) st4g<G, STORE>(wl, qi, cnt, vl);
+    st4g<G, STORE>(wg, qi, cnt, vg);
 }
 
 // peer_grads: [num_tensors][num_peers] pointers (own row left out), or unused when !SUM.
 // The grid walks the pieces of the chunk table: piece x belongs to chunk slot x / kPiecesPerChunk.
-template <bool SUM, int LOCAL, int GT>
+template <bool SUM, int LOCAL, int GT, int STORE>
 __global__ __launch_bounds__(CDSGD_FULL_BLOCK) void k_fused_full(const TensorDesc *__restrict__ tensors,
                                                                  const ChunkRef *__restrict__ chunks,
                                                                  unsigned long long num_pieces,
@@ -206,9 +213,9 @@ __global__ __launch_bounds__(CDSGD_FULL_BLOCK) void k_fused_full(const TensorDes
         const unsigned qi = (unsigned)(x % kPiecesPerChunk) * kFullBlock + threadIdx.x;
         const void *const *pg = SUM ? peer_grads + (size_t)cr.tensor * (size_t)num_peers : nullptr;
         if (cr.chunk < d.ext.full_chunks)
-            full_piece<false, SUM, LOCAL, GT>(d, pg, num_peers, self, quad0, qi, kChunkElems, lr_local, scale);
+            full_piece<false, SUM, LOCAL, GT, STORE>(d, pg, num_peers, self, quad0, qi, kChunkElems, lr_local, scale);
         else
-            full_piece<true, SUM, LOCAL, GT>(d, pg, num_peers, self, quad0, qi, d.ext.tail_elems, lr_local, scale);
+            full_piece<true, SUM, LOCAL, GT, STORE>(d, pg, num_peers, self, quad0, qi, d.ext.tail_elems, lr_local, scale);
     }
 }
 

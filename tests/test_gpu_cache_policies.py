@@ -79,3 +79,56 @@ def test_decode_sum_of_many_streams_equals_its_parts(B, N, n, t):
     torch.cuda.synchronize()
     assert torch.equal(whole[:n].view(torch.int32), part.view(torch.int32))
     assert bool((whole[n:] == 9.0).all()), "written past the end"
+
+
+def _list_state(B, n, N, grad, gen):
+    """One tensor's buffers and its peers' streams, in tensors that parts can be cut from."""
+    d = dict(device="cuda", generator=gen)
+    s = {"w_global": torch.randn(n, **d), "residual": torch.rand(n, **d) - 0.5, "grad": torch.randn(n, **d).to(grad),
+         "w_local": torch.zeros(n, device="cuda"),
+         "packed_self": torch.zeros(B.packed_words(n), dtype=torch.int32, device="cuda")}
+    peers = [torch.randint(-2 ** 31, 2 ** 31, (B.packed_words(n),), dtype=torch.int32, **d) for _ in range(N - 1)]
+    return s, peers
+
+
+def _run_list(B, s, peers, N, grad, a, b, call):
+    words = slice(a // 16, a // 16 + B.packed_words(b - a))
+    layer = {k: v[words] if k == "packed_self" else v[a:b] for k, v in s.items()}
+    plan = B.Plan([layer], [None] + [[p[words]] for p in peers], N, 0, grad_dtype=grad)
+    call(plan, a, b)
+    torch.cuda.synchronize()
+    plan.destroy()
+
+
+def _whole_equals_parts(B, n, N, grad, step, call):
+    gen = torch.Generator(device="cuda").manual_seed(n + N)
+    whole, peers = _list_state(B, n, N, grad, gen)
+    part = {k: v.clone() for k, v in whole.items()}
+    _run_list(B, whole, peers, N, grad, 0, n, call)
+    for a in range(0, n, step):
+        _run_list(B, part, peers, N, grad, a, min(n, a + step), call)
+    for k in ("w_global", "w_local", "residual", "packed_self"):
+        assert torch.equal(whole[k].view(torch.int32), part[k].view(torch.int32)), k
+
+
+# Above 32 workers and 112 MB of streams the workers' words are read non-temporally; 9 to 16 workers' results are written
+# through, but for long lists of 32-bit chains.  Parts of 1.6 M elements go the other way (or end in another place).
+@pytest.mark.parametrize("t", [0.25, 0.3])
+@pytest.mark.parametrize("N,n,grad", [(33, 13_600_003, torch.float32), (64, 7_001_003, torch.bfloat16),
+                                      (9, 17_000_013, torch.float32), (16, 51_000_001, torch.float32),
+                                      (16, 51_000_001, torch.float16)])
+def test_compressed_pass_equals_its_parts(B, N, n, grad, t):
+    _whole_equals_parts(B, n, N, grad, 4096 * 401, lambda p, a, b: p.step(1, 4, t, 0.05, 0.1))
+
+
+# a correction pass writes its results through below 2 M elements, up to 14 M with 4 workers and above 72 M with more
+@pytest.mark.parametrize("N,n,grad", [(4, (14 << 20) + 4097, torch.float32), (4, (14 << 20) - 3, torch.float16),
+                                      (8, (2 << 20) + 5, torch.bfloat16), (5, (72 << 20) + 7, torch.float32)])
+def test_correction_pass_equals_its_parts(B, N, n, grad):
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    full = [None] + [torch.randn(n, device="cuda", generator=gen).to(grad) for _ in range(N - 1)]
+
+    def call(plan, a, b):
+        plan.bind_full_grads([None if g is None else [g[a:b]] for g in full])
+        plan.step(0, 4, 0.5, 0.05, 0.1)
+    _whole_equals_parts(B, n, N, grad, 4096 * 397, call)
