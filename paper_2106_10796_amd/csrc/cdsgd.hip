@@ -173,6 +173,7 @@ inline int launch_status()
 struct PlanTables {
     TensorDesc *tensors = nullptr;
     ChunkRef *chunks = nullptr;
+    ArenaChunk *arena_chunks = nullptr;  // the same chunks of a list in arenas, or null
     const uint8_t **rows = nullptr;     // [num_tensors][row_entries(num_workers)], null where nothing is loaded
     const void **peer_grads = nullptr;  // [num_tensors][num_workers - 1], or null: correction passes read agg_full
     int num_tensors = 0;
@@ -192,6 +193,13 @@ struct PlanTables {
     // unless the plan has a limit or the launch would pass 2^32 - 1 threads (the kernels walk the units
     // with the grid's stride, so fewer workgroups than units is always correct).
     const ChunkRef *chunk_table() const { return chunks + first_chunk; }
+    template <int HOW>
+    auto table_for() const
+    {
+        if constexpr ((HOW & kArena) != 0) return (const ArenaChunk *)(arena_chunks + first_chunk);
+        else return chunk_table();
+    }
+    bool has_arenas() const { return arena_chunks != nullptr && !own_thresholds && !peers_sparse; }
 
     unsigned grid_size(unsigned long long units, unsigned lanes) const
     {
@@ -287,6 +295,37 @@ TensorDesc make_desc(const cdsgd_tensor &t)
     d.threshold = 0.0f;
     d.pad_ = 0;
     return d;
+}
+
+// The offset, in 16 elements, of tensor i's buffers from tensor 0's if every one of them is that far (agg_full
+// everywhere or nowhere) and the arenas' packed streams are below 4 GiB, -1 if not.
+long long arena_offset16(const cdsgd_tensor *tensors, int i, const uint32_t *const *const *peers, int num_workers,
+                         int self, unsigned grad_bytes)
+{
+    const cdsgd_tensor &z = tensors[0], &t = tensors[i];
+    const auto diff = [](const void *a, const void *b) {
+        return (long long)(reinterpret_cast<uintptr_t>(a) - reinterpret_cast<uintptr_t>(b));
+    };
+    const long long bytes = diff(t.w_global, z.w_global);
+    if (bytes < 0 || bytes % 64 != 0 || bytes / 64 > 0x3FFFFFFFll) return -1;
+    const long long off = bytes / 64;
+    if ((unsigned long long)off * 4ull + packed_bytes_of(t.n) > 0xFFFFFFFFull) return -1;
+    if (diff(t.w_local, z.w_local) != bytes || diff(t.residual, z.residual) != bytes ||
+        diff(t.grad, z.grad) != off * 16 * (long long)grad_bytes || diff(t.packed_self, z.packed_self) != off * 4)
+        return -1;
+    if ((t.agg_full == nullptr) != (z.agg_full == nullptr) || (t.agg_full && diff(t.agg_full, z.agg_full) != bytes))
+        return -1;
+    for (int j = 0; j < num_workers; ++j)
+        if (j != self && diff(peers[j][i], peers[j][0]) != off * 4) return -1;
+    return off;
+}
+
+bool in_arenas(const cdsgd_tensor *tensors, int num_tensors, const uint32_t *const *const *peers, int num_workers, int self,
+               unsigned grad_bytes)
+{
+    for (int i = 1; i < num_tensors; ++i)
+        if (arena_offset16(tensors, i, peers, num_workers, self, grad_bytes) < 0) return false;
+    return true;
 }
 
 // LDS bound of a pass that sums the workers' gradients in the kernel.  Measured, time of the pass with 26 waves per
@@ -566,6 +605,8 @@ int cdsgd_plan_create_typed(const cdsgd_tensor *tensors, int num_tensors, const 
     const int rc = check_layer_list(tensors, num_tensors, peers, num_workers, self, grad_dtype, &total_chunks, &all_agg);
     if (rc != CDSGD_OK) return rc;
     const unsigned row = row_entries(num_workers);
+    const unsigned grad_bytes = grad_dtype == CDSGD_GRAD_F32 ? 4u : 2u;
+    const bool arenas = in_arenas(tensors, num_tensors, peers, num_workers, self, grad_bytes);
 
     // host image of the device block
     const size_t bytes_t = sizeof(TensorDesc) * (size_t)num_tensors;
@@ -574,11 +615,13 @@ int cdsgd_plan_create_typed(const cdsgd_tensor *tensors, int num_tensors, const 
     const size_t bytes_p = sizeof(const uint8_t *) * ((size_t)num_tensors * row + CDSGD_MAX_WORKERS);
     const size_t off_c = (bytes_t + 255) & ~(size_t)255;
     const size_t off_p = (off_c + bytes_c + 255) & ~(size_t)255;
-    const size_t total = off_p + bytes_p;
+    const size_t off_a = (off_p + bytes_p + 255) & ~(size_t)255;
+    const size_t total = off_a + (arenas ? sizeof(ArenaChunk) * (size_t)total_chunks : 0);
     std::vector<unsigned char> image(total, 0);
     TensorDesc *ht = reinterpret_cast<TensorDesc *>(image.data());
     ChunkRef *hc = reinterpret_cast<ChunkRef *>(image.data() + off_c);
     const uint8_t **hp = reinterpret_cast<const uint8_t **>(image.data() + off_p);
+    ArenaChunk *ha = reinterpret_cast<ArenaChunk *>(image.data() + off_a);
     size_t ci = 0;
     std::vector<unsigned> chunk_start((size_t)num_tensors + 1, 0u);
     for (int i = 0; i < num_tensors; ++i) {
@@ -586,9 +629,15 @@ int cdsgd_plan_create_typed(const cdsgd_tensor *tensors, int num_tensors, const 
         ht[i] = make_desc(t);
         const unsigned nc = (unsigned)chunks_of(t.n);
         chunk_start[(size_t)i + 1] = chunk_start[(size_t)i] + nc;
+        const unsigned off16 = arenas && i > 0 ? (unsigned)arena_offset16(tensors, i, peers, num_workers, self, grad_bytes) : 0u;
         for (unsigned c = 0; c < nc; ++c) {
             hc[ci].tensor = (unsigned)i;
             hc[ci].chunk = c;
+            if (arenas) {
+                const size_t left = t.n - (size_t)c * kChunkElems;
+                ha[ci].off16 = off16 + c * (kChunkElems / 16u);
+                ha[ci].elems = (unsigned)(left < kChunkElems ? left : kChunkElems);
+            }
             ++ci;
         }
         for (int j = 0; j < num_workers; ++j)
@@ -612,6 +661,7 @@ int cdsgd_plan_create_typed(const cdsgd_tensor *tensors, int num_tensors, const 
     plan->tensors = reinterpret_cast<TensorDesc *>(base);
     plan->chunks = reinterpret_cast<ChunkRef *>(base + off_c);
     plan->rows = reinterpret_cast<const uint8_t **>(base + off_p);
+    if (arenas) plan->arena_chunks = reinterpret_cast<ArenaChunk *>(base + off_a);
     plan->num_tensors = num_tensors;
     plan->num_workers = num_workers;
     plan->self = self;
@@ -728,13 +778,19 @@ constexpr unsigned kWalkingGroups = 768;
 //   N = 33   8 M 1.07-1.08, 20 M .97-1.00, 50 M .96;  N = 48  8 M 1.06, 10 M .96;  N = 64  6 M 1.04, 8 M .95, 25 M .96-.98,
 //   VGG-16 .94-.99   (N = 17: 25 M .99-1.03, VGG-16 1.00-1.04;  N = 32: 25 M .98-.99, VGG-16 1.02-1.04;  N = 16 25 M 1.04)
 constexpr unsigned long long kStreamWordsBytes = 112000000;
+
+// Lists in arenas (ArenaChunk), up to 16 workers and 28 M elements: one trip to memory less before a group's first data
+// loads.  Time over that of the general kernels: 1 M elements .97-1.00, 2 M .97-.99, 4 M .98-.99, 8 M .99-1.00, 25 M
+// .99-1.01; ResNet-50-shaped list, N = 16, in 17 launches of a million elements and more 163.1 / 156.9 us, in one 107.0 /
+// 106.2.  (VGG-16-shaped .99-1.04, 1 GiB buckets 1.02.  Above 16 workers 1 M 1.12, 4 M 1.03, 25 M 1.01: more of the stream
+// pointers no longer fit the scalar registers beside the buffers'.)
 struct CompressedLaunch {
     unsigned waves, lds;
     int how;          // kLate, kWrittenOut, kStreamWords
     unsigned groups;  // launch at most this many (0: no bound)
 };
 
-CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int form, bool sparse, int grad_type,
+CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int form, bool sparse, bool arenas, int grad_type,
                                    unsigned max_workgroups)
 {
     const unsigned tiles = num_chunks * kTilesPerChunk;  // of 1024 elements
@@ -753,26 +809,40 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
         const bool all = !long_list || num_workers > kUpTo16 || (num_workers > kUpTo8 && form == kChain);
         return {4u, all ? 0u : 32768u, 0, 0u};
     }
+    const int arena = arenas && max_workgroups == 0 ? kArena : 0;
     if (num_workers <= kUpTo8) {
-        if (!mid_list) return {4u, 0u, 0, 0u};
-        if (tiles <= 48u * 1024u) return {1u, half && !long_list ? 6144u : 7168u, 0, 0u};
+        if (!mid_list) return {4u, 0u, arena, 0u};
+        if (tiles <= 48u * 1024u) return {1u, half && !long_list ? 6144u : 7168u, long_list ? 0 : arena, 0u};
         if (num_workers > 4) return {4u, 49152u, 0, 0u};
         return {1u, half ? 7168u : 8192u, 0, 0u};
     }
     if (num_workers <= kUpTo16 && form == kCount) {
-        if (tiles <= 6u * 1024u) return {4u, 0u, kWrittenOut, 0u};
-        if (!mid_list) return {4u, 24576u, kWrittenOut, 0u};
-        if (half) return {4u, 40960u, kWrittenOut, 0u};
-        return {4u, long_list ? 49152u : 32768u, kWrittenOut | kLate, 0u};
+        if (tiles <= 6u * 1024u) return {4u, 0u, kWrittenOut | arena, 0u};
+        if (!mid_list) return {4u, 24576u, kWrittenOut | arena, 0u};
+        if (half) return {4u, 40960u, kWrittenOut | (long_list ? 0 : arena), 0u};
+        if (long_list) return {4u, 49152u, kWrittenOut | kLate, 0u};
+        return {4u, 32768u, kWrittenOut | kLate | arena, 0u};
     }
     if (num_workers <= kUpTo16) {
         if (tiles > (half ? 80u * 1024u : kLongListTiles)) return {4u, 32768u, half || tiles <= 48u * 1024u ? kWrittenOut : 0, 0u};
-        return {4u, 0u, kWrittenOut | (mid_list ? kLate : 0), 0u};
+        return {4u, 0u, kWrittenOut | (mid_list ? kLate : 0) | (long_list ? 0 : arena), 0u};
     }
     if (num_workers > kUpTo32 && (unsigned long long)num_workers * tiles * kTileBytes > kStreamWordsBytes)
         return {4u, 32768u, kStreamWords, 0u};
     if (form == kCount) return {4u, mid_list ? 32768u : 0u, 0, 0u};
     return {4u, (half ? long_list : mid_list) ? 38912u : 0u, 0, 0u};
+}
+
+// The launch of a compressed pass over a plan's tables with the call's threshold, and the form of its decode.
+CompressedLaunch launch_of_pass(const PlanTables *plan, float threshold, int *form)
+{
+    // the count form of the decode needs every threshold in use to be a power of two; the chain form's multipliers
+    // need half of each to be exact
+    const bool pow2 = plan->own_thresholds ? plan->own_thresholds_pow2 : is_pow2_threshold(threshold);
+    const bool tiny = plan->own_thresholds ? plan->own_thresholds_tiny : is_tiny_threshold(threshold);
+    *form = pow2 ? kCount : (tiny ? kChainTiny : kChain);
+    return compressed_launch(plan->num_chunks, plan->num_workers, *form, plan->peers_sparse, plan->has_arenas(), plan->grad_type,
+                             plan->max_workgroups);
 }
 
 // One pass of FormalTraining's loop; with_local = false leaves eq. 11 out (split form).
@@ -787,20 +857,15 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
     const float scale = lr_global / (float)plan->num_workers;
     hipStream_t s = (hipStream_t)hip_stream;
     const int N = plan->num_workers;
-    // the count form of the decode needs every threshold in use to be a power of two; the chain form's multipliers
-    // need half of each to be exact
-    const bool pow2 = plan->own_thresholds ? plan->own_thresholds_pow2 : is_pow2_threshold(threshold);
-    const bool tiny = plan->own_thresholds ? plan->own_thresholds_tiny : is_tiny_threshold(threshold);
-    const int form = pow2 ? kCount : (tiny ? kChainTiny : kChain);
-    const CompressedLaunch shape = compressed_launch(plan->num_chunks, N, form, plan->peers_sparse, plan->grad_type,
-                                                     plan->max_workgroups);
+    int form;
+    const CompressedLaunch shape = launch_of_pass(plan, threshold, &form);
     const unsigned num_tiles = plan->num_chunks * (kChunkQuads / (64u * shape.waves));
     unsigned grid = plan->grid_size(num_tiles, 64u * shape.waves);
     if (shape.groups != 0 && grid > shape.groups) grid = shape.groups;
     const auto bound = [&](unsigned used) { return shape.lds <= used ? 0u : shape.lds - used; };
 #define CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, GT, SPARSE, HOW)                                            \
     hipLaunchKernelGGL((k_fused_compressed<SZ, WAVES, FORM, GT, SPARSE, HOW>), dim3(grid), dim3(64 * WAVES),   \
-                       bound(kTileLds<SZ, FORM, WAVES>), s, plan->tensors, plan->chunk_table(), plan->rows,    \
+                       bound(kTileLds<SZ, FORM, WAVES>), s, plan->tensors, plan->table_for<HOW>(), plan->rows, \
                        num_tiles, grid, N, plan->self, threshold, lr_local, scale, with_local ? 1 : 0)
 #define CDSGD_LAUNCH_COMPRESSED(SZ, WAVES, FORM, SPARSE, HOW)                                                  \
     do {                                                                                                       \
@@ -813,11 +878,15 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
         if (plan->peers_sparse && N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, true, 0);              \
         else if (plan->peers_sparse && N <= kUpTo16) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, true, 0);       \
         else if (plan->peers_sparse) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, true, 0);                   \
+        else if (shape.waves == 1u && shape.how == kArena) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 1, FORM, false, kArena); \
         else if (shape.waves == 1u) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 1, FORM, false, 0);                        \
+        else if (N <= kUpTo8 && shape.how == kArena) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, false, kArena);  \
         else if (N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, false, 0);                              \
-        else if (N > kUpTo16 && (shape.how & kStreamWords)) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, false, kStreamWords); \
+        else if (N > kUpTo16 && shape.how == kStreamWords) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, false, kStreamWords); \
         else if (N > kUpTo16) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, false, 0);                         \
+        else if (shape.how == (kWrittenOut | kLate | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kWrittenOut | kLate | kArena); \
         else if (shape.how == (kWrittenOut | kLate)) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kWrittenOut | kLate); \
+        else if (shape.how == (kWrittenOut | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kWrittenOut | kArena); \
         else if (shape.how == kWrittenOut) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kWrittenOut);      \
         else CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, 0);                                              \
     } while (0)
@@ -1162,28 +1231,6 @@ int static_scratch(unsigned char **out)
     return CDSGD_OK;
 }
 
-// The offset, in 16 elements, of tensor i's buffers from tensor 0's if every one of them is that far (agg_full
-// everywhere or nowhere), -1 if not.
-long long arena_offset16(const cdsgd_tensor *tensors, int i, const uint32_t *const *const *peers, int num_workers,
-                         int self, unsigned grad_bytes)
-{
-    const cdsgd_tensor &z = tensors[0], &t = tensors[i];
-    const auto diff = [](const void *a, const void *b) {
-        return (long long)(reinterpret_cast<uintptr_t>(a) - reinterpret_cast<uintptr_t>(b));
-    };
-    const long long bytes = diff(t.w_global, z.w_global);
-    if (bytes < 0 || bytes % 64 != 0 || bytes / 64 > 0xFFFFFFFFll) return -1;
-    const long long off = bytes / 64;
-    if (diff(t.w_local, z.w_local) != bytes || diff(t.residual, z.residual) != bytes ||
-        diff(t.grad, z.grad) != off * 16 * (long long)grad_bytes || diff(t.packed_self, z.packed_self) != off * 4)
-        return -1;
-    if ((t.agg_full == nullptr) != (z.agg_full == nullptr) || (t.agg_full && diff(t.agg_full, z.agg_full) != bytes))
-        return -1;
-    for (int j = 0; j < num_workers; ++j)
-        if (j != self && diff(peers[j][i], peers[j][0]) != off * 4) return -1;
-    return off;
-}
-
 template <typename Payload>
 int launch_static_build(const StaticTarget &to, const Payload &p, hipStream_t s)
 {
@@ -1194,15 +1241,17 @@ int launch_static_build(const StaticTarget &to, const Payload &p, hipStream_t s)
 }
 
 // Write the tables of a checked layer list into the static array at `base`.
+// arenas: the list lies in arenas; arena_chunks: the chunk table holds ArenaChunk entries (lists in arenas only).
 int build_static_tables(unsigned char *base, const cdsgd_tensor *tensors, int num_tensors,
                         const uint32_t *const *const *peers, int num_workers, int self, int grad_dtype, bool with_rows,
-                        hipStream_t s)
+                        bool arenas, bool arena_chunks, hipStream_t s)
 {
     const unsigned grad_bytes = grad_dtype == CDSGD_GRAD_F32 ? 4u : 2u;
     StaticTarget to;
     to.desc = reinterpret_cast<TensorDesc *>(base + kStaticOffDesc);
     to.chunks = reinterpret_cast<ChunkRef *>(base + kStaticOffChunks);
     to.rows = reinterpret_cast<const uint8_t **>(base + kStaticOffPeers);
+    to.arena_chunks = arena_chunks ? reinterpret_cast<ArenaChunk *>(base + kStaticOffChunks) : nullptr;
     to.row = with_rows ? row_entries(num_workers) : 0u;
     to.workers = with_rows ? (unsigned)num_workers : 0u;
     to.self = (unsigned)self;
@@ -1210,9 +1259,6 @@ int build_static_tables(unsigned char *base, const cdsgd_tensor *tensors, int nu
     to.slot0 = 0;
     const int streams = (int)to.workers;
     const auto bits = [](const void *p) { return (unsigned long long)reinterpret_cast<uintptr_t>(p); };
-    bool arenas = true;
-    for (int i = 1; i < num_tensors && arenas; ++i)
-        arenas = arena_offset16(tensors, i, peers, streams, self, grad_bytes) >= 0;
     StaticArenas flat;
     StaticPointers any;
     if (arenas) {
@@ -1276,9 +1322,6 @@ extern "C" int cdsgd_step_fused_static(const cdsgd_tensor *tensors, int num_tens
     if (rc != CDSGD_OK) return rc;
     hipStream_t s = (hipStream_t)hip_stream;
 
-    rc = build_static_tables(base, tensors, num_tensors, peers, num_workers, self, grad_dtype, compressed, s);
-    if (rc != CDSGD_OK) return rc;
-
     PlanTables pt;
     pt.tensors = reinterpret_cast<TensorDesc *>(base + kStaticOffDesc);
     pt.chunks = reinterpret_cast<ChunkRef *>(base + kStaticOffChunks);
@@ -1289,5 +1332,15 @@ extern "C" int cdsgd_step_fused_static(const cdsgd_tensor *tensors, int num_tens
     pt.num_chunks = (unsigned)total_chunks;
     pt.has_agg_full = all_agg;
     pt.grad_type = grad_dtype;
+
+    const bool arenas = in_arenas(tensors, num_tensors, peers, compressed ? num_workers : 0, self, grad_dtype == CDSGD_GRAD_F32 ? 4u : 2u);
+    if (compressed && arenas) {
+        pt.arena_chunks = reinterpret_cast<ArenaChunk *>(base + kStaticOffChunks);
+        int form;
+        if ((launch_of_pass(&pt, threshold, &form).how & kArena) == 0) pt.arena_chunks = nullptr;
+    }
+    rc = build_static_tables(base, tensors, num_tensors, peers, num_workers, self, grad_dtype, compressed, arenas,
+                             pt.arena_chunks != nullptr, s);
+    if (rc != CDSGD_OK) return rc;
     return launch_formal_pass(&pt, step, k, threshold, lr_local, lr_global, true, hip_stream);
 }

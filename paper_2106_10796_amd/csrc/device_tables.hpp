@@ -36,6 +36,14 @@ struct ChunkRef {
     unsigned chunk;   // chunk number inside that tensor
 };
 
+// The same for a list in arenas: every buffer of a tensor lies as far from tensor 0's as every other (in elements), and
+// a chunk is found from tensor 0's buffers without a look at its tensor's descriptor.
+struct ArenaChunk {
+    unsigned off16;  // the chunk's first element, counted from tensor 0's first in units of 16
+    unsigned elems;  // elements of the chunk
+};
+static_assert(sizeof(ArenaChunk) == sizeof(ChunkRef), "either kind of entry fits a chunk table");
+
 // Every kernel over a layer list walks the pieces of the chunk table from its workgroup number
 // in steps of the grid size.  Normally the grid has one workgroup per piece and the loop runs
 // once; a plan with a workgroup limit (cdsgd_plan_set_max_workgroups) launches fewer

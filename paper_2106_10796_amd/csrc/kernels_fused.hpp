@@ -23,7 +23,12 @@ constexpr bool kLocalFirst = SZ == kUpTo16 && FORM != kCount;
 //   kLate        the workers' words are asked for behind the tile's own streams instead of in front of them
 //   kWrittenOut  results are written through the L2 of the compute die (kThroughStream)
 //   kStreamWords the workers' words are read non-temporally
-constexpr int kLate = 1, kWrittenOut = 2, kStreamWords = 4;
+//   kArena       the list lies in arenas (ArenaChunk): entry, buffers and stream pointers come in one trip to memory
+constexpr int kLate = 1, kWrittenOut = 2, kStreamWords = 4, kArena = 8;
+template <int HOW>
+struct ChunkEntry { typedef ChunkRef type; };
+template <>
+struct ChunkEntry<kArena> { typedef ArenaChunk type; };
 
 template <bool G, int SZ, int WAVES, int FORM, int GT, bool SPARSE, int HOW>
 __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPointers<SZ, WAVES, SPARSE> &from, int num_workers,
@@ -35,7 +40,8 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
     constexpr int kStore = OUT ? kThroughStream : kStream;
     const unsigned tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
-    const size_t quad0 = (size_t)chunk * kChunkQuads + tile * (64u * WAVES);
+    // (kArena: `chunk` is the chunk's first quad, counted from tensor 0's)
+    const size_t quad0 = (size_t)chunk * ((HOW & kArena) ? 1u : kChunkQuads) + tile * (64u * WAVES);
     const void *__restrict__ grad = grad_at<GT>(d.grad, quad0);
     float *__restrict__ resid = d.residual + 4 * quad0;
     float *__restrict__ wg = d.w_global + 4 * quad0;
@@ -81,7 +87,7 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
 // write_local: eq. 11 as well (false: the global half of a split step)
 template <int SZ, int WAVES, int FORM, int GT, bool SPARSE, int HOW>
 __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDesc *__restrict__ tensors,
-                                                                 const ChunkRef *__restrict__ chunks,
+                                                                 const typename ChunkEntry<HOW & kArena>::type *__restrict__ chunks,
                                                                  const uint8_t *const *__restrict__ rows,
                                                                  unsigned num_tiles, unsigned grid, int num_workers,
                                                                  int self, float t_call, float lr_local, float scale,
@@ -92,24 +98,43 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     for (unsigned b = blockIdx.x;;) {
         const unsigned x = piece_of_workgroup<true>(b, kPerChunk, num_tiles);
-        const ChunkRef cr = chunks[x / kPerChunk];
-        StreamPointers<SZ, WAVES, SPARSE> from;
-        // (the select spares 9 to 16 sparse peers a load, 5-7 % of the time of the pass; up to 8 it costs long lists 1-2 %)
-        from.template load<SZ == kUpTo16>(rows + (size_t)cr.tensor * row_entries(num_workers), num_workers, wave, threadIdx.x & 63u);
-        const TensorDesc d = tensors[cr.tensor];
-        from.pin();
+        const auto at = chunks[x / kPerChunk];
         const unsigned tile = x % kPerChunk;
-        const float t = d.threshold > 0.0f ? d.threshold : t_call;
-        if (cr.chunk < d.ext.full_chunks) {
-            fused_tile<false, SZ, WAVES, FORM, GT, SPARSE, HOW>(d, from, num_workers, self, cr.chunk, tile, kQuads * 4u, kQuads,
-                                                    t, lr_local, scale, write_local != 0, lds);
-        } else if (tile * kQuads < d.ext.tail_bytes) {
-            // (the packed bytes of the ragged end cover its elements: tiles past them have nothing to do)
-            const unsigned elems0 = tile * kQuads * 4u;
-            fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, HOW>(d, from, num_workers, self, cr.chunk, tile,
-                                                   d.ext.tail_elems > elems0 ? d.ext.tail_elems - elems0 : 0u,
-                                                   d.ext.tail_bytes - tile * kQuads, t, lr_local, scale,
-                                                   write_local != 0, lds);
+        StreamPointers<SZ, WAVES, SPARSE> from;
+        if constexpr ((HOW & kArena) != 0) {
+            static_assert(!SPARSE, "arenas of packed streams");
+            from.template load<false>(rows, num_workers, wave, threadIdx.x & 63u);
+            TensorDesc d = tensors[0];
+            from.pin();
+            const unsigned quad = at.off16 * 4u, bytes = (at.elems + 15u) / 16u * 4u;
+            d.ext.full_chunks = 0u;
+            d.ext.tail_bytes = quad + bytes;  // where the chunk's codes end in a stream
+            if (at.elems == kChunkElems) {
+                fused_tile<false, SZ, WAVES, FORM, GT, SPARSE, HOW>(d, from, num_workers, self, quad, tile, kQuads * 4u, kQuads,
+                                                                    t_call, lr_local, scale, write_local != 0, lds);
+            } else if (tile * kQuads < bytes) {
+                const unsigned elems0 = tile * kQuads * 4u;
+                fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, HOW>(d, from, num_workers, self, quad, tile,
+                                                                   at.elems > elems0 ? at.elems - elems0 : 0u, bytes - tile * kQuads,
+                                                                   t_call, lr_local, scale, write_local != 0, lds);
+            }
+        } else {
+            // (the select spares 9 to 16 sparse peers a load, 5-7 % of the time of the pass; up to 8 it costs long lists 1-2 %)
+            from.template load<SZ == kUpTo16>(rows + (size_t)at.tensor * row_entries(num_workers), num_workers, wave, threadIdx.x & 63u);
+            const TensorDesc d = tensors[at.tensor];
+            from.pin();
+            const float t = d.threshold > 0.0f ? d.threshold : t_call;
+            if (at.chunk < d.ext.full_chunks) {
+                fused_tile<false, SZ, WAVES, FORM, GT, SPARSE, HOW>(d, from, num_workers, self, at.chunk, tile, kQuads * 4u, kQuads,
+                                                        t, lr_local, scale, write_local != 0, lds);
+            } else if (tile * kQuads < d.ext.tail_bytes) {
+                // (the packed bytes of the ragged end cover its elements: tiles past them have nothing to do)
+                const unsigned elems0 = tile * kQuads * 4u;
+                fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, HOW>(d, from, num_workers, self, at.chunk, tile,
+                                                       d.ext.tail_elems > elems0 ? d.ext.tail_elems - elems0 : 0u,
+                                                       d.ext.tail_bytes - tile * kQuads, t, lr_local, scale,
+                                                       write_local != 0, lds);
+            }
         }
         if (num_tiles - b <= grid) break;
         b += grid;

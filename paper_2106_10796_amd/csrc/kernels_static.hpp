@@ -18,6 +18,7 @@ constexpr int kStaticRoles = 6;  // w_global, w_local, residual, grad, packed_se
 struct StaticTarget {
     TensorDesc *desc;
     ChunkRef *chunks;
+    ArenaChunk *arena_chunks;  // in place of `chunks`, or null
     const uint8_t **rows;
     unsigned first, count;   // tensors [first, first + count) of the list
     unsigned slot0, slots;   // their entries of the chunk table
@@ -35,6 +36,7 @@ struct StaticArenas {
 
     __device__ unsigned n(unsigned i, unsigned) const { return t[i].n; }
     __device__ unsigned slot(unsigned i, unsigned) const { return t[i].slot; }
+    __device__ unsigned off16(unsigned i) const { return t[i].off16; }
     __device__ unsigned long long buffer(unsigned i, int r, unsigned grad_bytes, unsigned) const
     {
         if (role[r] == 0ull) return 0ull;
@@ -55,6 +57,7 @@ struct StaticPointers {
     __device__ __host__ static constexpr unsigned stride(unsigned workers) { return 1u + kStaticRoles + workers; }
     __device__ unsigned n(unsigned i, unsigned workers) const { return (unsigned)w[i * stride(workers)]; }
     __device__ unsigned slot(unsigned i, unsigned workers) const { return (unsigned)(w[i * stride(workers)] >> 32); }
+    __device__ unsigned off16(unsigned) const { return 0u; }  // (lists in arenas only)
     __device__ unsigned long long buffer(unsigned i, int r, unsigned, unsigned workers) const
     {
         return w[i * stride(workers) + 1u + (unsigned)r];
@@ -103,10 +106,19 @@ __global__ __launch_bounds__(256) void k_static_build(StaticTarget to, Payload p
             if (starts[mid] <= s) lo = mid;
             else hi = mid;
         }
-        ChunkRef cr;
-        cr.tensor = to.first + lo;
-        cr.chunk = s - starts[lo];
-        to.chunks[to.slot0 + s] = cr;
+        const unsigned chunk = s - starts[lo];
+        if (to.arena_chunks) {
+            const unsigned left = p.n(lo, to.workers) - chunk * kChunkElems;
+            ArenaChunk at;
+            at.off16 = p.off16(lo) + chunk * (kChunkElems / 16u);
+            at.elems = left < kChunkElems ? left : kChunkElems;
+            to.arena_chunks[to.slot0 + s] = at;
+        } else {
+            ChunkRef cr;
+            cr.tensor = to.first + lo;
+            cr.chunk = chunk;
+            to.chunks[to.slot0 + s] = cr;
+        }
     }
 }
 

@@ -1,0 +1,97 @@
+"""GPU parity of compressed passes over lists whose buffers lie in arenas, which find a chunk without its tensor's
+descriptor, against the same list with buffers that lie anywhere: bit for bit, for every kernel that has both forms."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2106_10796_amd import binding, build
+    build.ensure_built()
+    binding.lib()
+    assert torch.cuda.is_available()
+    return binding
+
+
+KEYS = ("w_global", "w_local", "residual", "packed_self")
+
+
+def _pair(B, sizes, N, rank, t, dtype, align=1024, extra=0):
+    """Plans over the same values: one list in arenas (gaps filled with a sentinel), one with every buffer on its own."""
+    at, total = [], 0
+    for n in sizes:
+        at.append(total)
+        total += (n + align - 1) // align * align + extra
+    gen = torch.Generator(device="cuda").manual_seed(sum(sizes) + N)
+    f32 = lambda s: torch.empty(total, device="cuda").normal_(0, s, generator=gen)
+    arena = dict(w_global=f32(1.0), w_local=f32(1.0), residual=f32(0.4 * t), grad=f32(t).to(dtype),
+                 packed_self=torch.full((total // 16,), 77, dtype=torch.int32, device="cuda"))
+    streams = [torch.randint(-2 ** 31, 2 ** 31, (total // 16,), dtype=torch.int32, device="cuda", generator=gen) for _ in range(N)]
+    cut = lambda k, v: [v[o // 16: o // 16 + B.packed_words(n)] if k in ("packed_self", "peer") else v[o: o + n]
+                        for o, n in zip(at, sizes)]
+    parts = {k: cut(k, v) for k, v in arena.items()}
+    mine = [{k: parts[k][i] for k in parts} for i in range(len(sizes))]
+    ref = [{k: v.clone() for k, v in d.items()} for d in mine]
+    peers = [None if j == rank else cut("peer", s) for j, s in enumerate(streams)] if N > 1 else None
+    apart = None if peers is None else [None if p is None else [x.clone() for x in p] for p in peers]
+    gaps = {k: torch.ones(arena[k].numel(), dtype=torch.bool, device="cuda") for k in KEYS}
+    for k in KEYS:
+        for x in parts[k]:
+            o = x.storage_offset()
+            gaps[k][o: o + x.numel()] = False
+    before = {k: arena[k].clone() for k in KEYS}
+
+    def check(where):
+        torch.cuda.synchronize()
+        for i in range(len(sizes)):
+            for k in KEYS:
+                assert torch.equal(mine[i][k].view(torch.int32), ref[i][k].view(torch.int32)), "%s: %s of tensor %d" % (where, k, i)
+        for k in KEYS:
+            assert torch.equal(arena[k][gaps[k]].view(torch.int32), before[k][gaps[k]].view(torch.int32)), "%s: %s between tensors" % (where, k)
+    return (B.Plan(mine, peers, N, rank, grad_dtype=dtype), B.Plan(ref, apart, N, rank, grad_dtype=dtype), mine, peers, check)
+
+
+RAGGED = [1, 4096, 17, 4095, 4097, 1024, 1027, 12288, 15, 16, 8191, 3 * 4096 + 1025, 64, 250]
+
+
+@pytest.mark.parametrize("t", [0.5, 0.3])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("N", [1, 2, 4, 5, 8, 9, 13, 16, 17])
+def test_ragged_list_in_arenas(B, N, dtype, t):
+    a, b, mine, peers, check = _pair(B, RAGGED, N, N // 2, t, dtype, align=64 if N % 2 else 1024)
+    for plan in (a, b):
+        plan.step(1, 4, t, 0.4, 0.7)
+    check("whole")
+    for first, count in ((9, 5), (3, 6), (0, 3)):
+        for plan in (a, b):
+            plan.step_range(first, count, 2, 4, t, 0.4, 0.7)
+    check("ranges")
+    own = [float(x) for x in 2.0 ** np.arange(-6, len(RAGGED) - 6)]
+    for plan in (a, b):
+        plan.set_thresholds(own)
+        plan.step(1, 4, t, 0.4, 0.7)
+        plan.set_thresholds(None)
+    check("thresholds of their own")
+    for plan in (a, b):
+        plan.set_max_workgroups(3)
+        plan.step(3, 4, t, 0.4, 0.7)
+        plan.set_max_workgroups(0)
+    check("workgroup limit")
+    B.cdsgd_step_fused_static(mine, peers, N, N // 2, 1, 4, t, 0.4, 0.7, grad_dtype=dtype)
+    b.step(1, 4, t, 0.4, 0.7)
+    check("static")
+
+
+# lists of more than 6 M, 16 M and 28 M elements have launch shapes of their own
+@pytest.mark.parametrize("N,t,dtype", [(4, 0.3, torch.bfloat16), (8, 0.5, torch.float32), (16, 0.5, torch.float32),
+                                       (16, 0.3, torch.float16), (12, 0.5, torch.bfloat16)])
+@pytest.mark.parametrize("n", [6_400_000, 17_000_000, 28_700_000])
+def test_long_lists_in_arenas(B, N, t, dtype, n):
+    sizes = [n // 3 + 5, 77, n // 3 + 4097, 4096, n // 3 - 9]
+    a, b, mine, peers, check = _pair(B, sizes, N, N - 1, t, dtype, extra=64)
+    for plan in (a, b):
+        plan.step(1, 4, t, 0.4, 0.7)
+    check("whole")
