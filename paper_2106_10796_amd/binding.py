@@ -1,8 +1,11 @@
-"""ctypes binding of libcdsgd.so: argument marshalling only.
+"""Binding of libcdsgd.so: argument marshalling only.
 
 Every step of the path runs in the HIP kernels behind the C ABI (include/cdsgd.h).
 PyTorch is used for device memory and the current stream, nothing else.  There
 is no fallback: a missing library is an error.
+
+The calls that a program makes per tensor or per step are marshalled in native code (csrc/py_calls.cpp), which
+declines (-1) whatever is not plainly good; ctypes and the checks below then convert it or say what is wrong.
 """
 import ctypes
 import os
@@ -49,11 +52,24 @@ class cdsgd_cost(ctypes.Structure):
 
 
 _lib = None
+_calls = None
+
+# in the order in which _calls.bind takes them
+_CALLED = ("cdsgd_quantize_pack", "cdsgd_decode_sum", "cdsgd_decode_sum_sparse", "cdsgd_update", "cdsgd_sparse_encode",
+           "cdsgd_sparse_words", "cdsgd_sparse_segments", "cdsgd_step_fused", "cdsgd_step_fused_range",
+           "cdsgd_step_fused_static")
+
+
+def _native():
+    """The native calls, bound to the loaded library; loads it."""
+    if _lib is None:
+        lib()
+    return _calls
 
 
 def lib():
     """The loaded C-ABI library; raises if it has not been built."""
-    global _lib
+    global _lib, _calls
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError("libcdsgd.so is not built (run: python -m paper_2106_10796_amd.build); "
@@ -128,7 +144,12 @@ def lib():
                                            ctypes.POINTER(cdsgd_cost)]
         L.cdsgd_cost_period_mean.restype = i
         L.cdsgd_cost_period_mean.argtypes = [ctypes.POINTER(cdsgd_cost_params), ctypes.POINTER(cdsgd_cost)]
-        _lib = L
+        try:
+            from . import _calls as native
+        except ImportError as e:
+            raise RuntimeError("the binding's native calls are not built (run: python -m paper_2106_10796_amd.build): %s" % e)
+        native.bind(*[ctypes.cast(getattr(L, name), vp).value for name in _CALLED])
+        _lib, _calls = L, native
     return _lib
 
 
@@ -185,20 +206,26 @@ def _check(status, where):
 
 
 def cdsgd_quantize_pack(grad, residual, packed, threshold):
-    n = grad.numel()
-    st = lib().cdsgd_quantize_pack(_dev(grad, torch.float32, None, "grad"),
-                                   _dev(residual, torch.float32, n, "residual"),
-                                   _dev(packed, PACKED_DTYPE, packed_words(n), "packed"),
-                                   n, float(threshold), _stream())
-    _check(st, "cdsgd_quantize_pack")
+    st = _native().quantize_pack(grad, residual, packed, threshold, _stream)
+    if st < 0:
+        n = grad.numel()
+        st = lib().cdsgd_quantize_pack(_dev(grad, torch.float32, None, "grad"),
+                                       _dev(residual, torch.float32, n, "residual"),
+                                       _dev(packed, PACKED_DTYPE, packed_words(n), "packed"),
+                                       n, float(threshold), _stream())
+    if st != OK:
+        _check(st, "cdsgd_quantize_pack")
 
 
 def cdsgd_decode_sum(packed_list, agg, threshold):
-    n = agg.numel()
-    N = len(packed_list)
-    arr = _dev_list(packed_list, PACKED_DTYPE, packed_words(n), "packed")
-    st = lib().cdsgd_decode_sum(arr, N, _dev(agg, torch.float32, None, "agg"), n, float(threshold), _stream())
-    _check(st, "cdsgd_decode_sum")
+    st = _native().decode_sum(packed_list, agg, threshold, _stream)
+    if st < 0:
+        n = agg.numel()
+        N = len(packed_list)
+        arr = _dev_list(packed_list, PACKED_DTYPE, packed_words(n), "packed")
+        st = lib().cdsgd_decode_sum(arr, N, _dev(agg, torch.float32, None, "agg"), n, float(threshold), _stream())
+    if st != OK:
+        _check(st, "cdsgd_decode_sum")
 
 
 PEERS_PACKED, PEERS_SPARSE = 0, 1   # cdsgd_peer_format
@@ -217,18 +244,24 @@ def new_sparse(n: int, device="cuda") -> torch.Tensor:
 
 
 def cdsgd_sparse_encode(packed, n, sparse, segment_words=None):
-    st = lib().cdsgd_sparse_encode(_dev(packed, PACKED_DTYPE, packed_words(n), "packed"), int(n),
-                                   _dev(sparse, PACKED_DTYPE, sparse_words(n), "sparse"),
-                                   _dev(segment_words, PACKED_DTYPE, sparse_segments(n), "segment_words"), _stream())
-    _check(st, "cdsgd_sparse_encode")
+    st = _native().sparse_encode(packed, n, sparse, segment_words, _stream)
+    if st < 0:
+        st = lib().cdsgd_sparse_encode(_dev(packed, PACKED_DTYPE, packed_words(n), "packed"), int(n),
+                                       _dev(sparse, PACKED_DTYPE, sparse_words(n), "sparse"),
+                                       _dev(segment_words, PACKED_DTYPE, sparse_segments(n), "segment_words"), _stream())
+    if st != OK:
+        _check(st, "cdsgd_sparse_encode")
 
 
 def cdsgd_decode_sum_sparse(sparse_list, agg, threshold):
-    n = agg.numel()
-    N = len(sparse_list)
-    arr = _dev_list(sparse_list, PACKED_DTYPE, sparse_words(n), "sparse")
-    st = lib().cdsgd_decode_sum_sparse(arr, N, _dev(agg, torch.float32, None, "agg"), n, float(threshold), _stream())
-    _check(st, "cdsgd_decode_sum_sparse")
+    st = _native().decode_sum_sparse(sparse_list, agg, threshold, _stream)
+    if st < 0:
+        n = agg.numel()
+        N = len(sparse_list)
+        arr = _dev_list(sparse_list, PACKED_DTYPE, sparse_words(n), "sparse")
+        st = lib().cdsgd_decode_sum_sparse(arr, N, _dev(agg, torch.float32, None, "agg"), n, float(threshold), _stream())
+    if st != OK:
+        _check(st, "cdsgd_decode_sum_sparse")
 
 
 def cdsgd_probe_streams(reads, writes, sink=None, lds_bytes=0):
@@ -242,13 +275,16 @@ def cdsgd_probe_streams(reads, writes, sink=None, lds_bytes=0):
 
 
 def cdsgd_update(w_global, w_local, grad_local, agg, lr_local, lr_global, num_workers):
-    n = w_global.numel()
-    st = lib().cdsgd_update(_dev(w_global, torch.float32, None, "w_global"),
-                            _dev(w_local, torch.float32, n, "w_local"),
-                            _dev(grad_local, torch.float32, n, "grad_local"),
-                            _dev(agg, torch.float32, n, "agg"),
-                            n, float(lr_local), float(lr_global), int(num_workers), _stream())
-    _check(st, "cdsgd_update")
+    st = _native().update(w_global, w_local, grad_local, agg, lr_local, lr_global, num_workers, _stream)
+    if st < 0:
+        n = w_global.numel()
+        st = lib().cdsgd_update(_dev(w_global, torch.float32, None, "w_global"),
+                                _dev(w_local, torch.float32, n, "w_local"),
+                                _dev(grad_local, torch.float32, n, "grad_local"),
+                                _dev(agg, torch.float32, n, "agg"),
+                                n, float(lr_local), float(lr_global), int(num_workers), _stream())
+    if st != OK:
+        _check(st, "cdsgd_update")
 
 
 def cdsgd_cost_iteration(tau, phi, psi, delta, k, i) -> dict:
@@ -320,12 +356,18 @@ class StaticLayerList:
         self._num_workers = int(num_workers)
         self._grad = GRAD_DTYPES[grad_dtype]
         self._arr, self._rows, self._rows_keep = _marshal_layer_list(tensors, peers, num_workers, grad_dtype)
+        self._arr_at = ctypes.addressof(self._arr)
+        self._rows_at = 0 if self._rows is None else ctypes.addressof(self._rows)
 
     def step(self, self_rank, step, k, threshold, lr_local, lr_global):
-        st = lib().cdsgd_step_fused_static(self._arr, self._n, self._rows, self._num_workers, int(self_rank),
-                                           self._grad, int(step), int(k), float(threshold), float(lr_local),
-                                           float(lr_global), _stream())
-        _check(st, "cdsgd_step_fused_static")
+        st = _calls.step_static(self._arr_at, self._n, self._rows_at, self._num_workers, self_rank, self._grad, step, k,
+                                threshold, lr_local, lr_global, _stream)
+        if st < 0:
+            st = lib().cdsgd_step_fused_static(self._arr, self._n, self._rows, self._num_workers, int(self_rank),
+                                               self._grad, int(step), int(k), float(threshold), float(lr_local),
+                                               float(lr_global), _stream())
+        if st != OK:
+            _check(st, "cdsgd_step_fused_static")
 
 
 class Plan:
@@ -352,14 +394,18 @@ class Plan:
                                                GRAD_DTYPES[grad_dtype], ctypes.byref(handle))
         _check(st, "cdsgd_plan_create")
         self._handle = handle
+        self._at = handle.value        # None once the plan is destroyed
         self.num_workers = int(num_workers)
         if peers_sparse:
             self.set_peer_format(PEERS_SPARSE)
 
     def step(self, step, k, threshold, lr_local, lr_global):
-        st = lib().cdsgd_step_fused(self._handle, int(step), int(k), float(threshold), float(lr_local),
-                                    float(lr_global), _stream())
-        _check(st, "cdsgd_step_fused")
+        st = _calls.step(self._at, step, k, threshold, lr_local, lr_global, _stream)
+        if st < 0:
+            st = lib().cdsgd_step_fused(self._handle, int(step), int(k), float(threshold), float(lr_local),
+                                        float(lr_global), _stream())
+        if st != OK:
+            _check(st, "cdsgd_step_fused")
 
     def set_thresholds(self, thresholds):
         """One threshold per tensor (list of floats), or None to go back to the call's threshold."""
@@ -391,9 +437,12 @@ class Plan:
 
     def step_range(self, first_tensor, num_tensors, step, k, threshold, lr_local, lr_global):
         """The fused pass over tensors [first_tensor, first_tensor + num_tensors) only (cdsgd_step_fused_range)."""
-        st = lib().cdsgd_step_fused_range(self._handle, int(first_tensor), int(num_tensors), int(step), int(k),
-                                          float(threshold), float(lr_local), float(lr_global), _stream())
-        _check(st, "cdsgd_step_fused_range")
+        st = _calls.step_range(self._at, first_tensor, num_tensors, step, k, threshold, lr_local, lr_global, _stream)
+        if st < 0:
+            st = lib().cdsgd_step_fused_range(self._handle, int(first_tensor), int(num_tensors), int(step), int(k),
+                                              float(threshold), float(lr_local), float(lr_global), _stream())
+        if st != OK:
+            _check(st, "cdsgd_step_fused_range")
 
     def step_local_range(self, first_tensor, num_tensors, lr_local):
         st = lib().cdsgd_step_local_range(self._handle, int(first_tensor), int(num_tensors), float(lr_local), _stream())
@@ -431,7 +480,7 @@ class Plan:
     def destroy(self):
         if self._handle is not None and self._handle.value:
             lib().cdsgd_plan_destroy(self._handle)
-        self._handle = None
+        self._handle = self._at = None
         self._keep = None
         self._keep_full = None
 

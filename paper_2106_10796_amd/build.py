@@ -1,10 +1,13 @@
-"""Build libcdsgd.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Build libcdsgd.so (HIP kernels + C ABI) for gfx950 with hipcc, and the binding's native calls, in-tree."""
 import hashlib
+import importlib.metadata
+import importlib.util
 import os
 import re
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -12,6 +15,9 @@ SRC = os.path.join(PKG, "csrc", "cdsgd.hip")
 SRC_HOST = [os.path.join(PKG, "csrc", "cdsgd_cost_model.cpp")]   # host-only parts of the library
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libcdsgd.so")
+SRC_CALLS = os.path.join(PKG, "csrc", "py_calls.cpp")            # host code against Python's and torch's headers
+CALLS = os.path.join(PKG, "_calls.so")
+CALLS_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-DUSE_ROCM=1"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -51,6 +57,12 @@ def source_id(extra_flags=()) -> str:
     return h.hexdigest()[:16]
 
 
+def calls_id() -> str:
+    """The same for the native calls, which also depend on the Python and the torch they are built against."""
+    parts = [source_id(), " ".join(CALLS_FLAGS), sysconfig.get_config_var("SOABI") or "", importlib.metadata.version("torch")]
+    return hashlib.sha256("\0".join(parts).encode()).hexdigest()[:16]
+
+
 def built_id(path=LIB):
     """The source identity a built library carries, or None (no library, or one without an identity)."""
     try:
@@ -78,11 +90,30 @@ def build(extra_flags=(), out=LIB, verbose=False) -> str:
     return out
 
 
+def build_calls(verbose=False) -> str:
+    torch_dir = importlib.util.find_spec("torch").submodule_search_locations[0]
+    tmp = CALLS + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), *CALLS_FLAGS, '-DCDSGD_BUILD_ID_HEX="%s"' % calls_id(), "-I", INCLUDE,
+           "-isystem", os.path.join(torch_dir, "include"), "-isystem", sysconfig.get_paths()["include"], SRC_CALLS,
+           "-L", os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("the compiler failed:\n" + r.stdout)
+    if verbose and r.stdout.strip():
+        print(r.stdout, flush=True)
+    os.replace(tmp, CALLS)
+    return CALLS
+
+
 def ensure_built() -> str:
-    """Build if no library is there or if the one that is there was made from other sources,
+    """Build (the library, and the binding's native calls) if none is there or if the one that is there was made from other sources,
     headers or flags than the tree now holds (tests, the smoke check and the benchmark call this;
     the binding itself never builds and never falls back).  The comparison is by content, not by
     file time, so a tree that was copied elsewhere together with its library is not rebuilt."""
+    if built_id(CALLS) != calls_id():
+        build_calls()
     if os.path.exists(LIB) and built_id(LIB) == source_id():
         return LIB
     return build()
@@ -90,3 +121,4 @@ def ensure_built() -> str:
 
 if __name__ == "__main__":
     print(build(extra_flags=sys.argv[1:], verbose=True))
+    print(build_calls(verbose=True))
