@@ -400,6 +400,17 @@ int launch_full_pass(const PlanTables *plan, int local_mode, float lr_local, flo
     return launch_status();
 }
 
+// Whether decode-and-sum and the global rule behind it store non-temporally: few workers' sums of a few million elements,
+// which pass from call to call through the dies' own caches.  Both calls, stored so / written through and staying, us:
+// N = 2, 1.6 M 8.2 / 8.5, 2 M 8.4 / 9.9, 4 M 12.0 / 12.6, 5 M 14.7 / 14.3;  N = 4 (sparse), 2 M 8.5 / 9.8, 4 M 12.4 / 12.8,
+// 5 M 15.4 / 14.5;  N = 8, 1.6 M 8.1 / 8.6, 2 M 8.6 / 9.2, 2.5 M 9.9 / 9.8;  N = 12, 1.6 M 8.1 / 8.4, 2 M 9.0 / 8.7;
+// N = 16 (sparse), 1.2 M 10.1 / 9.5;  0.1 M elements, N = 4 4.7 / 4.4.
+inline bool drains_results(size_t n, int num_workers)
+{
+    const size_t most = num_workers <= kUpTo4 ? 4500000u : (num_workers <= kUpTo8 ? 2250000u : (num_workers <= 12 ? 1750000u : 0u));
+    return n > 1250000u && n <= most;
+}
+
 // a4 for one tensor on checked arguments.
 //
 // Tiles of a group: 4 up to 16 workers; above that the loads of a wave are enough with one tile of packed streams
@@ -414,10 +425,11 @@ int launch_full_pass(const PlanTables *plan, int local_mode, float lr_local, flo
 // 169 with 6) and lose in the chain form; above 32 workers the count form gains from 16 M elements on (N = 64, 60 M:
 // decode-and-sum and update 288 us with all, 283 with 5).
 // Packed streams are read non-temporally when they are more than the caches between the workers' data and the compute
-// units hold on to: above 28 MB, and above 56 MB up to 8 workers, whose sums write more than they read (decode-and-sum
-// and update, default policy / non-temporal, us: N = 4, 25 M 62 / 63, 60 M 145 / 143;  N = 8, 25 M 66 / 67, 60 M 159 /
-// 154;  N = 16, 4 M 16.7 / 16.9, 9 M 32.1 / 31.6, 60 M 181 / 173;  N = 17, 4 M 16.7 / 17.5;  N = 32, 4 M 20.0 / 19.7,
-// 16 M 67 / 63;  N = 64, 1 M the same, 4 M 27.9 / 27.2, 60 M 327 / 313).
+// units hold on to: above 56 MB, and above 100 MB with more than 16 workers, whose sums write little (decode-and-sum and
+// update, default policy / non-temporal, us: N = 4, 32 M 77.3 / 79.0, 60 M 145.5 / 143.4;  N = 8, 25 M 66.3 / 67.7, 32 M
+// 86.4 / 84.1;  N = 9, 20 M 53.2 / 54.3, 25 M 69.5 / 68.2;  N = 12, 10 M 30.0 / 31.8, 60 M 167 / 161;  N = 24, 5 M 18.4 /
+// 20.0, 14 M the same;  N = 32, 10 M 40.2 / 40.6, 16 M 66.6 / 64.0;  N = 48, 7 M 31.6 / 33.0, 10 M 46.0 / 44.2;  N = 64,
+// 7 M the same, 14 M 76.3 / 72.0).
 template <bool SPARSE>
 int launch_decode_sum(const uint32_t *const *streams, int num_workers, float *agg, size_t n, float threshold, void *hip_stream)
 {
@@ -426,8 +438,9 @@ int launch_decode_sum(const uint32_t *const *streams, int num_workers, float *ag
     for (int j = 0; j < num_workers; ++j) tab.p[j] = reinterpret_cast<const uint8_t *>(streams[j]);
     const unsigned tiles = (unsigned)units_of(n, kTileQuads);
     const Extent ext = extent_of(n);
+    const int drain = drains_results(n, num_workers) ? 1 : 0;
     const int xcd = SPARSE || tiles > kLongListTiles ? 1 : 0;
-    const bool nt = !SPARSE && (unsigned long long)num_workers * packed_bytes_of(n) > (num_workers > kUpTo8 ? 28000000ull : 56000000ull);
+    const bool nt = !SPARSE && (unsigned long long)num_workers * packed_bytes_of(n) > (num_workers > kUpTo16 ? 100000000ull : 56000000ull);
     hipStream_t s = (hipStream_t)hip_stream;
 #define CDSGD_LAUNCH_DECODE(SZ, FORM, TILES, LDS)                                                              \
     do {                                                                                                       \
@@ -435,10 +448,10 @@ int launch_decode_sum(const uint32_t *const *streams, int num_workers, float *ag
         const unsigned more = want > used ? want - used : 0u;                                                   \
         if (!SPARSE && nt)                                                                                      \
             hipLaunchKernelGGL((k_decode_sum<SZ, FORM, SPARSE, TILES, !SPARSE>), dim3(groups), dim3(kTileQuads), \
-                               more, s, tab, num_workers, agg, ext, groups, xcd, threshold);                    \
+                               more, s, tab, num_workers, agg, ext, groups, xcd, drain, threshold);                    \
         else                                                                                                    \
             hipLaunchKernelGGL((k_decode_sum<SZ, FORM, SPARSE, TILES, false>), dim3(groups), dim3(kTileQuads),  \
-                               more, s, tab, num_workers, agg, ext, groups, xcd, threshold);                    \
+                               more, s, tab, num_workers, agg, ext, groups, xcd, drain, threshold);                    \
     } while (0)
     const bool count = is_pow2_threshold(threshold);
     constexpr unsigned kLdsCount = SPARSE ? 24576u : 32768u, kLdsChain = SPARSE ? 0u : 24576u;
@@ -582,7 +595,8 @@ int cdsgd_update(float *w_global, float *w_local, const float *grad_local, const
         else if (mid) CDSGD_LAUNCH_UPDATE(true, false, kMidTensor, kLdsFor26Waves);
         else CDSGD_LAUNCH_UPDATE(true, false, kLargeTensor, kLdsFor20Waves);
     } else {
-        if (small) CDSGD_LAUNCH_UPDATE(false, true, kSmallTensor, 0);
+        if (drains_results(n, num_workers)) CDSGD_LAUNCH_UPDATE(false, true, kDrainTensor, 0);
+        else if (small) CDSGD_LAUNCH_UPDATE(false, true, kSmallTensor, 0);
         else CDSGD_LAUNCH_UPDATE(false, true, kMidTensor, 0);
     }
 #undef CDSGD_LAUNCH_UPDATE

@@ -460,7 +460,7 @@ __device__ __forceinline__ f4 tile_sums(const unsigned (&w)[kWordsPerWave<SZ>], 
 // xcd: which order the tiles are dealt in.  The chunk-wise order pays where the tiles of a chunk share its segment
 // (sparse streams), and on long tensors (2^27 elements, N = 16: 421 against 428 us); on shorter ones the plain order
 // is 1 % faster (2^24: 71.5 against 72.5; both with the global update behind it).
-// The aggregate is written through and stays in the memory-side cache, where the global update that follows finds it
+// drain: the aggregate is stored non-temporally (drains_results).  Otherwise it is written through and stays in the memory-side cache, where the global update that follows finds it
 // (decode-and-sum and update, non-temporal store / now, us: N = 16, 50 M 162 / 150; N = 32, 16 M 70 / 66; N = 4, 4 M
 // 13.0 / 12.5; at the default policy the flush of the L2s at the end of the kernel costs what the update gains).
 // The workers' stream pointers of a single-tensor call; they travel in the kernel arguments.
@@ -470,7 +470,7 @@ struct StreamTable {
 
 template <int SZ, int FORM, bool SPARSE, int TILES, bool NT>
 __global__ __launch_bounds__(kTileQuads) void k_decode_sum(StreamTable tab, int num_workers, float *__restrict__ agg_out,
-                                                           Extent ext, unsigned num_groups, int xcd, float t)
+                                                           Extent ext, unsigned num_groups, int xcd, int drain, float t)
 {
     static_assert(kTilesPerChunk % TILES == 0, "the tiles of a group lie in one chunk");
     constexpr unsigned kPerChunk = kTilesPerChunk / TILES, kLds = kTileLds<SZ, FORM, 4>;
@@ -505,8 +505,10 @@ __global__ __launch_bounds__(kTileQuads) void k_decode_sum(StreamTable tab, int 
     for (unsigned k = 0; k < TILES; ++k) {
         const f4 agg = tile_get<SZ, FORM, 4>(f4{0.0f, 0.0f, 0.0f, 0.0f}, num_workers, t, lds + kLds * k, at);
         const unsigned qi = kTileQuads * k + tid;
-        if (chunk < ext.full_chunks) st4p<kThrough>(out, qi, agg);
-        else {
+        if (chunk < ext.full_chunks) {
+            if (drain) st4p<kStream>(out, qi, agg);
+            else st4p<kThrough>(out, qi, agg);
+        } else {
             const unsigned e0 = x % kPerChunk * (4u * kTileQuads * TILES);
             st4g<true, kThrough>(out, qi, quad_count<true>(ext.tail_elems > e0 ? ext.tail_elems - e0 : 0u, qi), agg);
         }

@@ -3,27 +3,24 @@
 
 namespace {
 
-// How the caches are used, by the length of the tensor (one tensor of elements, several sets of buffers in turn; time
-// over that of non-temporal loads and stores throughout).
-//   kSmallTensor  up to 1.5 M elements: results are written through and stay in the 256 MB memory-side cache
-//                 (0.1 M elements, local rule / global rule / both / quantise-and-pack: .93 / .92 / .94 / .96; 1 M 1.01 /
-//                 .99 / .94 / .97)
-//   kMidTensor    up to 24 M: they are written through and do not stay (2 M .98 / 1.04 / .97 / .94, 4 M .97 / 1.00 / .96 /
-//                 .92, 16 M .98 / 1.01 / .99 / .95; staying costs 16 M 1.16 / .84 / 1.13 / 1.11, the weights that the
-//                 global rule alone writes being in the cache still when it reads them next)
-//   kLargeTensor  the same, and the gradient does not stay either (80 M .97 / 1.00 / 1.00 / .97)
-// With decode-and-sum in front, which leaves the aggregate in the cache, the global rule gains as well (N = 32, 16 M,
-// both calls: 64.4 us, 63.2 now; N = 12, 60 M: 163.8 and 161.6).
-// Local update, quantise-and-pack and sparse encoding one after the other, before / now, us: 4 M 17.8 / 17.3, 9 M 39.2 /
-// 37.3, 16 M 61.7 / 58.8, 90 M 333.9 / 327.6.
+// How the caches are used, by the length of the tensor (several sets of buffers in turn).
+//   kSmallTensor  up to 7 M elements: results are written through and stay in the 256 MB memory-side cache
+//   kMidTensor    up to 24 M: they are written through and do not stay
+//   kLargeTensor  the same, and the gradient does not stay either
+//   kDrainTensor  results are stored non-temporally (the global rule alone, see drains_results)
+// Local update and quantise-and-pack, us, non-temporal stores / kMidTensor / kSmallTensor: 2 M elements 9.3 / 9.9 / 9.1, 3 M
+// 13.2 / 13.1 / 11.8, 5 M 19.0 / 18.1 / 16.9, 7 M 26.4 / 26.8 / 26.2, 8 M 31.3 / 29.8 / 30.2, 9.4 M and encoding 39.5 / 37.6
+// / 38.6, 13 M 48.6 / 46.6 / 52.2;  gradient kept or not, 90 M and encoding 333.9 / 327.6.
+// Decode-and-sum, which leaves the aggregate in the cache, and the global rule: N = 24, 3 M 13.5 / 12.9 / 12.1, 7 M 26.4 /
+// 24.7 / 24.1, 9 M 32.5 / 30.3 / 32.2, 12 M 42.0 / 40.9 / 43.6;  N = 8, 4 M 13.0 / 12.8 / 12.3, 9 M 26.8 / 25.5 / 24.7.
 // The gradient of a worker's own tensor is read twice, by the update and by the quantiser: up to kKeepElems elements
 // its loads take the default cache policy, and the second pass finds it in the memory-side cache.
 // Update and quantise-and-pack one after the other, non-temporal / default policy: 4 M elements 18.2 / 16.9 us, 9 M
 // 38.2 / 36.4, 16 M 65.1 / 62.3, 32 M 123.9 / 123.1, 64 M 241 / 241, 100 M 375 / 383.
-constexpr int kSmallTensor = 0, kMidTensor = 1, kLargeTensor = 2;
-constexpr size_t kSmallElems = (size_t)3 << 19, kKeepElems = (size_t)24 << 20;
+constexpr int kSmallTensor = 0, kMidTensor = 1, kLargeTensor = 2, kDrainTensor = 3;
+constexpr size_t kSmallElems = (size_t)7 << 20, kKeepElems = (size_t)24 << 20;
 template <int LEN>
-constexpr int kTensorStore = LEN == kSmallTensor ? kThrough : kThroughStream;
+constexpr int kTensorStore = LEN == kSmallTensor ? kThrough : (LEN == kDrainTensor ? kStream : kThroughStream);
 
 // a5 + a6 (eq. 10, eq. 11) for one tensor, both from the weight that was loaded, in single-wave pieces of
 // 64 quads (`ext` in pieces, as for k_quantize_pack; measured on 2^27 elements: 6.29 TB/s against 6.02 TB/s

@@ -19,14 +19,15 @@ def B():
     return binding
 
 
-SMALL, KEEP = 3 << 19, 24 << 20
+SMALL, KEEP = 7 << 20, 24 << 20
 
 
 def _floats(rng, n, scale):
     return rng.standard_normal(n, dtype=np.float32) * np.float32(scale)
 
 
-@pytest.mark.parametrize("n", [SMALL, SMALL + 3, KEEP, KEEP + 1])
+# (five workers' aggregates from 1.25 M to 2.25 M elements are stored non-temporally)
+@pytest.mark.parametrize("n", [1_250_000, 1_250_003, 2_250_000, 2_250_001, SMALL, SMALL + 3, KEEP, KEEP + 1])
 @pytest.mark.parametrize("mode", ["local", "global", "both"])
 def test_update_at_the_edges_of_its_lengths(B, oracle, n, mode):
     rng = np.random.default_rng(n + len(mode))
@@ -63,9 +64,10 @@ def test_quantize_pack_at_the_edges_of_its_lengths(B, oracle, n):
     assert bool((pad[n:] == 9.0).all()) and bool((packed[B.packed_words(n):] == 5).all()), "written past the end"
 
 
-# elements x workers / 4 bytes of streams: above 28 MB (56 MB up to eight workers) they are read non-temporally
+# elements x workers / 4 bytes of streams: above 56 MB (100 MB above 16 workers) they are read non-temporally
 @pytest.mark.parametrize("t", [0.25, 0.3, 1.1e-38])
-@pytest.mark.parametrize("N,n", [(4, 57_000_013), (7, 33_000_001), (16, 7_100_005), (17, 6_600_007), (64, 1_800_001)])
+@pytest.mark.parametrize("N,n", [(4, 57_000_013), (7, 33_000_001), (16, 7_100_005), (17, 6_600_007), (64, 1_800_001),
+                                 (1, 4_500_000), (4, 4_500_001), (8, 2_249_999), (12, 1_750_001), (16, 14_100_005), (17, 23_600_007), (64, 6_300_001)])
 def test_decode_sum_of_many_streams_equals_its_parts(B, N, n, t):
     gen = torch.Generator(device="cuda").manual_seed(N)
     streams = [torch.randint(-2 ** 31, 2 ** 31, (B.packed_words(n),), dtype=torch.int32, device="cuda", generator=gen)
