@@ -320,11 +320,16 @@ long long arena_offset16(const cdsgd_tensor *tensors, int i, const uint32_t *con
     return off;
 }
 
+// ... of all tensors of a list into `offsets`, or false.
 bool in_arenas(const cdsgd_tensor *tensors, int num_tensors, const uint32_t *const *const *peers, int num_workers, int self,
-               unsigned grad_bytes)
+               unsigned grad_bytes, unsigned *offsets)
 {
-    for (int i = 1; i < num_tensors; ++i)
-        if (arena_offset16(tensors, i, peers, num_workers, self, grad_bytes) < 0) return false;
+    offsets[0] = 0u;
+    for (int i = 1; i < num_tensors; ++i) {
+        const long long off = arena_offset16(tensors, i, peers, num_workers, self, grad_bytes);
+        if (off < 0) return false;
+        offsets[i] = (unsigned)off;
+    }
     return true;
 }
 
@@ -620,7 +625,8 @@ int cdsgd_plan_create_typed(const cdsgd_tensor *tensors, int num_tensors, const 
     if (rc != CDSGD_OK) return rc;
     const unsigned row = row_entries(num_workers);
     const unsigned grad_bytes = grad_dtype == CDSGD_GRAD_F32 ? 4u : 2u;
-    const bool arenas = in_arenas(tensors, num_tensors, peers, num_workers, self, grad_bytes);
+    std::vector<unsigned> offsets((size_t)num_tensors);
+    const bool arenas = in_arenas(tensors, num_tensors, peers, num_workers, self, grad_bytes, offsets.data());
 
     // host image of the device block
     const size_t bytes_t = sizeof(TensorDesc) * (size_t)num_tensors;
@@ -643,13 +649,12 @@ int cdsgd_plan_create_typed(const cdsgd_tensor *tensors, int num_tensors, const 
         ht[i] = make_desc(t);
         const unsigned nc = (unsigned)chunks_of(t.n);
         chunk_start[(size_t)i + 1] = chunk_start[(size_t)i] + nc;
-        const unsigned off16 = arenas && i > 0 ? (unsigned)arena_offset16(tensors, i, peers, num_workers, self, grad_bytes) : 0u;
         for (unsigned c = 0; c < nc; ++c) {
             hc[ci].tensor = (unsigned)i;
             hc[ci].chunk = c;
             if (arenas) {
                 const size_t left = t.n - (size_t)c * kChunkElems;
-                ha[ci].off16 = off16 + c * (kChunkElems / 16u);
+                ha[ci].off16 = offsets[(size_t)i] + c * (kChunkElems / 16u);
                 ha[ci].elems = (unsigned)(left < kChunkElems ? left : kChunkElems);
             }
             ++ci;
@@ -1254,12 +1259,72 @@ int launch_static_build(const StaticTarget &to, const Payload &p, hipStream_t s)
     return launch_status();
 }
 
+// Tensor 0's buffers, and its stream of each of the first `streams` workers; no tensors yet.
+void arenas_of(const cdsgd_tensor *tensors, const uint32_t *const *const *peers, int streams, int self, StaticArenas *flat)
+{
+    std::memset(flat, 0, sizeof(*flat));
+    const cdsgd_tensor &z = tensors[0];
+    const void *const role[kStaticRoles] = {z.w_global, z.w_local, z.residual, z.grad, z.packed_self, z.agg_full};
+    for (int r = 0; r < kStaticRoles; ++r) flat->role[r] = (unsigned long long)reinterpret_cast<uintptr_t>(role[r]);
+    for (int j = 0; j < streams; ++j)
+        if (j != self) flat->stream[j] = reinterpret_cast<const uint8_t *>(peers[j][0]);
+}
+
+// The compressed pass over a checked list in arenas of at most StaticArenas::kTensors tensors, described by the launch's
+// own arguments; `shape` has kArena.
+int launch_from_arguments(const cdsgd_tensor *tensors, int num_tensors, const uint32_t *const *const *peers, int num_workers,
+                          int self, int grad_dtype, const unsigned *offsets, unsigned num_chunks,
+                          const CompressedLaunch &shape, int form, float threshold, float lr_local, float lr_global, hipStream_t s)
+{
+    StaticArenas flat;
+    arenas_of(tensors, peers, num_workers, self, &flat);
+    unsigned slots = 0;
+    for (unsigned k = 0; k < StaticArenas::kTensors; ++k) {
+        if (k >= (unsigned)num_tensors) {
+            flat.slots[k] = StaticArenas::kNoSlot;
+            continue;
+        }
+        flat.offsets[k] = offsets[k];
+        flat.sizes[k] = (unsigned)tensors[k].n;
+        flat.slots[k] = slots;
+        slots += (unsigned)chunks_of(tensors[k].n);
+    }
+    const unsigned num_tiles = num_chunks * (kChunkQuads / (64u * shape.waves));
+    const float scale = lr_global / (float)num_workers;
+    const auto bound = [&](unsigned used) { return shape.lds <= used ? 0u : shape.lds - used; };
+#define CDSGD_LAUNCH_ARGUMENTS_S(SZ, WAVES, FORM, GT, HOW)                                                     \
+    hipLaunchKernelGGL((k_fused_arguments<SZ, WAVES, FORM, GT, HOW>), dim3(num_tiles), dim3(64 * WAVES),       \
+                       bound(kTileLds<SZ, FORM, WAVES>), s, num_tiles, (unsigned)num_tensors, num_workers, self, threshold, \
+                       lr_local, scale, flat)
+#define CDSGD_LAUNCH_ARGUMENTS(SZ, WAVES, FORM, HOW)                                                           \
+    do {                                                                                                       \
+        if (grad_dtype == CDSGD_GRAD_BF16) CDSGD_LAUNCH_ARGUMENTS_S(SZ, WAVES, FORM, kGradBF16, HOW);          \
+        else if (grad_dtype == CDSGD_GRAD_F16) CDSGD_LAUNCH_ARGUMENTS_S(SZ, WAVES, FORM, kGradF16, HOW);       \
+        else CDSGD_LAUNCH_ARGUMENTS_S(SZ, WAVES, FORM, kGradF32, HOW);                                         \
+    } while (0)
+#define CDSGD_LAUNCH_ARGUMENTS_F(FORM)                                                                         \
+    do {                                                                                                       \
+        if (shape.waves == 1u) CDSGD_LAUNCH_ARGUMENTS(kUpTo8, 1, FORM, kArena);                                \
+        else if (num_workers <= kUpTo8) CDSGD_LAUNCH_ARGUMENTS(kUpTo8, 4, FORM, kArena);                       \
+        else if (num_workers > kUpTo16) CDSGD_LAUNCH_ARGUMENTS(kAnyWorkers, 4, FORM, kArena);                  \
+        else if (shape.how & kLate) CDSGD_LAUNCH_ARGUMENTS(kUpTo16, 4, FORM, kWrittenOut | kLate | kArena);    \
+        else CDSGD_LAUNCH_ARGUMENTS(kUpTo16, 4, FORM, kWrittenOut | kArena);                                   \
+    } while (0)
+    if (form == kCount) CDSGD_LAUNCH_ARGUMENTS_F(kCount);
+    else CDSGD_LAUNCH_ARGUMENTS_F(kChain);
+#undef CDSGD_LAUNCH_ARGUMENTS_F
+#undef CDSGD_LAUNCH_ARGUMENTS
+#undef CDSGD_LAUNCH_ARGUMENTS_S
+    return launch_status();
+}
+
 // Write the tables of a checked layer list into the static array at `base`.
-// arenas: the list lies in arenas; arena_chunks: the chunk table holds ArenaChunk entries (lists in arenas only).
+// offsets: of a list in arenas (in_arenas), or null; arena_chunks: the chunk table holds ArenaChunk entries (lists in arenas only).
 int build_static_tables(unsigned char *base, const cdsgd_tensor *tensors, int num_tensors,
                         const uint32_t *const *const *peers, int num_workers, int self, int grad_dtype, bool with_rows,
-                        bool arenas, bool arena_chunks, hipStream_t s)
+                        const unsigned *offsets, bool arena_chunks, hipStream_t s)
 {
+    const bool arenas = offsets != nullptr;
     const unsigned grad_bytes = grad_dtype == CDSGD_GRAD_F32 ? 4u : 2u;
     StaticTarget to;
     to.desc = reinterpret_cast<TensorDesc *>(base + kStaticOffDesc);
@@ -1275,16 +1340,8 @@ int build_static_tables(unsigned char *base, const cdsgd_tensor *tensors, int nu
     const auto bits = [](const void *p) { return (unsigned long long)reinterpret_cast<uintptr_t>(p); };
     StaticArenas flat;
     StaticPointers any;
-    if (arenas) {
-        std::memset(&flat, 0, sizeof(flat));
-        const cdsgd_tensor &z = tensors[0];
-        const void *const role[kStaticRoles] = {z.w_global, z.w_local, z.residual, z.grad, z.packed_self, z.agg_full};
-        for (int r = 0; r < kStaticRoles; ++r) flat.role[r] = bits(role[r]);
-        for (int j = 0; j < streams; ++j)
-            if (j != self) flat.stream[j] = bits(peers[j][0]);
-    } else {
-        std::memset(&any, 0, sizeof(any));
-    }
+    if (arenas) arenas_of(tensors, peers, streams, self, &flat);
+    else std::memset(&any, 0, sizeof(any));
     const unsigned stride = StaticPointers::stride(to.workers);
     const unsigned part = arenas ? StaticArenas::kTensors : StaticPointers::kWords / stride;
     for (int first = 0; first < num_tensors; first += (int)part) {
@@ -1296,9 +1353,9 @@ int build_static_tables(unsigned char *base, const cdsgd_tensor *tensors, int nu
             const int i = first + (int)k;
             const cdsgd_tensor &t = tensors[i];
             if (arenas) {
-                flat.t[k].off16 = i == 0 ? 0u : (unsigned)arena_offset16(tensors, i, peers, streams, self, grad_bytes);
-                flat.t[k].n = (unsigned)t.n;
-                flat.t[k].slot = to.slots;
+                flat.offsets[k] = offsets[i];
+                flat.sizes[k] = (unsigned)t.n;
+                flat.slots[k] = to.slots;
             } else {
                 unsigned long long *w = any.w + (size_t)k * stride;
                 const void *const role[kStaticRoles] = {t.w_global, t.w_local, t.residual, t.grad, t.packed_self, t.agg_full};
@@ -1347,13 +1404,23 @@ extern "C" int cdsgd_step_fused_static(const cdsgd_tensor *tensors, int num_tens
     pt.has_agg_full = all_agg;
     pt.grad_type = grad_dtype;
 
-    const bool arenas = in_arenas(tensors, num_tensors, peers, compressed ? num_workers : 0, self, grad_dtype == CDSGD_GRAD_F32 ? 4u : 2u);
+    unsigned offsets[kStaticMaxTensors];
+    const bool arenas = in_arenas(tensors, num_tensors, peers, compressed ? num_workers : 0, self,
+                                  grad_dtype == CDSGD_GRAD_F32 ? 4u : 2u, offsets);
     if (compressed && arenas) {
         pt.arena_chunks = reinterpret_cast<ArenaChunk *>(base + kStaticOffChunks);
         int form;
-        if ((launch_of_pass(&pt, threshold, &form).how & kArena) == 0) pt.arena_chunks = nullptr;
+        CompressedLaunch shape = launch_of_pass(&pt, threshold, &form);
+        const bool chunks = (shape.how & kArena) != 0;
+        // (above 16 workers the kernel for arenas is the slower one, by less than the launch that it spares)
+        if (shape.how == 0 && num_workers > kUpTo16 && form != kChainTiny && total_chunks * kTilesPerChunk <= kMidListTiles)
+            shape.how = kArena;
+        if ((shape.how & kArena) != 0 && num_tensors <= (int)StaticArenas::kTensors)
+            return launch_from_arguments(tensors, num_tensors, peers, num_workers, self, grad_dtype, offsets, (unsigned)total_chunks,
+                                         shape, form, threshold, lr_local, lr_global, s);
+        if (!chunks) pt.arena_chunks = nullptr;
     }
-    rc = build_static_tables(base, tensors, num_tensors, peers, num_workers, self, grad_dtype, compressed, arenas,
+    rc = build_static_tables(base, tensors, num_tensors, peers, num_workers, self, grad_dtype, compressed, arenas ? offsets : nullptr,
                              pt.arena_chunks != nullptr, s);
     if (rc != CDSGD_OK) return rc;
     return launch_formal_pass(&pt, step, k, threshold, lr_local, lr_global, true, hip_stream);

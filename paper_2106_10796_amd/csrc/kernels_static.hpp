@@ -29,23 +29,24 @@ struct StaticTarget {
 struct StaticArenas {
     static constexpr unsigned kTensors = 256;
     unsigned long long role[kStaticRoles];            // tensor 0's buffers (0: none)
-    unsigned long long stream[CDSGD_MAX_WORKERS];     // tensor 0's stream of every worker
-    struct {
-        unsigned off16, n, slot;  // offset in 16 elements, elements, first chunk table entry (counted from slot0)
-    } t[kTensors];
+    const uint8_t *stream[CDSGD_MAX_WORKERS];         // tensor 0's stream of every worker (null: the own, and past the last)
+    // per tensor: first chunk table entry (counted from slot0; kNoSlot past the last), offset in 16 elements, elements
+    __attribute__((aligned(16))) unsigned slots[kTensors];
+    unsigned offsets[kTensors], sizes[kTensors];
+    static constexpr unsigned kNoSlot = 0xFFFFFFFFu;
 
-    __device__ unsigned n(unsigned i, unsigned) const { return t[i].n; }
-    __device__ unsigned slot(unsigned i, unsigned) const { return t[i].slot; }
-    __device__ unsigned off16(unsigned i) const { return t[i].off16; }
+    __device__ unsigned n(unsigned i, unsigned) const { return sizes[i]; }
+    __device__ unsigned slot(unsigned i, unsigned) const { return slots[i]; }
+    __device__ unsigned off16(unsigned i) const { return offsets[i]; }
     __device__ unsigned long long buffer(unsigned i, int r, unsigned grad_bytes, unsigned) const
     {
         if (role[r] == 0ull) return 0ull;
-        const unsigned long long off = (unsigned long long)t[i].off16;
+        const unsigned long long off = (unsigned long long)offsets[i];
         return role[r] + (r == 4 ? off * 4u : off * 16u * (r == 3 ? grad_bytes : 4u));
     }
     __device__ unsigned long long of_worker(unsigned i, unsigned j, unsigned) const
     {
-        return stream[j] + (unsigned long long)t[i].off16 * 4u;
+        return reinterpret_cast<unsigned long long>(stream[j]) + (unsigned long long)offsets[i] * 4u;
     }
 };
 
@@ -119,6 +120,57 @@ __global__ __launch_bounds__(256) void k_static_build(StaticTarget to, Payload p
             cr.chunk = chunk;
             to.chunks[to.slot0 + s] = cr;
         }
+    }
+}
+
+// The compressed pass over a list in arenas that fits one launch's arguments: no tables, one launch instead of two.  A wave
+// finds the tensor of its chunk by comparing the chunk's number with the first chunks of all of them, four to a lane, and
+// the chunk's place in the arenas follows from the tensor's entry: two trips to memory in front of the data, as with tables.
+// Bound by HBM above some million elements and by the launch below.  Time of the call, tables first / now, us: 10 k to 300 k
+// elements, N = 2 to 32 8.4 / 4.9, 1 M, N = 8, fp16 9.3 / 6.3, 4 M, N = 16 22.3 / 19.2, 14 M, N = 16, bf16 57.5 / 54.4;
+// ResNet-20-shaped, N = 8 10.0 / 6.6; ResNet-50-shaped, N = 2 101.3 / 100.5, N = 8, fp16 95.2 / 93.5, N = 16, bf16 104.3 /
+// 100.8; above 16 workers 1 M, N = 32 10.8 / 7.0, 4 M, N = 64 31.5 / 28.5.
+template <int SZ, int WAVES, int FORM, int GT, int HOW>
+__global__ __launch_bounds__(64 * WAVES) void k_fused_arguments(unsigned num_tiles, unsigned num_tensors, int num_workers, int self,
+                                                                float t, float lr_local, float scale, StaticArenas p)
+{
+    static_assert((HOW & kArena) != 0, "lists in arenas");
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kTileLds<SZ, FORM, WAVES>];
+    constexpr unsigned kQuads = 64u * WAVES, kPerChunk = kChunkQuads / kQuads;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const unsigned lane = threadIdx.x & 63u;
+    const unsigned x = piece_of_workgroup<true>((unsigned)blockIdx.x, kPerChunk, num_tiles);
+    const unsigned slot = x / kPerChunk, tile = x % kPerChunk;
+    StreamPointers<SZ, WAVES, false> from;
+    from.template load<false>(p.stream, num_workers, wave, lane);
+    TensorDesc d;
+    d.w_global = reinterpret_cast<float *>(p.role[0]);
+    d.w_local = reinterpret_cast<float *>(p.role[1]);
+    d.residual = reinterpret_cast<float *>(p.role[2]);
+    d.grad = reinterpret_cast<const void *>(p.role[3]);
+    d.packed_self = reinterpret_cast<uint8_t *>(p.role[4]);
+    from.pin();
+    unsigned i = 0;
+    if (num_tensors > 1u) {
+        static_assert(StaticArenas::kTensors == 256, "four tensors to a lane");
+        const u4 first = *reinterpret_cast<const u4 *>(p.slots + 4u * lane);
+        unsigned begun = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) begun += (unsigned)__builtin_popcountll(__ballot(first[c] <= slot));
+        i = begun - 1u;
+    }
+    const unsigned chunk = slot - p.slots[i], left = p.sizes[i] - chunk * kChunkElems;
+    const unsigned elems = left < kChunkElems ? left : kChunkElems;
+    const unsigned quad = (p.offsets[i] + chunk * (kChunkElems / 16u)) * 4u, bytes = (elems + 15u) / 16u * 4u;
+    d.ext.full_chunks = 0u;
+    d.ext.tail_bytes = quad + bytes;  // where the chunk's codes end in a stream
+    if (elems == kChunkElems) {
+        fused_tile<false, SZ, WAVES, FORM, GT, false, HOW>(d, from, num_workers, self, quad, tile, kQuads * 4u, kQuads, t, lr_local,
+                                                           scale, true, lds);
+    } else if (tile * kQuads < bytes) {
+        const unsigned elems0 = tile * kQuads * 4u;
+        fused_tile<true, SZ, WAVES, FORM, GT, false, HOW>(d, from, num_workers, self, quad, tile, elems > elems0 ? elems - elems0 : 0u,
+                                                          bytes - tile * kQuads, t, lr_local, scale, true, lds);
     }
 }
 

@@ -95,3 +95,27 @@ def test_long_lists_in_arenas(B, N, t, dtype, n):
     for plan in (a, b):
         plan.step(1, 4, t, 0.4, 0.7)
     check("whole")
+    B.cdsgd_step_fused_static(mine, peers, N, N - 1, 1, 4, t, 0.4, 0.7, grad_dtype=dtype)
+    b.step(1, 4, t, 0.4, 0.7)
+    check("static")
+
+
+# 256 tensors fit the arguments of one launch; above 16 workers that form ends at 16 M elements
+@pytest.mark.parametrize("T,N,t,dtype", [(2, 3, 0.5, torch.float32), (255, 8, 0.3, torch.bfloat16), (256, 16, 0.5, torch.float16),
+                                         (256, 33, 0.3, torch.float32), (257, 9, 0.5, torch.float32), (256, 64, 0.25, torch.float32)])
+def test_static_lists_at_the_edge_of_one_launch(B, T, N, t, dtype):
+    rng = np.random.default_rng(T + N)
+    sizes = [int(x) for x in 2.0 ** rng.uniform(0, 13.5, T)]
+    a, b, mine, peers, check = _pair(B, sizes, N, N // 2, t, dtype, align=64)
+    B.cdsgd_step_fused_static(mine, peers, N, N // 2, 1, 4, t, 0.4, 0.7, grad_dtype=dtype)
+    b.step(1, 4, t, 0.4, 0.7)
+    check("static")
+
+
+@pytest.mark.parametrize("n", [16 * 1024 * 1024 - 5000, 16 * 1024 * 1024 + 5])
+@pytest.mark.parametrize("t", [0.5, 0.3])
+def test_static_list_of_many_workers(B, n, t):
+    a, b, mine, peers, check = _pair(B, [n - 70_001, 4097, 60_000], 20, 3, t, torch.bfloat16)
+    B.cdsgd_step_fused_static(mine, peers, 20, 3, 1, 4, t, 0.4, 0.7, grad_dtype=torch.bfloat16)
+    b.step(1, 4, t, 0.4, 0.7)
+    check("static")
