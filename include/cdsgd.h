@@ -386,7 +386,7 @@ int cdsgd_probe_streams(const float *const *reads, int num_reads, float *const *
  * The tables are rebuilt on every call (a few small launches before the pass itself), so a
  * plan remains the faster form for a layer list that is stepped many times.  Most compressed
  * passes over a list in arenas (every buffer of tensor i as many elements from tensor 0's as
- * every other) of up to 256 tensors and 16 M elements, 28 M with up to 16 workers, need none:
+ * every other) of up to 256 tensors and 16 M elements, 28 M with up to 32 workers, need none:
  * the list fits the arguments of the pass's own launch.
  */
 #define CDSGD_STATIC_MAX_TENSORS 1024

@@ -792,16 +792,23 @@ constexpr unsigned kWalkingGroups = 768;
 //                     .99 / .98;  VGG-16 - / .99 / .99 / 1.00 / .98;  90 M 1.04 / - / .99 / 1.01 / .99;  260 M .99 / - /
 //                     .99 / 1.00 / .98   (long 32-bit chains gain nothing and 1 GiB buckets at t = 0.05 lose 1 %)
 //   up to 8 workers   N = 4, t = 0.3  4 M 1.03, 12 M .99, 25 M 1.00, VGG-16 1.06;  N = 8 1.02 / 1.00 / 1.01 / 1.00
-//   above 16          N = 17 / 32, t = 0.3  4 M 1.02 / 1.01;  25 M 1.00 / 1.00;  VGG-16 .98 / .99;  t = 0.5 .99 / 1.01
+// Kernels of their own for 17 to 32 workers, which hold half the stream pointers in scalar registers, over those for any
+// number (results written through / and the list in arenas), N = 17 / 24 / 32:
+//   t = 0.5, 32-bit   1 M .83 .83 .88 / .81 .82 .88;  4 M .98 .97 .98 / .98 .97 .97;  12 M .99 .99 .98 / .99 .99 .99;
+//                     ResNet-50-shaped .97 .98 .98 / .97 .97 .98;  VGG-16 .99 1.00 1.01
+//   t = 0.3, 32-bit   1 M .97 1.03 .97 / .93 .99 .96;  4 M .99 .99 1.00 / .98 .98 .98;  12 M 1.00 .99 .97 / .99 .99 .99;
+//                     ResNet-50-shaped .95 .97 .97 / .95 .95 .96;  VGG-16 .98 1.01 1.00
+//   t = 0.3, bf16     1 M .88 .94 1.02 / .88 .93 1.03;  4 M .99 / .98;  12 M 1.00 1.00 .98 / .99 .98 .98;  VGG-16 .96 .98 1.00
+// (Long 32-bit lists of more than 20 workers keep the general kernels.)
 // Words read non-temporally, as in decode-and-sum, and 5 groups, over the default policy at its own residency:
 //   N = 33   8 M 1.07-1.08, 20 M .97-1.00, 50 M .96;  N = 48  8 M 1.06, 10 M .96;  N = 64  6 M 1.04, 8 M .95, 25 M .96-.98,
 //   VGG-16 .94-.99   (N = 17: 25 M .99-1.03, VGG-16 1.00-1.04;  N = 32: 25 M .98-.99, VGG-16 1.02-1.04;  N = 16 25 M 1.04)
 constexpr unsigned long long kStreamWordsBytes = 112000000;
 
-// Lists in arenas (ArenaChunk), up to 16 workers and 28 M elements: one trip to memory less before a group's first data
+// Lists in arenas (ArenaChunk), up to 32 workers and 28 M elements: one trip to memory less before a group's first data
 // loads.  Time over that of the general kernels: 1 M elements .97-1.00, 2 M .97-.99, 4 M .98-.99, 8 M .99-1.00, 25 M
 // .99-1.01; ResNet-50-shaped list, N = 16, in 17 launches of a million elements and more 163.1 / 156.9 us, in one 107.0 /
-// 106.2.  (VGG-16-shaped .99-1.04, 1 GiB buckets 1.02.  Above 16 workers 1 M 1.12, 4 M 1.03, 25 M 1.01: more of the stream
+// 106.2.  (VGG-16-shaped .99-1.04, 1 GiB buckets 1.02.  Above 32 workers 1 M 1.12, 4 M 1.03, 25 M 1.01: more of the stream
 // pointers no longer fit the scalar registers beside the buffers'.)
 struct CompressedLaunch {
     unsigned waves, lds;
@@ -846,6 +853,10 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
         if (tiles > (half ? 80u * 1024u : kLongListTiles)) return {4u, 32768u, half || tiles <= 48u * 1024u ? kWrittenOut : 0, 0u};
         return {4u, 0u, kWrittenOut | (mid_list ? kLate : 0) | (long_list ? 0 : arena), 0u};
     }
+    if (num_workers <= kUpTo32 && max_workgroups == 0 && (half || !long_list || num_workers <= 20)) {
+        const bool bounded = form == kCount ? mid_list : (half ? long_list : mid_list);
+        return {4u, !bounded ? 0u : (form == kCount ? 32768u : 38912u), kWrittenOut | (long_list ? 0 : arena), 0u};
+    }
     if (num_workers > kUpTo32 && (unsigned long long)num_workers * tiles * kTileBytes > kStreamWordsBytes)
         return {4u, 32768u, kStreamWords, 0u};
     if (form == kCount) return {4u, mid_list ? 32768u : 0u, 0, 0u};
@@ -881,6 +892,11 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
     const unsigned num_tiles = plan->num_chunks * (kChunkQuads / (64u * shape.waves));
     unsigned grid = plan->grid_size(num_tiles, 64u * shape.waves);
     if (shape.groups != 0 && grid > shape.groups) grid = shape.groups;
+    // Sparse peers of 17 to 32 workers: the kernels for so many over those for any number, N = 17 / 24 / 32: t = 0.5 1 M 1.01 /
+    // 1.03 / .99, 4 M .97, ResNet-50-shaped .98;  t = 0.3 1 M .91 / .96 / .98, 4 M .94, ResNet-50-shaped .95 / .98 / .98,
+    // VGG-16-shaped 1.00 / 1.03 / 1.00;  t = 0.3, bf16 1 M .90 / .91 / .92, 4 M .93, VGG-16-shaped .94 / .97 / .98.
+    const bool sparse32 = N <= kUpTo32 && plan->max_workgroups == 0 &&
+                          (plan->grad_type != kGradF32 || plan->num_chunks * kTilesPerChunk <= kLongListTiles);
     const auto bound = [&](unsigned used) { return shape.lds <= used ? 0u : shape.lds - used; };
 #define CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, GT, SPARSE, HOW)                                            \
     hipLaunchKernelGGL((k_fused_compressed<SZ, WAVES, FORM, GT, SPARSE, HOW>), dim3(grid), dim3(64 * WAVES),   \
@@ -896,11 +912,14 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
     do {                                                                                                       \
         if (plan->peers_sparse && N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, true, 0);              \
         else if (plan->peers_sparse && N <= kUpTo16) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, true, 0);       \
+        else if (plan->peers_sparse && sparse32) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, true, 0);           \
         else if (plan->peers_sparse) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, true, 0);                   \
         else if (shape.waves == 1u && shape.how == kArena) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 1, FORM, false, kArena); \
         else if (shape.waves == 1u) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 1, FORM, false, 0);                        \
         else if (N <= kUpTo8 && shape.how == kArena) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, false, kArena);  \
         else if (N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, false, 0);                              \
+        else if (N > kUpTo16 && shape.how == (kWrittenOut | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, kWrittenOut | kArena); \
+        else if (N > kUpTo16 && shape.how == kWrittenOut) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, kWrittenOut); \
         else if (N > kUpTo16 && shape.how == kStreamWords) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, false, kStreamWords); \
         else if (N > kUpTo16) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, false, 0);                         \
         else if (shape.how == (kWrittenOut | kLate | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kWrittenOut | kLate | kArena); \
@@ -1306,7 +1325,8 @@ int launch_from_arguments(const cdsgd_tensor *tensors, int num_tensors, const ui
     do {                                                                                                       \
         if (shape.waves == 1u) CDSGD_LAUNCH_ARGUMENTS(kUpTo8, 1, FORM, kArena);                                \
         else if (num_workers <= kUpTo8) CDSGD_LAUNCH_ARGUMENTS(kUpTo8, 4, FORM, kArena);                       \
-        else if (num_workers > kUpTo16) CDSGD_LAUNCH_ARGUMENTS(kAnyWorkers, 4, FORM, kArena);                  \
+        else if (num_workers > kUpTo32) CDSGD_LAUNCH_ARGUMENTS(kAnyWorkers, 4, FORM, kArena);                  \
+        else if (num_workers > kUpTo16) CDSGD_LAUNCH_ARGUMENTS(kUpTo32, 4, FORM, kWrittenOut | kArena);        \
         else if (shape.how & kLate) CDSGD_LAUNCH_ARGUMENTS(kUpTo16, 4, FORM, kWrittenOut | kLate | kArena);    \
         else CDSGD_LAUNCH_ARGUMENTS(kUpTo16, 4, FORM, kWrittenOut | kArena);                                   \
     } while (0)
@@ -1412,8 +1432,8 @@ extern "C" int cdsgd_step_fused_static(const cdsgd_tensor *tensors, int num_tens
         int form;
         CompressedLaunch shape = launch_of_pass(&pt, threshold, &form);
         const bool chunks = (shape.how & kArena) != 0;
-        // (above 16 workers the kernel for arenas is the slower one, by less than the launch that it spares)
-        if (shape.how == 0 && num_workers > kUpTo16 && form != kChainTiny && total_chunks * kTilesPerChunk <= kMidListTiles)
+        // (above 32 workers the kernel for arenas is the slower one, by less than the launch that it spares)
+        if (shape.how == 0 && num_workers > kUpTo32 && form != kChainTiny && total_chunks * kTilesPerChunk <= kMidListTiles)
             shape.how = kArena;
         if ((shape.how & kArena) != 0 && num_tensors <= (int)StaticArenas::kTensors)
             return launch_from_arguments(tensors, num_tensors, peers, num_workers, self, grad_dtype, offsets, (unsigned)total_chunks,

@@ -106,7 +106,7 @@ struct StreamPointers {
         }
     }
 
-    // Keeps the compiler from moving the loads to where their pointers are used.  Above 16 workers a wave of the fused
+    // Keeps the compiler from moving the loads to where their pointers are used.  Above 32 workers a wave of the fused
     // kernels then holds more addresses than it has scalar registers for beside the descriptor: 4 (count form), 17
     // (chain) and 19 / 25 (sparse) of them are kept in lanes of a vector register, and 7 waves fit a SIMD instead of 8.
     // Short lists, where the early pointers count, gain all the same (figures at the head of kernels_fused.hpp); long

@@ -59,7 +59,7 @@ RAGGED = [1, 4096, 17, 4095, 4097, 1024, 1027, 12288, 15, 16, 8191, 3 * 4096 + 1
 
 @pytest.mark.parametrize("t", [0.5, 0.3])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16])
-@pytest.mark.parametrize("N", [1, 2, 4, 5, 8, 9, 13, 16, 17])
+@pytest.mark.parametrize("N", [1, 2, 4, 5, 8, 9, 13, 16, 17, 24, 29, 32, 33])
 def test_ragged_list_in_arenas(B, N, dtype, t):
     a, b, mine, peers, check = _pair(B, RAGGED, N, N // 2, t, dtype, align=64 if N % 2 else 1024)
     for plan in (a, b):
@@ -100,7 +100,7 @@ def test_long_lists_in_arenas(B, N, t, dtype, n):
     check("static")
 
 
-# 256 tensors fit the arguments of one launch; above 16 workers that form ends at 16 M elements
+# 256 tensors fit the arguments of one launch; above 32 workers that form ends at 16 M elements
 @pytest.mark.parametrize("T,N,t,dtype", [(2, 3, 0.5, torch.float32), (255, 8, 0.3, torch.bfloat16), (256, 16, 0.5, torch.float16),
                                          (256, 33, 0.3, torch.float32), (257, 9, 0.5, torch.float32), (256, 64, 0.25, torch.float32)])
 def test_static_lists_at_the_edge_of_one_launch(B, T, N, t, dtype):
@@ -113,9 +113,28 @@ def test_static_lists_at_the_edge_of_one_launch(B, T, N, t, dtype):
 
 
 @pytest.mark.parametrize("n", [16 * 1024 * 1024 - 5000, 16 * 1024 * 1024 + 5])
-@pytest.mark.parametrize("t", [0.5, 0.3])
-def test_static_list_of_many_workers(B, n, t):
-    a, b, mine, peers, check = _pair(B, [n - 70_001, 4097, 60_000], 20, 3, t, torch.bfloat16)
-    B.cdsgd_step_fused_static(mine, peers, 20, 3, 1, 4, t, 0.4, 0.7, grad_dtype=torch.bfloat16)
+@pytest.mark.parametrize("N,t", [(20, 0.5), (24, 0.3), (36, 0.5), (36, 0.3)])
+def test_static_list_of_many_workers(B, n, N, t):
+    a, b, mine, peers, check = _pair(B, [n - 70_001, 4097, 60_000], N, 3, t, torch.bfloat16)
+    B.cdsgd_step_fused_static(mine, peers, N, 3, 1, 4, t, 0.4, 0.7, grad_dtype=torch.bfloat16)
     b.step(1, 4, t, 0.4, 0.7)
     check("static")
+
+
+# sparse peers of 17 to 32 workers have kernels of their own, but for long lists of 32-bit gradients
+@pytest.mark.parametrize("t", [0.5, 0.3])
+@pytest.mark.parametrize("N,sizes,dtype", [(17, RAGGED, torch.float32), (24, RAGGED, torch.float16), (32, RAGGED, torch.bfloat16),
+                                           (20, [29_000_000, 77, 4097], torch.float32),
+                                           (20, [29_000_000, 77, 4097], torch.bfloat16)])
+def test_sparse_peers_equal_packed_ones(B, N, sizes, dtype, t):
+    a, b, mine, peers, check = _pair(B, sizes, N, 5, t, dtype)
+
+    def encode(stream, n):
+        out = B.new_sparse(n)
+        B.cdsgd_sparse_encode(stream, n, out)
+        return out
+    encoded = [None if p is None else [encode(x, n) for x, n in zip(p, sizes)] for p in peers]
+    sparse = B.Plan(mine, encoded, N, 5, grad_dtype=dtype, peers_sparse=True)
+    sparse.step(1, 4, t, 0.4, 0.7)
+    b.step(1, 4, t, 0.4, 0.7)
+    check("sparse")

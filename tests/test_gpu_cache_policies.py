@@ -113,12 +113,13 @@ def _whole_equals_parts(B, n, N, grad, step, call):
         assert torch.equal(whole[k].view(torch.int32), part[k].view(torch.int32)), k
 
 
-# Above 32 workers and 112 MB of streams the workers' words are read non-temporally; 9 to 16 workers' results are written
-# through, but for long lists of 32-bit chains.  Parts of 1.6 M elements go the other way (or end in another place).
+# Above 32 workers and 112 MB of streams the workers' words are read non-temporally; 9 to 32 workers' results are written
+# through, but for long lists of 32-bit chains and of more than 20 workers.  Parts of 1.6 M elements go the other way (or end in another place).
 @pytest.mark.parametrize("t", [0.25, 0.3])
 @pytest.mark.parametrize("N,n,grad", [(33, 13_600_003, torch.float32), (64, 7_001_003, torch.bfloat16),
                                       (9, 17_000_013, torch.float32), (16, 51_000_001, torch.float32),
-                                      (16, 51_000_001, torch.float16)])
+                                      (16, 51_000_001, torch.float16), (20, 29_000_003, torch.float32),
+                                      (21, 29_000_003, torch.float32), (32, 29_000_003, torch.bfloat16)])
 def test_compressed_pass_equals_its_parts(B, N, n, grad, t):
     _whole_equals_parts(B, n, N, grad, 4096 * 401, lambda p, a, b: p.step(1, 4, t, 0.05, 0.1))
 
