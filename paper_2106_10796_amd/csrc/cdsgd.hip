@@ -406,13 +406,18 @@ int launch_full_pass(const PlanTables *plan, int local_mode, float lr_local, flo
 }
 
 // Whether decode-and-sum and the global rule behind it store non-temporally: few workers' sums of a few million elements,
-// which pass from call to call through the dies' own caches.  Both calls, stored so / written through and staying, us:
-// N = 2, 1.6 M 8.2 / 8.5, 2 M 8.4 / 9.9, 4 M 12.0 / 12.6, 5 M 14.7 / 14.3;  N = 4 (sparse), 2 M 8.5 / 9.8, 4 M 12.4 / 12.8,
-// 5 M 15.4 / 14.5;  N = 8, 1.6 M 8.1 / 8.6, 2 M 8.6 / 9.2, 2.5 M 9.9 / 9.8;  N = 12, 1.6 M 8.1 / 8.4, 2 M 9.0 / 8.7;
-// N = 16 (sparse), 1.2 M 10.1 / 9.5;  0.1 M elements, N = 4 4.7 / 4.4.
+// which pass from call to call through the dies' own caches.  (Neither call knows whether the streams of the other are
+// packed or sparse, so the line lies where nothing loses against non-temporal stores throughout.)  Both calls, stored so /
+// written through and staying, us, packed streams unless said:
+//   N = 2    1.6 M 8.2 / 8.5, 2 M 8.4 / 9.9, 4 M 12.0 / 12.6, 5 M 14.7 / 14.3      N = 4 (sparse)  4 M 12.4 / 12.8, 5 M 15.4 / 14.5
+//   N = 8    1.6 M 8.1 / 8.6, 2.2 M 8.8 / 9.3, 2.7 M 10.0 / 10.1, 3.5 M 12.7 / 12.1
+//   N = 12   1.6 M 8.1 / 8.7, 2.2 M 9.2 / 8.7, 2.7 M 10.6 / 10.1
+//   N = 16, sparse, one code in 256   1.6 M 8.3 / 9.3, 2.2 M 9.6 / 10.8, 3 M 11.5 / 11.8, 3.5 M 13.4 / 12.9; one in 16
+//            1.6 M 8.5 / 8.7, 2.2 M 10.5 / 9.9
+//   N = 32, sparse, one code in 256   1.6 M 9.4 / 9.5, 2.2 M 11.0 / 10.9;  N = 64 1.6 M 12.2 / 12.1;  0.1 M, N = 4 4.7 / 4.4
 inline bool drains_results(size_t n, int num_workers)
 {
-    const size_t most = num_workers <= kUpTo4 ? 4500000u : (num_workers <= kUpTo8 ? 2250000u : (num_workers <= 12 ? 1750000u : 0u));
+    const size_t most = num_workers <= kUpTo4 ? 4500000u : (num_workers <= kUpTo16 ? 3200000u : (num_workers <= kUpTo32 ? 1750000u : 0u));
     return n > 1250000u && n <= most;
 }
 

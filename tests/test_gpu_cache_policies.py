@@ -26,8 +26,8 @@ def _floats(rng, n, scale):
     return rng.standard_normal(n, dtype=np.float32) * np.float32(scale)
 
 
-# (five workers' aggregates from 1.25 M to 2.25 M elements are stored non-temporally)
-@pytest.mark.parametrize("n", [1_250_000, 1_250_003, 2_250_000, 2_250_001, SMALL, SMALL + 3, KEEP, KEEP + 1])
+# (five workers' aggregates from 1.25 M to 3.2 M elements are stored non-temporally)
+@pytest.mark.parametrize("n", [1_250_000, 1_250_003, 3_200_000, 3_200_001, SMALL, SMALL + 3, KEEP, KEEP + 1])
 @pytest.mark.parametrize("mode", ["local", "global", "both"])
 def test_update_at_the_edges_of_its_lengths(B, oracle, n, mode):
     rng = np.random.default_rng(n + len(mode))
@@ -67,7 +67,7 @@ def test_quantize_pack_at_the_edges_of_its_lengths(B, oracle, n):
 # elements x workers / 4 bytes of streams: above 56 MB (100 MB above 16 workers) they are read non-temporally
 @pytest.mark.parametrize("t", [0.25, 0.3, 1.1e-38])
 @pytest.mark.parametrize("N,n", [(4, 57_000_013), (7, 33_000_001), (16, 7_100_005), (17, 6_600_007), (64, 1_800_001),
-                                 (1, 4_500_000), (4, 4_500_001), (8, 2_249_999), (12, 1_750_001), (16, 14_100_005), (17, 23_600_007), (64, 6_300_001)])
+                                 (1, 4_500_000), (4, 4_500_001), (8, 3_199_999), (16, 3_200_001), (32, 1_750_000), (16, 14_100_005), (17, 23_600_007), (64, 6_300_001)])
 def test_decode_sum_of_many_streams_equals_its_parts(B, N, n, t):
     gen = torch.Generator(device="cuda").manual_seed(N)
     streams = [torch.randint(-2 ** 31, 2 ** 31, (B.packed_words(n),), dtype=torch.int32, device="cuda", generator=gen)
