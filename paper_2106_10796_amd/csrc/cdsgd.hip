@@ -70,7 +70,8 @@ namespace {
 //   quantise-and-pack               6.71 / 6.72 / - / 6.83 / - / 6.88 / 6.09 / 5.10
 //   update, both rules              6.36 / 6.34 / - / 6.55 / - / 6.50 / 6.55 / 6.18
 //   correction pass, sum in kernel  6.19 / 6.39-6.41 / 6.35 / 6.24 / - / 5.97   (by size and type: lds_of_kernel_sum)
-// eq. 11 alone loses with any bound and gets none; the compressed pass has a rule of its own (compressed_launch).
+// eq. 11 alone over a list loses with any bound and gets none; the single-tensor calls have theirs by length (small ones none);
+// the compressed pass has a rule of its own (compressed_launch).
 // The same bound stated to the compiler instead (amdgpu_waves_per_eu with a maximum of 5) gives 6.55 and 6.45 TB/s on
 // the first and the third line: most of the gain, not all of it.  While a pass launched this way runs it holds the
 // compute units' LDS, so a kernel of another stream that needs LDS waits for it; a full-gradient pass with a
@@ -796,6 +797,9 @@ constexpr unsigned kWalkingGroups = 768;
 //                     .99 / .98;  18 M 1.00 / - / .98 / 1.00 / .99;  25 M - / .99 / .97 / .97 / .98;  40 M .98 / - / .98 /
 //                     .99 / .98;  VGG-16 - / .99 / .99 / 1.00 / .98;  90 M 1.04 / - / .99 / 1.01 / .99;  260 M .99 / - /
 //                     .99 / 1.00 / .98   (long 32-bit chains gain nothing and 1 GiB buckets at t = 0.05 lose 1 %)
+//   (short lists, whose results the next pass finds in a cache, are slower so: N = 9 / 16, t = 0.3, bf16 0.3 M 1.16 / 1.16,
+//   0.45 M 1.24 / 1.23, 0.7 M 1.14 / 1.07, 1 M .98 / .98, 1.4 M 1.00 / .99;  N = 17 / 32 0.45 M 1.15 / 1.07, 1 M 1.04 / 1.07,
+//   1.4 M 1.03 / 1.01;  32-bit, t = 0.3, N = 16 / 32 0.45 M 1.10 / 1.00, 1 M .99 / 1.05, 1.4 M 1.02 / 1.02)
 //   up to 8 workers   N = 4, t = 0.3  4 M 1.03, 12 M .99, 25 M 1.00, VGG-16 1.06;  N = 8 1.02 / 1.00 / 1.01 / 1.00
 // Kernels of their own for 17 to 32 workers, which hold half the stream pointers in scalar registers, over those for any
 // number (results written through / and the list in arenas), N = 17 / 24 / 32:
@@ -815,9 +819,10 @@ constexpr unsigned long long kStreamWordsBytes = 112000000;
 // .99-1.01; ResNet-50-shaped list, N = 16, in 17 launches of a million elements and more 163.1 / 156.9 us, in one 107.0 /
 // 106.2.  (VGG-16-shaped .99-1.04, 1 GiB buckets 1.02.  Above 32 workers 1 M 1.12, 4 M 1.03, 25 M 1.01: more of the stream
 // pointers no longer fit the scalar registers beside the buffers'.)
+constexpr int kUpTo32Rows = 16;  // host side only: the kernels for up to 32 workers
 struct CompressedLaunch {
     unsigned waves, lds;
-    int how;          // kLate, kWrittenOut, kStreamWords
+    int how;          // kLate, kWrittenOut, kStreamWords, kArena, kUpTo32Rows
     unsigned groups;  // launch at most this many (0: no bound)
 };
 
@@ -841,6 +846,7 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
         return {4u, all ? 0u : 32768u, 0, 0u};
     }
     const int arena = arenas && max_workgroups == 0 ? kArena : 0;
+    const int out = tiles > (num_workers <= kUpTo16 ? 1024u : 2048u) ? kWrittenOut : 0;
     if (num_workers <= kUpTo8) {
         if (!mid_list) return {4u, 0u, arena, 0u};
         if (tiles <= 48u * 1024u) return {1u, half && !long_list ? 6144u : 7168u, long_list ? 0 : arena, 0u};
@@ -848,7 +854,7 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
         return {1u, half ? 7168u : 8192u, 0, 0u};
     }
     if (num_workers <= kUpTo16 && form == kCount) {
-        if (tiles <= 6u * 1024u) return {4u, 0u, kWrittenOut | arena, 0u};
+        if (tiles <= 6u * 1024u) return {4u, 0u, out | arena, 0u};
         if (!mid_list) return {4u, 24576u, kWrittenOut | arena, 0u};
         if (half) return {4u, 40960u, kWrittenOut | (long_list ? 0 : arena), 0u};
         if (long_list) return {4u, 49152u, kWrittenOut | kLate, 0u};
@@ -856,11 +862,11 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
     }
     if (num_workers <= kUpTo16) {
         if (tiles > (half ? 80u * 1024u : kLongListTiles)) return {4u, 32768u, half || tiles <= 48u * 1024u ? kWrittenOut : 0, 0u};
-        return {4u, 0u, kWrittenOut | (mid_list ? kLate : 0) | (long_list ? 0 : arena), 0u};
+        return {4u, 0u, out | (mid_list ? kLate : 0) | (long_list ? 0 : arena), 0u};
     }
     if (num_workers <= kUpTo32 && max_workgroups == 0 && (half || !long_list || num_workers <= 20)) {
         const bool bounded = form == kCount ? mid_list : (half ? long_list : mid_list);
-        return {4u, !bounded ? 0u : (form == kCount ? 32768u : 38912u), kWrittenOut | (long_list ? 0 : arena), 0u};
+        return {4u, !bounded ? 0u : (form == kCount ? 32768u : 38912u), kUpTo32Rows | out | (long_list ? 0 : arena), 0u};
     }
     if (num_workers > kUpTo32 && (unsigned long long)num_workers * tiles * kTileBytes > kStreamWordsBytes)
         return {4u, 32768u, kStreamWords, 0u};
@@ -923,14 +929,17 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
         else if (shape.waves == 1u) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 1, FORM, false, 0);                        \
         else if (N <= kUpTo8 && shape.how == kArena) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, false, kArena);  \
         else if (N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, false, 0);                              \
-        else if (N > kUpTo16 && shape.how == (kWrittenOut | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, kWrittenOut | kArena); \
-        else if (N > kUpTo16 && shape.how == kWrittenOut) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, kWrittenOut); \
+        else if (shape.how == (kUpTo32Rows | kWrittenOut | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, kWrittenOut | kArena); \
+        else if (shape.how == (kUpTo32Rows | kWrittenOut)) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, kWrittenOut); \
+        else if (shape.how == (kUpTo32Rows | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, kArena); \
+        else if (shape.how == kUpTo32Rows) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, 0);                \
         else if (N > kUpTo16 && shape.how == kStreamWords) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, false, kStreamWords); \
         else if (N > kUpTo16) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, false, 0);                         \
         else if (shape.how == (kWrittenOut | kLate | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kWrittenOut | kLate | kArena); \
         else if (shape.how == (kWrittenOut | kLate)) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kWrittenOut | kLate); \
         else if (shape.how == (kWrittenOut | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kWrittenOut | kArena); \
         else if (shape.how == kWrittenOut) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kWrittenOut);      \
+        else if (shape.how == kArena) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kArena);                \
         else CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, 0);                                              \
     } while (0)
     if (form == kCount && shape.how == kLate) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, kCount, false, kLate);  // walking groups
@@ -1331,9 +1340,11 @@ int launch_from_arguments(const cdsgd_tensor *tensors, int num_tensors, const ui
         if (shape.waves == 1u) CDSGD_LAUNCH_ARGUMENTS(kUpTo8, 1, FORM, kArena);                                \
         else if (num_workers <= kUpTo8) CDSGD_LAUNCH_ARGUMENTS(kUpTo8, 4, FORM, kArena);                       \
         else if (num_workers > kUpTo32) CDSGD_LAUNCH_ARGUMENTS(kAnyWorkers, 4, FORM, kArena);                  \
-        else if (num_workers > kUpTo16) CDSGD_LAUNCH_ARGUMENTS(kUpTo32, 4, FORM, kWrittenOut | kArena);        \
+        else if (num_workers > kUpTo16 && (shape.how & kWrittenOut)) CDSGD_LAUNCH_ARGUMENTS(kUpTo32, 4, FORM, kWrittenOut | kArena); \
+        else if (num_workers > kUpTo16) CDSGD_LAUNCH_ARGUMENTS(kUpTo32, 4, FORM, kArena);                      \
         else if (shape.how & kLate) CDSGD_LAUNCH_ARGUMENTS(kUpTo16, 4, FORM, kWrittenOut | kLate | kArena);    \
-        else CDSGD_LAUNCH_ARGUMENTS(kUpTo16, 4, FORM, kWrittenOut | kArena);                                   \
+        else if (shape.how & kWrittenOut) CDSGD_LAUNCH_ARGUMENTS(kUpTo16, 4, FORM, kWrittenOut | kArena);      \
+        else CDSGD_LAUNCH_ARGUMENTS(kUpTo16, 4, FORM, kArena);                                                 \
     } while (0)
     if (form == kCount) CDSGD_LAUNCH_ARGUMENTS_F(kCount);
     else CDSGD_LAUNCH_ARGUMENTS_F(kChain);
