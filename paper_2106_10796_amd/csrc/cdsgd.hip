@@ -357,13 +357,15 @@ unsigned lds_of_kernel_sum(unsigned num_chunks, int num_workers, int grad_type)
 //        N = 4    2 M .95 / .87, 4 M .99 / 1.01, 8 M .94 / .94, 16 M 1.02 / 1.02, 80 M 1.01 / .99, VGG-16 1.01 / .99
 //        N = 8    2 M .99 / .91, 4 M 1.00 / 1.01, 8 M .97 / .95, 16 M 1.01 / 1.02, 80 M .99 / .99, VGG-16 .98 / .99
 //        N = 16   2 M .98 / .96, 3 M 1.02 / 1.13, 8 M .99 / .98, 16 M 1.01 / 1.03, 80 M .99 / .98, VGG-16 .98 / .98
+//   sum, N = 8 / 16, 32-bit: 0.1 M 1.08 / 1.04, 0.3 M .93 / .96, 0.5 M .98 / 1.00, 1.2 M .99 / .98; bf16 0.1 M 1.03 / 1.07, 0.3 M
+//                 1.03 / .88, 0.5 M .91 / .99, 1.2 M .96 / .96
 //   agg_full      1 M 1.00 / 1.00, 4 M .99 / 1.01, 12 M .97 / .97, 25 M 1.01 / 1.01, VGG-16 1.02 / .98
 // (not staying, as the compressed pass stores: 4 M 1.03-1.09, VGG-16 .99-1.01)
 bool keeps_results(unsigned num_chunks, int num_workers, bool sum)
 {
     const unsigned tiles = num_chunks * kTilesPerChunk;
     const bool many = sum && num_workers > 4;
-    return tiles <= 2u * 1024u || (many ? tiles > 72u * 1024u : tiles <= 14u * 1024u);
+    return many ? (tiles > 256u && tiles <= 2u * 1024u) || tiles > 72u * 1024u : tiles <= 14u * 1024u;
 }
 
 // Launch one full-gradient pass (see k_fused_full) for a plan.
