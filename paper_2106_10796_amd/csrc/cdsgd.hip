@@ -469,8 +469,9 @@ int launch_decode_sum(const uint32_t *const *streams, int num_workers, float *ag
     const bool count = is_pow2_threshold(threshold);
     constexpr unsigned kLdsCount = SPARSE ? 24576u : 32768u, kLdsChain = SPARSE ? 0u : 24576u;
     constexpr int kTilesMany = SPARSE ? 2 : 1;
-    // (Thresholds whose half is not exact have the shapes of the other chains, 25 M elements, N = 2 / 16: 37.6 and 50.9 us
-    // with the general kernel, 18.2 and 39.8; packed streams of 17 to 32 workers keep it: N = 24 67.4 us, 71.7.)
+    // (Thresholds whose half may not be exact have the shapes of the other chains; 25 M elements, packed, us, with the kernel
+    // for any number of workers / so: N = 2 43.7 / 21.1, 8 41.2 / 28.8, 16 44.0 / 38.0, 17 46.5 / 42.1, 24 51.3 / 48.2,
+    // 32 59.4 / 58.3;  sparse N = 16 55.9 / 41.5, 24 68.6 / 57.1.)
     const bool tiny = !count && is_tiny_threshold(threshold);
 #define CDSGD_LAUNCH_DECODE_CHAIN(SZ, TILES, LDS)                                                              \
     do {                                                                                                       \
@@ -488,7 +489,6 @@ int launch_decode_sum(const uint32_t *const *streams, int num_workers, float *ag
         else CDSGD_LAUNCH_DECODE_CHAIN(kUpTo16, 4, (tiles > kMidListTiles ? kLdsChain : 0u));
     } else if (num_workers <= kUpTo32) {
         if (count) CDSGD_LAUNCH_DECODE(kUpTo32, kCount, kTilesMany, 0u);
-        else if (tiny && !SPARSE) CDSGD_LAUNCH_DECODE(kAnyWorkers, kChainTiny, 1, 0u);
         else CDSGD_LAUNCH_DECODE_CHAIN(kUpTo32, kTilesMany, 0u);
     } else {
         if (count) CDSGD_LAUNCH_DECODE(kAnyWorkers, kCount, kTilesMany, (!SPARSE && tiles > kMidListTiles ? kLdsCount : 0u));

@@ -37,7 +37,7 @@ inline constexpr unsigned row_entries(int num_workers)
 
 // Decode forms.  kCount: thresholds that are powers of two, where every partial sum is exact and the sum is
 // count x t bit for bit.  kChain: one rounded add per worker and element, in worker order.  kChainTiny: the same
-// for thresholds below 2^-125, whose half is not exact (kAnyWorkers kernels only).
+// for thresholds below 2^-125, whose half may not be exact (the passes over a list have it for any number of workers only).
 constexpr int kCount = 0, kChain = 1, kChainTiny = 2;
 
 // One word of a buffer of `bytes` bytes at byte offset `off`; 0 past the end (the buffer's own range check), which
@@ -277,22 +277,23 @@ constexpr int kPlanes = SZ == kUpTo4 ? 1 : (SZ == kUpTo8 ? 2 : (SZ == kUpTo16 ? 
 // read from half a register.  The top two bits of a 16-bit float are its sign and the top bit of its exponent:
 // 01 is +2, 11 is -2 and 00 is 0, which is the two's-complement form of a code's value.  So a word's codes become
 // multipliers with one shift and one mask for two elements, and the products are exact with t / 2.
+// The half of a threshold below 2^-125 is not exact if its last bit is odd.  Such sums (kChainTiny) are formed 2^64 times
+// as large and scaled back at the end, which changes no bit: every term and partial sum is a multiple of 2^-149, so
+// those below 2^-125 are exact in either place and those above are normal numbers in both.
 // A bit more than 2 vector operations per worker and element, against 4.25 with a bit-field extract, a convert and a
 // multiply-add per element of every byte (25 M elements, N = 64, bf16 gradients: 0.226 ms before, 0.164 now).
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 
 // Two of a word's eight pairs: elements i and i + 8, i + 1 and i + 9, from the word's signed fields; shift = 14 - 2 i.
-template <bool TINY>
 __device__ __forceinline__ void chain_pairs(float (&acc)[4], unsigned fields, unsigned shift, float t)
 {
-    const float factor = TINY ? t : 0.5f * t;
-    const float unit = TINY ? 0.5f : 1.0f;
+    const float factor = 0.5f * t;
     const h2 a = __builtin_bit_cast(h2, (fields << shift) & 0xC000C000u);
     const h2 b = __builtin_bit_cast(h2, (fields << (shift - 2u)) & 0xC000C000u);
-    acc[0] = __builtin_fmaf(unit * (float)a.x, factor, acc[0]);
-    acc[1] = __builtin_fmaf(unit * (float)b.x, factor, acc[1]);
-    acc[2] = __builtin_fmaf(unit * (float)a.y, factor, acc[2]);
-    acc[3] = __builtin_fmaf(unit * (float)b.y, factor, acc[3]);
+    acc[0] = __builtin_fmaf((float)a.x, factor, acc[0]);
+    acc[1] = __builtin_fmaf((float)b.x, factor, acc[1]);
+    acc[2] = __builtin_fmaf((float)a.y, factor, acc[2]);
+    acc[3] = __builtin_fmaf((float)b.y, factor, acc[3]);
 }
 
 // A quad's four codes, from the byte of signed fields.
@@ -403,6 +404,8 @@ __device__ __forceinline__ f4 tile_get(f4 own_value, int num_workers, float t, u
         agg = agg + own_value;
     } else {
         const unsigned *rows = reinterpret_cast<const unsigned *>(lds);
+        const bool tiny = FORM == kChainTiny && t < 0x1p-125f;  // (a list's own thresholds may be of either kind)
+        if (tiny) t *= 0x1p64f;
         if constexpr (kByBytes<SZ>) {
             // every lane adds up its own quad, a byte of every row: one operation more per worker than by words, no exchange
             agg = f4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -420,7 +423,7 @@ __device__ __forceinline__ f4 tile_get(f4 own_value, int num_workers, float t, u
             const unsigned shift = 14u - 4u * (unsigned)wave;
             for (int j0 = 0; j0 < num_workers; j0 += 4) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) chain_pairs<FORM == kChainTiny>(acc, rows[kTileWords * (j0 + k) + lane], shift, t);
+                for (int k = 0; k < 4; ++k) chain_pairs(acc, rows[kTileWords * (j0 + k) + lane], shift, t);
             }
             // elements 2 v, 2 v + 1 and 2 v + 8, 2 v + 9 of word l -> quads
             typedef float f2 __attribute__((ext_vector_type(2)));
@@ -430,6 +433,7 @@ __device__ __forceinline__ f4 tile_get(f4 own_value, int num_workers, float t, u
             group_sync<WAVES>();
             agg = reinterpret_cast<const f4 *>(sums)[tid];
         }
+        if (tiny) agg = agg * 0x1p-64f;
     }
     return agg;
 }

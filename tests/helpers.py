@@ -5,6 +5,12 @@ REL_TOL = 1e-6      # aggregate and weights: |x - y| <= REL_TOL * max(|x|, |y|) 
 ABS_FLOOR = 1e-12
 
 
+# Thresholds whose half is not exact: below 2^-125, with an odd last bit.  The smallest float, another of a few units, two
+# denormals and the largest normal ones; their even neighbours' halves are exact.
+ODD_TINY = [float(np.uint32(b).view(np.float32)) for b in (1, 3, 0x0057AE15, 0x0077C787, 0x00FFFFFF)]
+assert all(np.float32(2.0) * (np.float32(0.5) * np.float32(t)) != np.float32(t) for t in ODD_TINY)
+
+
 def bits(a):
     a = np.ascontiguousarray(a)
     if a.dtype == np.float32:

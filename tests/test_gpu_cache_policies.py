@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import assert_bits_equal
+from helpers import ODD_TINY, assert_bits_equal
 
 pytestmark = pytest.mark.gpu
 
@@ -65,7 +65,7 @@ def test_quantize_pack_at_the_edges_of_its_lengths(B, oracle, n):
 
 
 # elements x workers / 4 bytes of streams: above 56 MB (100 MB above 16 workers) they are read non-temporally
-@pytest.mark.parametrize("t", [0.25, 0.3, 1.1e-38])
+@pytest.mark.parametrize("t", [0.25, 0.3, ODD_TINY[3]])
 @pytest.mark.parametrize("N,n", [(4, 57_000_013), (7, 33_000_001), (16, 7_100_005), (17, 6_600_007), (64, 1_800_001),
                                  (1, 4_500_000), (4, 4_500_001), (8, 3_199_999), (16, 3_200_001), (32, 1_750_000), (16, 14_100_005), (17, 23_600_007), (64, 6_300_001)])
 def test_decode_sum_of_many_streams_equals_its_parts(B, N, n, t):

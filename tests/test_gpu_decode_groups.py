@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import assert_bits_equal
+from helpers import ODD_TINY, assert_bits_equal
 
 pytestmark = pytest.mark.gpu
 
@@ -23,7 +23,7 @@ def B():
 
 
 @pytest.mark.parametrize("sparse", [False, True])
-@pytest.mark.parametrize("t", [0.25, 0.3, 1.1e-38])
+@pytest.mark.parametrize("t", [0.25, 0.3, *ODD_TINY])
 @pytest.mark.parametrize("N", [1, 3, 4, 5, 8, 9, 16, 17, 20, 31, 32, 33, 64])
 def test_decode_sum_at_group_and_batch_edges(B, oracle, N, t, sparse):
     rng = np.random.default_rng(41 * N + int(sparse))

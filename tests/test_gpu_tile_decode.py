@@ -5,12 +5,12 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import assert_bits_equal
+from helpers import ODD_TINY, assert_bits_equal
 
 pytestmark = pytest.mark.gpu
 
 SIZES = [1, 5, 16, 255, 257, 1023, 1024, 1025, 2048 + 15, 4096, 4096 + 1024 + 3, 2 * 4096 - 1, 3 * 4096 + 256]
-TINY = float(np.float32(1.37 * 2.0 ** -127))   # a denormal with an odd last bit: its half is not exact
+TINY = ODD_TINY[2]   # about 1.37 * 2^-127: its half is not exact
 
 
 @pytest.fixture(scope="module")
@@ -72,6 +72,37 @@ def test_compressed_pass_at_tile_and_batch_edges(B, oracle, N, t, sparse):
         agg = oracle.decode_sum([streams[j][i] for j in range(N)], n, t)
         assert_bits_equal(full[:n].cpu().numpy(), agg, "agg N=%d n=%d t=%g" % (N, n, t))
         assert bool((full[n:] == 9.0).all())
+    plan.destroy()
+
+
+@pytest.mark.parametrize("sparse", [False, True])
+@pytest.mark.parametrize("N", [1, 4, 9, 17, 64])
+def test_own_thresholds_of_every_kind_in_one_list(B, oracle, N, sparse):
+    """Thresholds whose half is not exact beside ordinary and very large ones: one kernel decodes them all."""
+    rng = np.random.default_rng(7 * N + int(sparse))
+    ts = [*ODD_TINY, 0.3, 0.5, 2.0 ** -125, float(np.nextafter(np.float32(2.0 ** -125), np.float32(1))), 1e30, 1e36]
+    n, f = 2 * 4096 + 1027, lambda a: torch.from_numpy(a).cuda()
+    layers, want, streams = [], [], []
+    for t in ts:
+        g, r = rng.normal(0, t, n).astype(np.float32), (rng.uniform(-1, 1, n) * t).astype(np.float32)
+        w = (rng.uniform(-1, 1, n) * 64 * t).astype(np.float32)
+        layers.append(dict(w_global=f(w), w_local=f(np.zeros(n, np.float32)), residual=f(r), grad=f(g), packed_self=B.new_packed(n)))
+        given = [_words(oracle, rng, n) for _ in range(N)]
+        r2, w2, l2 = r.copy(), w.copy(), np.zeros(n, np.float32)
+        given[0] = own = oracle.quantize_pack(g, r2, t)
+        oracle.update(w2, l2, g, oracle.decode_sum(given, n, t), 0.4, 0.7, N)
+        want.append((r2, own, w2, l2))
+        streams.append(given)
+    on_gpu = lambda w: f((oracle.sparse_encode(w, n, fill=0x7F7F7F7F)[0] if sparse else w).view(np.int32))
+    peers = [None] + [[on_gpu(s[j]) for s in streams] for j in range(1, N)]
+    plan = B.Plan(layers, peers if N > 1 else None, N, 0, peers_sparse=sparse)
+    plan.set_thresholds(ts)
+    plan.step(1, 4, 0.5, 0.4, 0.7)
+    torch.cuda.synchronize()
+    for i, t in enumerate(ts):
+        for key, ref in zip(("residual", "packed_self", "w_global", "w_local"), want[i]):
+            ref = ref.view(np.int32) if key == "packed_self" else ref
+            assert_bits_equal(layers[i][key].cpu().numpy(), ref, "%s N=%d t=%g" % (key, N, t))
     plan.destroy()
 
 
