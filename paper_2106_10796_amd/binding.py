@@ -5,10 +5,12 @@ PyTorch is used for device memory and the current stream, nothing else.  There
 is no fallback: a missing library is an error.
 
 The calls that a program makes per tensor or per step are marshalled in native code (csrc/py_calls.cpp), which
-declines (-1) whatever is not plainly good; ctypes and the checks below then convert it or say what is wrong.
+declines (-1) whatever is not plainly good; ctypes and the checks below then convert it or say what is wrong.  Where
+that module is not there, or was built for another library, torch or Python, ctypes serves every call.
 """
 import ctypes
 import os
+import sysconfig
 
 import torch
 
@@ -51,8 +53,19 @@ class cdsgd_cost(ctypes.Structure):
         return {n: getattr(self, n) for n, _ in self._fields_}
 
 
+class _Declines:
+    """In the place of the native calls: every call declines."""
+
+    def __getattr__(self, name):
+        return self._decline
+
+    @staticmethod
+    def _decline(*_):
+        return -1
+
+
 _lib = None
-_calls = None
+_calls = _Declines()
 
 # in the order in which _calls.bind takes them
 _CALLED = ("cdsgd_quantize_pack", "cdsgd_decode_sum", "cdsgd_decode_sum_sparse", "cdsgd_update", "cdsgd_sparse_encode",
@@ -65,6 +78,18 @@ def _native():
     if _lib is None:
         lib()
     return _calls
+
+
+def _load_calls(L):
+    try:
+        from . import _calls as native
+    except ImportError:
+        return _Declines()
+    here = (L.cdsgd_build_id().decode(), str(torch.__version__), sysconfig.get_config_var("SOABI") or "")
+    if getattr(native, "made_for", None) != here:
+        return _Declines()
+    native.bind(*[ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _CALLED])
+    return native
 
 
 def lib():
@@ -144,12 +169,8 @@ def lib():
                                            ctypes.POINTER(cdsgd_cost)]
         L.cdsgd_cost_period_mean.restype = i
         L.cdsgd_cost_period_mean.argtypes = [ctypes.POINTER(cdsgd_cost_params), ctypes.POINTER(cdsgd_cost)]
-        try:
-            from . import _calls as native
-        except ImportError as e:
-            raise RuntimeError("the binding's native calls are not built (run: python -m paper_2106_10796_amd.build): %s" % e)
-        native.bind(*[ctypes.cast(getattr(L, name), vp).value for name in _CALLED])
-        _lib, _calls = L, native
+        _calls = _load_calls(L)
+        _lib = L                       # last: another thread that sees it finds the calls bound
     return _lib
 
 

@@ -1,6 +1,5 @@
 """Build libcdsgd.so (HIP kernels + C ABI) for gfx950 with hipcc, and the binding's native calls, in-tree."""
 import hashlib
-import importlib.metadata
 import importlib.util
 import os
 import re
@@ -41,12 +40,13 @@ def hipcc_path() -> str:
 
 
 def source_id(extra_flags=()) -> str:
-    """Identity of what a build is made from: the sources, the headers and the flags (16 hex digits).
+    """Identity of what the library is made from: its sources, the headers and the flags (16 hex digits).
     It is compiled into the library (cdsgd_build_id) so that a library can be matched to the tree."""
     h = hashlib.sha256()
     headers = sorted(os.path.join(INCLUDE, f) for f in os.listdir(INCLUDE) if f.endswith(".h"))
     csrc = os.path.dirname(SRC)                       # cdsgd.hip includes the kernels' .hpp files beside it
     sources = sorted(os.path.join(csrc, f) for f in os.listdir(csrc) if f.endswith((".hip", ".hpp", ".cpp")))
+    sources = [p for p in sources if os.path.basename(p) != os.path.basename(SRC_CALLS)]
     assert SRC in sources and all(p in sources for p in SRC_HOST)
     for path in [*sources, *headers]:
         h.update(os.path.basename(path).encode() + b"\0")
@@ -57,9 +57,32 @@ def source_id(extra_flags=()) -> str:
     return h.hexdigest()[:16]
 
 
-def calls_id() -> str:
-    """The same for the native calls, which also depend on the Python and the torch they are built against."""
-    parts = [source_id(), " ".join(CALLS_FLAGS), sysconfig.get_config_var("SOABI") or "", importlib.metadata.version("torch")]
+def _torch_dir():
+    spec = importlib.util.find_spec("torch")
+    if spec is None or not spec.submodule_search_locations:
+        raise RuntimeError("torch is not installed")
+    return spec.submodule_search_locations[0]
+
+
+def _torch_version() -> str:
+    """torch.__version__, without the import."""
+    try:
+        with open(os.path.join(_torch_dir(), "version.py")) as fh:
+            m = re.search(r"^__version__ = ['\"](.*)['\"]", fh.read(), re.M)
+    except (OSError, RuntimeError):
+        return ""
+    return m.group(1) if m else ""
+
+
+def calls_for(library: str) -> tuple:
+    """What the native calls are built for: a library (its identity), a torch and a Python."""
+    return library, _torch_version(), sysconfig.get_config_var("SOABI") or ""
+
+
+def calls_id(library=None) -> str:
+    """Identity of the native calls, which also depend on what they are built for."""
+    with open(SRC_CALLS, "rb") as fh:
+        parts = [fh.read().decode(), " ".join(CALLS_FLAGS), *calls_for(library or source_id())]
     return hashlib.sha256("\0".join(parts).encode()).hexdigest()[:16]
 
 
@@ -73,52 +96,61 @@ def built_id(path=LIB):
     return m.group(1).decode() if m else None
 
 
-def build(extra_flags=(), out=LIB, verbose=False) -> str:
-    tmp = out + ".tmp%d" % os.getpid()
-    cmd = [hipcc_path(), *HIPCC_FLAGS, *extra_flags, '-DCDSGD_BUILD_ID_HEX="%s"' % source_id(extra_flags),
-           "-I", INCLUDE, SRC, *SRC_HOST, "-o", tmp]
+def _compile(cmd, out, tmp, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("%s failed:\n%s" % (os.path.basename(cmd[0]), r.stdout))
     # the host pass does not know the packed-fp32 target feature: harmless
     log = "\n".join(l for l in r.stdout.splitlines() if "packed-fp32-ops" not in l and l.strip())
-    if r.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + r.stdout)
     if verbose and log:
         print(log, flush=True)
     os.replace(tmp, out)
     return out
 
 
-def build_calls(verbose=False) -> str:
-    torch_dir = importlib.util.find_spec("torch").submodule_search_locations[0]
+def build(extra_flags=(), out=LIB, verbose=False) -> str:
+    """The library, and beside it (the default place) the native calls where they can be built."""
+    library = source_id(extra_flags)
+    tmp = out + ".tmp%d" % os.getpid()
+    _compile([hipcc_path(), *HIPCC_FLAGS, *extra_flags, '-DCDSGD_BUILD_ID_HEX="%s"' % library,
+              "-I", INCLUDE, SRC, *SRC_HOST, "-o", tmp], out, tmp, verbose)
+    if out == LIB:
+        _build_calls_if_possible(library, verbose)
+    return out
+
+
+def build_calls(verbose=False, library=None) -> str:
+    torch_dir = _torch_dir()
     tmp = CALLS + ".tmp%d" % os.getpid()
-    cmd = [os.environ.get("CXX", "g++"), *CALLS_FLAGS, '-DCDSGD_BUILD_ID_HEX="%s"' % calls_id(), "-I", INCLUDE,
-           "-isystem", os.path.join(torch_dir, "include"), "-isystem", sysconfig.get_paths()["include"], SRC_CALLS,
-           "-L", os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if r.returncode != 0:
-        raise RuntimeError("the compiler failed:\n" + r.stdout)
-    if verbose and r.stdout.strip():
-        print(r.stdout, flush=True)
-    os.replace(tmp, CALLS)
-    return CALLS
+    made_for = ['-DCDSGD_CALLS_%s="%s"' % kv for kv in zip(("LIBRARY", "TORCH", "SOABI"), calls_for(library or source_id()))]
+    return _compile([os.environ.get("CXX", "g++"), *CALLS_FLAGS, '-DCDSGD_BUILD_ID_HEX="%s"' % calls_id(library), *made_for,
+                     "-I", INCLUDE, "-isystem", os.path.join(torch_dir, "include"),
+                     "-isystem", sysconfig.get_paths()["include"], SRC_CALLS, "-L", os.path.join(torch_dir, "lib"),
+                     "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", tmp], CALLS, tmp, verbose)
+
+
+def _build_calls_if_possible(library=None, verbose=False):
+    """The binding does without the native calls (by ctypes, a microsecond or more slower a call), so a machine
+    without a C++ compiler or without Python's or torch's headers still has a library it can use."""
+    try:
+        build_calls(verbose, library)
+    except (OSError, RuntimeError) as e:
+        print("the binding's native calls were not built, it will use ctypes: %s" % str(e).strip()[:400], file=sys.stderr, flush=True)
 
 
 def ensure_built() -> str:
-    """Build (the library, and the binding's native calls) if none is there or if the one that is there was made from other sources,
-    headers or flags than the tree now holds (tests, the smoke check and the benchmark call this;
-    the binding itself never builds and never falls back).  The comparison is by content, not by
+    """Build (the library, and the binding's native calls) if none is there or if the one that is there was made from other
+    sources, headers or flags than the tree now holds (tests, the smoke check and the benchmark call this;
+    the binding itself never builds).  The comparison is by content, not by
     file time, so a tree that was copied elsewhere together with its library is not rebuilt."""
+    if not os.path.exists(LIB) or built_id(LIB) != source_id():
+        return build()
     if built_id(CALLS) != calls_id():
-        build_calls()
-    if os.path.exists(LIB) and built_id(LIB) == source_id():
-        return LIB
-    return build()
+        _build_calls_if_possible()
+    return LIB
 
 
 if __name__ == "__main__":
     print(build(extra_flags=sys.argv[1:], verbose=True))
-    print(build_calls(verbose=True))

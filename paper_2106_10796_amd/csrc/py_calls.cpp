@@ -270,8 +270,25 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nul
 #ifndef CDSGD_BUILD_ID_HEX
 #define CDSGD_BUILD_ID_HEX "0000000000000000"
 #endif
+#ifndef CDSGD_CALLS_LIBRARY
+#define CDSGD_CALLS_LIBRARY ""
+#define CDSGD_CALLS_TORCH ""
+#define CDSGD_CALLS_SOABI ""
+#endif
 
 // The identity of what the module was built from; the marker makes it findable in the file.
 extern "C" __attribute__((used, visibility("default"))) const char cdsgd_calls_id[] = "CDSGD_BUILD_ID=" CDSGD_BUILD_ID_HEX;
 
-PyMODINIT_FUNC PyInit__calls(void) { return PyModule_Create(&module); }
+// made_for: the library (its identity), the torch and the Python that the module may be used with.
+PyMODINIT_FUNC PyInit__calls(void)
+{
+    PyObject *m = PyModule_Create(&module);
+    if (!m) return nullptr;
+    PyObject *made_for = Py_BuildValue("(sss)", CDSGD_CALLS_LIBRARY, CDSGD_CALLS_TORCH, CDSGD_CALLS_SOABI);
+    if (!made_for || PyModule_AddObject(m, "made_for", made_for) != 0) {
+        Py_XDECREF(made_for);
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}
