@@ -921,34 +921,47 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
         else if (plan->grad_type == kGradF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF16, SPARSE, HOW); \
         else CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF32, SPARSE, HOW);                                \
     } while (0)
-#define CDSGD_LAUNCH_COMPRESSED_F(FORM)                                                                        \
+// (the count form of 9 to 16 workers asks for the words last with 32-bit gradients only: compressed_launch)
+#define CDSGD_LAUNCH_COMPRESSED_32BIT(SZ, WAVES, FORM, SPARSE, HOW)                                            \
     do {                                                                                                       \
-        if (plan->peers_sparse && N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, true, 0);              \
+        if (plan->grad_type != kGradF32) return CDSGD_ERR_DEVICE;                                              \
+        CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF32, SPARSE, HOW);                                     \
+    } while (0)
+// Every shape has a kernel of its own; one that has none is an error, for another kernel may read the tables otherwise.
+#define CDSGD_LAUNCH_COMPRESSED_F(FORM, LAUNCH_LATE)                                                           \
+    do {                                                                                                       \
+        if (plan->peers_sparse && shape.how != 0) return CDSGD_ERR_DEVICE;                                     \
+        else if (plan->peers_sparse && N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, true, 0);         \
         else if (plan->peers_sparse && N <= kUpTo16) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, true, 0);       \
         else if (plan->peers_sparse && sparse32) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, true, 0);           \
         else if (plan->peers_sparse) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, true, 0);                   \
         else if (shape.waves == 1u && shape.how == kArena) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 1, FORM, false, kArena); \
-        else if (shape.waves == 1u) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 1, FORM, false, 0);                        \
+        else if (shape.waves == 1u && shape.how == 0) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 1, FORM, false, 0);      \
         else if (N <= kUpTo8 && shape.how == kArena) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, false, kArena);  \
-        else if (N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, false, 0);                              \
+        else if (N <= kUpTo8 && shape.how == 0) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, false, 0);            \
+        else if (N <= kUpTo8) return CDSGD_ERR_DEVICE;                                                         \
         else if (shape.how == (kUpTo32Rows | kWrittenOut | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, kWrittenOut | kArena); \
         else if (shape.how == (kUpTo32Rows | kWrittenOut)) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, kWrittenOut); \
         else if (shape.how == (kUpTo32Rows | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, kArena); \
         else if (shape.how == kUpTo32Rows) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, 0);                \
         else if (N > kUpTo16 && shape.how == kStreamWords) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, false, kStreamWords); \
-        else if (N > kUpTo16) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, false, 0);                         \
-        else if (shape.how == (kWrittenOut | kLate | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kWrittenOut | kLate | kArena); \
-        else if (shape.how == (kWrittenOut | kLate)) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kWrittenOut | kLate); \
+        else if (N > kUpTo16 && shape.how == 0) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, false, 0);       \
+        else if (N > kUpTo16) return CDSGD_ERR_DEVICE;                                                         \
+        else if (shape.how == (kWrittenOut | kLate | kArena)) LAUNCH_LATE(kUpTo16, 4, FORM, false, kWrittenOut | kLate | kArena); \
+        else if (shape.how == (kWrittenOut | kLate)) LAUNCH_LATE(kUpTo16, 4, FORM, false, kWrittenOut | kLate); \
         else if (shape.how == (kWrittenOut | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kWrittenOut | kArena); \
         else if (shape.how == kWrittenOut) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kWrittenOut);      \
         else if (shape.how == kArena) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, kArena);                \
-        else CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, 0);                                              \
+        else if (shape.how == 0) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, false, 0);                          \
+        else return CDSGD_ERR_DEVICE;                                                                          \
     } while (0)
+    if (form == kChainTiny && shape.how != 0) return CDSGD_ERR_DEVICE;
     if (form == kCount && shape.how == kLate) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, kCount, false, kLate);  // walking groups
-    else if (form == kCount) CDSGD_LAUNCH_COMPRESSED_F(kCount);
-    else if (form == kChain) CDSGD_LAUNCH_COMPRESSED_F(kChain);
+    else if (form == kCount) CDSGD_LAUNCH_COMPRESSED_F(kCount, CDSGD_LAUNCH_COMPRESSED_32BIT);
+    else if (form == kChain) CDSGD_LAUNCH_COMPRESSED_F(kChain, CDSGD_LAUNCH_COMPRESSED);
     else if (plan->peers_sparse) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, kChainTiny, true, 0);
     else CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, kChainTiny, false, 0);
+#undef CDSGD_LAUNCH_COMPRESSED_32BIT
 #undef CDSGD_LAUNCH_COMPRESSED
 #undef CDSGD_LAUNCH_COMPRESSED_F
 #undef CDSGD_LAUNCH_COMPRESSED_S
@@ -1337,20 +1350,26 @@ int launch_from_arguments(const cdsgd_tensor *tensors, int num_tensors, const ui
         else if (grad_dtype == CDSGD_GRAD_F16) CDSGD_LAUNCH_ARGUMENTS_S(SZ, WAVES, FORM, kGradF16, HOW);       \
         else CDSGD_LAUNCH_ARGUMENTS_S(SZ, WAVES, FORM, kGradF32, HOW);                                         \
     } while (0)
-#define CDSGD_LAUNCH_ARGUMENTS_F(FORM)                                                                         \
+#define CDSGD_LAUNCH_ARGUMENTS_32BIT(SZ, WAVES, FORM, HOW)                                                     \
+    do {                                                                                                       \
+        if (grad_dtype != CDSGD_GRAD_F32) return CDSGD_ERR_DEVICE;                                             \
+        CDSGD_LAUNCH_ARGUMENTS_S(SZ, WAVES, FORM, kGradF32, HOW);                                              \
+    } while (0)
+#define CDSGD_LAUNCH_ARGUMENTS_F(FORM, LAUNCH_LATE)                                                            \
     do {                                                                                                       \
         if (shape.waves == 1u) CDSGD_LAUNCH_ARGUMENTS(kUpTo8, 1, FORM, kArena);                                \
         else if (num_workers <= kUpTo8) CDSGD_LAUNCH_ARGUMENTS(kUpTo8, 4, FORM, kArena);                       \
         else if (num_workers > kUpTo32) CDSGD_LAUNCH_ARGUMENTS(kAnyWorkers, 4, FORM, kArena);                  \
         else if (num_workers > kUpTo16 && (shape.how & kWrittenOut)) CDSGD_LAUNCH_ARGUMENTS(kUpTo32, 4, FORM, kWrittenOut | kArena); \
         else if (num_workers > kUpTo16) CDSGD_LAUNCH_ARGUMENTS(kUpTo32, 4, FORM, kArena);                      \
-        else if (shape.how & kLate) CDSGD_LAUNCH_ARGUMENTS(kUpTo16, 4, FORM, kWrittenOut | kLate | kArena);    \
+        else if (shape.how & kLate) LAUNCH_LATE(kUpTo16, 4, FORM, kWrittenOut | kLate | kArena);               \
         else if (shape.how & kWrittenOut) CDSGD_LAUNCH_ARGUMENTS(kUpTo16, 4, FORM, kWrittenOut | kArena);      \
         else CDSGD_LAUNCH_ARGUMENTS(kUpTo16, 4, FORM, kArena);                                                 \
     } while (0)
-    if (form == kCount) CDSGD_LAUNCH_ARGUMENTS_F(kCount);
-    else CDSGD_LAUNCH_ARGUMENTS_F(kChain);
+    if (form == kCount) CDSGD_LAUNCH_ARGUMENTS_F(kCount, CDSGD_LAUNCH_ARGUMENTS_32BIT);
+    else CDSGD_LAUNCH_ARGUMENTS_F(kChain, CDSGD_LAUNCH_ARGUMENTS);
 #undef CDSGD_LAUNCH_ARGUMENTS_F
+#undef CDSGD_LAUNCH_ARGUMENTS_32BIT
 #undef CDSGD_LAUNCH_ARGUMENTS
 #undef CDSGD_LAUNCH_ARGUMENTS_S
     return launch_status();
