@@ -799,6 +799,10 @@ constexpr unsigned kWalkingGroups = 768;
 //                     .99 / .98;  18 M 1.00 / - / .98 / 1.00 / .99;  25 M - / .99 / .97 / .97 / .98;  40 M .98 / - / .98 /
 //                     .99 / .98;  VGG-16 - / .99 / .99 / 1.00 / .98;  90 M 1.04 / - / .99 / 1.01 / .99;  260 M .99 / - /
 //                     .99 / 1.00 / .98   (long 32-bit chains gain nothing and 1 GiB buckets at t = 0.05 lose 1 %)
+//   (Where the buffers lie moves long lists by more than that.  Count form, 32-bit, lowest - highest, mean over 8 to 20 lengths
+//   and places:  30 to 60 M elements N = 9 to 12 .96 - .99, .98;  13 to 16 .95 - 1.00, .98;  64 to 150 M N = 9 .95 - 1.05, .99;
+//   10 .96 - 1.06, .99;  11 .98 - 1.04, .99;  12 .94 - 1.09, 1.00;  13 .97 - 1.03, .99;  14 to 16 .97 - 1.00, .99.  Non-temporal stores
+//   for 9 to 12 workers above 60 M take the worst places back and cost 1 % in the mean.)
 //   (short lists, whose results the next pass finds in a cache, are slower so: N = 9 / 16, t = 0.3, bf16 0.3 M 1.16 / 1.16,
 //   0.45 M 1.24 / 1.23, 0.7 M 1.14 / 1.07, 1 M .98 / .98, 1.4 M 1.00 / .99;  N = 17 / 32 0.45 M 1.15 / 1.07, 1 M 1.04 / 1.07,
 //   1.4 M 1.03 / 1.01;  32-bit, t = 0.3, N = 16 / 32 0.45 M 1.10 / 1.00, 1 M .99 / 1.05, 1.4 M 1.02 / 1.02)
@@ -859,7 +863,7 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
         if (tiles <= 6u * 1024u) return {4u, 0u, out | arena, 0u};
         if (!mid_list) return {4u, 24576u, kWrittenOut | arena, 0u};
         if (half) return {4u, 40960u, kWrittenOut | (long_list ? 0 : arena), 0u};
-        if (long_list) return {4u, 49152u, kWrittenOut | kLate, 0u};
+        if (long_list) return {4u, 49152u, num_workers <= 12 && tiles > 60u * 1024u ? kLate : kWrittenOut | kLate, 0u};
         return {4u, 32768u, kWrittenOut | kLate | arena, 0u};
     }
     if (num_workers <= kUpTo16) {
