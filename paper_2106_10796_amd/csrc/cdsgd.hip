@@ -863,7 +863,7 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
         if (tiles <= 6u * 1024u) return {4u, 0u, out | arena, 0u};
         if (!mid_list) return {4u, 24576u, kWrittenOut | arena, 0u};
         if (half) return {4u, 40960u, kWrittenOut | (long_list ? 0 : arena), 0u};
-        if (long_list) return {4u, 49152u, num_workers <= 12 && tiles > 60u * 1024u ? kLate : kWrittenOut | kLate, 0u};
+        if (long_list) return {4u, 49152u, kWrittenOut | kLate, 0u};
         return {4u, 32768u, kWrittenOut | kLate | arena, 0u};
     }
     if (num_workers <= kUpTo16) {
