@@ -424,6 +424,19 @@ inline bool drains_results(size_t n, int num_workers)
     return n > 1250000u && n <= most;
 }
 
+// Whether weights that the global rule leaves in the memory-side cache push out streams that a later decode-and-sum would
+// find there.  Decode-and-sum and update, time over that of non-temporal stores in both, 3 / 4 sets of buffers in turn, weights staying,
+// then not staying:
+//   N = 33   5 M .92 / .96, .94 / .94;  6 M .95 / 1.01, .95 / .94;  7 M .99 / 1.01, .95 / .96
+//   N = 48   4 M .94 / 1.04, .96 / .98;  5 M 1.00 / 1.03, .96 / .98;  6 M 1.01 / 1.05, .97 / .94;  7 M 1.04 / 1.05, .97 / .94
+//   N = 64   3 M .96 / .99, .97 / .97;  4 M 1.00 / 1.04, .98 / .98;  5 M 1.04 / 1.01, .99 / .90;  6 M 1.08 / 1.01, .96 / .94
+//   N = 64, sparse, one code in 16   4 M .97 / 1.13, .96 / .99;  6 M 1.12 / 1.02, .99 / .95
+// (With two sets, which fit, staying is 2 % faster throughout.)
+inline bool crowds_streams(size_t n, int num_workers)
+{
+    return (unsigned long long)num_workers * packed_bytes_of(n) > 48000000ull;
+}
+
 // a4 for one tensor on checked arguments.
 //
 // Tiles of a group: 4 up to 16 workers; above that the loads of a wave are enough with one tile of packed streams
@@ -609,7 +622,7 @@ int cdsgd_update(float *w_global, float *w_local, const float *grad_local, const
         else CDSGD_LAUNCH_UPDATE(true, false, kLargeTensor, kLdsFor20Waves);
     } else {
         if (drains_results(n, num_workers)) CDSGD_LAUNCH_UPDATE(false, true, kDrainTensor, 0);
-        else if (small) CDSGD_LAUNCH_UPDATE(false, true, kSmallTensor, 0);
+        else if (small && !crowds_streams(n, num_workers)) CDSGD_LAUNCH_UPDATE(false, true, kSmallTensor, 0);
         else CDSGD_LAUNCH_UPDATE(false, true, kMidTensor, 0);
     }
 #undef CDSGD_LAUNCH_UPDATE

@@ -26,20 +26,22 @@ def _floats(rng, n, scale):
     return rng.standard_normal(n, dtype=np.float32) * np.float32(scale)
 
 
-# (five workers' aggregates from 1.25 M to 3.2 M elements are stored non-temporally)
-@pytest.mark.parametrize("n", [1_250_000, 1_250_003, 3_200_000, 3_200_001, SMALL, SMALL + 3, KEEP, KEEP + 1])
+# (five workers' aggregates from 1.25 M to 3.2 M elements are stored non-temporally; weights do not stay in the
+# memory-side cache above 48 MB of streams, 64 workers and 3 M elements)
+@pytest.mark.parametrize("n,N", [(1_250_000, 5), (1_250_003, 5), (3_200_000, 5), (3_200_001, 5), (SMALL, 5), (SMALL + 3, 5),
+                                 (KEEP, 5), (KEEP + 1, 5), (3_000_000, 64), (3_000_003, 64)])
 @pytest.mark.parametrize("mode", ["local", "global", "both"])
-def test_update_at_the_edges_of_its_lengths(B, oracle, n, mode):
+def test_update_at_the_edges_of_its_lengths(B, oracle, n, N, mode):
     rng = np.random.default_rng(n + len(mode))
     w, g, a = (_floats(rng, n, s) for s in (1.0, 0.1, 3.0))
     host = {"w": w, "l": np.full(n, 7.0, np.float32), "g": g if mode != "global" else None, "a": a if mode != "local" else None}
     want_w, want_l = w.copy(), (host["l"].copy() if mode != "global" else None)
-    oracle.update(want_w, want_l, host["g"], host["a"], 0.05, 0.1, 5)
+    oracle.update(want_w, want_l, host["g"], host["a"], 0.05, 0.1, N)
     pad = {k: torch.full((n + 8,), 9.0, device="cuda") for k in ("w", "l")}
     for k in pad:
         pad[k][:n] = torch.from_numpy(host[k]).cuda()
     dev = {k: None if host[k] is None else torch.from_numpy(host[k]).cuda() for k in ("g", "a")}
-    B.cdsgd_update(pad["w"][:n], pad["l"][:n] if mode != "global" else None, dev["g"], dev["a"], 0.05, 0.1, 5)
+    B.cdsgd_update(pad["w"][:n], pad["l"][:n] if mode != "global" else None, dev["g"], dev["a"], 0.05, 0.1, N)
     torch.cuda.synchronize()
     assert_bits_equal(pad["w"][:n].cpu().numpy(), want_w, "w_global")
     if mode != "global":
