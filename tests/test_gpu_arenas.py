@@ -85,10 +85,10 @@ def test_ragged_list_in_arenas(B, N, dtype, t):
     check("static")
 
 
-# lists of more than 6 M, 16 M and 28 M elements have launch shapes of their own
+# lists of more than 6, 16 and 28 times 2^20 elements have launch shapes of their own, and the longest no arenas
 @pytest.mark.parametrize("N,t,dtype", [(4, 0.3, torch.bfloat16), (8, 0.5, torch.float32), (16, 0.5, torch.float32),
                                        (16, 0.3, torch.float16), (12, 0.5, torch.bfloat16)])
-@pytest.mark.parametrize("n", [6_400_000, 17_000_000, 28_700_000])
+@pytest.mark.parametrize("n", [6_400_000, 17_000_000, 29_500_000])
 def test_long_lists_in_arenas(B, N, t, dtype, n):
     sizes = [n // 3 + 5, 77, n // 3 + 4097, 4096, n // 3 - 9]
     a, b, mine, peers, check = _pair(B, sizes, N, N - 1, t, dtype, extra=64)
@@ -112,7 +112,7 @@ def test_static_lists_at_the_edge_of_one_launch(B, T, N, t, dtype):
     check("static")
 
 
-@pytest.mark.parametrize("n", [16 * 1024 * 1024 - 5000, 16 * 1024 * 1024 + 5])
+@pytest.mark.parametrize("n", [16 * 1024 * 1024 - 5000, 16 * 1024 * 1024 + 8192])
 @pytest.mark.parametrize("N,t", [(20, 0.5), (24, 0.3), (36, 0.5), (36, 0.3)])
 def test_static_list_of_many_workers(B, n, N, t):
     a, b, mine, peers, check = _pair(B, [n - 70_001, 4097, 60_000], N, 3, t, torch.bfloat16)
@@ -124,8 +124,8 @@ def test_static_list_of_many_workers(B, n, N, t):
 # sparse peers of 17 to 32 workers have kernels of their own, but for long lists of 32-bit gradients
 @pytest.mark.parametrize("t", [0.5, 0.3])
 @pytest.mark.parametrize("N,sizes,dtype", [(17, RAGGED, torch.float32), (24, RAGGED, torch.float16), (32, RAGGED, torch.bfloat16),
-                                           (20, [29_000_000, 77, 4097], torch.float32),
-                                           (20, [29_000_000, 77, 4097], torch.bfloat16)])
+                                           (20, [29_500_000, 77, 4097], torch.float32),
+                                           (20, [29_500_000, 77, 4097], torch.bfloat16)])
 def test_sparse_peers_equal_packed_ones(B, N, sizes, dtype, t):
     a, b, mine, peers, check = _pair(B, sizes, N, 5, t, dtype)
 

@@ -1,6 +1,7 @@
 """GPU parity of the single-tensor calls on either side of the sizes where the cache policy of their loads and stores
 changes, and of the lanes behind a ragged end there: bit for bit against the oracle (update, quantise-and-pack) and,
-for decode-and-sum, against the call on parts that are short enough for the other policy."""
+for decode-and-sum, against the call on parts that are short enough for the other policy, and against the oracle at the
+ends.  Passes over long lists go the same way, against the pass on their parts."""
 import numpy as np
 import pytest
 import torch
@@ -66,23 +67,27 @@ def test_quantize_pack_at_the_edges_of_its_lengths(B, oracle, n):
     assert bool((pad[n:] == 9.0).all()) and bool((packed[B.packed_words(n):] == 5).all()), "written past the end"
 
 
-# elements x workers / 4 bytes of streams: above 56 MB (100 MB above 16 workers) they are read non-temporally
+# elements x workers / 4 bytes of streams: above 56 MB (100 MB above 16 workers) they are read non-temporally; aggregates from
+# 1.25 M elements up to 4.5 M (4 workers), 3.2 M (16) and 1.75 M (32) are stored so, which the parts are too short for
 @pytest.mark.parametrize("t", [0.25, 0.3, ODD_TINY[3]])
 @pytest.mark.parametrize("N,n", [(4, 57_000_013), (7, 33_000_001), (16, 7_100_005), (17, 6_600_007), (64, 1_800_001),
                                  (1, 4_500_000), (4, 4_500_001), (8, 3_199_999), (16, 3_200_001), (32, 1_750_000), (16, 14_100_005), (17, 23_600_007), (64, 6_300_001)])
-def test_decode_sum_of_many_streams_equals_its_parts(B, N, n, t):
+def test_decode_sum_of_many_streams_equals_its_parts(B, oracle, N, n, t):
     gen = torch.Generator(device="cuda").manual_seed(N)
     streams = [torch.randint(-2 ** 31, 2 ** 31, (B.packed_words(n),), dtype=torch.int32, device="cuda", generator=gen)
                for _ in range(N)]
     whole, part = torch.full((n + 8,), 9.0, device="cuda"), torch.zeros(n, device="cuda")
     B.cdsgd_decode_sum(streams, whole[:n], t)
-    step = 4096 * 401
+    step = 4096 * 303
     for a in range(0, n, step):
         b = min(n, a + step)
         B.cdsgd_decode_sum([s[a // 16: a // 16 + B.packed_words(b - a)] for s in streams], part[a:b], t)
     torch.cuda.synchronize()
     assert torch.equal(whole[:n].view(torch.int32), part.view(torch.int32))
     assert bool((whole[n:] == 9.0).all()), "written past the end"
+    for a, b in ((0, 20_000), (n // 16 * 16 - 16_000, n)):
+        words = [s[a // 16: a // 16 + B.packed_words(b - a)].cpu().numpy().view(np.uint32) for s in streams]
+        assert_bits_equal(whole[a:b].cpu().numpy(), oracle.decode_sum(words, b - a, t), "[%d, %d)" % (a, b))
 
 
 def _list_state(B, n, N, grad, gen):
@@ -115,25 +120,27 @@ def _whole_equals_parts(B, n, N, grad, step, call):
         assert torch.equal(whole[k].view(torch.int32), part[k].view(torch.int32)), k
 
 
-# Above 32 workers and 112 MB of streams the workers' words are read non-temporally; 9 to 32 workers' results are written
-# through, but for long lists of 32-bit chains and of more than 20 workers.  Parts of 1.6 M elements go the other way (or end in another place).
+# Above 32 workers and 112 MB of streams the workers' words are read non-temporally, and parts of 1.6 M elements are not; results
+# of 9 to 16 workers are written through above 1 M elements and of 17 to 32 above 2 M, but for 32-bit chains of 9 to 16 above 48 M
+# and 32-bit lists of more than 20 above 28 M.
 @pytest.mark.parametrize("t", [0.25, 0.3])
 @pytest.mark.parametrize("N,n,grad", [(33, 13_600_003, torch.float32), (64, 7_001_003, torch.bfloat16),
                                       (9, 17_000_013, torch.float32), (16, 51_000_001, torch.float32),
-                                      (16, 51_000_001, torch.float16), (20, 29_000_003, torch.float32),
-                                      (21, 29_000_003, torch.float32), (32, 29_000_003, torch.bfloat16)])
+                                      (16, 51_000_001, torch.float16), (20, 29_400_003, torch.float32),
+                                      (21, 29_400_003, torch.float32), (32, 29_400_003, torch.bfloat16)])
 def test_compressed_pass_equals_its_parts(B, N, n, grad, t):
     _whole_equals_parts(B, n, N, grad, 4096 * 401, lambda p, a, b: p.step(1, 4, t, 0.05, 0.1))
 
 
-# a correction pass writes its results through below 2 M elements, up to 14 M with 4 workers and above 72 M with more
-@pytest.mark.parametrize("N,n,grad", [(4, (14 << 20) + 4097, torch.float32), (4, (14 << 20) - 3, torch.float16),
-                                      (8, (2 << 20) + 5, torch.bfloat16), (5, (72 << 20) + 7, torch.float32)])
-def test_correction_pass_equals_its_parts(B, N, n, grad):
+# a correction pass of more than 4 workers writes its results through from 0.25 M to 2 M elements and above 72 M; one of fewer
+# up to 14 M.  Parts of 1.6 M elements are written through, so the longest list is taken in parts of 3.2 M.
+@pytest.mark.parametrize("N,n,grad,chunks", [(4, (14 << 20) + 4097, torch.float32, 397), (8, (2 << 20) + 5, torch.bfloat16, 397),
+                                             (16, (2 << 20) + 5, torch.float32, 397), (5, (72 << 20) + 7, torch.float32, 794)])
+def test_correction_pass_equals_its_parts(B, N, n, grad, chunks):
     gen = torch.Generator(device="cuda").manual_seed(n)
     full = [None] + [torch.randn(n, device="cuda", generator=gen).to(grad) for _ in range(N - 1)]
 
     def call(plan, a, b):
         plan.bind_full_grads([None if g is None else [g[a:b]] for g in full])
         plan.step(0, 4, 0.5, 0.05, 0.1)
-    _whole_equals_parts(B, n, N, grad, 4096 * 397, call)
+    _whole_equals_parts(B, n, N, grad, 4096 * chunks, call)

@@ -1,0 +1,129 @@
+"""GPU parity of passes over lists just below and just above the lengths at which their launch shape or the cache policy
+of their stores changes, where that happens on short lists: every element against the oracle bit for bit, with a ragged
+tensor in the list, buffers in arenas and not, and sentinels between and behind the tensors."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import assert_bits_equal
+
+pytestmark = pytest.mark.gpu
+
+TILE, CHUNK, GAP = 1024, 4096, 64
+LR_LOCAL, LR_GLOBAL = 0.4, 0.7
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2106_10796_amd import binding, build
+    build.ensure_built()
+    binding.lib()
+    assert torch.cuda.is_available()
+    return binding
+
+
+def _sizes(tiles, above):
+    """Two ragged tensors of `tiles` tiles, or of one chunk more."""
+    return [tiles * TILE - CHUNK - 3, CHUNK + 1 if above else CHUNK - 1]
+
+
+class _Buffer:
+    """A buffer of every tensor of a list in one allocation, `skew` elements farther apart than in other roles."""
+
+    def __init__(self, values, skew, dtype=torch.float32, per_word=1):
+        at, total = [], 0
+        for v in values:
+            at.append(total)
+            total += (v.size * per_word + GAP - 1) // GAP * GAP + GAP + skew
+        packed = dtype == torch.int32
+        self.all = torch.full((total // per_word,), 0x5A5A5A5A if packed else 9.0, dtype=dtype, device="cuda")
+        self.views = [self.all[a // per_word: a // per_word + v.size] for a, v in zip(at, values)]
+        for view, v in zip(self.views, values):
+            view.copy_(torch.from_numpy(v.view(np.int32) if packed else v))
+        self.between = torch.ones(self.all.numel(), dtype=torch.bool, device="cuda")
+        for a, v in zip(at, values):
+            self.between[a // per_word: a // per_word + v.size] = False
+
+    def check(self, want, what):
+        for i, (view, ref) in enumerate(zip(self.views, want)):
+            assert_bits_equal(view.cpu().numpy(), ref.view(np.int32) if view.dtype == torch.int32 else ref, "%s of tensor %d" % (what, i))
+        left = 0x5A5A5A5A if self.all.dtype == torch.int32 else 9.0
+        assert bool((self.all[self.between] == left).all()), "%s: written between or behind the tensors" % what
+
+
+def _layers(sizes, rng, t, dtype, arenas):
+    widened = lambda a: torch.from_numpy(a).to(dtype).float().numpy()
+    host = dict(w_global=[rng.standard_normal(n, dtype=np.float32) for n in sizes],
+                residual=[rng.standard_normal(n, dtype=np.float32) * np.float32(0.4 * t) for n in sizes],
+                grad=[widened(rng.standard_normal(n, dtype=np.float32) * np.float32(t)) for n in sizes],
+                w_local=[np.zeros(n, np.float32) for n in sizes],
+                packed_self=[np.zeros((n + 15) // 16, np.uint32) for n in sizes])
+    skew = lambda k: 0 if arenas else GAP * k
+    dev = {role: _Buffer(v, skew(k), dtype if role == "grad" else (torch.int32 if role == "packed_self" else torch.float32),
+                         16 if role == "packed_self" else 1) for k, (role, v) in enumerate(host.items())}
+    return host, dev, [{role: dev[role].views[i] for role in dev} for i in range(len(sizes))]
+
+
+# 9 to 16 workers' results are written through above 1024 tiles, and the count form's groups are bounded above 6 * 1024;
+# 17 to 32 workers' are written through above 2048
+@pytest.mark.parametrize("arenas", [True, False])
+@pytest.mark.parametrize("above", [False, True])
+@pytest.mark.parametrize("N,tiles,t,dtype", [(9, 1024, 0.5, torch.float32), (16, 1024, 0.3, torch.bfloat16), (12, 1024, 0.3, torch.float32),
+                                             (16, 1024, 0.25, torch.float16), (16, 6144, 0.5, torch.float32), (10, 6144, 0.5, torch.bfloat16),
+                                             (17, 2048, 0.5, torch.float32), (24, 2048, 0.3, torch.bfloat16), (32, 2048, 0.3, torch.float32),
+                                             (32, 2048, 0.5, torch.float16), (8, 1024, 0.3, torch.bfloat16), (33, 2048, 0.5, torch.float32)])
+def test_compressed_pass(B, oracle, N, tiles, t, dtype, above, arenas):
+    rng = np.random.default_rng(N * tiles + above)
+    sizes, rank = _sizes(tiles, above), N // 2
+    host, dev, layers = _layers(sizes, rng, t, dtype, arenas)
+    words = [[rng.integers(0, 2 ** 32, (n + 15) // 16, dtype=np.uint32) for n in sizes] for _ in range(N)]
+    streams = [_Buffer(w, 0 if arenas else GAP * j, torch.int32, 16) for j, w in enumerate(words)]
+    peers = [None if j == rank else s.views for j, s in enumerate(streams)]
+    plan = B.Plan(layers, peers, N, rank, grad_dtype=dtype)
+    for step in (1, 2):                             # the plan's pass, then the one that allocates nothing
+        for i, n in enumerate(sizes):
+            words[rank][i] = oracle.quantize_pack(host["grad"][i], host["residual"][i], t)
+            host["packed_self"][i] = words[rank][i]
+            oracle.update(host["w_global"][i], host["w_local"][i], host["grad"][i],
+                          oracle.decode_sum([w[i] for w in words], n, t), LR_LOCAL, LR_GLOBAL, N)
+        if step == 1:
+            plan.step(step, 4, t, LR_LOCAL, LR_GLOBAL)
+        else:
+            B.cdsgd_step_fused_static(layers, peers, N, rank, step, 4, t, LR_LOCAL, LR_GLOBAL, grad_dtype=dtype)
+        torch.cuda.synchronize()
+        for role in ("packed_self", "residual", "w_local", "w_global"):
+            dev[role].check(host[role], "%s, step %d" % (role, step))
+    plan.destroy()
+
+
+# a correction pass writes its results through up to 14 * 1024 tiles (agg_full, or the sum of up to 4 workers), or above 256
+# and up to 2048 (more workers)
+@pytest.mark.parametrize("above", [False, True])
+@pytest.mark.parametrize("N,tiles,dtype,bound", [(5, 256, torch.float32, True), (16, 256, torch.bfloat16, True),
+                                                 (8, 2048, torch.float16, True), (16, 2048, torch.float32, True),
+                                                 (4, 14 * 1024, torch.float32, True), (2, 14 * 1024, torch.bfloat16, True),
+                                                 (8, 14 * 1024, torch.bfloat16, False), (1, 14 * 1024, torch.float32, False)])
+def test_correction_pass(B, oracle, N, tiles, dtype, bound, above):
+    rng = np.random.default_rng(N * tiles + above)
+    sizes, rank = _sizes(tiles, above), N // 2
+    host, dev, layers = _layers(sizes, rng, 0.5, dtype, True)
+    if bound or N == 1:
+        grads = [[torch.from_numpy(rng.standard_normal(n, dtype=np.float32)).to(dtype) for n in sizes] for _ in range(N)]
+        agg = [oracle.full_sum([host["grad"][i] if j == rank else grads[j][i].float().numpy() for j in range(N)])
+               for i in range(len(sizes))]
+    else:
+        agg = [rng.standard_normal(n, dtype=np.float32) for n in sizes]
+        for layer, a in zip(layers, agg):
+            layer["agg_full"] = torch.from_numpy(a).cuda()
+    words = [[np.zeros((n + 15) // 16, np.uint32) for n in sizes] for _ in range(N)]
+    peers = [None if j == rank else [torch.from_numpy(w.view(np.int32)).cuda() for w in words[j]] for j in range(N)] if N > 1 else None
+    plan = B.Plan(layers, peers, N, rank, grad_dtype=dtype)
+    if bound:
+        plan.bind_full_grads([None if j == rank else [g.cuda() for g in grads[j]] for j in range(N)])
+    plan.step(0, 4, 0.5, LR_LOCAL, LR_GLOBAL)
+    torch.cuda.synchronize()
+    for i in range(len(sizes)):
+        oracle.update(host["w_global"][i], host["w_local"][i], host["grad"][i], agg[i], LR_LOCAL, LR_GLOBAL, N)
+    for role in ("packed_self", "residual", "w_local", "w_global"):
+        dev[role].check(host[role], role)
+    plan.destroy()
