@@ -36,6 +36,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -637,7 +638,7 @@ int cdsgd_plan_create(const cdsgd_tensor *tensors, int num_tensors, const uint32
 
 int cdsgd_plan_create_typed(const cdsgd_tensor *tensors, int num_tensors, const uint32_t *const *const *peers,
                             int num_workers, int self, int grad_dtype, cdsgd_plan **out)
-{
+try {
     if (!out) return CDSGD_ERR_NULL;
     *out = nullptr;
     unsigned long long total_chunks = 0;
@@ -684,17 +685,16 @@ int cdsgd_plan_create_typed(const cdsgd_tensor *tensors, int num_tensors, const 
             if (j != self) hp[(size_t)i * row + (size_t)j] = reinterpret_cast<const uint8_t *>(peers[j][i]);
     }
 
-    cdsgd_plan *plan = new (std::nothrow) cdsgd_plan;
-    if (!plan) return CDSGD_ERR_DEVICE;
+    std::unique_ptr<cdsgd_plan, int (*)(cdsgd_plan *)> plan(new cdsgd_plan, cdsgd_plan_destroy);
+    plan->host_tensors.assign(ht, ht + num_tensors);
+    plan->chunk_start.swap(chunk_start);
     if (hipMalloc(&plan->device_block, total) != hipSuccess) {
         (void)hipGetLastError();
-        delete plan;
+        plan->device_block = nullptr;
         return CDSGD_ERR_DEVICE;
     }
     if (hipMemcpy(plan->device_block, image.data(), total, hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipGetLastError();
-        (void)hipFree(plan->device_block);
-        delete plan;
         return CDSGD_ERR_DEVICE;
     }
     unsigned char *base = static_cast<unsigned char *>(plan->device_block);
@@ -708,10 +708,10 @@ int cdsgd_plan_create_typed(const cdsgd_tensor *tensors, int num_tensors, const 
     plan->num_chunks = (unsigned)total_chunks;
     plan->has_agg_full = all_agg;
     plan->grad_type = grad_dtype;
-    plan->host_tensors.assign(ht, ht + num_tensors);
-    plan->chunk_start.swap(chunk_start);
-    *out = plan;
+    *out = plan.release();
     return CDSGD_OK;
+} catch (const std::bad_alloc &) {
+    return CDSGD_ERR_DEVICE;
 }
 
 int cdsgd_plan_destroy(cdsgd_plan *plan)
@@ -1064,7 +1064,7 @@ int cdsgd_step_global_range(cdsgd_plan *plan, int first_tensor, int num_tensors,
 }
 
 int cdsgd_plan_bind_full_grads(cdsgd_plan *plan, const float *const *const *peer_grads)
-{
+try {
     if (!plan) return CDSGD_ERR_NULL;
     const int np = plan->num_workers - 1;
     if (np == 0) return CDSGD_OK;  // a single worker's sum is its own gradient
@@ -1094,11 +1094,13 @@ int cdsgd_plan_bind_full_grads(cdsgd_plan *plan, const float *const *const *peer
     plan->peer_grads_block = dev;
     plan->peer_grads = (const void **)dev;
     return CDSGD_OK;
+} catch (const std::bad_alloc &) {
+    return CDSGD_ERR_DEVICE;
 }
 
 
 int cdsgd_plan_set_thresholds(cdsgd_plan *plan, const float *thresholds)
-{
+try {
     if (!plan) return CDSGD_ERR_NULL;
     bool all_pow2 = true, any_tiny = false;
     if (thresholds)
@@ -1118,6 +1120,8 @@ int cdsgd_plan_set_thresholds(cdsgd_plan *plan, const float *thresholds)
     plan->own_thresholds_pow2 = thresholds != nullptr && all_pow2;
     plan->own_thresholds_tiny = any_tiny;
     return CDSGD_OK;
+} catch (const std::bad_alloc &) {
+    return CDSGD_ERR_DEVICE;
 }
 
 size_t cdsgd_sparse_segments(size_t n) { return ((n + 15) / 16 + kSegWords - 1) / kSegWords; }

@@ -391,3 +391,27 @@ def test_native_client_builds_and_needs_a_gpu():
         return
     r = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=60)
     assert r.returncode == 2 and "abi client ok" not in r.stdout
+
+
+def test_out_of_host_memory_is_a_status(L):
+    """A plan of the longest list, whose tables' host image does not fit: a status, not an exception through the C entry."""
+    import subprocess
+    import sys
+    code = """
+import ctypes, resource
+from paper_2106_10796_amd import binding as B
+L = B.lib()
+t = B.cdsgd_tensor()
+for k, name in enumerate(("w_global", "w_local", "residual", "grad", "packed_self")):
+    setattr(t, name, (k + 1) << 40)
+t.n = 16_000_000_000
+out = ctypes.c_void_p()
+with open("/proc/self/statm") as fh:
+    used = int(fh.read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + (24 << 20), resource.getrlimit(resource.RLIMIT_AS)[1]))
+st = L.cdsgd_plan_create(ctypes.pointer(t), 1, None, 1, 0, ctypes.byref(out))
+print(st, out.value)
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    from paper_2106_10796_amd.binding import ERR_DEVICE
+    assert r.returncode == 0 and r.stdout.split() == [str(ERR_DEVICE), "None"], r.stderr
