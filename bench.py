@@ -33,9 +33,8 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per k_fused_compressed launch.  NOT measured by this run: constants taken from earlier
 # rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE runs of this file, scaled by the same counters' readings
 # for a 1 GiB device copy (FETCH_SIZE x 2.0, WRITE_SIZE x 1.0 on this GPU); the summaries are
-# profiles/k_fused_compressed_<workload>.md (c3_resnet50: read side from the current kernel, write
-# side from an earlier build with the same stores).
-PROFILED_TRAFFIC_BYTES = {"c4_vgg16": 3.8785e9, "c3_resnet50": 0.7168e9, "c5_flat4g": 30.098e9}
+# profiles/k_fused_compressed_<workload>.md (c3_resnet50: write side from TCC_EA0_WRREQ, 64 bytes each).
+PROFILED_TRAFFIC_BYTES = {"c4_vgg16": 3.8785e9, "c3_resnet50": 0.7166e9, "c5_flat4g": 30.098e9}
 MIN_TIMED_SECONDS = 1.0     # sustained: the timed blocks of the headline cover at least this much GPU time
 MIN_BLOCKS = 10
 

@@ -352,8 +352,8 @@ unsigned lds_of_kernel_sum(unsigned num_chunks, int num_workers, int grad_type)
     return long_list && num_workers <= 8 ? kLdsFor20Waves : kLdsFor22Waves;
 }
 
-// Whether a pass on 32-bit gradients writes its results through, and leaves them in the memory-side cache, instead of
-// non-temporally.  Measured with both rules, time over that of non-temporal stores, 32-bit / bf16:
+// Whether a correction pass (gradients of any type) writes its results through, and leaves them in the memory-side cache, instead
+// of non-temporally.  Measured with both rules, time over that of non-temporal stores, 32-bit / bf16:
 //   sum, N = 2    2 M .94 / .78, 4 M 1.00 / .97, 8 M .97 / .97, 16 M 1.03 / 1.04, 80 M 1.01 / .98, VGG-16 1.02 / .99
 //        N = 4    2 M .95 / .87, 4 M .99 / 1.01, 8 M .94 / .94, 16 M 1.02 / 1.02, 80 M 1.01 / .99, VGG-16 1.01 / .99
 //        N = 8    2 M .99 / .91, 4 M 1.00 / 1.01, 8 M .97 / .95, 16 M 1.01 / 1.02, 80 M .99 / .99, VGG-16 .98 / .99
@@ -820,8 +820,8 @@ constexpr unsigned kWalkingGroups = 768;
 //   0.45 M 1.24 / 1.23, 0.7 M 1.14 / 1.07, 1 M .98 / .98, 1.4 M 1.00 / .99;  N = 17 / 32 0.45 M 1.15 / 1.07, 1 M 1.04 / 1.07,
 //   1.4 M 1.03 / 1.01;  32-bit, t = 0.3, N = 16 / 32 0.45 M 1.10 / 1.00, 1 M .99 / 1.05, 1.4 M 1.02 / 1.02)
 //   up to 8 workers   N = 4, t = 0.3  4 M 1.03, 12 M .99, 25 M 1.00, VGG-16 1.06;  N = 8 1.02 / 1.00 / 1.01 / 1.00
-// Kernels of their own for 17 to 32 workers, which hold half the stream pointers in scalar registers, over those for any
-// number (results written through / and the list in arenas), N = 17 / 24 / 32:
+// Kernels of their own for 17 to 32 workers, which hold half the stream pointers in scalar registers (but 1 to 6 of them where the
+// list lies in arenas), over those for any number (results written through / and the list in arenas), N = 17 / 24 / 32:
 //   t = 0.5, 32-bit   1 M .83 .83 .88 / .81 .82 .88;  4 M .98 .97 .98 / .98 .97 .97;  12 M .99 .99 .98 / .99 .99 .99;
 //                     ResNet-50-shaped .97 .98 .98 / .97 .97 .98;  VGG-16 .99 1.00 1.01
 //   t = 0.3, 32-bit   1 M .97 1.03 .97 / .93 .99 .96;  4 M .99 .99 1.00 / .98 .98 .98;  12 M 1.00 .99 .97 / .99 .99 .99;
@@ -835,7 +835,7 @@ constexpr unsigned long long kStreamWordsBytes = 112000000;
 
 // Lists in arenas (ArenaChunk), up to 32 workers and 28 M elements: one trip to memory less before a group's first data
 // loads.  Time over that of the general kernels: 1 M elements .97-1.00, 2 M .97-.99, 4 M .98-.99, 8 M .99-1.00, 25 M
-// .99-1.01; ResNet-50-shaped list, N = 16, in 17 launches of a million elements and more 163.1 / 156.9 us, in one 107.0 /
+// .99-1.01; ResNet-50-shaped list, N = 16, in 19 launches of a million elements and more 163.1 / 156.9 us, in one 107.0 /
 // 106.2.  (VGG-16-shaped .99-1.04, 1 GiB buckets 1.02.  Above 32 workers 1 M 1.12, 4 M 1.03, 25 M 1.01: more of the stream
 // pointers no longer fit the scalar registers beside the buffers'.)
 constexpr int kUpTo32Rows = 16;  // host side only: the kernels for up to 32 workers

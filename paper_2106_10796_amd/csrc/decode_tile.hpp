@@ -107,8 +107,9 @@ struct StreamPointers {
     }
 
     // Keeps the compiler from moving the loads to where their pointers are used.  Above 32 workers a wave of the fused
-    // kernels then holds more addresses than it has scalar registers for beside the descriptor: 4 (count form), 17
-    // (chain) and 19 / 25 (sparse) of them are kept in lanes of a vector register, and 7 waves fit a SIMD instead of 8.
+    // kernels then holds more addresses than it has scalar registers for beside the descriptor: 5 (count form), 19
+    // (chain) and 19 / 27 (sparse) of them are kept in lanes of a vector register, and 7 waves fit a SIMD instead of 8
+    // (17 to 32 workers, list in arenas: 1 or 3 in the count form, 1 to 6 in the chain).
     // Short lists, where the early pointers count, gain all the same (figures at the head of kernels_fused.hpp); long
     // ones do not use the eighth wave.  The single-tensor decode has no descriptor and spills none.
     __device__ __forceinline__ void pin()
@@ -464,9 +465,10 @@ __device__ __forceinline__ f4 tile_sums(const unsigned (&w)[kWordsPerWave<SZ>], 
 // xcd: which order the tiles are dealt in.  The chunk-wise order pays where the tiles of a chunk share its segment
 // (sparse streams), and on long tensors (2^27 elements, N = 16: 421 against 428 us); on shorter ones the plain order
 // is 1 % faster (2^24: 71.5 against 72.5; both with the global update behind it).
-// drain: the aggregate is stored non-temporally (drains_results).  Otherwise it is written through and stays in the memory-side cache, where the global update that follows finds it
-// (decode-and-sum and update, non-temporal store / now, us: N = 16, 50 M 162 / 150; N = 32, 16 M 70 / 66; N = 4, 4 M
-// 13.0 / 12.5; at the default policy the flush of the L2s at the end of the kernel costs what the update gains).
+// drain: the aggregate is stored non-temporally (drains_results).  Otherwise it is written through and stays in the
+// memory-side cache, where the global update that follows finds it (decode-and-sum and update, non-temporal store / now,
+// us: N = 16, 50 M 162 / 150; N = 32, 16 M 70 / 66; N = 4, 4 M 13.0 / 12.5; at the default policy the flush of the L2s at
+// the end of the kernel costs what the update gains).
 // The workers' stream pointers of a single-tensor call; they travel in the kernel arguments.
 struct StreamTable {
     const uint8_t *p[CDSGD_MAX_WORKERS];  // null past the last worker

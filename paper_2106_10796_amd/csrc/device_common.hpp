@@ -50,7 +50,9 @@ __device__ __forceinline__ void st4(float *base, unsigned qi, f4 v)
 }
 
 // Stores that are written through the L2 of the compute die to memory, so that no dirty line is left for the flush at
-// the end of the kernel (2.2 us after a kernel that writes at the default policy; non-temporal stores leave some).
+// the end of the kernel (2.2 us after a kernel that writes at the default policy).  Non-temporal stores leave some: the
+// lines that the flush wrote back were 33,000 of 383,000 in a compressed pass over 4 M elements, N = 16, 55,000 of 192,000
+// over 2 M in bf16, and are none so (TCC_ALL_TC_OP_WB_WRITEBACK; TCC_WRITEBACK).
 //   kThrough        the lines stay in the 256 MB memory-side cache: for what the next call reads
 //   kThroughStream  they do not: for what is read again a training step later
 // Policies of a buffer instruction: 1 and 16 are the scope bits sc0 and sc1, 2 is nt.

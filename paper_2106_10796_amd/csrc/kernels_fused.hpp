@@ -9,7 +9,7 @@ namespace {
 // Bound by HBM (24 + N / 4 bytes per element): every load of a group is in flight at once, so a group's life is the
 // table lookups (chunk, then descriptor and stream pointers together), one round trip to memory, the decode and the
 // stores.  (Stream pointers fetched behind the descriptor, one worker after the other above 16 workers: layer ranges of
-// a million elements, N = 16 169.3 us for 17 launches, 166.5 now; 300 k elements, N = 64 6.3 us, 6.1; 1 M elements
+// a million elements, N = 16 169.3 us for 19 launches, 166.5 now; 300 k elements, N = 64 6.3 us, 6.1; 1 M elements
 // decoded and updated, N = 64 29.6 us, 28.6.  Longer lists are bound by HBM and gain nothing.)
 // A persistent grid whose groups fetch the next tile before they finish one is 15 % slower: its groups drift apart,
 // and the streams' requests in flight with them (2^26 elements, N = 16: 0.366 ms against 0.293).
