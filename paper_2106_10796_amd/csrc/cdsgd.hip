@@ -352,21 +352,26 @@ unsigned lds_of_kernel_sum(unsigned num_chunks, int num_workers, int grad_type)
     return long_list && num_workers <= 8 ? kLdsFor20Waves : kLdsFor22Waves;
 }
 
-// Whether a correction pass (gradients of any type) writes its results through, and leaves them in the memory-side cache, instead
-// of non-temporally.  Measured with both rules, time over that of non-temporal stores, 32-bit / bf16:
-//   sum, N = 2    2 M .94 / .78, 4 M 1.00 / .97, 8 M .97 / .97, 16 M 1.03 / 1.04, 80 M 1.01 / .98, VGG-16 1.02 / .99
-//        N = 4    2 M .95 / .87, 4 M .99 / 1.01, 8 M .94 / .94, 16 M 1.02 / 1.02, 80 M 1.01 / .99, VGG-16 1.01 / .99
-//        N = 8    2 M .99 / .91, 4 M 1.00 / 1.01, 8 M .97 / .95, 16 M 1.01 / 1.02, 80 M .99 / .99, VGG-16 .98 / .99
-//        N = 16   2 M .98 / .96, 3 M 1.02 / 1.13, 8 M .99 / .98, 16 M 1.01 / 1.03, 80 M .99 / .98, VGG-16 .98 / .98
-//   sum, N = 8 / 16, 32-bit: 0.1 M 1.08 / 1.04, 0.3 M .93 / .96, 0.5 M .98 / 1.00, 1.2 M .99 / .98; bf16 0.1 M 1.03 / 1.07, 0.3 M
-//                 1.03 / .88, 0.5 M .91 / .99, 1.2 M .96 / .96
-//   agg_full      1 M 1.00 / 1.00, 4 M .99 / 1.01, 12 M .97 / .97, 25 M 1.01 / 1.01, VGG-16 1.02 / .98
-// (not staying, as the compressed pass stores: 4 M 1.03-1.09, VGG-16 .99-1.01)
+// Whether a correction pass (gradients of any type) writes its results through, the global weights staying in the memory-side
+// cache and the local ones not, instead of storing both non-temporally.  A program that corrects every k steps finds none of a
+// list's buffers in that cache, a small one that does little else may find all, so the line lies where neither loses.
+// Time over that of non-temporal stores: three sets of buffers in turn (up to some million elements they fit the cache) /
+// 600 MB of sets / 1500 MB of sets:
+//   sum, N = 2, 32-bit   0.5 M .99 / 1.02 / 1.00, 1 M .91 / 1.00 / 1.02, 3 M .99 / 1.00 / 1.01, 6 M .98 / .96 / 1.02, 14 M .96 / .96 / .97
+//   sum, N = 2, bf16     0.5 M 1.00 / 1.01 / 1.00, 1 M .99 / 1.00 / 1.04, 1.9 M .76 / .99 / 1.10, 3 M .99 - 1.03 / 1.03 / .99 - 1.09, 6 M 1.01 / .98 / 1.01,
+//                        14 M .96 / .96 / 1.02
+//   sum, N = 4, 32-bit   0.5 M .98 / 1.10 / 1.07, 1 M 1.03 / 1.07 / 1.05, 3 M .99 / .99 / .98, 6 M .95 / .95 / .94, 14 M .93 / .94 / .93
+//   sum, N = 4, bf16     0.5 M 1.00 / 1.07 / 1.07, 1 M .89 / 1.10 / 1.11, 3 M .97 / 1.03 / 1.08, 6 M 1.00 / .98 / 1.05, 14 M .94 / .95 / .97
+//   agg_full             0.5 M .99 / .99 / 1.02, 1 M .81 / 1.03 / 1.04, 4 M 1.01 / .97 / 1.03, 8 M .97 / .95 / .98, 13 M .96 / .96 / .99
+//   sum, N = 8 / 16      0.3 to 1.9 M, 32-bit .94 to 1.01 / .99 to 1.15 / 1.04 to 1.14;  bf16 .92 to 1.00 / 1.10 to 1.23 / 1.10 to 1.20
+//   sum, lists that fit no cache   75 M 1.00;  100 M N = 5 .99 - 1.01, 8 .99 - 1.01, 16 .99;  130 M .98 - 1.00;  VGG-16 N = 5 .99 - 1.01, 8 .97 - .99,
+//                        12 .98 - 1.02, 16 .95 - 1.00
+// (both staying: 14 M 1.03, and 1 to 2 M 2 to 14 % slower than so where the sets do not fit)
 bool keeps_results(unsigned num_chunks, int num_workers, bool sum)
 {
     const unsigned tiles = num_chunks * kTilesPerChunk;
-    const bool many = sum && num_workers > 4;
-    return many ? (tiles > 256u && tiles <= 2u * 1024u) || tiles > 72u * 1024u : tiles <= 14u * 1024u;
+    if (sum && num_workers > 4) return tiles > 72u * 1024u;
+    return tiles > (sum && num_workers > 2 ? 4u * 1024u : 768u) && tiles <= 14u * 1024u;
 }
 
 // Launch one full-gradient pass (see k_fused_full) for a plan.

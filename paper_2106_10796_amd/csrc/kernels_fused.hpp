@@ -172,6 +172,8 @@ constexpr unsigned kPiecesPerChunk = kChunkQuads / kFullBlock;
 static_assert(kChunkQuads % kFullBlock == 0 && kFullBlock % 64 == 0, "pieces tile a chunk, whole waves");
 
 // One piece of one chunk: quad qi of the chunk for this lane, cnt of its elements exist.
+// STORE: how the global weights are stored.  kThrough (keeps_results): written through and staying in the memory-side cache,
+// where the next pass reads them; the local ones, which no pass reads, are then written through and do not stay.
 template <bool G, bool SUM, int LOCAL, int GT, int STORE>
 __device__ __forceinline__ void full_piece(const TensorDesc &d, const void *const *__restrict__ pg,
                                            int num_peers, int self, size_t quad0, unsigned qi,
@@ -216,7 +218,7 @@ __device__ __forceinline__ void full_piece(const TensorDesc &d, const void *cons
         vg[c] = __builtin_fmaf(-scale, a[c], w[c]);
         vl[c] = LOCAL == kLocalRule ? __builtin_fmaf(-lr_local, g[c], w[c]) : vg[c];
     }
-    if (LOCAL != kLocalNone) st4g<G, STORE>(wl, qi, cnt, vl);
+    if (LOCAL != kLocalNone) st4g<G, STORE == kThrough ? kThroughStream : STORE>(wl, qi, cnt, vl);
     st4g<G, STORE>(wg, qi, cnt, vg);
 }
 

@@ -132,15 +132,15 @@ def test_compressed_pass_equals_its_parts(B, N, n, grad, t):
     _whole_equals_parts(B, n, N, grad, 4096 * 401, lambda p, a, b: p.step(1, 4, t, 0.05, 0.1))
 
 
-# a correction pass of more than 4 workers writes its results through from 0.25 M to 2 M elements and above 72 M; one of fewer
-# up to 14 M.  Parts of 1.6 M elements are written through, so the longest list is taken in parts of 3.2 M.
-@pytest.mark.parametrize("N,n,grad,chunks", [(4, (14 << 20) + 4097, torch.float32, 397), (8, (2 << 20) + 5, torch.bfloat16, 397),
-                                             (16, (2 << 20) + 5, torch.float32, 397), (5, (72 << 20) + 7, torch.float32, 794)])
-def test_correction_pass_equals_its_parts(B, N, n, grad, chunks):
+# a correction pass of more than 4 workers writes its results through above 72 * 2^20 elements, one of 4 from 4 to 14 times 2^20;
+# parts of 1.6 M elements are stored non-temporally
+@pytest.mark.parametrize("N,n,grad", [(4, (14 << 20) - 4097, torch.float32), (3, (4 << 20) + 4097, torch.float16),
+                                      (16, (2 << 20) + 5, torch.float32), (5, (72 << 20) + 7, torch.float32)])
+def test_correction_pass_equals_its_parts(B, N, n, grad):
     gen = torch.Generator(device="cuda").manual_seed(n)
     full = [None] + [torch.randn(n, device="cuda", generator=gen).to(grad) for _ in range(N - 1)]
 
     def call(plan, a, b):
         plan.bind_full_grads([None if g is None else [g[a:b]] for g in full])
         plan.step(0, 4, 0.5, 0.05, 0.1)
-    _whole_equals_parts(B, n, N, grad, 4096 * chunks, call)
+    _whole_equals_parts(B, n, N, grad, 4096 * 397, call)

@@ -96,11 +96,11 @@ def test_compressed_pass(B, oracle, N, tiles, t, dtype, above, arenas):
     plan.destroy()
 
 
-# a correction pass writes its results through up to 14 * 1024 tiles (agg_full, or the sum of up to 4 workers), or above 256
-# and up to 2048 (more workers)
+# a correction pass writes its results through above 768 (agg_full, or the sum of up to 2 workers) or 4 * 1024 tiles (4 workers) and
+# up to 14 * 1024; the sum of more workers on long lists only
 @pytest.mark.parametrize("above", [False, True])
-@pytest.mark.parametrize("N,tiles,dtype,bound", [(5, 256, torch.float32, True), (16, 256, torch.bfloat16, True),
-                                                 (8, 2048, torch.float16, True), (16, 2048, torch.float32, True),
+@pytest.mark.parametrize("N,tiles,dtype,bound", [(2, 768, torch.float32, True), (1, 768, torch.bfloat16, True), (8, 768, torch.float16, False),
+                                                 (3, 4096, torch.float16, True), (4, 4096, torch.float32, True), (16, 768, torch.bfloat16, True),
                                                  (4, 14 * 1024, torch.float32, True), (2, 14 * 1024, torch.bfloat16, True),
                                                  (8, 14 * 1024, torch.bfloat16, False), (1, 14 * 1024, torch.float32, False)])
 def test_correction_pass(B, oracle, N, tiles, dtype, bound, above):
