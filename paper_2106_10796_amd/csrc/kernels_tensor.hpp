@@ -22,6 +22,13 @@ constexpr int kSmallTensor = 0, kMidTensor = 1, kLargeTensor = 2, kDrainTensor =
 constexpr size_t kSmallElems = (size_t)7 << 20, kKeepElems = (size_t)24 << 20;
 template <int LEN>
 constexpr int kTensorStore = LEN == kSmallTensor ? kThrough : (LEN == kDrainTensor ? kStream : kThroughStream);
+// ... of the local weights, which neither call reads again: they are left out of the cache at every length.  Local update and
+// quantise-and-pack, time over that of non-temporal stores throughout, three sets of buffers in turn / 600 MB of sets / 1500 MB of
+// sets, with the local weights staying, then so: 2 M .99 / 1.02 / .98, .99 / .95 / .97;  3 M .88 / 1.03 / 1.02, .90 / .95 / .98;  4 M .90 /
+// 1.00 / .99, .91 / .91 / .99;  5 M .90 / 1.01 / 1.00, .91 / .94 / .99;  6 M .98 / 1.06 / 1.08, .91 / .97 / 1.02;  7 M 1.02 / 1.04 / 1.11, .92 /
+// .95 / 1.04.
+template <int LEN>
+constexpr int kLocalStore = LEN == kSmallTensor ? kStream : kTensorStore<LEN>;
 
 // a5 + a6 (eq. 10, eq. 11) for one tensor, both from the weight that was loaded, in single-wave pieces of
 // 64 quads (`ext` in pieces, as for k_quantize_pack; measured on 2^27 elements: 6.29 TB/s against 6.02 TB/s
@@ -41,7 +48,7 @@ __device__ __forceinline__ void update_piece(float *__restrict__ wg, float *__re
         f4 v;
 #pragma unroll
         for (unsigned c = 0; c < 4; ++c) v[c] = __builtin_fmaf(-lr_local, g[c], w[c]);
-        st4g<G, kTensorStore<LEN>>(wl, lane, cnt, v);
+        st4g<G, kLocalStore<LEN>>(wl, lane, cnt, v);
     }
     if (GLOBAL) {
         f4 v;
