@@ -430,17 +430,23 @@ inline bool drains_results(size_t n, int num_workers)
     return n > 1250000u && n <= most;
 }
 
-// Whether weights that the global rule leaves in the memory-side cache push out streams that a later decode-and-sum would
-// find there.  Decode-and-sum and update, time over that of non-temporal stores in both, 3 / 4 sets of buffers in turn, weights staying,
-// then not staying:
-//   N = 33   5 M .92 / .96, .94 / .94;  6 M .95 / 1.01, .95 / .94;  7 M .99 / 1.01, .95 / .96
-//   N = 48   4 M .94 / 1.04, .96 / .98;  5 M 1.00 / 1.03, .96 / .98;  6 M 1.01 / 1.05, .97 / .94;  7 M 1.04 / 1.05, .97 / .94
-//   N = 64   3 M .96 / .99, .97 / .97;  4 M 1.00 / 1.04, .98 / .98;  5 M 1.04 / 1.01, .99 / .90;  6 M 1.08 / 1.01, .96 / .94
-//   N = 64, sparse, one code in 16   4 M .97 / 1.13, .96 / .99;  6 M 1.12 / 1.02, .99 / .95
-// (With two sets, which fit, staying is 2 % faster throughout.)
-inline bool crowds_streams(size_t n, int num_workers)
+// Whether the weights that the global rule writes stay in the memory-side cache for the next one: not where they push out
+// streams that a later decode-and-sum would find there, and not where few programs come back before they are pushed out
+// themselves.  Decode-and-sum and update, time over that of non-temporal stores in both, weights staying, then not staying:
+//   three / four sets of buffers in turn
+//     N = 33   5 M .92 / .96, .94 / .94;  6 M .95 / 1.01, .95 / .94;  7 M .99 / 1.01, .95 / .96
+//     N = 48   4 M .94 / 1.04, .96 / .98;  5 M 1.00 / 1.03, .96 / .98;  6 M 1.01 / 1.05, .97 / .94;  7 M 1.04 / 1.05, .97 / .94
+//     N = 64   3 M .96 / .99, .97 / .97;  4 M 1.00 / 1.04, .98 / .98;  5 M 1.04 / 1.01, .99 / .90;  6 M 1.08 / 1.01, .96 / .94
+//     N = 64, sparse, one code in 16   4 M .97 / 1.13, .96 / .99;  6 M 1.12 / 1.02, .99 / .95
+//   (With two sets, which fit, staying is 2 % faster throughout.)
+//   three sets / 1500 MB of sets
+//     N = 2    5 M .97 / .93, 1.05 / .94;  6.5 M .92 / .95, 1.00 / .95      N = 4    5 M .95 / .97, 1.01 / .94;  6.5 M .92 / 1.00, .97 / .94
+//     N = 8    4 M .93 / 1.00, .97 / .95;  5 M .92 / 1.00, .95 / .96;  6.5 M .91 / 1.03, .96 / .95;  sparse 6 M .93 / 1.07, .96 / .93
+//     N = 16   5 M .92 / .98, .95 / .95;  sparse 6 M .93 / 1.02, .95 / .94       N = 24   6.5 M .91 / .95, .95 / .94
+inline bool weights_stay(size_t n, int num_workers)
 {
-    return (unsigned long long)num_workers * packed_bytes_of(n) > 48000000ull;
+    return n <= (num_workers <= kUpTo4 ? kSmallElems : (size_t)5000000u) &&
+           (unsigned long long)num_workers * packed_bytes_of(n) <= 48000000ull;
 }
 
 // a4 for one tensor on checked arguments.
@@ -628,7 +634,7 @@ int cdsgd_update(float *w_global, float *w_local, const float *grad_local, const
         else CDSGD_LAUNCH_UPDATE(true, false, kLargeTensor, kLdsFor20Waves);
     } else {
         if (drains_results(n, num_workers)) CDSGD_LAUNCH_UPDATE(false, true, kDrainTensor, 0);
-        else if (small && !crowds_streams(n, num_workers)) CDSGD_LAUNCH_UPDATE(false, true, kSmallTensor, 0);
+        else if (weights_stay(n, num_workers)) CDSGD_LAUNCH_UPDATE(false, true, kSmallTensor, 0);
         else CDSGD_LAUNCH_UPDATE(false, true, kMidTensor, 0);
     }
 #undef CDSGD_LAUNCH_UPDATE

@@ -4,7 +4,7 @@
 namespace {
 
 // How the caches are used, by the length of the tensor (several sets of buffers in turn).
-//   kSmallTensor  up to 7 M elements (the global rule behind many streams: fewer, see crowds_streams): results are written
+//   kSmallTensor  up to 7 M elements (the global rule: see weights_stay): results are written
 //                 through and stay in the 256 MB memory-side cache
 //   kMidTensor    up to 24 M: they are written through and do not stay
 //   kLargeTensor  the same, and the gradient does not stay either

@@ -27,10 +27,11 @@ def _floats(rng, n, scale):
     return rng.standard_normal(n, dtype=np.float32) * np.float32(scale)
 
 
-# (five workers' aggregates from 1.25 M to 3.2 M elements are stored non-temporally; weights do not stay in the
-# memory-side cache above 48 MB of streams, 64 workers and 3 M elements)
+# (five workers' aggregates from 1.25 M to 3.2 M elements are stored non-temporally; weights of the global
+# rule of more than four workers do not stay in the memory-side cache above 5 M elements, or 48 MB of streams, 64 workers and 3 M elements)
 @pytest.mark.parametrize("n,N", [(1_250_000, 5), (1_250_003, 5), (3_200_000, 5), (3_200_001, 5), (SMALL, 5), (SMALL + 3, 5),
-                                 (KEEP, 5), (KEEP + 1, 5), (3_000_000, 64), (3_000_003, 64)])
+                                 (KEEP, 5), (KEEP + 1, 5), (5_000_000, 5), (5_000_001, 5),
+                                 (3_000_000, 64), (3_000_003, 64)])
 @pytest.mark.parametrize("mode", ["local", "global", "both"])
 def test_update_at_the_edges_of_its_lengths(B, oracle, n, N, mode):
     rng = np.random.default_rng(n + len(mode))
