@@ -4,8 +4,8 @@
 namespace {
 
 // How the caches are used, by the length of the tensor (several sets of buffers in turn).
-//   kSmallTensor  up to 7 M elements (the global rule: see weights_stay): results are written
-//                 through and stay in the 256 MB memory-side cache
+//   kSmallTensor  up to 7 M elements (the global rule: see weights_stay): results are written through and stay in the
+//                 256 MB memory-side cache, but for the local weights (kLocalStore)
 //   kMidTensor    up to 24 M: they are written through and do not stay
 //   kLargeTensor  the same, and the gradient does not stay either
 //   kDrainTensor  results are stored non-temporally (the global rule alone, see drains_results)
