@@ -516,7 +516,7 @@ __global__ __launch_bounds__(kTileQuads) void k_decode_sum(StreamTable tab, int 
             else st4p<kThrough>(out, qi, agg);
         } else {
             const unsigned e0 = x % kPerChunk * (4u * kTileQuads * TILES);
-            st4g<true, kThrough>(out, qi, quad_count<true>(ext.tail_elems > e0 ? ext.tail_elems - e0 : 0u, qi), agg);
+            st4g<true, kThrough>(out, qi, elems_from(e0, ext.tail_elems), agg);
         }
     }
 }

@@ -87,34 +87,48 @@ __device__ __forceinline__ void st_code(uint8_t *base, unsigned qi, unsigned byt
     }
 }
 
-// cnt = number of elements of this quad that exist (4 in the interior).
-template <bool G>
-__device__ __forceinline__ f4 ld4g(const float *base, unsigned qi, int cnt)
+// Ragged ends (G): a quad of a buffer of which `elems` elements are left from `base` on (the same in all lanes).  The range
+// check of a buffer instruction, which works word by word, stands in for the tests: what lies past the end is loaded as 0 and
+// not stored.  The loads of a ragged tile then wait for one another no more than those of a whole one; with a load per element
+// behind a test of its own, and 16-bit elements widened behind each test, the last tile of a list ended several trips to
+// memory after all others (16-bit gradients, an odd number of elements, us, before / now: compressed pass, N = 4, 0.7 M 5.1 / 4.0,
+// 1 M 6.4 / 4.5, 2 M 9.7 / 8.7, 4 M 16.2 / 16.0;  correction pass with the kernel sum, N = 16, 0.25 M 12.1 / 6.3, 1 M 14.7 / 9.1,
+// 4 M 31.3 / 28.5;  32-bit gradients the same within 1 %, update and quantise-and-pack of 2 M 9.2 / 8.8).
+constexpr int kLoad = CDSGD_NT_LOAD ? kStream : 0;
+
+// Elements left from `first` on, in a scalar register (a difference that saturates is a vector operation to the compiler).
+__device__ __forceinline__ unsigned elems_from(unsigned first, unsigned elems)
 {
-    if (!G || cnt == 4) return ld4(base, qi);
-    f4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-    const CDSGD_GLOBAL float *p = global_ptr(base) + 4u * qi;
-    if (cnt > 0) v.x = p[0];
-    if (cnt > 1) v.y = p[1];
-    if (cnt > 2) v.z = p[2];
-    return v;
+    return (unsigned)__builtin_amdgcn_readfirstlane((int)(elems > first ? elems - first : 0u));
+}
+
+template <bool G, int POLICY = kLoad>
+__device__ __forceinline__ f4 ld4g(const float *base, unsigned qi, unsigned elems)
+{
+    static_assert(POLICY == kStream || POLICY == 0, "policies in use");
+    if constexpr (!G) {
+        return POLICY == kStream ? ld4(base, qi) : ld4_kept(base, qi);
+    } else {
+        const __amdgpu_buffer_rsrc_t rsrc =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, (int)(elems * 4u), kBufferFlags);
+        return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(qi * 16u), 0, POLICY));
+    }
 }
 
 template <bool G, int POLICY = kStream>
-__device__ __forceinline__ void st4g(float *base, unsigned qi, int cnt, f4 v)
+__device__ __forceinline__ void st4g(float *base, unsigned qi, unsigned elems, f4 v)
 {
-    if (!G || cnt == 4) {
+    if constexpr (!G) {
         st4p<POLICY>(base, qi, v);
-        return;
+    } else {
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)(elems * 4u), kBufferFlags);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), rsrc, (int)(qi * 16u), 0, POLICY);
     }
-    CDSGD_GLOBAL float *p = global_ptr(base) + 4u * qi;
-    if (cnt > 0) p[0] = v.x;
-    if (cnt > 1) p[1] = v.y;
-    if (cnt > 2) p[2] = v.z;
 }
 
-// Gradient element types: fp32, or bf16 / fp16 widened exactly to fp32 on load
-// (everything downstream of the load is the fp32 path).
+// Gradient element types: fp32, or bf16 / fp16 widened exactly to fp32 (everything downstream is the fp32 path).  A load
+// and its widening are two steps, so that several loads can be asked for before the first is waited for.
 constexpr int kGradF32 = 0, kGradBF16 = 1, kGradF16 = 2;
 
 template <int GT>
@@ -125,6 +139,43 @@ __device__ __forceinline__ constexpr unsigned grad_bytes()
 
 typedef unsigned u2 __attribute__((ext_vector_type(2)));
 
+// A quad as it was loaded.  last: a ragged end's last element where its word is only half inside the buffer, else 0.
+template <int GT>
+struct GradQuad {
+    u2 v;
+    unsigned last;
+};
+template <>
+struct GradQuad<kGradF32> {
+    f4 v;
+};
+
+// One quad of a gradient buffer; `base` is the chunk's (or piece's) first element.
+template <bool G, int GT>
+__device__ __forceinline__ GradQuad<GT> load_grad(const void *base, unsigned qi, unsigned elems)
+{
+    GradQuad<GT> q;
+    if constexpr (GT == kGradF32) {
+        q.v = ld4g<G>(static_cast<const float *>(base), qi, elems);
+    } else if constexpr (!G) {
+        const CDSGD_GLOBAL u2 *p = global_ptr(static_cast<const u2 *>(base)) + qi;
+#if CDSGD_NT_LOAD
+        q.v = __builtin_nontemporal_load(p);
+#else
+        q.v = *p;
+#endif
+        q.last = 0u;
+    } else {
+        void *b = const_cast<void *>(base);
+        const __amdgpu_buffer_rsrc_t words = __builtin_amdgcn_make_buffer_rsrc(b, 0, (int)(elems / 2u * 4u), kBufferFlags);
+        const __amdgpu_buffer_rsrc_t halves = __builtin_amdgcn_make_buffer_rsrc(b, 0, (int)(elems * 2u), kBufferFlags);
+        q.v = __builtin_bit_cast(u2, __builtin_amdgcn_raw_buffer_load_b64(words, (int)(qi * 8u), 0, kLoad));
+        const bool mine = (elems & 1u) != 0u && qi == elems / 4u;
+        q.last = __builtin_amdgcn_raw_buffer_load_b16(halves, mine ? (int)(elems * 2u - 2u) : 0x7FFFFFF0, 0, kLoad);
+    }
+    return q;
+}
+
 template <int GT>
 __device__ __forceinline__ float widen16(unsigned h)  // h: the 16-bit pattern in the low half
 {
@@ -132,41 +183,25 @@ __device__ __forceinline__ float widen16(unsigned h)  // h: the 16-bit pattern i
     return (float)__builtin_bit_cast(_Float16, (unsigned short)h);
 }
 
-// One quad of a gradient buffer; `base` is the chunk's first element.
 template <bool G, int GT>
-__device__ __forceinline__ f4 ldgrad(const void *base, unsigned qi, int cnt)
+__device__ __forceinline__ f4 widen(GradQuad<GT> q, unsigned elems)
 {
-    if (GT == kGradF32) return ld4g<G>(static_cast<const float *>(base), qi, cnt);
-    if (!G || cnt == 4) {
-        const CDSGD_GLOBAL u2 *p = global_ptr(static_cast<const u2 *>(base)) + qi;
-#if CDSGD_NT_LOAD
-        const u2 v = __builtin_nontemporal_load(p);
-#else
-        const u2 v = *p;
-#endif
-        return f4{widen16<GT>(v.x & 0xFFFFu), widen16<GT>(v.x >> 16), widen16<GT>(v.y & 0xFFFFu),
-                  widen16<GT>(v.y >> 16)};
+    if constexpr (GT == kGradF32) {
+        return q.v;
+    } else {
+        if constexpr (G) {  // (the word that it belongs to was loaded as 0)
+            if ((elems & 2u) != 0u) q.v.y |= q.last;
+            else q.v.x |= q.last;
+        }
+        return f4{widen16<GT>(q.v.x & 0xFFFFu), widen16<GT>(q.v.x >> 16), widen16<GT>(q.v.y & 0xFFFFu),
+                  widen16<GT>(q.v.y >> 16)};
     }
-    f4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-    const CDSGD_GLOBAL unsigned short *p = global_ptr(static_cast<const unsigned short *>(base)) + 4u * qi;
-    if (cnt > 0) v.x = widen16<GT>(p[0]);
-    if (cnt > 1) v.y = widen16<GT>(p[1]);
-    if (cnt > 2) v.z = widen16<GT>(p[2]);
-    return v;
 }
 
 template <int GT>
 __device__ __forceinline__ const void *grad_at(const void *grad, size_t quad0)
 {
     return static_cast<const char *>(grad) + quad0 * (4u * grad_bytes<GT>());
-}
-
-template <bool G>
-__device__ __forceinline__ int quad_count(unsigned rem_elems, unsigned qi)
-{
-    if (!G) return 4;
-    int c = (int)rem_elems - (int)(4u * qi);
-    return c < 0 ? 0 : (c > 4 ? 4 : c);
 }
 
 // ---------------------------------------------------------------------------

@@ -47,7 +47,6 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
     float *__restrict__ wg = d.w_global + 4 * quad0;
     float *__restrict__ wl = d.w_local + 4 * quad0;
     uint8_t *pself = d.packed_self + quad0;
-    const int cnt = quad_count<G>(rem_elems, tid);
 
     TileStreams s;
     s.num_workers = num_workers;
@@ -57,31 +56,32 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
     s.tile = tile;
     unsigned words[kWordsPerWave<SZ>];
     if (!LATE) load_words<SZ, WAVES, SPARSE, NT>(words, from, s, wave, tid & 63u);
-    const f4 g = ldgrad<G, GT>(grad, tid, cnt);
-    f4 r = ld4g<G>(resid, tid, cnt);
-    const f4 w = ld4g<G>(wg, tid, cnt);
+    const GradQuad<GT> loaded = load_grad<G, GT>(grad, tid, rem_elems);
+    f4 r = ld4g<G>(resid, tid, rem_elems);
+    const f4 w = ld4g<G>(wg, tid, rem_elems);
     if (LATE) {
         __builtin_amdgcn_sched_barrier(0);
         load_words<SZ, WAVES, SPARSE, NT>(words, from, s, wave, tid & 63u);
     }
 
     // own codes: quantise, keep the residual, write what would be pushed
+    const f4 g = widen<G, GT>(loaded, rem_elems);
     f4 sent;
     const unsigned own = quantize_quad(g, r, t, sent);
-    st4g<G, kStore>(resid, tid, cnt, r);
+    st4g<G, kStore>(resid, tid, rem_elems, r);
     if (!G || tid < rem_bytes) st_code<OUT>(pself, tid, own);
 
     // eq. 11 and eq. 10 from the same loaded weight
     f4 vl, vg;
 #pragma unroll
     for (unsigned c = 0; c < 4; ++c) vl[c] = __builtin_fmaf(-lr_local, g[c], w[c]);
-    if (kLocalFirst<SZ, FORM> && write_local) st4g<G, kStore>(wl, tid, cnt, vl);
+    if (kLocalFirst<SZ, FORM> && write_local) st4g<G, kStore>(wl, tid, rem_elems, vl);
 
     const f4 agg = tile_sums<SZ, FORM, WAVES>(words, own, sent, self, num_workers, t, lds);
 #pragma unroll
     for (unsigned c = 0; c < 4; ++c) vg[c] = __builtin_fmaf(-scale, agg[c], w[c]);
-    if (!kLocalFirst<SZ, FORM> && write_local) st4g<G, kStore>(wl, tid, cnt, vl);
-    st4g<G, kStore>(wg, tid, cnt, vg);
+    if (!kLocalFirst<SZ, FORM> && write_local) st4g<G, kStore>(wl, tid, rem_elems, vl);
+    st4g<G, kStore>(wg, tid, rem_elems, vg);
 }
 
 // write_local: eq. 11 as well (false: the global half of a split step)
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
             } else if (tile * kQuads < bytes) {
                 const unsigned elems0 = tile * kQuads * 4u;
                 fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, HOW>(d, from, num_workers, self, quad, tile,
-                                                                   at.elems > elems0 ? at.elems - elems0 : 0u, bytes - tile * kQuads,
+                                                                   elems_from(elems0, at.elems), bytes - tile * kQuads,
                                                                    t_call, lr_local, scale, write_local != 0, lds);
             }
         } else {
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
                 // (the packed bytes of the ragged end cover its elements: tiles past them have nothing to do)
                 const unsigned elems0 = tile * kQuads * 4u;
                 fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, HOW>(d, from, num_workers, self, at.chunk, tile,
-                                                       d.ext.tail_elems > elems0 ? d.ext.tail_elems - elems0 : 0u,
+                                                       elems_from(elems0, d.ext.tail_elems),
                                                        d.ext.tail_bytes - tile * kQuads, t, lr_local, scale,
                                                        write_local != 0, lds);
             }
@@ -171,7 +171,7 @@ constexpr unsigned kFullBlock = CDSGD_FULL_BLOCK;            // lanes per workgr
 constexpr unsigned kPiecesPerChunk = kChunkQuads / kFullBlock;
 static_assert(kChunkQuads % kFullBlock == 0 && kFullBlock % 64 == 0, "pieces tile a chunk, whole waves");
 
-// One piece of one chunk: quad qi of the chunk for this lane, cnt of its elements exist.
+// One piece of one chunk: quad qi of the chunk for this lane; rem_elems elements of the chunk exist.
 // STORE: how the global weights are stored.  kThrough (keeps_results): written through and staying in the memory-side cache,
 // where the next pass reads them; the local ones, which no pass reads, are then written through and do not stay.
 template <bool G, bool SUM, int LOCAL, int GT, int STORE>
@@ -182,31 +182,30 @@ __device__ __forceinline__ void full_piece(const TensorDesc &d, const void *cons
     float *__restrict__ wg = d.w_global + 4 * quad0;
     float *__restrict__ wl = d.w_local + 4 * quad0;
     const void *__restrict__ grad = grad_at<GT>(d.grad, quad0);
-    const int cnt = quad_count<G>(rem_elems, qi);
-    if (G && cnt == 0) return;
-    const f4 w = ld4g<G>(wg, qi, cnt);
+    if (G && 4u * qi >= rem_elems) return;
+    const f4 w = ld4g<G>(wg, qi, rem_elems);
     f4 g = {0.0f, 0.0f, 0.0f, 0.0f}, a = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (SUM || LOCAL == kLocalRule || LOCAL == kLocalOnly) g = ldgrad<G, GT>(grad, qi, cnt);
+    if (SUM || LOCAL == kLocalRule || LOCAL == kLocalOnly) g = widen<G, GT>(load_grad<G, GT>(grad, qi, rem_elems), rem_elems);
     if (LOCAL == kLocalOnly) {
         f4 vl;
 #pragma unroll
         for (unsigned c = 0; c < 4; ++c) vl[c] = __builtin_fmaf(-lr_local, g[c], w[c]);
-        st4g<G, STORE>(wl, qi, cnt, vl);
+        st4g<G, STORE>(wl, qi, rem_elems, vl);
         return;
     }
-    if (!SUM) a = ld4g<G>(d.agg_full + 4 * quad0, qi, cnt);
+    if (!SUM) a = ld4g<G>(d.agg_full + 4 * quad0, qi, rem_elems);
     if (SUM) {
+        const auto load = [&](const void *peer) { return load_grad<G, GT>(grad_at<GT>(peer, quad0), qi, rem_elems); };
         // 32-bit gradients one at a time, each add waiting for its load, 16-bit ones (half the bytes a load) in pairs:
         // see the note on the launch shape
         const auto add = [&](int p, int end) {
             if (GT != kGradF32)
                 for (; p + 1 < end; p += 2) {
-                    const f4 u = ldgrad<G, GT>(grad_at<GT>(pg[p], quad0), qi, cnt);
-                    const f4 v = ldgrad<G, GT>(grad_at<GT>(pg[p + 1], quad0), qi, cnt);
-                    a = a + u;
-                    a = a + v;
+                    const GradQuad<GT> u = load(pg[p]), v = load(pg[p + 1]);
+                    a = a + widen<G, GT>(u, rem_elems);
+                    a = a + widen<G, GT>(v, rem_elems);
                 }
-            for (; p < end; ++p) a = a + ldgrad<G, GT>(grad_at<GT>(pg[p], quad0), qi, cnt);
+            for (; p < end; ++p) a = a + widen<G, GT>(load(pg[p]), rem_elems);
         };
         add(0, self);
         a = a + g;
@@ -218,8 +217,8 @@ __device__ __forceinline__ void full_piece(const TensorDesc &d, const void *cons
         vg[c] = __builtin_fmaf(-scale, a[c], w[c]);
         vl[c] = LOCAL == kLocalRule ? __builtin_fmaf(-lr_local, g[c], w[c]) : vg[c];
     }
-    if (LOCAL != kLocalNone) st4g<G, STORE == kThrough ? kThroughStream : STORE>(wl, qi, cnt, vl);
-    st4g<G, STORE>(wg, qi, cnt, vg);
+    if (LOCAL != kLocalNone) st4g<G, STORE == kThrough ? kThroughStream : STORE>(wl, qi, rem_elems, vl);
+    st4g<G, STORE>(wg, qi, rem_elems, vg);
 }
 
 // peer_grads: [num_tensors][num_peers] pointers (own row left out), or unused when !SUM.

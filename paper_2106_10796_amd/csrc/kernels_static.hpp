@@ -169,7 +169,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_arguments(unsigned num_til
                                                            scale, true, lds);
     } else if (tile * kQuads < bytes) {
         const unsigned elems0 = tile * kQuads * 4u;
-        fused_tile<true, SZ, WAVES, FORM, GT, false, HOW>(d, from, num_workers, self, quad, tile, elems > elems0 ? elems - elems0 : 0u,
+        fused_tile<true, SZ, WAVES, FORM, GT, false, HOW>(d, from, num_workers, self, quad, tile, elems_from(elems0, elems),
                                                           bytes - tile * kQuads, t, lr_local, scale, true, lds);
     }
 }

@@ -39,22 +39,21 @@ __device__ __forceinline__ void update_piece(float *__restrict__ wg, float *__re
                                              unsigned rem_elems, float lr_local, float scale)
 {
     const unsigned lane = threadIdx.x;
-    const int cnt = quad_count<G>(rem_elems, lane);
-    const f4 w = ld4g<G>(wg, lane, cnt);
+    const f4 w = ld4g<G>(wg, lane, rem_elems);
     f4 g = {0.0f, 0.0f, 0.0f, 0.0f}, a = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (LOCAL) g = LEN != kLargeTensor && (!G || cnt == 4) ? ld4_kept(grad, lane) : ld4g<G>(grad, lane, cnt);
-    if (GLOBAL) a = ld4g<G>(agg, lane, cnt);
+    if (LOCAL) g = ld4g<G, LEN != kLargeTensor ? 0 : kLoad>(grad, lane, rem_elems);
+    if (GLOBAL) a = ld4g<G>(agg, lane, rem_elems);
     if (LOCAL) {
         f4 v;
 #pragma unroll
         for (unsigned c = 0; c < 4; ++c) v[c] = __builtin_fmaf(-lr_local, g[c], w[c]);
-        st4g<G, kLocalStore<LEN>>(wl, lane, cnt, v);
+        st4g<G, kLocalStore<LEN>>(wl, lane, rem_elems, v);
     }
     if (GLOBAL) {
         f4 v;
 #pragma unroll
         for (unsigned c = 0; c < 4; ++c) v[c] = __builtin_fmaf(-scale, a[c], w[c]);
-        st4g<G, kTensorStore<LEN>>(wg, lane, cnt, v);
+        st4g<G, kTensorStore<LEN>>(wg, lane, rem_elems, v);
     }
 }
 
@@ -95,11 +94,10 @@ __global__ __launch_bounds__(L) void k_quantize_pack(const float *__restrict__ g
         st4p<kTensorStore<LEN>>(resid, lane, r);
         packed[lane] = (uint8_t)b;
     } else {
-        const int cnt = quad_count<true>(ext.tail_elems, lane);
-        const f4 g = ld4g<true>(grad, lane, cnt);
-        f4 r = ld4g<true>(resid, lane, cnt);
+        const f4 g = ld4g<true, LEN != kLargeTensor ? 0 : kLoad>(grad, lane, ext.tail_elems);
+        f4 r = ld4g<true>(resid, lane, ext.tail_elems);
         const unsigned b = quantize_quad(g, r, t, sent);
-        st4g<true, kTensorStore<LEN>>(resid, lane, cnt, r);
+        st4g<true, kTensorStore<LEN>>(resid, lane, ext.tail_elems, r);
         if (lane < ext.tail_bytes) packed[lane] = (uint8_t)b;
     }
 }
