@@ -374,6 +374,20 @@ bool keeps_results(unsigned num_chunks, int num_workers, bool sum)
     return tiles > (sum && num_workers > 2 ? 4u * 1024u : 768u) && tiles <= 14u * 1024u;
 }
 
+// Whether a pass that sums the workers' gradients asks for several workers' at once (kTogether): on short lists, which have
+// too few waves to keep the memory busy with one load (16-bit gradients: two) in flight each.  Time over that in order, three
+// sets of buffers in turn (N = 16 in us):
+//   32-bit   N = 6   0.1 M .98, 0.5 M .80, 0.7 M .93, 1 M .95, 1.5 M 1.00, 3 M 1.03      N = 8   .92, .72, .88, .97, 1.04, 1.05
+//            N = 16  0.1 M 7.6 / 4.0, 0.25 M 13.0 / 7.5, 0.5 M 10.5 / 7.1, 0.7 M 11.6 / 9.6, 1 M 13.7 / 13.1, 1.5 M 18.2 / 19.5
+//   16-bit   N = 6   0.5 M .99, 0.7 M 1.00, 1 M 1.04 (600 MB of sets .97), 2 M 1.07       N = 8   .94, .92, .96, 1.03
+//            N = 16  0.25 M 6.3 / 4.6, 0.5 M 7.0 / 5.3, 0.7 M 7.9 / 6.4, 1 M 8.9 / 8.3, 1.5 M 11.3 / 11.5
+// (Up to 4 workers nothing is gained and 1 M in 16 bits loses 11 %; 4 at once gain less up to 0.5 M, 16 at once are slower
+// from 0.7 M on.  Above, the order of the streams decides: 8 M, N = 16 92 / 107.)
+bool sums_together(unsigned num_chunks, int num_workers)
+{
+    return num_workers > 4 && num_chunks * kTilesPerChunk <= (num_workers > 6 ? 1024u : 768u);
+}
+
 // Launch one full-gradient pass (see k_fused_full) for a plan.
 int launch_full_pass(const PlanTables *plan, int local_mode, float lr_local, float lr_global, void *hip_stream)
 {
@@ -387,27 +401,31 @@ int launch_full_pass(const PlanTables *plan, int local_mode, float lr_local, flo
     // a pass with a workgroup limit is meant to share the GPU with other kernels: it leaves the LDS to them
     const unsigned lds_plain = plan->max_workgroups ? 0u : kLdsFor20Waves;
     const unsigned lds_sum = plan->max_workgroups ? 0u : lds_of_kernel_sum(plan->num_chunks, plan->num_workers, plan->grad_type);
-#define CDSGD_LAUNCH_FULL_T(SUM, LOCAL, GT, STORE)                                                             \
-    hipLaunchKernelGGL((k_fused_full<SUM, LOCAL, GT, STORE>), grid, block, (SUM ? lds_sum : lds_plain), s,              \
+#define CDSGD_LAUNCH_FULL_T(SUM, LOCAL, GT, STORE, IN_FLIGHT)                                                  \
+    hipLaunchKernelGGL((k_fused_full<SUM, LOCAL, GT, STORE, IN_FLIGHT>), grid, block, (SUM ? lds_sum : lds_plain), s,   \
                        plan->tensors, plan->chunk_table(),                                                      \
                        num_pieces, plan->peer_grads, np, plan->self, lr_local, scale)
-#define CDSGD_LAUNCH_FULL(SUM, LOCAL, STORE)                                                                   \
+#define CDSGD_LAUNCH_FULL(SUM, LOCAL, STORE, IN_FLIGHT)                                                        \
     do {                                                                                                       \
-        if (plan->grad_type == kGradBF16) CDSGD_LAUNCH_FULL_T(SUM, LOCAL, kGradBF16, STORE);                   \
-        else if (plan->grad_type == kGradF16) CDSGD_LAUNCH_FULL_T(SUM, LOCAL, kGradF16, STORE);                \
-        else CDSGD_LAUNCH_FULL_T(SUM, LOCAL, kGradF32, STORE);                                                 \
+        if (plan->grad_type == kGradBF16) CDSGD_LAUNCH_FULL_T(SUM, LOCAL, kGradBF16, STORE, IN_FLIGHT);        \
+        else if (plan->grad_type == kGradF16) CDSGD_LAUNCH_FULL_T(SUM, LOCAL, kGradF16, STORE, IN_FLIGHT);     \
+        else CDSGD_LAUNCH_FULL_T(SUM, LOCAL, kGradF32, STORE, IN_FLIGHT);                                      \
     } while (0)
     const bool keep = plan->max_workgroups == 0 && keeps_results(plan->num_chunks, plan->num_workers, sum);
-    if (sum) {
-        if (local_mode == kLocalNone) CDSGD_LAUNCH_FULL(true, kLocalNone, kStream);
-        else if (local_mode == kLocalCopy) CDSGD_LAUNCH_FULL(true, kLocalCopy, kStream);
-        else if (keep) CDSGD_LAUNCH_FULL(true, kLocalRule, kThrough);
-        else CDSGD_LAUNCH_FULL(true, kLocalRule, kStream);
+    if (sum && sums_together(plan->num_chunks, plan->num_workers)) {
+        if (local_mode == kLocalNone) CDSGD_LAUNCH_FULL(true, kLocalNone, kStream, kTogether);
+        else if (local_mode == kLocalCopy) CDSGD_LAUNCH_FULL(true, kLocalCopy, kStream, kTogether);
+        else CDSGD_LAUNCH_FULL(true, kLocalRule, kStream, kTogether);
+    } else if (sum) {
+        if (local_mode == kLocalNone) CDSGD_LAUNCH_FULL(true, kLocalNone, kStream, kInOrder);
+        else if (local_mode == kLocalCopy) CDSGD_LAUNCH_FULL(true, kLocalCopy, kStream, kInOrder);
+        else if (keep) CDSGD_LAUNCH_FULL(true, kLocalRule, kThrough, kInOrder);
+        else CDSGD_LAUNCH_FULL(true, kLocalRule, kStream, kInOrder);
     } else {
-        if (local_mode == kLocalNone) CDSGD_LAUNCH_FULL(false, kLocalNone, kStream);
-        else if (local_mode == kLocalCopy) CDSGD_LAUNCH_FULL(false, kLocalCopy, kStream);
-        else if (keep) CDSGD_LAUNCH_FULL(false, kLocalRule, kThrough);
-        else CDSGD_LAUNCH_FULL(false, kLocalRule, kStream);
+        if (local_mode == kLocalNone) CDSGD_LAUNCH_FULL(false, kLocalNone, kStream, kInOrder);
+        else if (local_mode == kLocalCopy) CDSGD_LAUNCH_FULL(false, kLocalCopy, kStream, kInOrder);
+        else if (keep) CDSGD_LAUNCH_FULL(false, kLocalRule, kThrough, kInOrder);
+        else CDSGD_LAUNCH_FULL(false, kLocalRule, kStream, kInOrder);
     }
 #undef CDSGD_LAUNCH_FULL
 #undef CDSGD_LAUNCH_FULL_T
@@ -1015,7 +1033,7 @@ int launch_local_pass(const PlanTables *plan, float lr_local, void *hip_stream)
     const dim3 grid(plan->grid_size(num_pieces, kFullBlock)), block(kFullBlock);
     hipStream_t s = (hipStream_t)hip_stream;
 #define CDSGD_LAUNCH_LOCAL(GT)                                                                                 \
-    hipLaunchKernelGGL((k_fused_full<false, kLocalOnly, GT, kStream>), grid, block, 0, s, plan->tensors,                  \
+    hipLaunchKernelGGL((k_fused_full<false, kLocalOnly, GT, kStream, kInOrder>), grid, block, 0, s, plan->tensors,                  \
                        plan->chunk_table(), num_pieces, (const void *const *)nullptr, 0, plan->self, lr_local,   \
                        0.0f)
     if (plan->grad_type == kGradBF16) CDSGD_LAUNCH_LOCAL(kGradBF16);

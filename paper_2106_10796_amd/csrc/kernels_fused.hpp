@@ -167,14 +167,18 @@ constexpr int kLocalOnly = 3;  // eq. 11 alone: w_local = W - lr_local * g, the 
 // worse with 32-bit gradients (VGG-16-shaped, N = 8 / 16: 0.967 / 1.731 ms, 0.918 / 1.631 one at a time; 25 M
 // elements, N = 16: 327 and 309 us) and better with 16-bit ones, whose loads are half as large (VGG-16-shaped,
 // N = 16: 0.929 ms, 1.148 one at a time; 25 M elements, N = 16: 183 and 204 us; 4 M, N = 8: 20.7 and 21.4 us).
+// On short lists there are too few waves for that: with each worker's pointer and gradient waited for in turn the pass took two
+// trips to memory a worker, whatever its length.  There kTogether of them are asked for at once, their pointers in one piece
+// (sums_together, with the times).
 constexpr unsigned kFullBlock = CDSGD_FULL_BLOCK;            // lanes per workgroup = quads per piece
 constexpr unsigned kPiecesPerChunk = kChunkQuads / kFullBlock;
+constexpr int kInOrder = 0, kTogether = 8;  // IN_FLIGHT
 static_assert(kChunkQuads % kFullBlock == 0 && kFullBlock % 64 == 0, "pieces tile a chunk, whole waves");
 
 // One piece of one chunk: quad qi of the chunk for this lane; rem_elems elements of the chunk exist.
 // STORE: how the global weights are stored.  kThrough (keeps_results): written through and staying in the memory-side cache,
 // where the next pass reads them; the local ones, which no pass reads, are then written through and do not stay.
-template <bool G, bool SUM, int LOCAL, int GT, int STORE>
+template <bool G, bool SUM, int LOCAL, int GT, int STORE, int IN_FLIGHT>
 __device__ __forceinline__ void full_piece(const TensorDesc &d, const void *const *__restrict__ pg,
                                            int num_peers, int self, size_t quad0, unsigned qi,
                                            unsigned rem_elems, float lr_local, float scale)
@@ -196,20 +200,41 @@ __device__ __forceinline__ void full_piece(const TensorDesc &d, const void *cons
     if (!SUM) a = ld4g<G>(d.agg_full + 4 * quad0, qi, rem_elems);
     if (SUM) {
         const auto load = [&](const void *peer) { return load_grad<G, GT>(grad_at<GT>(peer, quad0), qi, rem_elems); };
-        // 32-bit gradients one at a time, each add waiting for its load, 16-bit ones (half the bytes a load) in pairs:
-        // see the note on the launch shape
-        const auto add = [&](int p, int end) {
-            if (GT != kGradF32)
-                for (; p + 1 < end; p += 2) {
-                    const GradQuad<GT> u = load(pg[p]), v = load(pg[p + 1]);
-                    a = a + widen<G, GT>(u, rem_elems);
-                    a = a + widen<G, GT>(v, rem_elems);
-                }
-            for (; p < end; ++p) a = a + widen<G, GT>(load(pg[p]), rem_elems);
-        };
-        add(0, self);
-        a = a + g;
-        add(self, num_peers);
+        if constexpr (IN_FLIGHT == kInOrder) {
+            // 32-bit gradients one at a time, each add waiting for its load, 16-bit ones (half the bytes a load) in pairs:
+            // see the note on the launch shape
+            const auto add = [&](int p, int end) {
+                if (GT != kGradF32)
+                    for (; p + 1 < end; p += 2) {
+                        const GradQuad<GT> u = load(pg[p]), v = load(pg[p + 1]);
+                        a = a + widen<G, GT>(u, rem_elems);
+                        a = a + widen<G, GT>(v, rem_elems);
+                    }
+                for (; p < end; ++p) a = a + widen<G, GT>(load(pg[p]), rem_elems);
+            };
+            add(0, self);
+            a = a + g;
+            add(self, num_peers);
+        } else {
+            for (int p = 0; p < num_peers; p += IN_FLIGHT) {
+                const void *peer[IN_FLIGHT];  // fetched in one piece, then all the loads
+                GradQuad<GT> u[IN_FLIGHT];
+#pragma unroll
+                for (int k = 0; k < IN_FLIGHT; ++k) peer[k] = pg[p + k < num_peers ? p + k : num_peers - 1];
+#pragma unroll
+                for (int k = 0; k < IN_FLIGHT; ++k) asm volatile("" : "+s"(peer[k]));
+#pragma unroll
+                for (int k = 0; k < IN_FLIGHT; ++k)
+                    if (p + k < num_peers) u[k] = load(peer[k]);
+#pragma unroll
+                for (int k = 0; k < IN_FLIGHT; ++k)
+                    if (p + k < num_peers) {
+                        if (p + k == self) a = a + g;
+                        a = a + widen<G, GT>(u[k], rem_elems);
+                    }
+            }
+            if (self == num_peers) a = a + g;
+        }
     }
     f4 vg, vl;
 #pragma unroll
@@ -223,7 +248,7 @@ __device__ __forceinline__ void full_piece(const TensorDesc &d, const void *cons
 
 // peer_grads: [num_tensors][num_peers] pointers (own row left out), or unused when !SUM.
 // The grid walks the pieces of the chunk table: piece x belongs to chunk slot x / kPiecesPerChunk.
-template <bool SUM, int LOCAL, int GT, int STORE>
+template <bool SUM, int LOCAL, int GT, int STORE, int IN_FLIGHT>
 __global__ __launch_bounds__(CDSGD_FULL_BLOCK) void k_fused_full(const TensorDesc *__restrict__ tensors,
                                                                  const ChunkRef *__restrict__ chunks,
                                                                  unsigned long long num_pieces,
@@ -239,9 +264,9 @@ __global__ __launch_bounds__(CDSGD_FULL_BLOCK) void k_fused_full(const TensorDes
         const unsigned qi = (unsigned)(x % kPiecesPerChunk) * kFullBlock + threadIdx.x;
         const void *const *pg = SUM ? peer_grads + (size_t)cr.tensor * (size_t)num_peers : nullptr;
         if (cr.chunk < d.ext.full_chunks)
-            full_piece<false, SUM, LOCAL, GT, STORE>(d, pg, num_peers, self, quad0, qi, kChunkElems, lr_local, scale);
+            full_piece<false, SUM, LOCAL, GT, STORE, IN_FLIGHT>(d, pg, num_peers, self, quad0, qi, kChunkElems, lr_local, scale);
         else
-            full_piece<true, SUM, LOCAL, GT, STORE>(d, pg, num_peers, self, quad0, qi, d.ext.tail_elems, lr_local, scale);
+            full_piece<true, SUM, LOCAL, GT, STORE, IN_FLIGHT>(d, pg, num_peers, self, quad0, qi, d.ext.tail_elems, lr_local, scale);
     }
 }
 
