@@ -1167,8 +1167,9 @@ int cdsgd_sparse_encode(const uint32_t *packed, size_t n, uint32_t *sparse, uint
     if (overlap2(packed, pb, sparse, sb) || overlap2(packed, pb, segment_words, cb) ||
         overlap2(sparse, sb, segment_words, cb))
         return CDSGD_ERR_ALIAS;
-    hipLaunchKernelGGL(k_sparse_encode, dim3((unsigned)cdsgd_sparse_segments(n)), dim3(256), 0,
-                       (hipStream_t)hip_stream, packed, (unsigned long long)((n + 15) / 16), sparse, segment_words);
+    const unsigned segments = (unsigned)cdsgd_sparse_segments(n);
+    hipLaunchKernelGGL(k_sparse_encode, dim3((segments + kEncodeWaves - 1u) / kEncodeWaves), dim3(64 * kEncodeWaves), 0,
+                       (hipStream_t)hip_stream, packed, (unsigned long long)((n + 15) / 16), sparse, segment_words, segments);
     return launch_status();
 }
 
