@@ -75,13 +75,13 @@ __device__ __forceinline__ void st4p(float *base, unsigned qi, f4 v)
     }
 }
 
-// A lane's byte of the packed stream, at most a chunk behind `base`.  THROUGH: written through (kThroughStream).
-template <bool THROUGH>
+// A lane's byte of the packed stream, at most a chunk behind `base`.  POLICY 0: the default.
+template <int POLICY>
 __device__ __forceinline__ void st_code(uint8_t *base, unsigned qi, unsigned byte)
 {
-    if constexpr (THROUGH) {
+    if constexpr (POLICY != 0) {
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)kChunkQuads, kBufferFlags);
-        __builtin_amdgcn_raw_buffer_store_b8((unsigned char)byte, rsrc, (int)qi, 0, kThroughStream);
+        __builtin_amdgcn_raw_buffer_store_b8((unsigned char)byte, rsrc, (int)qi, 0, POLICY);
     } else {
         global_ptr(base)[qi] = (uint8_t)byte;
     }

@@ -69,7 +69,7 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
     f4 sent;
     const unsigned own = quantize_quad(g, r, t, sent);
     st4g<G, kStore>(resid, tid, rem_elems, r);
-    if (!G || tid < rem_bytes) st_code<OUT>(pself, tid, own);
+    if (!G || tid < rem_bytes) st_code<OUT ? kThroughStream : 0>(pself, tid, own);
 
     // eq. 11 and eq. 10 from the same loaded weight
     f4 vl, vg;
