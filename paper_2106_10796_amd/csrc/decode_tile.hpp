@@ -20,12 +20,13 @@ constexpr int kWordsPerWave = kMaxRows<SZ> / 4;
 
 typedef unsigned u4 __attribute__((ext_vector_type(4)));
 
-// values of the codes of a register, as 2-bit two's-complement fields (01 -> +1, 10 -> -1, else 0)
+// values of the codes of a register, as 2-bit two's-complement fields (01 -> +1, 10 -> -1, else 0): the low bit is low ^ high,
+// the high bit high & ~low.
 __device__ __forceinline__ unsigned signed_fields(unsigned w)
 {
-    const unsigned x = w & 0x55555555u;
-    const unsigned y = (w >> 1) & 0x55555555u;
-    return (x ^ y) | ((y & ~x) << 1);
+    constexpr unsigned kLow = 0x55555555u;
+    const unsigned low = __builtin_amdgcn_bitop3_b32(w, w >> 1, kLow, 0x28);    // (w ^ w >> 1) & kLow
+    return __builtin_amdgcn_bitop3_b32(low, w, (w << 1) | kLow, 0xF4);          // low | w & ~(w << 1 | kLow)
 }
 
 // A row of stream pointers: one entry per worker, in worker order, null where there is nothing to load (the own
@@ -317,10 +318,15 @@ __device__ __forceinline__ void chain_byte(f4 &acc, unsigned byte, float t)
 // exchange the sums (decode-and-sum of 2^27 elements, N = 32: 0.270 ms by words, 0.298 by bytes).
 template <int SZ>
 constexpr bool kByBytes = SZ != kAnyWorkers && SZ <= kUpTo16;
+template <int SZ>
+constexpr bool kSlotTests = SZ == kUpTo4 || SZ == kUpTo8;  // tile_put
+template <int SZ>
+constexpr unsigned kSpareRow = (unsigned)kMaxRows<SZ>;  // written and not read; where there are sums they follow later
+template <int SZ>
+constexpr unsigned kRowsLds = (unsigned)kMaxRows<SZ> * kTileBytes +
+                              (!kByBytes<SZ> ? 16u * kTileQuads : (kSlotTests<SZ> ? 0u : kTileBytes));
 template <int SZ, int FORM, int WAVES>
-constexpr unsigned kTileLds = (FORM == kCount ? 4u * 4u * kTileQuads
-                                              : (unsigned)kMaxRows<SZ> * kTileBytes + (kByBytes<SZ> ? 0u : 16u * kTileQuads)) *
-                              WAVES / 4;
+constexpr unsigned kTileLds = (FORM == kCount ? 4u * 4u * kTileQuads : kRowsLds<SZ>) * WAVES / 4;
 
 template <int WAVES>
 __device__ __forceinline__ void group_sync()
@@ -353,7 +359,7 @@ struct TilePlace {
 // come as this lane's packed byte and as the values it stands for, own_at is their place in the order (-1: none).
 // In two halves, with a barrier between them: the first leaves in LDS what the waves know of their workers, the second
 // reads it.  Everything a group has written to LDS before has been read when it starts over (a barrier of the caller's).
-template <int SZ, int FORM, int WAVES>
+template <int SZ, int FORM, int WAVES, bool SPARSE>
 __device__ __forceinline__ void tile_put(const unsigned (&w)[kWordsPerWave<SZ>], unsigned own_code, int own_at,
                                          int num_workers, uint8_t *lds, TilePlace<WAVES> at)
 {
@@ -376,12 +382,23 @@ __device__ __forceinline__ void tile_put(const unsigned (&w)[kWordsPerWave<SZ>],
         q[3] = __builtin_amdgcn_perm(y1, x1, 0x07060302u);
         reinterpret_cast<u4 *>(lds)[tid] = q;  // [wave][word][quad]
     } else {
-        // rows of signed fields, worker by worker; the rows up to the next multiple of four are zero
+        // Rows of signed fields, worker by worker; those past the last worker are zero.  Packed streams of more than eight
+        // workers: every slot is written without a test.  Behind a test of its own (a slot past the last worker, the own one) the compiler puts the load of
+        // the slot's word as well, and a wave of the kernels for any number of workers then waited for memory twice: 16.7 M
+        // elements decoded and updated, t = 0.3, N = 33 / 48 / 64 80.3 / 88.2 / 103.6 us, 68.0 / 79.0 / 91.8 so;  4 M 22.3 /
+        // 25.0 / 29.4, 19.5 / 22.5 / 25.6;  compressed pass 0.5 M N = 32 / 64 4.6 / 6.8, 4.4 / 6.3;  1 M 7.2 / 10.2, 6.9 / 9.8;
+        // 4 M 22.4 / 28.0, 22.1 / 27.6.  The own row is made of the lanes' own codes; what the wave holds for it goes to
+        // the spare row.  (Sparse streams, whose words have to wait for their bitmaps: N = 64 2-6 % faster without tests, 33 to 48
+        // 1-5 % slower; packed streams of 5 to 8 workers, 60 M elements 1 % slower.)
         unsigned *rows = reinterpret_cast<unsigned *>(lds);
 #pragma unroll
         for (int i = 0; i < kWordsPerWave<SZ>; ++i) {
             const int j = worker_of<SZ>(wave, i);
-            if (j != own_at && (SZ != kAnyWorkers || 16 * (i / 4) < num_workers)) rows[kWords * (unsigned)j + lane] = signed_fields(w[i]);
+            if constexpr (SPARSE || kSlotTests<SZ>) {
+                if (j != own_at && (SZ != kAnyWorkers || 16 * (i / 4) < num_workers)) rows[kWords * (unsigned)j + lane] = signed_fields(w[i]);
+            } else {
+                rows[kWords * (j != own_at ? (unsigned)j : kSpareRow<SZ>) + lane] = signed_fields(w[i]);
+            }
         }
         if (own_at >= 0) lds[kBytes * (unsigned)own_at + tid] = (uint8_t)signed_fields(own_code);
     }
@@ -439,12 +456,12 @@ __device__ __forceinline__ f4 tile_get(f4 own_value, int num_workers, float t, u
     return agg;
 }
 
-template <int SZ, int FORM, int WAVES>
+template <int SZ, int FORM, int WAVES, bool SPARSE>
 __device__ __forceinline__ f4 tile_sums(const unsigned (&w)[kWordsPerWave<SZ>], unsigned own_code, f4 own_value,
                                         int own_at, int num_workers, float t, uint8_t *lds)
 {
     const TilePlace<WAVES> at;
-    tile_put<SZ, FORM, WAVES>(w, own_code, own_at, num_workers, lds, at);
+    tile_put<SZ, FORM, WAVES, SPARSE>(w, own_code, own_at, num_workers, lds, at);
     group_sync<WAVES>();
     return tile_get<SZ, FORM, WAVES>(own_value, num_workers, t, lds, at);
 }
@@ -504,7 +521,7 @@ __global__ __launch_bounds__(kTileQuads) void k_decode_sum(StreamTable tab, int 
         else load_packed<SZ, NT>(words[k], from.p, s, wave, tid & 63u);
     }
 #pragma unroll
-    for (unsigned k = 0; k < TILES; ++k) tile_put<SZ, FORM, 4>(words[k], 0u, -1, num_workers, lds + kLds * k, at);
+    for (unsigned k = 0; k < TILES; ++k) tile_put<SZ, FORM, 4, SPARSE>(words[k], 0u, -1, num_workers, lds + kLds * k, at);
     group_sync<4>();
     float *out = agg_out + (size_t)x * (4u * kTileQuads * TILES);
 #pragma unroll

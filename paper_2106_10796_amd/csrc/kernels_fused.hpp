@@ -77,7 +77,7 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
     for (unsigned c = 0; c < 4; ++c) vl[c] = __builtin_fmaf(-lr_local, g[c], w[c]);
     if (kLocalFirst<SZ, FORM> && write_local) st4g<G, kStore>(wl, tid, rem_elems, vl);
 
-    const f4 agg = tile_sums<SZ, FORM, WAVES>(words, own, sent, self, num_workers, t, lds);
+    const f4 agg = tile_sums<SZ, FORM, WAVES, SPARSE>(words, own, sent, self, num_workers, t, lds);
 #pragma unroll
     for (unsigned c = 0; c < 4; ++c) vg[c] = __builtin_fmaf(-scale, agg[c], w[c]);
     if (!kLocalFirst<SZ, FORM> && write_local) st4g<G, kStore>(wl, tid, rem_elems, vl);
