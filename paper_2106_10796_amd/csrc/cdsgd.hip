@@ -956,22 +956,30 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
     // VGG-16-shaped 1.00 / 1.03 / 1.00;  t = 0.3, bf16 1 M .90 / .91 / .92, 4 M .93, VGG-16-shaped .94 / .97 / .98.
     const bool sparse32 = N <= kUpTo32 && plan->max_workgroups == 0 &&
                           (plan->grad_type != kGradF32 || plan->num_chunks * kTilesPerChunk <= kLongListTiles);
+    // 17 to 32 workers, lists of 2 to 16 M elements (in arenas, written through): the weights are asked for behind gradient and
+    // residual.  Time over that of asking for all at once, three and six sets of buffers in turn, 2.2 / 3 / 5 / 8 / 12 / 16.5 M:
+    //   N = 17, t = 0.5  .99 .99 .99 .99 .99 .99, bf16 .98 .98 .98 .99 .99 .99, fp16 .98-1.00;  N = 20, t = 0.3  .97 .98 .99 .99 .99 .99-1.00,
+    //   bf16 .95-.96 .96 .97 .98 .99 .99;  N = 24, t = 0.3  .98 .98 .99 .99 .99 1.00, bf16 .96 .96 .98 .98 .99 .99;  N = 32, t = 0.5 .98 .99
+    //   .99 .99 .98-.99 .99, bf16 .97 .97 .98 .99 .99 .99;  N = 32, t = 0.3  .98 .98 .99 .99 .99 1.00, bf16 .96 .97 .99 .99 .99 .99
+    // (25 M 1.00-1.02, VGG-16-shaped 1.00;  9 to 16 workers, t = 0.5: 1.1 M .96, 1.5 M 1.02, 3 M 1.01, 8 to 16 M .99, 25 M 1.01, 25 M in bf16 1.03)
+    const bool weights_wait = plan->num_chunks * kTilesPerChunk <= kMidListTiles;
     const auto bound = [&](unsigned used) { return shape.lds <= used ? 0u : shape.lds - used; };
-#define CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, GT, SPARSE, HOW)                                            \
-    hipLaunchKernelGGL((k_fused_compressed<SZ, WAVES, FORM, GT, SPARSE, HOW>), dim3(grid), dim3(64 * WAVES),   \
+#define CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT)                                      \
+    hipLaunchKernelGGL((k_fused_compressed<SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT>), dim3(grid), dim3(64 * WAVES), \
                        bound(kTileLds<SZ, FORM, WAVES>), s, plan->tensors, plan->table_for<HOW>(), plan->rows, \
                        num_tiles, grid, N, plan->self, threshold, lr_local, scale, with_local ? 1 : 0)
-#define CDSGD_LAUNCH_COMPRESSED(SZ, WAVES, FORM, SPARSE, HOW)                                                  \
+#define CDSGD_LAUNCH_COMPRESSED_W(SZ, WAVES, FORM, SPARSE, HOW, WAIT)                                          \
     do {                                                                                                       \
-        if (plan->grad_type == kGradBF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradBF16, SPARSE, HOW);  \
-        else if (plan->grad_type == kGradF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF16, SPARSE, HOW); \
-        else CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF32, SPARSE, HOW);                                \
+        if (plan->grad_type == kGradBF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradBF16, SPARSE, HOW, WAIT); \
+        else if (plan->grad_type == kGradF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF16, SPARSE, HOW, WAIT); \
+        else CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF32, SPARSE, HOW, WAIT);                          \
     } while (0)
+#define CDSGD_LAUNCH_COMPRESSED(SZ, WAVES, FORM, SPARSE, HOW) CDSGD_LAUNCH_COMPRESSED_W(SZ, WAVES, FORM, SPARSE, HOW, false)
 // (the count form of 9 to 16 workers asks for the words last with 32-bit gradients only: compressed_launch)
 #define CDSGD_LAUNCH_COMPRESSED_32BIT(SZ, WAVES, FORM, SPARSE, HOW)                                            \
     do {                                                                                                       \
         if (plan->grad_type != kGradF32) return CDSGD_ERR_DEVICE;                                              \
-        CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF32, SPARSE, HOW);                                     \
+        CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF32, SPARSE, HOW, false);                              \
     } while (0)
 // Every shape has a kernel of its own; one that has none is an error, for another kernel may read the tables otherwise.
 #define CDSGD_LAUNCH_COMPRESSED_F(FORM, LAUNCH_LATE)                                                           \
@@ -986,6 +994,7 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
         else if (N <= kUpTo8 && shape.how == kArena) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, false, kArena);  \
         else if (N <= kUpTo8 && shape.how == 0) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, false, 0);            \
         else if (N <= kUpTo8) return CDSGD_ERR_DEVICE;                                                         \
+        else if (shape.how == (kUpTo32Rows | kWrittenOut | kArena) && weights_wait) CDSGD_LAUNCH_COMPRESSED_W(kUpTo32, 4, FORM, false, kWrittenOut | kArena, true); \
         else if (shape.how == (kUpTo32Rows | kWrittenOut | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, kWrittenOut | kArena); \
         else if (shape.how == (kUpTo32Rows | kWrittenOut)) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, kWrittenOut); \
         else if (shape.how == (kUpTo32Rows | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, kArena); \
@@ -1009,6 +1018,7 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
     else CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, kChainTiny, false, 0);
 #undef CDSGD_LAUNCH_COMPRESSED_32BIT
 #undef CDSGD_LAUNCH_COMPRESSED
+#undef CDSGD_LAUNCH_COMPRESSED_W
 #undef CDSGD_LAUNCH_COMPRESSED_F
 #undef CDSGD_LAUNCH_COMPRESSED_S
     return launch_status();

@@ -30,7 +30,9 @@ struct ChunkEntry { typedef ChunkRef type; };
 template <>
 struct ChunkEntry<kArena> { typedef ArenaChunk type; };
 
-template <bool G, int SZ, int WAVES, int FORM, int GT, bool SPARSE, int HOW>
+// WAIT: the weights are asked for when gradient and residual are there, not with them: less in flight at a time, and on lists
+// of a few million elements that is served faster (launch_formal_pass, with the times).
+template <bool G, int SZ, int WAVES, int FORM, int GT, bool SPARSE, int HOW, bool WAIT>
 __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPointers<SZ, WAVES, SPARSE> &from, int num_workers,
                                            int self, unsigned chunk, unsigned tile, unsigned rem_elems,
                                            unsigned rem_bytes, float t, float lr_local, float scale, bool write_local,
@@ -58,7 +60,8 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
     if (!LATE) load_words<SZ, WAVES, SPARSE, NT>(words, from, s, wave, tid & 63u);
     const GradQuad<GT> loaded = load_grad<G, GT>(grad, tid, rem_elems);
     f4 r = ld4g<G>(resid, tid, rem_elems);
-    const f4 w = ld4g<G>(wg, tid, rem_elems);
+    f4 w;
+    if (!WAIT) w = ld4g<G>(wg, tid, rem_elems);
     if (LATE) {
         __builtin_amdgcn_sched_barrier(0);
         load_words<SZ, WAVES, SPARSE, NT>(words, from, s, wave, tid & 63u);
@@ -66,6 +69,12 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
 
     // own codes: quantise, keep the residual, write what would be pushed
     const f4 g = widen<G, GT>(loaded, rem_elems);
+    if (WAIT) {
+        asm volatile("" ::"v"(g.x), "v"(r.x));
+        __builtin_amdgcn_sched_barrier(0);
+        w = ld4g<G>(wg, tid, rem_elems);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     f4 sent;
     const unsigned own = quantize_quad(g, r, t, sent);
     st4g<G, kStore>(resid, tid, rem_elems, r);
@@ -85,7 +94,7 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
 }
 
 // write_local: eq. 11 as well (false: the global half of a split step)
-template <int SZ, int WAVES, int FORM, int GT, bool SPARSE, int HOW>
+template <int SZ, int WAVES, int FORM, int GT, bool SPARSE, int HOW, bool WAIT>
 __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDesc *__restrict__ tensors,
                                                                  const typename ChunkEntry<HOW & kArena>::type *__restrict__ chunks,
                                                                  const uint8_t *const *__restrict__ rows,
@@ -110,11 +119,11 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
             d.ext.full_chunks = 0u;
             d.ext.tail_bytes = quad + bytes;  // where the chunk's codes end in a stream
             if (at.elems == kChunkElems) {
-                fused_tile<false, SZ, WAVES, FORM, GT, SPARSE, HOW>(d, from, num_workers, self, quad, tile, kQuads * 4u, kQuads,
+                fused_tile<false, SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT>(d, from, num_workers, self, quad, tile, kQuads * 4u, kQuads,
                                                                     t_call, lr_local, scale, write_local != 0, lds);
             } else if (tile * kQuads < bytes) {
                 const unsigned elems0 = tile * kQuads * 4u;
-                fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, HOW>(d, from, num_workers, self, quad, tile,
+                fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT>(d, from, num_workers, self, quad, tile,
                                                                    elems_from(elems0, at.elems), bytes - tile * kQuads,
                                                                    t_call, lr_local, scale, write_local != 0, lds);
             }
@@ -125,12 +134,12 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
             from.pin();
             const float t = d.threshold > 0.0f ? d.threshold : t_call;
             if (at.chunk < d.ext.full_chunks) {
-                fused_tile<false, SZ, WAVES, FORM, GT, SPARSE, HOW>(d, from, num_workers, self, at.chunk, tile, kQuads * 4u, kQuads,
+                fused_tile<false, SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT>(d, from, num_workers, self, at.chunk, tile, kQuads * 4u, kQuads,
                                                         t, lr_local, scale, write_local != 0, lds);
             } else if (tile * kQuads < d.ext.tail_bytes) {
                 // (the packed bytes of the ragged end cover its elements: tiles past them have nothing to do)
                 const unsigned elems0 = tile * kQuads * 4u;
-                fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, HOW>(d, from, num_workers, self, at.chunk, tile,
+                fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT>(d, from, num_workers, self, at.chunk, tile,
                                                        elems_from(elems0, d.ext.tail_elems),
                                                        d.ext.tail_bytes - tile * kQuads, t, lr_local, scale,
                                                        write_local != 0, lds);
