@@ -492,8 +492,8 @@ struct StreamTable {
 };
 
 template <int SZ, int FORM, bool SPARSE, int TILES, bool NT>
-__global__ __launch_bounds__(kTileQuads) void k_decode_sum(StreamTable tab, int num_workers, float *__restrict__ agg_out,
-                                                           Extent ext, unsigned num_groups, int xcd, int drain, float t)
+__global__ __launch_bounds__(kTileQuads) void k_decode_sum(float *__restrict__ agg_out, Extent ext, int num_workers,
+                                                           unsigned num_groups, int xcd, int drain, float t, StreamTable tab)
 {
     static_assert(kTilesPerChunk % TILES == 0, "the tiles of a group lie in one chunk");
     constexpr unsigned kPerChunk = kTilesPerChunk / TILES, kLds = kTileLds<SZ, FORM, 4>;
