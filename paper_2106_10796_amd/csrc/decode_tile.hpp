@@ -404,7 +404,7 @@ __device__ __forceinline__ void tile_put(const unsigned (&w)[kWordsPerWave<SZ>],
     }
 }
 
-template <int SZ, int FORM, int WAVES>
+template <int SZ, int FORM, int WAVES, bool SPREAD>
 __device__ __forceinline__ f4 tile_get(f4 own_value, int num_workers, float t, uint8_t *lds, TilePlace<WAVES> at)
 {
     constexpr unsigned kQuads = 64u * WAVES, kBytes = kQuads;
@@ -443,13 +443,19 @@ __device__ __forceinline__ f4 tile_get(f4 own_value, int num_workers, float t, u
 #pragma unroll
                 for (int k = 0; k < 4; ++k) chain_pairs(acc, rows[kTileWords * (j0 + k) + lane], shift, t);
             }
-            // elements 2 v, 2 v + 1 and 2 v + 8, 2 v + 9 of word l -> quads
+            // Elements 2 v, 2 v + 1 and 2 v + 8, 2 v + 9 of word l -> quads.  SPREAD: word l's four quads lie in an order that goes
+            // by l / 4; in plain order the lanes of a wave write to an eighth of the banks.  Time spread over plain: decode and
+            // update, sparse streams, t = 0.3 1.5 M elements N = 17 / 24 / 32 / 64 .98 / .97 / .97 / .99, 4 M .99, 16.7 and 40 M .99-1.00;
+            // compressed pass N = 32 0.5 M .96, bf16 .98, 4 M .99, N = 64 0.5 M .96, bf16 .95, 1 M .98, 12 and 25 M 1.00.  Packed streams
+            // of a single tensor keep the plain order: 1.5 M .98-1.00, but 8 to 40 M 1.01-1.03 (with rows 20 floats apart the
+            // same): their groups are through sooner, and the order in which memory is asked is the worse one.
             typedef float f2 __attribute__((ext_vector_type(2)));
             float *sums = reinterpret_cast<float *>(lds + (unsigned)kMaxRows<SZ> * kTileBytes);
-            *reinterpret_cast<f2 *>(sums + 16u * lane + 2u * (unsigned)wave) = f2{acc[0], acc[1]};
-            *reinterpret_cast<f2 *>(sums + 16u * lane + 2u * (unsigned)wave + 8u) = f2{acc[2], acc[3]};
+            const unsigned quad = 4u * lane + (((unsigned)wave >> 1) ^ (SPREAD ? lane >> 2 & 3u : 0u)), half = 2u * ((unsigned)wave & 1u);
+            *reinterpret_cast<f2 *>(sums + 4u * quad + half) = f2{acc[0], acc[1]};
+            *reinterpret_cast<f2 *>(sums + 4u * (quad ^ 2u) + half) = f2{acc[2], acc[3]};
             group_sync<WAVES>();
-            agg = reinterpret_cast<const f4 *>(sums)[tid];
+            agg = reinterpret_cast<const f4 *>(sums)[tid ^ (SPREAD ? tid >> 4 & 3u : 0u)];
         }
         if (tiny) agg = agg * 0x1p-64f;
     }
@@ -463,7 +469,7 @@ __device__ __forceinline__ f4 tile_sums(const unsigned (&w)[kWordsPerWave<SZ>], 
     const TilePlace<WAVES> at;
     tile_put<SZ, FORM, WAVES, SPARSE>(w, own_code, own_at, num_workers, lds, at);
     group_sync<WAVES>();
-    return tile_get<SZ, FORM, WAVES>(own_value, num_workers, t, lds, at);
+    return tile_get<SZ, FORM, WAVES, true>(own_value, num_workers, t, lds, at);
 }
 
 // ---------------------------------------------------------------------------
@@ -526,7 +532,7 @@ __global__ __launch_bounds__(kTileQuads) void k_decode_sum(float *__restrict__ a
     float *out = agg_out + (size_t)x * (4u * kTileQuads * TILES);
 #pragma unroll
     for (unsigned k = 0; k < TILES; ++k) {
-        const f4 agg = tile_get<SZ, FORM, 4>(f4{0.0f, 0.0f, 0.0f, 0.0f}, num_workers, t, lds + kLds * k, at);
+        const f4 agg = tile_get<SZ, FORM, 4, SPARSE>(f4{0.0f, 0.0f, 0.0f, 0.0f}, num_workers, t, lds + kLds * k, at);
         const unsigned qi = kTileQuads * k + tid;
         if (chunk < ext.full_chunks) {
             if (drain) st4p<kStream>(out, qi, agg);
