@@ -807,6 +807,14 @@ namespace {
 //     N = 9 / 16, t = 0.5      VGG-16   .97 / 1.01, .97 / .99     1.00 / .98, 1.03 / 1.01
 //     N = 16, t = 0.3          VGG-16   .88 / .99     .93 / 1.01
 //   (The bound of the sparse count form above 8 workers costs 3 % where few codes are sent and saves as much where many are.)
+// Six groups (kLdsForSixGroups) where the kernels' registers would admit seven or eight ("all" above is six in those rows: they
+// held more scalar registers then).  Time over that of six, 7 / 6:
+//   9 to 16 workers, chain    N = 9, 12, 16, t = 0.1  bf16 20 M 1.01-1.02 / 1, 40 M 1.02-1.03, 60 M 1.02-1.04, 32-bit 25 M 1.00
+//   the same, sparse          one code in 16  25 M .99-1.01, 60 M 1.00-1.01, VGG-16-shaped 1.04-1.07, 260 M 1.06-1.09, bf16 138 M 1.05-1.08
+//   17 to 32 workers, sparse  138 M, bf16  N = 17 / 20 1.04 / 1.03, t = 0.5 1.02 / 1.02, N = 32 1.00  (18 to 25 M .99: no bound there)
+//   up to 8 workers, sparse   18 to 25 M  N = 4 1.00-1.01, N = 8 1.00-1.02  (4 M .99-1.02)
+// Five groups over six, 16-bit chains: N = 9 / 12 / 13 / 16  50 M 1.03 / 1.02 / .98 / .98, 80 M .99 / .99 / .98-.99 / .98;  17 to 32 workers, 18 to
+// 25 M  N = 24 .98-1.02, N = 28 / 30 / 32 .98-.99 / .97 / .96, ResNet-50-shaped .98 / 1.00 / .96.
 // The same buffers pass after pass with nothing in between are another matter: up to 64 M elements part of them is
 // still in the memory-side cache, and lists of 28 to 64 M elements of 9 to 16 workers would run up to 7 % faster with
 // all groups (N = 16, t = 0.3, 64 M: 267 us, 284 with 5).  No training step leaves the cache alone like that.
@@ -868,6 +876,7 @@ constexpr unsigned long long kStreamWordsBytes = 112000000;
 // 106.2.  (VGG-16-shaped .99-1.04, 1 GiB buckets 1.02.  Above 32 workers 1 M 1.12, 4 M 1.03, 25 M 1.01: more of the stream
 // pointers no longer fit the scalar registers beside the buffers'.)
 constexpr int kUpTo32Rows = 16;  // host side only: the kernels for up to 32 workers
+constexpr unsigned kLdsForSixGroups = 26624;  // (see the note on residency above)
 struct CompressedLaunch {
     unsigned waves, lds;
     int how;          // kLate, kWrittenOut, kStreamWords, kArena, kUpTo32Rows
@@ -890,8 +899,8 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
         return {4u, all ? 0u : (num_workers <= kUpTo16 ? 32768u : 38912u), 0, 0u};
     }
     if (sparse) {
-        const bool all = !long_list || num_workers > kUpTo16 || (num_workers > kUpTo8 && form == kChain);
-        return {4u, all ? 0u : 32768u, 0, 0u};
+        const bool five = long_list && (num_workers <= kUpTo8 || (num_workers <= kUpTo16 && form == kCount));
+        return {4u, five ? 32768u : ((num_workers > kUpTo16 ? long_list : mid_list) ? kLdsForSixGroups : 0u), 0, 0u};
     }
     const int arena = arenas && max_workgroups == 0 ? kArena : 0;
     const int out = tiles > (num_workers <= kUpTo16 ? 1024u : 2048u) ? kWrittenOut : 0;
@@ -909,11 +918,12 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
         return {4u, 32768u, kWrittenOut | kLate | arena, 0u};
     }
     if (num_workers <= kUpTo16) {
-        if (tiles > (half ? 80u * 1024u : kLongListTiles)) return {4u, 32768u, half || tiles <= 48u * 1024u ? kWrittenOut : 0, 0u};
-        return {4u, 0u, out | (mid_list ? kLate : 0) | (long_list ? 0 : arena), 0u};
+        if (tiles > (half ? (num_workers > 12 ? 48u : 80u) * 1024u : kLongListTiles))
+            return {4u, 32768u, half || tiles <= 48u * 1024u ? kWrittenOut : 0, 0u};
+        return {4u, mid_list ? kLdsForSixGroups : 0u, out | (mid_list ? kLate : 0) | (long_list ? 0 : arena), 0u};
     }
     if (num_workers <= kUpTo32 && max_workgroups == 0 && (half || !long_list || num_workers <= 20)) {
-        const bool bounded = form == kCount ? mid_list : (half ? long_list : mid_list);
+        const bool bounded = half && form != kCount && num_workers < 28 ? long_list : mid_list;
         return {4u, !bounded ? 0u : (form == kCount ? 32768u : 38912u), kUpTo32Rows | out | (long_list ? 0 : arena), 0u};
     }
     if (num_workers > kUpTo32 && (unsigned long long)num_workers * tiles * kTileBytes > kStreamWordsBytes)
