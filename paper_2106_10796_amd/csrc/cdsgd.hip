@@ -228,6 +228,42 @@ struct cdsgd_trainer {
 
 namespace {
 
+// Whether every peer's stream of checked tensors is there, is aligned and lies off this worker's buffers; false where one may
+// not be (check_layer_list then says which fault comes first).  A call that makes its tables anew looks at all of them, and this is
+// most of what it takes on small layers: no branches, and one comparison for each buffer, against the interval of addresses from
+// which a stream of the tensor's length would reach into it.  us, cdsgd_step_fused_static on a ResNet-20-shaped list (65 tensors), the
+// pointers looked at one by one here and in in_arenas / so:  N = 4 5.03 / 4.87, 8 5.65 / 5.28, 16 6.93 / 5.99, 32 9.6 / 7.7, 64 14.7 / 10.75.
+bool streams_are_clear(const cdsgd_tensor *tensors, int num_tensors, const uint32_t *const *const *peers, int num_workers, int self)
+{
+    constexpr int kAtATime = 128, kBuffers = 4;
+    uintptr_t from[kBuffers][kAtATime], span[kBuffers][kAtATime];
+    for (int first = 0; first < num_tensors; first += kAtATime) {
+        const int count = num_tensors - first < kAtATime ? num_tensors - first : kAtATime;
+        for (int i = 0; i < count; ++i) {
+            const cdsgd_tensor &t = tensors[first + i];
+            const uintptr_t fb = t.n * sizeof(float), pb = (uintptr_t)packed_bytes_of(t.n);
+            const void *buffer[kBuffers] = {t.w_global, t.w_local, t.residual, t.packed_self};
+            for (int b = 0; b < kBuffers; ++b) {
+                from[b][i] = reinterpret_cast<uintptr_t>(buffer[b]) - pb + 1u;
+                span[b][i] = (b == kBuffers - 1 ? pb : fb) + pb - 1u;
+            }
+        }
+        for (int j = 0; j < num_workers; ++j) {
+            if (j == self) continue;
+            if (!peers[j]) return false;
+            const uint32_t *const *streams = peers[j] + first;
+            uintptr_t bad = 0;
+            for (int i = 0; i < count; ++i) {
+                const uintptr_t p = reinterpret_cast<uintptr_t>(streams[i]);
+                bad |= (p & 3u) | (uintptr_t)(p == 0);
+                for (int b = 0; b < kBuffers; ++b) bad |= (uintptr_t)(p - from[b][i] < span[b][i]);
+            }
+            if (bad) return false;
+        }
+    }
+    return true;
+}
+
 // Host-side checks of a layer list and its peers (no HIP call): what cdsgd_plan_create_typed
 // and cdsgd_step_fused_static share.  Returns the number of chunks and whether every tensor
 // has an agg_full buffer.
@@ -265,6 +301,9 @@ int check_layer_list(const cdsgd_tensor *tensors, int num_tensors, const uint32_
         total_chunks += chunks_of(t.n);
         if (total_chunks > kMaxGrid) return CDSGD_ERR_SIZE;
     }
+    *total_chunks_out = total_chunks;
+    *all_agg_out = all_agg;
+    if (streams_are_clear(tensors, num_tensors, peers, num_workers, self)) return CDSGD_OK;
     for (int j = 0; j < num_workers; ++j) {
         if (j == self) continue;
         if (!peers[j]) return CDSGD_ERR_NULL;
@@ -279,8 +318,6 @@ int check_layer_list(const cdsgd_tensor *tensors, int num_tensors, const uint32_
                 return CDSGD_ERR_ALIAS;
         }
     }
-    *total_chunks_out = total_chunks;
-    *all_agg_out = all_agg;
     return CDSGD_OK;
 }
 
@@ -299,10 +336,9 @@ TensorDesc make_desc(const cdsgd_tensor &t)
     return d;
 }
 
-// The offset, in 16 elements, of tensor i's buffers from tensor 0's if every one of them is that far (agg_full
+// The offset, in 16 elements, of tensor i's buffers from tensor 0's if every one of its own is that far (agg_full
 // everywhere or nowhere) and the arenas' packed streams are below 4 GiB, -1 if not.
-long long arena_offset16(const cdsgd_tensor *tensors, int i, const uint32_t *const *const *peers, int num_workers,
-                         int self, unsigned grad_bytes)
+long long arena_offset16(const cdsgd_tensor *tensors, int i, unsigned grad_bytes)
 {
     const cdsgd_tensor &z = tensors[0], &t = tensors[i];
     const auto diff = [](const void *a, const void *b) {
@@ -317,8 +353,6 @@ long long arena_offset16(const cdsgd_tensor *tensors, int i, const uint32_t *con
         return -1;
     if ((t.agg_full == nullptr) != (z.agg_full == nullptr) || (t.agg_full && diff(t.agg_full, z.agg_full) != bytes))
         return -1;
-    for (int j = 0; j < num_workers; ++j)
-        if (j != self && diff(peers[j][i], peers[j][0]) != off * 4) return -1;
     return off;
 }
 
@@ -328,9 +362,17 @@ bool in_arenas(const cdsgd_tensor *tensors, int num_tensors, const uint32_t *con
 {
     offsets[0] = 0u;
     for (int i = 1; i < num_tensors; ++i) {
-        const long long off = arena_offset16(tensors, i, peers, num_workers, self, grad_bytes);
+        const long long off = arena_offset16(tensors, i, grad_bytes);
         if (off < 0) return false;
         offsets[i] = (unsigned)off;
+    }
+    for (int j = 0; j < num_workers; ++j) {  // worker by worker, as the pointers lie
+        if (j == self) continue;
+        uintptr_t other = 0;
+        const uintptr_t zero = reinterpret_cast<uintptr_t>(peers[j][0]);
+        for (int i = 1; i < num_tensors; ++i)
+            other |= (reinterpret_cast<uintptr_t>(peers[j][i]) - zero) ^ ((uintptr_t)offsets[i] * 4u);
+        if (other) return false;
     }
     return true;
 }
