@@ -93,6 +93,20 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
     st4g<G, kStore>(wg, tid, rem_elems, vg);
 }
 
+// Lists in arenas, 17 to 32 workers: stream pointers and buffers are the same for every tile, and the compiler fetched them
+// in front of the loop over tiles and kept them all through it: 4 to 18 of them in lanes of a vector register, and the
+// chunk's entry asked for only behind the wait for them, one trip to memory more.  An offset that it cannot see through
+// makes them the tile's own.  The kernels then need 81 to 92 scalar registers, which admit seven groups to a compute unit
+// where 102 admit six (800 registers a SIMD; a wave takes its own and 16 more, in sixteens), and long lists run better with
+// six, so a register that nothing uses is named (bounds by LDS would take LDS from other streams' kernels).  Time over that
+// of the kernels before, so / without the named register, N = 17 / 24 / 32:
+//   t = 0.5, 32-bit   0.9 M .98 .99 .94 / .96 .98 .94;  1.5 M .98 .97 .97 / .98 .97 .97;  1.9 M .97 .97 .97 / .95 .95 .97;  3.5 to 26 M .99-1.00 / .99-1.00
+//   t = 0.5, bf16     0.9 M .97 .98 .97 / .97 .98 .97;  1.5 M .99 .97 .99 / .99 .98 .99;  5 M .99 1.01 1.00 / 1.01 1.01 1.01;  12 and 16 M 1.00 / 1.01
+//   t = 0.1, 32-bit   0.9 to 3.5 M .99-1.01 / .99-1.03;  12 and 16 M 1.00 / 1.01;  18 M .98 .99 1.00 / .97 .99 1.00
+//   t = 0.1, bf16     0.9 M .99 .99 .96 / .99 .98 .96;  1.5 M .98 .97 .97;  3.5 M 1.00 .99 1.00;  12 and 16 M 1.00 / 1.01-1.02;  23 and 26 M .99-1.00 / .99-1.02
+template <int SZ, int HOW>
+constexpr bool kManyPointers = SZ == kUpTo32 && (HOW & kArena) != 0;
+
 // write_local: eq. 11 as well (false: the global half of a split step)
 template <int SZ, int WAVES, int FORM, int GT, bool SPARSE, int HOW, bool WAIT>
 __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDesc *__restrict__ tensors,
@@ -105,6 +119,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
     __shared__ __attribute__((aligned(16))) uint8_t lds[kTileLds<SZ, FORM, WAVES>];
     constexpr unsigned kQuads = 64u * WAVES, kPerChunk = kChunkQuads / kQuads;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if constexpr (kManyPointers<SZ, HOW>) asm volatile("" ::: "s97");
     for (unsigned b = blockIdx.x;;) {
         const unsigned x = piece_of_workgroup<true>(b, kPerChunk, num_tiles);
         const auto at = chunks[x / kPerChunk];
@@ -112,8 +127,10 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
         StreamPointers<SZ, WAVES, SPARSE> from;
         if constexpr ((HOW & kArena) != 0) {
             static_assert(!SPARSE, "arenas of packed streams");
-            from.template load<false>(rows, num_workers, wave, threadIdx.x & 63u);
-            TensorDesc d = tensors[0];
+            unsigned none = 0u;
+            if constexpr (kManyPointers<SZ, HOW>) asm volatile("s_mov_b32 %0, 0" : "=s"(none));
+            from.template load<false>(rows + none, num_workers, wave, threadIdx.x & 63u);
+            TensorDesc d = tensors[none];
             from.pin();
             const unsigned quad = at.off16 * 4u, bytes = (at.elems + 15u) / 16u * 4u;
             d.ext.full_chunks = 0u;

@@ -52,3 +52,31 @@ def test_passes_from_arguments():
     add(32, 4, both, TYPES, (0, OUT))
     add(ANY, 4, both, TYPES, (0,))
     assert _held(rb"k_fused_arguments", rb"ILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)E") == want
+
+
+def _resources(name):
+    """What the code object says of every kernel of that name: {mangled name: {key: number}}."""
+    build.ensure_built()
+    with open(build.LIB, "rb") as fh:
+        text = fh.read()
+    number = rb"([\x00-\x7f]|\xcc.|\xcd..)"           # msgpack's short unsigned numbers
+    got = {}
+    for m in re.finditer(rb"\.group_segment_fixed_size" + number + rb"(?:(?!\.group_segment_fixed_size).)*?\.name(?:\xd9.|\xda..)(_ZN\w*?"
+                         + name + rb"\w*)\xbb\.private_segment_fixed_size" + number + rb"\xab\.sgpr_count" + number
+                         + rb"\xb1\.sgpr_spill_count" + number, text, re.S):
+        lds, _, sgprs, spilled = (int.from_bytes(x[1:] or x, "big") for x in (m[1], m[3], m[4], m[5]))
+        got[m[2]] = {"lds": lds, "sgprs": sgprs, "spilled": spilled}
+    return got
+
+
+def test_scalar_registers_of_passes_over_arenas():
+    """Up to 32 workers no stream pointer is kept in lanes of a vector register; six groups of 17 to 32 workers' passes fit a
+    compute unit (a SIMD has 800 scalar registers; a wave takes its own and 16 more, in sixteens)."""
+    kernels = {k: v for k, v in _resources(b"k_fused_compressed").items() if re.search(rb"ILi(8|16|32)ELi\dELi\dELi\dELb0E", k)}
+    arenas = {k: v for k, v in kernels.items() if re.search(rb"ELb0ELi(8|10|11)E", k)}
+    assert len(arenas) > 40
+    for k, v in kernels.items():
+        assert v["spilled"] == 0, (k, v)
+    for k, v in arenas.items():
+        if b"ILi32E" in k:
+            assert 800 // (-(-(v["sgprs"] + 16) // 16) * 16) == 6, (k, v)
