@@ -318,13 +318,13 @@ __device__ __forceinline__ void chain_byte(f4 &acc, unsigned byte, float t)
 // exchange the sums (decode-and-sum of 2^27 elements, N = 32: 0.270 ms by words, 0.298 by bytes).
 template <int SZ>
 constexpr bool kByBytes = SZ != kAnyWorkers && SZ <= kUpTo16;
-template <int SZ>
-constexpr bool kSlotTests = SZ == kUpTo4 || SZ == kUpTo8;  // tile_put
+template <int SZ, bool SPARSE>
+constexpr bool kSlotTests = SPARSE || SZ == kUpTo4 || SZ == kUpTo8;  // tile_put
 template <int SZ>
 constexpr unsigned kSpareRow = (unsigned)kMaxRows<SZ>;  // written and not read; where there are sums they follow later
 template <int SZ>
 constexpr unsigned kRowsLds = (unsigned)kMaxRows<SZ> * kTileBytes +
-                              (!kByBytes<SZ> ? 16u * kTileQuads : (kSlotTests<SZ> ? 0u : kTileBytes));
+                              (!kByBytes<SZ> ? 16u * kTileQuads : (kSlotTests<SZ, false> ? 0u : kTileBytes));
 template <int SZ, int FORM, int WAVES>
 constexpr unsigned kTileLds = (FORM == kCount ? 4u * 4u * kTileQuads : kRowsLds<SZ>) * WAVES / 4;
 
@@ -359,7 +359,7 @@ struct TilePlace {
 // come as this lane's packed byte and as the values it stands for, own_at is their place in the order (-1: none).
 // In two halves, with a barrier between them: the first leaves in LDS what the waves know of their workers, the second
 // reads it.  Everything a group has written to LDS before has been read when it starts over (a barrier of the caller's).
-template <int SZ, int FORM, int WAVES, bool SPARSE>
+template <int SZ, int FORM, int WAVES, bool TESTS>
 __device__ __forceinline__ void tile_put(const unsigned (&w)[kWordsPerWave<SZ>], unsigned own_code, int own_at,
                                          int num_workers, uint8_t *lds, TilePlace<WAVES> at)
 {
@@ -389,12 +389,12 @@ __device__ __forceinline__ void tile_put(const unsigned (&w)[kWordsPerWave<SZ>],
         // 25.0 / 29.4, 19.5 / 22.5 / 25.6;  compressed pass 0.5 M N = 32 / 64 4.6 / 6.8, 4.4 / 6.3;  1 M 7.2 / 10.2, 6.9 / 9.8;
         // 4 M 22.4 / 28.0, 22.1 / 27.6.  The own row is made of the lanes' own codes; what the wave holds for it goes to
         // the spare row.  (Sparse streams, whose words have to wait for their bitmaps: N = 64 2-6 % faster without tests, 33 to 48
-        // 1-5 % slower; packed streams of 5 to 8 workers, 60 M elements 1 % slower.)
+        // 1-5 % slower; packed streams of 5 to 8 workers, 60 M elements 1 % slower.  MID of the compressed pass: there.)
         unsigned *rows = reinterpret_cast<unsigned *>(lds);
 #pragma unroll
         for (int i = 0; i < kWordsPerWave<SZ>; ++i) {
             const int j = worker_of<SZ>(wave, i);
-            if constexpr (SPARSE || kSlotTests<SZ>) {
+            if constexpr (TESTS) {
                 if (j != own_at && (SZ != kAnyWorkers || 16 * (i / 4) < num_workers)) rows[kWords * (unsigned)j + lane] = signed_fields(w[i]);
             } else {
                 rows[kWords * (j != own_at ? (unsigned)j : kSpareRow<SZ>) + lane] = signed_fields(w[i]);
@@ -462,14 +462,14 @@ __device__ __forceinline__ f4 tile_get(f4 own_value, int num_workers, float t, u
     return agg;
 }
 
-template <int SZ, int FORM, int WAVES, bool SPARSE>
+template <int SZ, int FORM, int WAVES, bool TESTS, bool SPREAD>
 __device__ __forceinline__ f4 tile_sums(const unsigned (&w)[kWordsPerWave<SZ>], unsigned own_code, f4 own_value,
                                         int own_at, int num_workers, float t, uint8_t *lds)
 {
     const TilePlace<WAVES> at;
-    tile_put<SZ, FORM, WAVES, SPARSE>(w, own_code, own_at, num_workers, lds, at);
+    tile_put<SZ, FORM, WAVES, TESTS>(w, own_code, own_at, num_workers, lds, at);
     group_sync<WAVES>();
-    return tile_get<SZ, FORM, WAVES, true>(own_value, num_workers, t, lds, at);
+    return tile_get<SZ, FORM, WAVES, SPREAD>(own_value, num_workers, t, lds, at);
 }
 
 // ---------------------------------------------------------------------------
@@ -527,7 +527,7 @@ __global__ __launch_bounds__(kTileQuads) void k_decode_sum(float *__restrict__ a
         else load_packed<SZ, NT>(words[k], from.p, s, wave, tid & 63u);
     }
 #pragma unroll
-    for (unsigned k = 0; k < TILES; ++k) tile_put<SZ, FORM, 4, SPARSE>(words[k], 0u, -1, num_workers, lds + kLds * k, at);
+    for (unsigned k = 0; k < TILES; ++k) tile_put<SZ, FORM, 4, kSlotTests<SZ, SPARSE>>(words[k], 0u, -1, num_workers, lds + kLds * k, at);
     group_sync<4>();
     float *out = agg_out + (size_t)x * (4u * kTileQuads * TILES);
 #pragma unroll

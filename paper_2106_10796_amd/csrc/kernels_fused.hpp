@@ -32,7 +32,8 @@ struct ChunkEntry<kArena> { typedef ArenaChunk type; };
 
 // WAIT: the weights are asked for when gradient and residual are there, not with them: less in flight at a time, and on lists
 // of a few million elements that is served faster (launch_formal_pass, with the times).
-template <bool G, int SZ, int WAVES, int FORM, int GT, bool SPARSE, int HOW, bool WAIT>
+// MID: the chain's rows are written behind tests and its sums not spread over the banks (tile_put, tile_get).
+template <bool G, int SZ, int WAVES, int FORM, int GT, bool SPARSE, int HOW, bool WAIT, bool MID>
 __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPointers<SZ, WAVES, SPARSE> &from, int num_workers,
                                            int self, unsigned chunk, unsigned tile, unsigned rem_elems,
                                            unsigned rem_bytes, float t, float lr_local, float scale, bool write_local,
@@ -86,7 +87,7 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
     for (unsigned c = 0; c < 4; ++c) vl[c] = __builtin_fmaf(-lr_local, g[c], w[c]);
     if (kLocalFirst<SZ, FORM> && write_local) st4g<G, kStore>(wl, tid, rem_elems, vl);
 
-    const f4 agg = tile_sums<SZ, FORM, WAVES, SPARSE>(words, own, sent, self, num_workers, t, lds);
+    const f4 agg = tile_sums<SZ, FORM, WAVES, kSlotTests<SZ, SPARSE> || MID, !MID>(words, own, sent, self, num_workers, t, lds);
 #pragma unroll
     for (unsigned c = 0; c < 4; ++c) vg[c] = __builtin_fmaf(-scale, agg[c], w[c]);
     if (!kLocalFirst<SZ, FORM> && write_local) st4g<G, kStore>(wl, tid, rem_elems, vl);
@@ -119,6 +120,11 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
     __shared__ __attribute__((aligned(16))) uint8_t lds[kTileLds<SZ, FORM, WAVES>];
     constexpr unsigned kQuads = 64u * WAVES, kPerChunk = kChunkQuads / kQuads;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    // The kernels of 32-bit lists in arenas of 16 to 28 M elements, 17 to 32 workers: their groups are through sooner without the
+    // tests and with the sums spread, and the order in which memory is asked is the worse one, at any residency.  Chain, time
+    // over that so, 17 / 19 / 21 / 24 / 27 M elements: N = 17 1.02 1.03 1.02 1.01 1.00, 18 1.02 1.02 1.02 1.01 1.00, 20 1.02 1.01
+    // 1.00 1.00 .99, 24 1.01 1.00 1.00 1.00 1.00, 28 and 32 1.00.  (16-bit gradients, N = 17, 18 M: even.)
+    constexpr bool MID = kManyPointers<SZ, HOW> && (HOW & kWrittenOut) != 0 && !WAIT && GT == kGradF32;
     if constexpr (kManyPointers<SZ, HOW>) asm volatile("" ::: "s97");
     for (unsigned b = blockIdx.x;;) {
         const unsigned x = piece_of_workgroup<true>(b, kPerChunk, num_tiles);
@@ -136,11 +142,11 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
             d.ext.full_chunks = 0u;
             d.ext.tail_bytes = quad + bytes;  // where the chunk's codes end in a stream
             if (at.elems == kChunkElems) {
-                fused_tile<false, SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT>(d, from, num_workers, self, quad, tile, kQuads * 4u, kQuads,
+                fused_tile<false, SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT, MID>(d, from, num_workers, self, quad, tile, kQuads * 4u, kQuads,
                                                                     t_call, lr_local, scale, write_local != 0, lds);
             } else if (tile * kQuads < bytes) {
                 const unsigned elems0 = tile * kQuads * 4u;
-                fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT>(d, from, num_workers, self, quad, tile,
+                fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT, MID>(d, from, num_workers, self, quad, tile,
                                                                    elems_from(elems0, at.elems), bytes - tile * kQuads,
                                                                    t_call, lr_local, scale, write_local != 0, lds);
             }
@@ -151,12 +157,12 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
             from.pin();
             const float t = d.threshold > 0.0f ? d.threshold : t_call;
             if (at.chunk < d.ext.full_chunks) {
-                fused_tile<false, SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT>(d, from, num_workers, self, at.chunk, tile, kQuads * 4u, kQuads,
+                fused_tile<false, SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT, MID>(d, from, num_workers, self, at.chunk, tile, kQuads * 4u, kQuads,
                                                         t, lr_local, scale, write_local != 0, lds);
             } else if (tile * kQuads < d.ext.tail_bytes) {
                 // (the packed bytes of the ragged end cover its elements: tiles past them have nothing to do)
                 const unsigned elems0 = tile * kQuads * 4u;
-                fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT>(d, from, num_workers, self, at.chunk, tile,
+                fused_tile<true, SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT, MID>(d, from, num_workers, self, at.chunk, tile,
                                                        elems_from(elems0, d.ext.tail_elems),
                                                        d.ext.tail_bytes - tile * kQuads, t, lr_local, scale,
                                                        write_local != 0, lds);

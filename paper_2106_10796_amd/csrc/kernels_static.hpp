@@ -165,11 +165,11 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_arguments(unsigned num_til
     d.ext.full_chunks = 0u;
     d.ext.tail_bytes = quad + bytes;  // where the chunk's codes end in a stream
     if (elems == kChunkElems) {
-        fused_tile<false, SZ, WAVES, FORM, GT, false, HOW, false>(d, from, num_workers, self, quad, tile, kQuads * 4u, kQuads, t, lr_local,
+        fused_tile<false, SZ, WAVES, FORM, GT, false, HOW, false, false>(d, from, num_workers, self, quad, tile, kQuads * 4u, kQuads, t, lr_local,
                                                            scale, true, lds);
     } else if (tile * kQuads < bytes) {
         const unsigned elems0 = tile * kQuads * 4u;
-        fused_tile<true, SZ, WAVES, FORM, GT, false, HOW, false>(d, from, num_workers, self, quad, tile, elems_from(elems0, elems),
+        fused_tile<true, SZ, WAVES, FORM, GT, false, HOW, false, false>(d, from, num_workers, self, quad, tile, elems_from(elems0, elems),
                                                           bytes - tile * kQuads, t, lr_local, scale, true, lds);
     }
 }
