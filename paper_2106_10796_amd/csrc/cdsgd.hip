@@ -423,11 +423,14 @@ bool keeps_results(unsigned num_chunks, int num_workers, bool sum)
 //            N = 16  0.1 M 7.6 / 4.0, 0.25 M 13.0 / 7.5, 0.5 M 10.5 / 7.1, 0.7 M 11.6 / 9.6, 1 M 13.7 / 13.1, 1.5 M 18.2 / 19.5
 //   16-bit   N = 6   0.5 M .99, 0.7 M 1.00, 1 M 1.04 (600 MB of sets .97), 2 M 1.07       N = 8   .94, .92, .96, 1.03
 //            N = 16  0.25 M 6.3 / 4.6, 0.5 M 7.0 / 5.3, 0.7 M 7.9 / 6.4, 1 M 8.9 / 8.3, 1.5 M 11.3 / 11.5
+// and on either side of the lines
+//   32-bit   N = 5   0.25 M .79, 0.5 M .81, 0.65 M .92, 0.75 M 1.01, 1 M 1.00      N = 7   0.25 M .66, 0.5 M .78, 0.75 M .93, 1 M .96, 1.2 M 1.03
+//   16-bit   N = 5   0.25 M 1.04, 0.5 M 1.06, 0.75 M 1.06, 1 M 1.11, 2 M 1.01      N = 7   0.25 M .93, 0.5 M .83, 0.75 M .90, 1 M .91, 2 M 1.03
 // (Up to 4 workers nothing is gained and 1 M in 16 bits loses 11 %; 4 at once gain less up to 0.5 M, 16 at once are slower
 // from 0.7 M on.  Above, the order of the streams decides: 8 M, N = 16 92 / 107.)
-bool sums_together(unsigned num_chunks, int num_workers)
+bool sums_together(unsigned num_chunks, int num_workers, int grad_type)
 {
-    return num_workers > 4 && num_chunks * kTilesPerChunk <= (num_workers > 6 ? 1024u : 768u);
+    return num_workers > (grad_type == kGradF32 ? 4 : 5) && num_chunks * kTilesPerChunk <= (num_workers > 6 ? 1024u : 768u);
 }
 
 // Launch one full-gradient pass (see k_fused_full) for a plan.
@@ -454,7 +457,7 @@ int launch_full_pass(const PlanTables *plan, int local_mode, float lr_local, flo
         else CDSGD_LAUNCH_FULL_T(SUM, LOCAL, kGradF32, STORE, IN_FLIGHT);                                      \
     } while (0)
     const bool keep = plan->max_workgroups == 0 && keeps_results(plan->num_chunks, plan->num_workers, sum);
-    if (sum && sums_together(plan->num_chunks, plan->num_workers)) {
+    if (sum && sums_together(plan->num_chunks, plan->num_workers, plan->grad_type)) {
         if (local_mode == kLocalNone) CDSGD_LAUNCH_FULL(true, kLocalNone, kStream, kTogether);
         else if (local_mode == kLocalCopy) CDSGD_LAUNCH_FULL(true, kLocalCopy, kStream, kTogether);
         else CDSGD_LAUNCH_FULL(true, kLocalRule, kStream, kTogether);
