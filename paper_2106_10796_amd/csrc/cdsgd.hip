@@ -1011,12 +1011,16 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
     // VGG-16-shaped 1.00 / 1.03 / 1.00;  t = 0.3, bf16 1 M .90 / .91 / .92, 4 M .93, VGG-16-shaped .94 / .97 / .98.
     const bool sparse32 = N <= kUpTo32 && plan->max_workgroups == 0 &&
                           (plan->grad_type != kGradF32 || plan->num_chunks * kTilesPerChunk <= kLongListTiles);
-    // 17 to 32 workers, lists of 2 to 16 M elements (in arenas, written through): the weights are asked for behind gradient and
-    // residual.  Time over that of asking for all at once, three and six sets of buffers in turn, 2.2 / 3 / 5 / 8 / 12 / 16.5 M:
-    //   N = 17, t = 0.5  .99 .99 .99 .99 .99 .99, bf16 .98 .98 .98 .99 .99 .99, fp16 .98-1.00;  N = 20, t = 0.3  .97 .98 .99 .99 .99 .99-1.00,
-    //   bf16 .95-.96 .96 .97 .98 .99 .99;  N = 24, t = 0.3  .98 .98 .99 .99 .99 1.00, bf16 .96 .96 .98 .98 .99 .99;  N = 32, t = 0.5 .98 .99
-    //   .99 .99 .98-.99 .99, bf16 .97 .97 .98 .99 .99 .99;  N = 32, t = 0.3  .98 .98 .99 .99 .99 1.00, bf16 .96 .97 .99 .99 .99 .99
-    // (25 M 1.00-1.02, VGG-16-shaped 1.00;  9 to 16 workers, t = 0.5: 1.1 M .96, 1.5 M 1.02, 3 M 1.01, 8 to 16 M .99, 25 M 1.01, 25 M in bf16 1.03)
+    // Passes in which the weights are asked for behind gradient and residual.  Time over that of asking for all at once:
+    // 17 to 32 workers, lists of 2 to 16 M elements in arenas, written through, six and three sets of buffers in turn, 2.2 / 3 / 5 / 8 / 12 / 16 M:
+    //   t = 0.1  N = 17 .97 .98 .99 .99 .99 .99;  20 .97 .98 .99 1.00 .99 .99;  24 .98 .98 .99 .99 .99 .99;  32 .98 .98 .99 .99 1.00 .99
+    //   t = 0.1, bf16  N = 17 .99 .99 .99 .99 .99 .99;  20 1.00 .99 .99 .99 1.00 .99;  24 .99 .99 .99 .99 .99 1.00;  32 1.00 .99 1.00 1.00 1.00 1.01
+    //   t = 0.5  N = 17 1.01 1.00 1.00 1.00 .99 .99;  20 1.01 1.00 1.00 1.00 1.00 .99;  24 1.00 1.00 1.01 1.00 .99 1.00;  32 1.00 1.00 1.00 1.00 1.00 1.00
+    //   (25 M 1.00-1.02;  9 to 16 workers, t = 0.5: 1.1 M .96, 1.5 M 1.02, 3 M 1.01, 8 to 16 M .99, 25 M 1.01, 25 M in bf16 1.03)
+    // Count form above 32 workers, words read non-temporally, 9 / 14 / 18 / 26 / 40 / 64 / 100 M:
+    //   32-bit  N = 33 1.00 .99 .98 1.00 .99 1.00 1.00;  48 1.00 .99 1.00 1.00 1.00 .99 1.00;  64 .99 .99 .99 .99 1.00 .99 1.00
+    //   bf16    N = 33 1.00 .99 1.00 1.00 1.00 .99 .99;  48 1.00 .99 .99 .99 1.00 .99 .99;  64 .98 .99 .99 .99 1.00 .99 .99
+    //   (the chain there: .99-1.01)
     const bool weights_wait = plan->num_chunks * kTilesPerChunk <= kMidListTiles;
     const auto bound = [&](unsigned used) { return shape.lds <= used ? 0u : shape.lds - used; };
 #define CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT)                                      \
@@ -1054,7 +1058,7 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
         else if (shape.how == (kUpTo32Rows | kWrittenOut)) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, kWrittenOut); \
         else if (shape.how == (kUpTo32Rows | kArena)) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, kArena); \
         else if (shape.how == kUpTo32Rows) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, false, 0);                \
-        else if (N > kUpTo16 && shape.how == kStreamWords) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, false, kStreamWords); \
+        else if (N > kUpTo16 && shape.how == kStreamWords) CDSGD_LAUNCH_COMPRESSED_W(kAnyWorkers, 4, FORM, false, kStreamWords, FORM == kCount); \
         else if (N > kUpTo16 && shape.how == 0) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, FORM, false, 0);       \
         else if (N > kUpTo16) return CDSGD_ERR_DEVICE;                                                         \
         else if (shape.how == (kWrittenOut | kLate | kArena)) LAUNCH_LATE(kUpTo16, 4, FORM, false, kWrittenOut | kLate | kArena); \

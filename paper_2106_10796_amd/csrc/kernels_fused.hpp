@@ -30,8 +30,8 @@ struct ChunkEntry { typedef ChunkRef type; };
 template <>
 struct ChunkEntry<kArena> { typedef ArenaChunk type; };
 
-// WAIT: the weights are asked for when gradient and residual are there, not with them: less in flight at a time, and on lists
-// of a few million elements that is served faster (launch_formal_pass, with the times).
+// WAIT: the weights are asked for when gradient and residual are there, not with them: fewer streams in flight at a time, which
+// memory serves a little faster in some passes (launch_formal_pass, with the times).
 // MID: the chain's rows are written behind tests and its sums not spread over the banks (tile_put, tile_get).
 template <bool G, int SZ, int WAVES, int FORM, int GT, bool SPARSE, int HOW, bool WAIT, bool MID>
 __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPointers<SZ, WAVES, SPARSE> &from, int num_workers,

@@ -20,14 +20,15 @@ def _held(name, pattern):
 def test_passes_over_a_plan():
     want = set()
 
-    def add(size, waves, forms, types, sparse, hows):
-        want.update((size, waves, f, t, s, h) for f, t, s, h in itertools.product(forms, types, sparse, hows))
+    def add(size, waves, forms, types, sparse, hows, weights_wait=(0,)):
+        want.update((size, waves, *x) for x in itertools.product(forms, types, sparse, hows, weights_wait))
     both = (COUNT, CHAIN)
     add(8, 4, both, TYPES, (1,), (0,))
     add(16, 4, both, TYPES, (1,), (0,))
     add(32, 4, both, TYPES, (1,), (0,))
     add(ANY, 4, (COUNT, CHAIN, TINY), TYPES, (0, 1), (0,))
-    add(ANY, 4, both, TYPES, (0,), (NT_WORDS,))
+    add(ANY, 4, (COUNT,), TYPES, (0,), (NT_WORDS,), (1,))
+    add(ANY, 4, (CHAIN,), TYPES, (0,), (NT_WORDS,))
     add(8, 1, both, TYPES, (0,), (0, ARENA))
     add(8, 4, both, TYPES, (0,), (0, ARENA))
     add(16, 4, both, TYPES, (0,), (0, OUT, ARENA, OUT | ARENA))
@@ -35,7 +36,8 @@ def test_passes_over_a_plan():
     add(16, 4, (COUNT,), F32, (0,), (OUT | LATE, OUT | LATE | ARENA))
     add(16, 4, (COUNT,), TYPES, (0,), (LATE,))
     add(32, 4, both, TYPES, (0,), (0, OUT, ARENA, OUT | ARENA))
-    assert _held(rb"k_fused_compressed", rb"ILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELi(\d+)E") == want
+    add(32, 4, both, TYPES, (0,), (OUT | ARENA,), (1,))
+    assert _held(rb"k_fused_compressed", rb"ILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELi(\d+)ELb([01])EEE") == want
 
 
 def test_passes_from_arguments():
