@@ -852,12 +852,15 @@ namespace {
 //     N = 9 / 16, t = 0.5      VGG-16   .97 / 1.01, .97 / .99     1.00 / .98, 1.03 / 1.01
 //     N = 16, t = 0.3          VGG-16   .88 / .99     .93 / 1.01
 //   (The bound of the sparse count form above 8 workers costs 3 % where few codes are sent and saves as much where many are.)
-// Six groups (kLdsForSixGroups) where the kernels' registers would admit seven or eight ("all" above is six in those rows: they
-// held more scalar registers then).  Time over that of six, 7 / 6:
+// Six groups (kSix) where the kernels' registers would admit seven or eight ("all" above is six in those rows: they held more
+// scalar registers then).  Time over that of six, 7 groups / 6:
 //   9 to 16 workers, chain    N = 9, 12, 16, t = 0.1  bf16 20 M 1.01-1.02 / 1, 40 M 1.02-1.03, 60 M 1.02-1.04, 32-bit 25 M 1.00
-//   the same, sparse          one code in 16  25 M .99-1.01, 60 M 1.00-1.01, VGG-16-shaped 1.04-1.07, 260 M 1.06-1.09, bf16 138 M 1.05-1.08
-//   17 to 32 workers, sparse  138 M, bf16  N = 17 / 20 1.04 / 1.03, t = 0.5 1.02 / 1.02, N = 32 1.00  (18 to 25 M .99: no bound there)
-//   up to 8 workers, sparse   18 to 25 M  N = 4 1.00-1.01, N = 8 1.00-1.02  (4 M .99-1.02)
+//   the same, sparse          one code in 16  25 M .99-1.01, 60 M 1.00-1.03, VGG-16-shaped 1.04-1.07, 260 M 1.06-1.09, bf16 138 M 1.05-1.08
+//                             (below 16 M six take longer: 2 M 1.05, 4 M 1.01-1.04)
+//   17 to 32 workers, sparse  138 M, bf16  N = 17 / 20 1.04 / 1.01-1.03, t = 0.5 1.02 / 1.02, N = 32 .99-1.00;  60 M 1.00, N = 32 .99  (18 to 25 M .99: no bound there)
+//   up to 8 workers, sparse   25 M, t = 0.1  N = 4 1.005, N = 8 1.015;  18 M 1.000, 1.006;  t = 0.5 18 and 25 M 1.00: no bound there
+//   9 to 16 workers, sparse, t = 0.5   18 and 25 M 1.00: no bound there
+//   (Above 32 workers the registers admit six.)
 // Five groups over six, 16-bit chains: N = 9 / 12 / 13 / 16  50 M 1.03 / 1.02 / .98 / .98, 80 M .99 / .99 / .98-.99 / .98;  17 to 32 workers, 18 to
 // 25 M  N = 24 .98-1.02, N = 28 / 30 / 32 .98-.99 / .97 / .96, ResNet-50-shaped .98 / 1.00 / .96.
 // The same buffers pass after pass with nothing in between are another matter: up to 64 M elements part of them is
@@ -921,10 +924,9 @@ constexpr unsigned long long kStreamWordsBytes = 112000000;
 // 106.2.  (VGG-16-shaped .99-1.04, 1 GiB buckets 1.02.  Above 32 workers 1 M 1.12, 4 M 1.03, 25 M 1.01: more of the stream
 // pointers no longer fit the scalar registers beside the buffers'.)
 constexpr int kUpTo32Rows = 16;  // host side only: the kernels for up to 32 workers
-constexpr unsigned kLdsForSixGroups = 26624;  // (see the note on residency above)
 struct CompressedLaunch {
     unsigned waves, lds;
-    int how;          // kLate, kWrittenOut, kStreamWords, kArena, kUpTo32Rows
+    int how;          // kLate, kWrittenOut, kStreamWords, kArena, kSixGroups, kUpTo32Rows
     unsigned groups;  // launch at most this many (0: no bound)
 };
 
@@ -945,7 +947,8 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
     }
     if (sparse) {
         const bool five = long_list && (num_workers <= kUpTo8 || (num_workers <= kUpTo16 && form == kCount));
-        return {4u, five ? 32768u : ((num_workers > kUpTo16 ? long_list : mid_list) ? kLdsForSixGroups : 0u), 0, 0u};
+        const bool six = num_workers <= kUpTo16 ? mid_list && form == kChain : long_list && half && num_workers <= kUpTo32;
+        return {4u, five ? 32768u : 0u, six && !five ? kSixGroups : 0, 0u};
     }
     const int arena = arenas && max_workgroups == 0 ? kArena : 0;
     const int out = tiles > (num_workers <= kUpTo16 ? 1024u : 2048u) ? kWrittenOut : 0;
@@ -965,7 +968,7 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
     if (num_workers <= kUpTo16) {
         if (tiles > (half ? (num_workers > 12 ? 48u : 80u) * 1024u : kLongListTiles))
             return {4u, 32768u, half || tiles <= 48u * 1024u ? kWrittenOut : 0, 0u};
-        return {4u, mid_list ? kLdsForSixGroups : 0u, out | (mid_list ? kLate : 0) | (long_list ? 0 : arena), 0u};
+        return {4u, 0u, out | (mid_list ? kLate : 0) | (long_list ? 0 : arena), 0u};
     }
     if (num_workers <= kUpTo32 && max_workgroups == 0 && (half || !long_list || num_workers <= 20)) {
         const bool bounded = half && form != kCount && num_workers < 28 ? long_list : mid_list;
@@ -1040,10 +1043,20 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
         if (plan->grad_type != kGradF32) return CDSGD_ERR_DEVICE;                                              \
         CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF32, SPARSE, HOW, false);                              \
     } while (0)
+#define CDSGD_LAUNCH_COMPRESSED_16BIT(SZ, WAVES, FORM, SPARSE, HOW)                                            \
+    do {                                                                                                       \
+        if (plan->grad_type == kGradBF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradBF16, SPARSE, HOW, false); \
+        else if (plan->grad_type == kGradF16) CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF16, SPARSE, HOW, false); \
+        else return CDSGD_ERR_DEVICE;                                                                          \
+    } while (0)
 // Every shape has a kernel of its own; one that has none is an error, for another kernel may read the tables otherwise.
 #define CDSGD_LAUNCH_COMPRESSED_F(FORM, LAUNCH_LATE)                                                           \
     do {                                                                                                       \
-        if (plan->peers_sparse && shape.how != 0) return CDSGD_ERR_DEVICE;                                     \
+        if (plan->peers_sparse && shape.how != 0 && shape.how != kSixGroups) return CDSGD_ERR_DEVICE;          \
+        else if (shape.how == kSixGroups && (!plan->peers_sparse || N > kUpTo32 || (N <= kUpTo16 && FORM != kChain))) return CDSGD_ERR_DEVICE; \
+        else if (shape.how == kSixGroups && N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, kChain, true, kSixGroups); \
+        else if (shape.how == kSixGroups && N <= kUpTo16) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, kChain, true, kSixGroups); \
+        else if (shape.how == kSixGroups) CDSGD_LAUNCH_COMPRESSED_16BIT(kUpTo32, 4, FORM, true, kSixGroups);   \
         else if (plan->peers_sparse && N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, true, 0);         \
         else if (plan->peers_sparse && N <= kUpTo16) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, true, 0);       \
         else if (plan->peers_sparse && sparse32) CDSGD_LAUNCH_COMPRESSED(kUpTo32, 4, FORM, true, 0);           \
@@ -1076,6 +1089,7 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
     else if (plan->peers_sparse) CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, kChainTiny, true, 0);
     else CDSGD_LAUNCH_COMPRESSED(kAnyWorkers, 4, kChainTiny, false, 0);
 #undef CDSGD_LAUNCH_COMPRESSED_32BIT
+#undef CDSGD_LAUNCH_COMPRESSED_16BIT
 #undef CDSGD_LAUNCH_COMPRESSED
 #undef CDSGD_LAUNCH_COMPRESSED_W
 #undef CDSGD_LAUNCH_COMPRESSED_F

@@ -24,7 +24,8 @@ constexpr bool kLocalFirst = SZ == kUpTo16 && FORM != kCount;
 //   kWrittenOut  results are written through the L2 of the compute die (kThroughStream)
 //   kStreamWords the workers' words are read non-temporally
 //   kArena       the list lies in arenas (ArenaChunk): entry, buffers and stream pointers come in one trip to memory
-constexpr int kLate = 1, kWrittenOut = 2, kStreamWords = 4, kArena = 8;
+//   kSixGroups   no more than six groups to a compute unit
+constexpr int kLate = 1, kWrittenOut = 2, kStreamWords = 4, kArena = 8, kSixGroups = 32;
 template <int HOW>
 struct ChunkEntry { typedef ChunkRef type; };
 template <>
@@ -98,15 +99,26 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
 // in front of the loop over tiles and kept them all through it: 4 to 18 of them in lanes of a vector register, and the
 // chunk's entry asked for only behind the wait for them, one trip to memory more.  An offset that it cannot see through
 // makes them the tile's own.  The kernels then need 81 to 92 scalar registers, which admit seven groups to a compute unit
-// where 102 admit six (800 registers a SIMD; a wave takes its own and 16 more, in sixteens), and long lists run better with
-// six, so a register that nothing uses is named (bounds by LDS would take LDS from other streams' kernels).  Time over that
-// of the kernels before, so / without the named register, N = 17 / 24 / 32:
+// where 102 admit six, and long lists run better with six (kSix).  Time over that
+// of the kernels before, so / with seven, N = 17 / 24 / 32:
 //   t = 0.5, 32-bit   0.9 M .98 .99 .94 / .96 .98 .94;  1.5 M .98 .97 .97 / .98 .97 .97;  1.9 M .97 .97 .97 / .95 .95 .97;  3.5 to 26 M .99-1.00 / .99-1.00
 //   t = 0.5, bf16     0.9 M .97 .98 .97 / .97 .98 .97;  1.5 M .99 .97 .99 / .99 .98 .99;  5 M .99 1.01 1.00 / 1.01 1.01 1.01;  12 and 16 M 1.00 / 1.01
 //   t = 0.1, 32-bit   0.9 to 3.5 M .99-1.01 / .99-1.03;  12 and 16 M 1.00 / 1.01;  18 M .98 .99 1.00 / .97 .99 1.00
 //   t = 0.1, bf16     0.9 M .99 .99 .96 / .99 .98 .96;  1.5 M .98 .97 .97;  3.5 M 1.00 .99 1.00;  12 and 16 M 1.00 / 1.01-1.02;  23 and 26 M .99-1.00 / .99-1.02
 template <int SZ, int HOW>
 constexpr bool kManyPointers = SZ == kUpTo32 && (HOW & kArena) != 0;
+
+// Kernels of which a compute unit runs six groups (compressed_launch, with the times) although their registers would admit
+// more: they name a scalar register that nothing uses.  A SIMD has 800; a wave takes its own and 16 more, in sixteens: 102
+// admit six, 80 eight.  A bound by LDS takes as long and keeps 156 KiB of a compute unit's 160 from kernels of other streams.
+template <int SZ, int FORM, int HOW>
+constexpr bool kSix = kManyPointers<SZ, HOW> || (HOW & kSixGroups) != 0 || (SZ == kUpTo16 && FORM == kChain && (HOW & kLate) != 0);
+
+template <int SZ, int FORM, int HOW>
+__device__ __forceinline__ void admit_six_groups()
+{
+    if constexpr (kSix<SZ, FORM, HOW>) asm volatile("" ::: "s97");
+}
 
 // write_local: eq. 11 as well (false: the global half of a split step)
 template <int SZ, int WAVES, int FORM, int GT, bool SPARSE, int HOW, bool WAIT>
@@ -125,7 +137,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
     // over that so, 17 / 19 / 21 / 24 / 27 M elements: N = 17 1.02 1.03 1.02 1.01 1.00, 18 1.02 1.02 1.02 1.01 1.00, 20 1.02 1.01
     // 1.00 1.00 .99, 24 1.01 1.00 1.00 1.00 1.00, 28 and 32 1.00.  (16-bit gradients, N = 17, 18 M: even.)
     constexpr bool MID = kManyPointers<SZ, HOW> && (HOW & kWrittenOut) != 0 && !WAIT && GT == kGradF32;
-    if constexpr (kManyPointers<SZ, HOW>) asm volatile("" ::: "s97");
+    admit_six_groups<SZ, FORM, HOW>();
     for (unsigned b = blockIdx.x;;) {
         const unsigned x = piece_of_workgroup<true>(b, kPerChunk, num_tiles);
         const auto at = chunks[x / kPerChunk];

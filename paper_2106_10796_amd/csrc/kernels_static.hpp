@@ -138,6 +138,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_arguments(unsigned num_til
     __shared__ __attribute__((aligned(16))) uint8_t lds[kTileLds<SZ, FORM, WAVES>];
     constexpr unsigned kQuads = 64u * WAVES, kPerChunk = kChunkQuads / kQuads;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    admit_six_groups<SZ, FORM, HOW & ~kArena>();
     const unsigned lane = threadIdx.x & 63u;
     const unsigned x = piece_of_workgroup<true>((unsigned)blockIdx.x, kPerChunk, num_tiles);
     const unsigned slot = x / kPerChunk, tile = x % kPerChunk;

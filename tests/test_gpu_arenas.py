@@ -138,3 +138,11 @@ def test_sparse_peers_equal_packed_ones(B, N, sizes, dtype, t):
     sparse.step(1, 4, t, 0.4, 0.7)
     b.step(1, 4, t, 0.4, 0.7)
     check("sparse")
+
+
+# sparse peers, chain form: passes over more than 16 M elements (17 to 32 workers: 28 M, 16-bit gradients) have kernels of their own
+@pytest.mark.parametrize("N,tiles,dtype", [(6, 16384, torch.float32), (8, 16384, torch.bfloat16), (9, 16384, torch.float16), (16, 16384, torch.float32),
+                                           (18, 28 * 1024, torch.float16)])
+def test_sparse_peers_on_either_side_of_six_groups(B, N, tiles, dtype):
+    for more in (0, 1):
+        test_sparse_peers_equal_packed_ones(B, N, [tiles * 1024 - 4096 - 1, 4096 + more], dtype, 0.3)

@@ -6,7 +6,7 @@ import re
 from paper_2106_10796_amd import build
 
 COUNT, CHAIN, TINY = 0, 1, 2
-LATE, OUT, NT_WORDS, ARENA = 1, 2, 4, 8
+LATE, OUT, NT_WORDS, ARENA, SIX = 1, 2, 4, 8, 32
 TYPES, F32 = (0, 1, 2), (0,)
 ANY = 0
 
@@ -26,6 +26,9 @@ def test_passes_over_a_plan():
     add(8, 4, both, TYPES, (1,), (0,))
     add(16, 4, both, TYPES, (1,), (0,))
     add(32, 4, both, TYPES, (1,), (0,))
+    add(8, 4, (CHAIN,), TYPES, (1,), (SIX,))
+    add(16, 4, (CHAIN,), TYPES, (1,), (SIX,))
+    add(32, 4, both, (1, 2), (1,), (SIX,))
     add(ANY, 4, (COUNT, CHAIN, TINY), TYPES, (0, 1), (0,))
     add(ANY, 4, (COUNT,), TYPES, (0,), (NT_WORDS,), (1,))
     add(ANY, 4, (CHAIN,), TYPES, (0,), (NT_WORDS,))
@@ -71,9 +74,14 @@ def _resources(name):
     return got
 
 
+def _groups(kernel):
+    """Groups of four waves that a compute unit's scalar registers admit: a SIMD has 800, a wave takes its own and 16 more, in sixteens."""
+    return 800 // (-(-(kernel["sgprs"] + 16) // 16) * 16)
+
+
 def test_scalar_registers_of_passes_over_arenas():
     """Up to 32 workers no stream pointer is kept in lanes of a vector register; six groups of 17 to 32 workers' passes fit a
-    compute unit (a SIMD has 800 scalar registers; a wave takes its own and 16 more, in sixteens)."""
+    compute unit."""
     kernels = {k: v for k, v in _resources(b"k_fused_compressed").items() if re.search(rb"ILi(8|16|32)ELi\dELi\dELi\dELb0E", k)}
     arenas = {k: v for k, v in kernels.items() if re.search(rb"ELb0ELi(8|10|11)E", k)}
     assert len(arenas) > 40
@@ -81,4 +89,14 @@ def test_scalar_registers_of_passes_over_arenas():
         assert v["spilled"] == 0, (k, v)
     for k, v in arenas.items():
         if b"ILi32E" in k:
-            assert 800 // (-(-(v["sgprs"] + 16) // 16) * 16) == 6, (k, v)
+            assert _groups(v) == 6, (k, v)
+
+
+def test_groups_bounded_by_registers():
+    """Passes of which a compute unit is to run six groups say so in registers, not in LDS, which other streams' kernels may want."""
+    late = {**_resources(b"k_fused_compressedILi16ELi4ELi1ELi\\dELb0ELi(?:3|11)E"), **_resources(b"k_fused_argumentsILi16ELi4ELi1ELi\\dELi11E")}
+    sparse = _resources(b"k_fused_compressedILi\\d+ELi4ELi\\dELi\\dELb1ELi32E")
+    anyone = _resources(b"k_fused_compressedILi0ELi4ELi\\dELi\\dELb1ELi0E")   # any number of workers, sparse
+    assert (len(late), len(sparse), len(anyone)) == (9, 10, 9)
+    for k, v in {**late, **sparse, **anyone}.items():
+        assert _groups(v) == 6, (k, v)
