@@ -545,7 +545,7 @@ int launch_decode_sum(const uint32_t *const *streams, int num_workers, float *ag
     hipStream_t s = (hipStream_t)hip_stream;
 #define CDSGD_LAUNCH_DECODE(SZ, FORM, TILES, LDS)                                                              \
     do {                                                                                                       \
-        const unsigned groups = (tiles + TILES - 1u) / TILES, used = kTileLds<SZ, FORM, 4> * TILES, want = LDS; \
+        const unsigned groups = (tiles + TILES - 1u) / TILES, used = kTileLds<SZ, FORM, 4, SPARSE, false> * TILES, want = LDS; \
         const unsigned more = want > used ? want - used : 0u;                                                   \
         if (!SPARSE && nt)                                                                                      \
             hipLaunchKernelGGL((k_decode_sum<SZ, FORM, SPARSE, TILES, !SPARSE>), dim3(groups), dim3(kTileQuads), \
@@ -1028,7 +1028,7 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
     const auto bound = [&](unsigned used) { return shape.lds <= used ? 0u : shape.lds - used; };
 #define CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT)                                      \
     hipLaunchKernelGGL((k_fused_compressed<SZ, WAVES, FORM, GT, SPARSE, HOW, WAIT>), dim3(grid), dim3(64 * WAVES), \
-                       bound(kTileLds<SZ, FORM, WAVES>), s, plan->tensors, plan->table_for<HOW>(), plan->rows, \
+                       bound(kTileLds<SZ, FORM, WAVES, SPARSE, true>), s, plan->tensors, plan->table_for<HOW>(), plan->rows, \
                        num_tiles, grid, N, plan->self, threshold, lr_local, scale, with_local ? 1 : 0)
 #define CDSGD_LAUNCH_COMPRESSED_W(SZ, WAVES, FORM, SPARSE, HOW, WAIT)                                          \
     do {                                                                                                       \
@@ -1476,7 +1476,7 @@ int launch_from_arguments(const cdsgd_tensor *tensors, int num_tensors, const ui
     const auto bound = [&](unsigned used) { return shape.lds <= used ? 0u : shape.lds - used; };
 #define CDSGD_LAUNCH_ARGUMENTS_S(SZ, WAVES, FORM, GT, HOW)                                                     \
     hipLaunchKernelGGL((k_fused_arguments<SZ, WAVES, FORM, GT, HOW>), dim3(num_tiles), dim3(64 * WAVES),       \
-                       bound(kTileLds<SZ, FORM, WAVES>), s, num_tiles, (unsigned)num_tensors, num_workers, self, threshold, \
+                       bound(kTileLds<SZ, FORM, WAVES, false, true>), s, num_tiles, (unsigned)num_tensors, num_workers, self, threshold, \
                        lr_local, scale, flat)
 #define CDSGD_LAUNCH_ARGUMENTS(SZ, WAVES, FORM, HOW)                                                           \
     do {                                                                                                       \

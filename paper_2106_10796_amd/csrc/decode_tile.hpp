@@ -322,11 +322,11 @@ template <int SZ, bool SPARSE>
 constexpr bool kSlotTests = SPARSE || SZ == kUpTo4 || SZ == kUpTo8;  // tile_put
 template <int SZ>
 constexpr unsigned kSpareRow = (unsigned)kMaxRows<SZ>;  // written and not read; where there are sums they follow later
-template <int SZ>
-constexpr unsigned kRowsLds = (unsigned)kMaxRows<SZ> * kTileBytes +
-                              (!kByBytes<SZ> ? 16u * kTileQuads : (kSlotTests<SZ, false> ? 0u : kTileBytes));
-template <int SZ, int FORM, int WAVES>
-constexpr unsigned kTileLds = (FORM == kCount ? 4u * 4u * kTileQuads : kRowsLds<SZ>) * WAVES / 4;
+// SPARE: there is an own row that is not tested for (tile_put).
+template <int SZ, bool SPARE>
+constexpr unsigned kRowsLds = (unsigned)kMaxRows<SZ> * kTileBytes + (!kByBytes<SZ> ? 16u * kTileQuads : (SPARE ? kTileBytes : 0u));
+template <int SZ, int FORM, int WAVES, bool SPARSE, bool OWN>
+constexpr unsigned kTileLds = (FORM == kCount ? 4u * 4u * kTileQuads : kRowsLds<SZ, OWN && !kSlotTests<SZ, SPARSE>>) * WAVES / 4;
 
 template <int WAVES>
 __device__ __forceinline__ void group_sync()
@@ -502,7 +502,7 @@ __global__ __launch_bounds__(kTileQuads) void k_decode_sum(float *__restrict__ a
                                                            unsigned num_groups, int xcd, int drain, float t, StreamTable tab)
 {
     static_assert(kTilesPerChunk % TILES == 0, "the tiles of a group lie in one chunk");
-    constexpr unsigned kPerChunk = kTilesPerChunk / TILES, kLds = kTileLds<SZ, FORM, 4>;
+    constexpr unsigned kPerChunk = kTilesPerChunk / TILES, kLds = kTileLds<SZ, FORM, 4, SPARSE, false>;
     __shared__ __attribute__((aligned(16))) uint8_t lds[kLds * TILES];
     const unsigned tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));

@@ -129,7 +129,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_compressed(const TensorDes
                                                                  int self, float t_call, float lr_local, float scale,
                                                                  int write_local)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[kTileLds<SZ, FORM, WAVES>];
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kTileLds<SZ, FORM, WAVES, SPARSE, true>];
     constexpr unsigned kQuads = 64u * WAVES, kPerChunk = kChunkQuads / kQuads;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     // The kernels of 32-bit lists in arenas of 16 to 28 M elements, 17 to 32 workers: their groups are through sooner without the

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_fused_arguments(unsigned num_til
                                                                 float t, float lr_local, float scale, StaticArenas p)
 {
     static_assert((HOW & kArena) != 0, "lists in arenas");
-    __shared__ __attribute__((aligned(16))) uint8_t lds[kTileLds<SZ, FORM, WAVES>];
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kTileLds<SZ, FORM, WAVES, false, true>];
     constexpr unsigned kQuads = 64u * WAVES, kPerChunk = kChunkQuads / kQuads;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     admit_six_groups<SZ, FORM, HOW & ~kArena>();

@@ -100,3 +100,13 @@ def test_groups_bounded_by_registers():
     assert (len(late), len(sparse), len(anyone)) == (9, 10, 9)
     for k, v in {**late, **sparse, **anyone}.items():
         assert _groups(v) == 6, (k, v)
+
+
+def test_no_row_without_an_own_worker():
+    """The chain form's LDS of up to 16 workers holds their rows, and a spare one only where an own row is written without a test."""
+    for size, rows in ((4, 4), (8, 8), (16, 16)):
+        decode = _resources(b"k_decode_sumILi%dELi[12]ELb[01]ELi4E" % size)
+        assert len(decode) == 6
+        assert all(v["lds"] == 4 * 256 * rows for v in decode.values()), decode
+    sparse = _resources(b"k_fused_compressedILi16ELi4ELi1ELi\\dELb1E")
+    assert len(sparse) == 6 and all(v["lds"] == 256 * 16 for v in sparse.values()), sparse
