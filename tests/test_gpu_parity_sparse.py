@@ -54,6 +54,22 @@ def test_sparse_encode(B, oracle, n, density):
     assert_bits_equal(sparse.cpu().numpy(), want.view(np.int32), "sparse, no counts")
 
 
+@pytest.mark.parametrize("last", [1, 2, 3, 4, 5, 255, 256])
+@pytest.mark.parametrize("segments", [1, 2, 3, 4, 5, 8])
+def test_sparse_encode_in_larger_buffers(B, oracle, segments, last):
+    """Non-zero words behind the stream, sentinels around the buffers that are written: every remainder of a group's segments and of a lane's words."""
+    n, GUARD = 16 * (256 * (segments - 1) + last) - 3, 300
+    word = _words(np.random.default_rng(segments * 1000 + last), n, 0.5)
+    want, want_seg = oracle.sparse_encode(word, n, fill=0x5A5A5A5A)
+    dpacked = torch.full((word.size + GUARD,), -1, dtype=torch.int32, device="cuda")
+    dpacked[:word.size] = torch.from_numpy(word.view(np.int32))
+    out = {k: torch.full((size + 2 * GUARD,), 0x5A5A5A5A, dtype=torch.int32, device="cuda") for k, size in (("sparse", want.size), ("counts", want_seg.size))}
+    B.cdsgd_sparse_encode(dpacked[:word.size], n, *(v[GUARD: -GUARD] for v in out.values()))
+    torch.cuda.synchronize()
+    for got, ref in zip(out.values(), (want, want_seg)):
+        assert_bits_equal(got.cpu().numpy(), np.pad(ref, GUARD, constant_values=0x5A5A5A5A).view(np.int32), "%d segments, %d words" % (segments, last))
+
+
 @pytest.mark.parametrize("t", [0.5, 0.05])
 @pytest.mark.parametrize("N", [1, 3, 4, 5, 16, 17, 64])
 def test_decode_sum_sparse(B, oracle, N, t):

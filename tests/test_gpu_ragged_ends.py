@@ -1,6 +1,7 @@
 """GPU parity of every pass at ragged ends, where loads and stores are clipped word by word at the end of a tensor: all
 remainders of a quad, a word of codes, a wave, a tile and a chunk, each gradient type, against the oracle bit for bit.  What
-lies between and behind the tensors is NaN, so that a value read from there would show, and has to be what it was."""
+lies between and behind the tensors has to be what it was: NaN, but for gradients and residuals values past the threshold and for streams
+codes that are sent, so that one read from there would show in the codes behind a tensor's last one."""
 import numpy as np
 import pytest
 import torch
@@ -23,15 +24,16 @@ def B():
 
 
 class _Arena:
-    """A tensor of every size in one allocation, NaN (or -1 in packed words) between and behind them."""
+    """A tensor of every size in one allocation, `fill` (in packed words: all codes 01) between and behind them."""
 
-    def __init__(self, values, dtype):
+    def __init__(self, values, dtype, fill=9.0):
         self.packed, per = dtype == torch.int32, 16 if dtype == torch.int32 else 1
+        self.fill = 0x55555555 if self.packed else fill
         at, total = [], 0
         for n in SIZES:
             at.append(total // per)
             total += (n + 63) // 64 * 64 + 64
-        self.all = torch.full((total // per,), -1 if self.packed else float("nan"), dtype=dtype, device="cuda")
+        self.all = torch.full((total // per,), self.fill, dtype=dtype, device="cuda")
         self.views = [self.all[a: a + v.size] for a, v in zip(at, values)]
         self.between = torch.ones(self.all.numel(), dtype=torch.bool, device="cuda")
         for a, v in zip(at, values):
@@ -44,7 +46,7 @@ class _Arena:
 
     def check(self, want, what):
         left = self.all[self.between]
-        assert bool((left == -1).all() if self.packed else torch.isnan(left).all()), "%s: written between tensors" % what
+        assert bool((left == self.fill).all() if self.fill == self.fill else torch.isnan(left).all()), "%s: written between tensors" % what
         for n, view, ref in zip(SIZES, self.views, want):
             assert_bits_equal((view if self.packed else view.float()).cpu().numpy(), ref.view(np.int32) if self.packed else ref, "%s of %d elements" % (what, n))
 
@@ -57,7 +59,8 @@ def test_every_pass_at_ragged_ends(B, oracle, dtype):
     widened = lambda vs: [torch.from_numpy(v).to(dtype).float().numpy() for v in vs]
     host = dict(w_global=values(1.0), w_local=values(1.0), residual=values(0.2), grad=widened(values(0.5)), agg_full=values(1.0),
                 packed_self=[np.zeros((n + 15) // 16, np.uint32) for n in SIZES])
-    dev = {k: _Arena(v, dtype if k == "grad" else (torch.int32 if k == "packed_self" else torch.float32)) for k, v in host.items()}
+    dev = {k: _Arena(v, dtype if k == "grad" else (torch.int32 if k == "packed_self" else torch.float32),
+                     9.0 if k in ("grad", "residual") else float("nan")) for k, v in host.items()}
     words = [[oracle.pack(rng.integers(0, 4, n).astype(np.uint8)) for n in SIZES] for _ in range(N)]
     peers = [None if j == rank else _Arena(words[j], torch.int32).views for j in range(N)]
     grads = [host["grad"] if j == rank else widened(values(0.5)) for j in range(N)]

@@ -1,5 +1,6 @@
 """Compressed passes over lists in arenas around the lengths between which the weights are asked for behind the other streams,
-against the same lists with buffers that lie anywhere, whose kernels ask for all at once: bit for bit."""
+against the same lists with buffers that lie anywhere, whose kernels ask for all at once: bit for bit.  (Lists of
+17 to 32 workers against the oracle: test_gpu_dispatch_lines.py.  Longer lists of more workers against their parts: test_gpu_cache_policies.py.)"""
 import pytest
 import torch
 
