@@ -905,8 +905,8 @@ constexpr unsigned kWalkingGroups = 768;
 //   0.45 M 1.24 / 1.23, 0.7 M 1.14 / 1.07, 1 M .98 / .98, 1.4 M 1.00 / .99;  N = 17 / 32 0.45 M 1.15 / 1.07, 1 M 1.04 / 1.07,
 //   1.4 M 1.03 / 1.01;  32-bit, t = 0.3, N = 16 / 32 0.45 M 1.10 / 1.00, 1 M .99 / 1.05, 1.4 M 1.02 / 1.02)
 //   up to 8 workers   N = 4, t = 0.3  4 M 1.03, 12 M .99, 25 M 1.00, VGG-16 1.06;  N = 8 1.02 / 1.00 / 1.01 / 1.00
-// Kernels of their own for 17 to 32 workers, which hold half the stream pointers in scalar registers (but 1 to 6 of them where the
-// list lies in arenas), over those for any number (results written through / and the list in arenas), N = 17 / 24 / 32:
+// Kernels of their own for 17 to 32 workers, whose waves hold half as many stream pointers, over those for any number (results
+// written through / and the list in arenas), N = 17 / 24 / 32:
 //   t = 0.5, 32-bit   1 M .83 .83 .88 / .81 .82 .88;  4 M .98 .97 .98 / .98 .97 .97;  12 M .99 .99 .98 / .99 .99 .99;
 //                     ResNet-50-shaped .97 .98 .98 / .97 .97 .98;  VGG-16 .99 1.00 1.01
 //   t = 0.3, 32-bit   1 M .97 1.03 .97 / .93 .99 .96;  4 M .99 .99 1.00 / .98 .98 .98;  12 M 1.00 .99 .97 / .99 .99 .99;
@@ -921,8 +921,9 @@ constexpr unsigned long long kStreamWordsBytes = 112000000;
 // Lists in arenas (ArenaChunk), up to 32 workers and 28 M elements: one trip to memory less before a group's first data
 // loads.  Time over that of the general kernels: 1 M elements .97-1.00, 2 M .97-.99, 4 M .98-.99, 8 M .99-1.00, 25 M
 // .99-1.01; ResNet-50-shaped list, N = 16, in 19 launches of a million elements and more 163.1 / 156.9 us, in one 107.0 /
-// 106.2.  (VGG-16-shaped .99-1.04, 1 GiB buckets 1.02.  Above 32 workers 1 M 1.12, 4 M 1.03, 25 M 1.01: more of the stream
-// pointers no longer fit the scalar registers beside the buffers'.)
+// 106.2;  N = 32, t = 0.5 / 0.1 / 0.1 in bf16  0.3 M .92 / .99 / .99, 0.9 M .95 / .96 / .97, 1.5 M .97 / .99 / .98, 3 M .98 / .98 / .97,
+// 8 M .99 / 1.00 / .99, 20 M 1.00 / 1.00 / .99, 26 M 1.01 / 1.00 / 1.00.  (VGG-16-shaped .99-1.04, 1 GiB buckets 1.02.  Above 32
+// workers 1 M 1.12, 4 M 1.03, 25 M 1.01, in kernels that held the pointers, more than there are scalar registers, through the loop over tiles.)
 constexpr int kUpTo32Rows = 16;  // host side only: the kernels for up to 32 workers
 struct CompressedLaunch {
     unsigned waves, lds;
@@ -1474,6 +1475,9 @@ int launch_from_arguments(const cdsgd_tensor *tensors, int num_tensors, const ui
     const unsigned num_tiles = num_chunks * (kChunkQuads / (64u * shape.waves));
     const float scale = lr_global / (float)num_workers;
     const auto bound = [&](unsigned used) { return shape.lds <= used ? 0u : shape.lds - used; };
+    // (17 to 32 workers ask for all streams at once, as the kernels with tables do not: weights behind gradient and residual over that,
+    // 2.2 / 5 / 12 / 20 M: chain N = 17 .99 .99 1.00 1.01, 24 .99 .99 1.00 .99, 32 .98 1.00 1.00 .99, bf16 .98 .99 .99 .99;  count
+    // N = 17 1.03 1.01 1.00 1.02, 20 1.02 1.01 1.01 1.03, 24 1.01 1.00 1.01 1.00, 32 1.00 1.00 .99 1.00.)
 #define CDSGD_LAUNCH_ARGUMENTS_S(SZ, WAVES, FORM, GT, HOW)                                                     \
     hipLaunchKernelGGL((k_fused_arguments<SZ, WAVES, FORM, GT, HOW>), dim3(num_tiles), dim3(64 * WAVES),       \
                        bound(kTileLds<SZ, FORM, WAVES, false, true>), s, num_tiles, (unsigned)num_tensors, num_workers, self, threshold, \

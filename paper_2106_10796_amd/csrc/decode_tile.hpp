@@ -108,11 +108,11 @@ struct StreamPointers {
     }
 
     // Keeps the compiler from moving the loads to where their pointers are used.  Above 32 workers a wave of the fused
-    // kernels then holds more addresses than it has scalar registers for beside the descriptor: 5 (count form), 19
-    // (chain) and 19 / 27 (sparse) of them are kept in lanes of a vector register, and 7 waves fit a SIMD instead of 8
-    // (17 to 32 workers, list in arenas: 1 or 3 in the count form, 1 to 6 in the chain).
+    // kernels then needs all 106 scalar registers, which admit six groups to a compute unit (kSix); with sparse peers, which
+    // have more addresses, 10 (count form) and 13 to 15 (chain) of them are kept in lanes of a vector register, and in the
+    // form for tiny thresholds 1.
     // Short lists, where the early pointers count, gain all the same (figures at the head of kernels_fused.hpp); long
-    // ones do not use the eighth wave.  The single-tensor decode has no descriptor and spills none.
+    // ones run no better with more groups.  The single-tensor decode has no descriptor and spills none.
     __device__ __forceinline__ void pin()
     {
         if constexpr (WAVES != 1) {
