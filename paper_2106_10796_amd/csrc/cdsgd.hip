@@ -858,8 +858,9 @@ namespace {
 //   the same, sparse          one code in 16  25 M .99-1.01, 60 M 1.00-1.03, VGG-16-shaped 1.04-1.07, 260 M 1.06-1.09, bf16 138 M 1.05-1.08
 //                             (below 16 M six take longer: 2 M 1.05, 4 M 1.01-1.04)
 //   17 to 32 workers, sparse  138 M, bf16  N = 17 / 20 1.04 / 1.01-1.03, t = 0.5 1.02 / 1.02, N = 32 .99-1.00;  60 M 1.00, N = 32 .99  (18 to 25 M .99: no bound there)
-//   up to 8 workers, sparse   25 M, t = 0.1  N = 4 1.005, N = 8 1.015;  18 M 1.000, 1.006;  t = 0.5 18 and 25 M 1.00: no bound there
-//   9 to 16 workers, sparse, t = 0.5   18 and 25 M 1.00: no bound there
+//   up to 8 workers, sparse   18 M, t = 0.1  N = 4 1.000, N = 8 1.006;  25 M N = 4 1.005, N = 8 1.015;  t = 0.5 1.00;  ResNet-50-shaped,
+//                             t = 0.5, N = 8 1.01, one code in 256, bf16 1.006-1.008
+//   9 to 16 workers, sparse, t = 0.5   18 and 25 M 1.00;  ResNet-50-shaped 1.00, one code in 256, bf16 1.003-1.006
 //   (Above 32 workers the registers admit six.)
 // Five groups over six, 16-bit chains: N = 9 / 12 / 13 / 16  50 M 1.03 / 1.02 / .98 / .98, 80 M .99 / .99 / .98-.99 / .98;  17 to 32 workers, 18 to
 // 25 M  N = 24 .98-1.02, N = 28 / 30 / 32 .98-.99 / .97 / .96, ResNet-50-shaped .98 / 1.00 / .96.
@@ -948,7 +949,7 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
     }
     if (sparse) {
         const bool five = long_list && (num_workers <= kUpTo8 || (num_workers <= kUpTo16 && form == kCount));
-        const bool six = num_workers <= kUpTo16 ? mid_list && form == kChain : long_list && half && num_workers <= kUpTo32;
+        const bool six = num_workers <= kUpTo16 ? mid_list : long_list && half && num_workers <= kUpTo32;
         return {4u, five ? 32768u : 0u, six && !five ? kSixGroups : 0, 0u};
     }
     const int arena = arenas && max_workgroups == 0 ? kArena : 0;
@@ -1054,9 +1055,9 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
 #define CDSGD_LAUNCH_COMPRESSED_F(FORM, LAUNCH_LATE)                                                           \
     do {                                                                                                       \
         if (plan->peers_sparse && shape.how != 0 && shape.how != kSixGroups) return CDSGD_ERR_DEVICE;          \
-        else if (shape.how == kSixGroups && (!plan->peers_sparse || N > kUpTo32 || (N <= kUpTo16 && FORM != kChain))) return CDSGD_ERR_DEVICE; \
-        else if (shape.how == kSixGroups && N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, kChain, true, kSixGroups); \
-        else if (shape.how == kSixGroups && N <= kUpTo16) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, kChain, true, kSixGroups); \
+        else if (shape.how == kSixGroups && (!plan->peers_sparse || N > kUpTo32)) return CDSGD_ERR_DEVICE;     \
+        else if (shape.how == kSixGroups && N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, true, kSixGroups); \
+        else if (shape.how == kSixGroups && N <= kUpTo16) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, true, kSixGroups); \
         else if (shape.how == kSixGroups) CDSGD_LAUNCH_COMPRESSED_16BIT(kUpTo32, 4, FORM, true, kSixGroups);   \
         else if (plan->peers_sparse && N <= kUpTo8) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, true, 0);         \
         else if (plan->peers_sparse && N <= kUpTo16) CDSGD_LAUNCH_COMPRESSED(kUpTo16, 4, FORM, true, 0);       \
