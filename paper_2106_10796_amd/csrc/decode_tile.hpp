@@ -404,7 +404,8 @@ __device__ __forceinline__ void tile_put(const unsigned (&w)[kWordsPerWave<SZ>],
     }
 }
 
-template <int SZ, int FORM, int WAVES, bool SPREAD>
+// ALONE: packed streams of one tensor (k_decode_sum).
+template <int SZ, int FORM, int WAVES, bool SPREAD, bool ALONE>
 __device__ __forceinline__ f4 tile_get(f4 own_value, int num_workers, float t, uint8_t *lds, TilePlace<WAVES> at)
 {
     constexpr unsigned kQuads = 64u * WAVES, kBytes = kQuads;
@@ -427,15 +428,32 @@ __device__ __forceinline__ f4 tile_get(f4 own_value, int num_workers, float t, u
         if constexpr (kByBytes<SZ>) {
             // every lane adds up its own quad, a byte of every row: one operation more per worker than by words, no exchange
             agg = f4{0.0f, 0.0f, 0.0f, 0.0f};
-            unsigned code[SZ];
+            if constexpr (ALONE) {
+                // One test and then all rows, their bytes read at once.  With a test for every four rows the compiler puts the reads
+                // behind it as well, or in front of all of them, as it sees fit: a trip to LDS for every four rows.  Decode-and-sum
+                // of 1 / 1.6 / 2.2 / 3 / 6 / 16 M elements, t = 0.1, time over that:  N = 9 .89 .95 .95 .94 .96 .99;  12 .89 .95 .95 .95
+                // .96 .98;  13 .92 .95 .97 .97 .99 1.00;  16 .93 .96 .98 .99 .99 1.00;  5 and 8, 2 to 16 M .96-.99.
+                const auto add = [&](auto rows) {
+                    constexpr int ROWS = decltype(rows)::value;
+                    unsigned code[ROWS];
 #pragma unroll
-            for (int j = 0; j < SZ; ++j) code[j] = lds[kBytes * (unsigned)j + tid];
+                    for (int j = 0; j < ROWS; ++j) code[j] = lds[kBytes * (unsigned)j + tid];
 #pragma unroll
-            for (int j0 = 0; j0 < SZ; j0 += 4)
-                if (j0 < num_workers) {
+                    for (int j = 0; j < ROWS; ++j) chain_byte(agg, code[j], t);
+                };
+                if (SZ == kUpTo16 && num_workers <= 12) add(std::integral_constant<int, 12 < SZ ? 12 : SZ>{});
+                else add(std::integral_constant<int, SZ>{});
+            } else {
+                unsigned code[SZ];
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) chain_byte(agg, code[j0 + k], t);
-                }
+                for (int j = 0; j < SZ; ++j) code[j] = lds[kBytes * (unsigned)j + tid];
+#pragma unroll
+                for (int j0 = 0; j0 < SZ; j0 += 4)
+                    if (j0 < num_workers) {
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) chain_byte(agg, code[j0 + k], t);
+                    }
+            }
         } else {
             float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
             const unsigned shift = 14u - 4u * (unsigned)wave;
@@ -469,7 +487,7 @@ __device__ __forceinline__ f4 tile_sums(const unsigned (&w)[kWordsPerWave<SZ>], 
     const TilePlace<WAVES> at;
     tile_put<SZ, FORM, WAVES, TESTS>(w, own_code, own_at, num_workers, lds, at);
     group_sync<WAVES>();
-    return tile_get<SZ, FORM, WAVES, SPREAD>(own_value, num_workers, t, lds, at);
+    return tile_get<SZ, FORM, WAVES, SPREAD, false>(own_value, num_workers, t, lds, at);
 }
 
 // ---------------------------------------------------------------------------
@@ -532,7 +550,7 @@ __global__ __launch_bounds__(kTileQuads) void k_decode_sum(float *__restrict__ a
     float *out = agg_out + (size_t)x * (4u * kTileQuads * TILES);
 #pragma unroll
     for (unsigned k = 0; k < TILES; ++k) {
-        const f4 agg = tile_get<SZ, FORM, 4, SPARSE>(f4{0.0f, 0.0f, 0.0f, 0.0f}, num_workers, t, lds + kLds * k, at);
+        const f4 agg = tile_get<SZ, FORM, 4, SPARSE, !SPARSE>(f4{0.0f, 0.0f, 0.0f, 0.0f}, num_workers, t, lds + kLds * k, at);
         const unsigned qi = kTileQuads * k + tid;
         if (chunk < ext.full_chunks) {
             if (drain) st4p<kStream>(out, qi, agg);
