@@ -550,10 +550,10 @@ int launch_decode_sum(const uint32_t *const *streams, int num_workers, float *ag
         const unsigned more = want > used ? want - used : 0u;                                                   \
         if (!SPARSE && nt)                                                                                      \
             hipLaunchKernelGGL((k_decode_sum<SZ, FORM, SPARSE, TILES, !SPARSE>), dim3(groups), dim3(kTileQuads), \
-                               more, s, agg, ext.full_chunks, ext.tail_elems, ext.tail_bytes, num_workers, groups, xcd, drain, threshold, tab); \
+                               more, s, agg, ext, num_workers, groups, xcd, drain, threshold, tab);                    \
         else                                                                                                    \
             hipLaunchKernelGGL((k_decode_sum<SZ, FORM, SPARSE, TILES, false>), dim3(groups), dim3(kTileQuads),  \
-                               more, s, agg, ext.full_chunks, ext.tail_elems, ext.tail_bytes, num_workers, groups, xcd, drain, threshold, tab); \
+                               more, s, agg, ext, num_workers, groups, xcd, drain, threshold, tab);                    \
     } while (0)
     const bool count = is_pow2_threshold(threshold);
     constexpr unsigned kLdsCount = SPARSE ? 24576u : 32768u, kLdsChain = SPARSE ? 0u : 24576u;

@@ -515,13 +515,9 @@ struct StreamTable {
     const uint8_t *p[CDSGD_MAX_WORKERS];  // null past the last worker
 };
 
-// full_chunks, tail_elems, tail_bytes: the tensor's Extent, by its members, for a structure is not among the arguments that arrive in
-// registers, and nothing behind it is.  Time over that with the structure: 1.6 to 16 M elements, N = 2 to 16 .98-1.01;  1.6 / 4 /
-// 16 M, t = 0.1  N = 17 .98 .98 .99, 24 .99 .98 .99, 32 .97 .98 .99, 48 .99 .99 .99, 64 .99 .99 1.00, sparse .98-1.00;  t = 0.5 .98-1.00.
 template <int SZ, int FORM, bool SPARSE, int TILES, bool NT>
-__global__ __launch_bounds__(kTileQuads) void k_decode_sum(float *__restrict__ agg_out, unsigned full_chunks, unsigned tail_elems,
-                                                           unsigned tail_bytes, int num_workers, unsigned num_groups, int xcd,
-                                                           int drain, float t, StreamTable tab)
+__global__ __launch_bounds__(kTileQuads) void k_decode_sum(float *__restrict__ agg_out, Extent ext, int num_workers,
+                                                           unsigned num_groups, int xcd, int drain, float t, StreamTable tab)
 {
     static_assert(kTilesPerChunk % TILES == 0, "the tiles of a group lie in one chunk");
     constexpr unsigned kPerChunk = kTilesPerChunk / TILES, kLds = kTileLds<SZ, FORM, 4, SPARSE, false>;
@@ -535,7 +531,7 @@ __global__ __launch_bounds__(kTileQuads) void k_decode_sum(float *__restrict__ a
     from.pin();
     TileStreams s;
     s.num_workers = num_workers;
-    s.stream_bytes = full_chunks * kChunkQuads + tail_bytes;
+    s.stream_bytes = ext.full_chunks * kChunkQuads + ext.tail_bytes;
     s.segment_at = (size_t)chunk * (4u * kSegStride);
     u2 bitmap = {0u, 0u};
     if constexpr (SPARSE) bitmap = load_bitmap(from.bitmap, s, tid & 63u);
@@ -556,12 +552,12 @@ __global__ __launch_bounds__(kTileQuads) void k_decode_sum(float *__restrict__ a
     for (unsigned k = 0; k < TILES; ++k) {
         const f4 agg = tile_get<SZ, FORM, 4, SPARSE, !SPARSE>(f4{0.0f, 0.0f, 0.0f, 0.0f}, num_workers, t, lds + kLds * k, at);
         const unsigned qi = kTileQuads * k + tid;
-        if (chunk < full_chunks) {
+        if (chunk < ext.full_chunks) {
             if (drain) st4p<kStream>(out, qi, agg);
             else st4p<kThrough>(out, qi, agg);
         } else {
             const unsigned e0 = x % kPerChunk * (4u * kTileQuads * TILES);
-            st4g<true, kThrough>(out, qi, elems_from(e0, tail_elems), agg);
+            st4g<true, kThrough>(out, qi, elems_from(e0, ext.tail_elems), agg);
         }
     }
 }
