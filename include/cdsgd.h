@@ -279,11 +279,10 @@ int cdsgd_plan_set_peer_format(cdsgd_plan *plan, int format);
  * for any limit below a sixth of its 1024-element tiles: more of them are slower.)
  * LDS left to other streams, of 160 KiB per compute unit: without a limit, compressed passes over
  * more than 6 M elements and full-gradient passes of any length may ask for LDS to bound the
- * workgroups resident, 120 to 160 KiB in all (three groups of 48 KiB, or one-wave groups of 6 to
- * 8 KiB), so a kernel of another stream that needs more than the rest waits until groups end.  With
- * a limit a full-gradient pass asks for none, and a compressed pass at most for 32 KiB in each of three
- * groups, as long as the limit is below that sixth.  The
- * results are bit for bit the same for every limit.  0 removes the limit; negative values are
+ * workgroups resident, 120 to 160 KiB in all (three groups of 48 KiB, four of 38 or 40, five of 32, six
+ * of 24, or one-wave groups of 6 to 8 KiB), so a kernel of another stream that needs more than the rest
+ * waits until groups end.  With a limit a full-gradient pass asks for none, and a compressed pass at most
+ * for 32 KiB in each of three groups, as long as the limit is below that sixth.  The results are bit for bit the same for every limit.  0 removes the limit; negative values are
  * CDSGD_ERR_PARAM.  Host-side setting only: it applies to passes enqueued after the call.
  */
 int cdsgd_plan_set_max_workgroups(cdsgd_plan *plan, int max_workgroups);

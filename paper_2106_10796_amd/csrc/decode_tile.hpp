@@ -384,10 +384,11 @@ __device__ __forceinline__ void tile_put(const unsigned (&w)[kWordsPerWave<SZ>],
     } else {
         // Rows of signed fields, worker by worker; those past the last worker are zero.  Packed streams of more than eight
         // workers: every slot is written without a test.  Behind a test of its own (a slot past the last worker, the own one) the compiler puts the load of
-        // the slot's word as well, and a wave of the kernels for any number of workers then waited for memory twice: 16.7 M
-        // elements decoded and updated, t = 0.3, N = 33 / 48 / 64 80.3 / 88.2 / 103.6 us, 68.0 / 79.0 / 91.8 so;  4 M 22.3 /
-        // 25.0 / 29.4, 19.5 / 22.5 / 25.6;  compressed pass 0.5 M N = 32 / 64 4.6 / 6.8, 4.4 / 6.3;  1 M 7.2 / 10.2, 6.9 / 9.8;
-        // 4 M 22.4 / 28.0, 22.1 / 27.6.  The own row is made of the lanes' own codes; what the wave holds for it goes to
+        // the slot's word as well, as it sees fit, and a wave of the kernels for any number of workers then waits for memory twice.
+        // With tests / so, us: 16.7 M elements decoded and updated, t = 0.3, N = 33 / 48 / 64 80.3 / 87.5 / 103.0, 66.5 / 77.5 / 90.1;  4 M
+        // 21.9 / 24.4 / 29.0, 19.0 / 22.3 / 25.7;  compressed pass 0.5 M N = 32 / 64 4.3 / 6.5, 4.2 / 6.1;  1 M 7.1 / 9.9, 6.7 / 9.5;
+        // 4 M 21.4 / 28.2, 21.4 / 27.7.  (With tests and the fields made without bitop3 the decode waited once: 67.1 / 78.2 /
+        // 91.4 and 19.5 / 22.8 / 26.6.)  The own row is made of the lanes' own codes; what the wave holds for it goes to
         // the spare row.  (Sparse streams, whose words have to wait for their bitmaps: N = 64 2-6 % faster without tests, 33 to 48
         // 1-5 % slower; packed streams of 5 to 8 workers, 60 M elements 1 % slower.  MID of the compressed pass: there.)
         unsigned *rows = reinterpret_cast<unsigned *>(lds);

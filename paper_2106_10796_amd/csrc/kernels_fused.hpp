@@ -105,6 +105,9 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
 //   t = 0.5, bf16     0.9 M .97 .98 .97 / .97 .98 .97;  1.5 M .99 .97 .99 / .99 .98 .99;  5 M .99 1.01 1.00 / 1.01 1.01 1.01;  12 and 16 M 1.00 / 1.01
 //   t = 0.1, 32-bit   0.9 to 3.5 M .99-1.01 / .99-1.03;  12 and 16 M 1.00 / 1.01;  18 M .98 .99 1.00 / .97 .99 1.00
 //   t = 0.1, bf16     0.9 M .99 .99 .96 / .99 .98 .96;  1.5 M .98 .97 .97;  3.5 M 1.00 .99 1.00;  12 and 16 M 1.00 / 1.01-1.02;  23 and 26 M .99-1.00 / .99-1.02
+// (9 to 16 workers hold theirs through the loop in 98 to 106 registers and spill none; 93 to 101 before ragged ends were clipped.
+// Time over that, N = 9 / 12 / 16: count form 32-bit 1.1 M 1.00 1.01 1.00, 1.6 M .99 .98 .98, 2.2 M 1.00 1.00 .98, 3 and 5 M .99-1.00,
+// bf16 1.1 M .90 .93 .92, 1.6 M .91 .91 .89, 2.2 to 5 M .96-.99;  chain 0.3 and 0.5 M the launch, 1 to 12 M 32-bit .97-1.00, 0.9 and 1.6 M bf16 .94-.99.)
 template <int SZ, int HOW>
 constexpr bool kManyPointers = SZ == kUpTo32 && (HOW & kArena) != 0;
 
