@@ -929,7 +929,7 @@ constexpr unsigned long long kStreamWordsBytes = 112000000;
 constexpr int kUpTo32Rows = 16;  // host side only: the kernels for up to 32 workers
 struct CompressedLaunch {
     unsigned waves, lds;
-    int how;          // kLate, kWrittenOut, kStreamWords, kArena, kSixGroups, kUpTo32Rows
+    int how;          // kLate, kWrittenOut, kStreamWords, kArena, kSixGroups, kFewGroups, kUpTo32Rows
     unsigned groups;  // launch at most this many (0: no bound)
 };
 
@@ -940,8 +940,15 @@ CompressedLaunch compressed_launch(unsigned num_chunks, int num_workers, int for
     const bool mid_list = tiles > kMidListTiles, long_list = tiles > kLongListTiles, half = grad_type != kGradF32;
     if (max_workgroups != 0) {
         const bool walk = max_workgroups <= tiles / 6u, count16 = form == kCount && num_workers > kUpTo8 && num_workers <= kUpTo16;
-        if (!mid_list || (sparse && !(walk && long_list && count16))) return {4u, 0u, 0, 0u};
-        if (walk) return {4u, 32768u, !sparse && count16 && (half || max_workgroups <= 512u) ? kLate : 0, kWalkingGroups};
+        // Up to 8 workers, few groups that walk the list, each waiting for the last of its loads.  Since ragged ends are read without tests
+        // the compiler asks for the words behind gradient and residual; the chain's rows it reads in two trips.  Time over that with the
+        // tests, in the compiler's order / so, 16 to 256 groups:  count form, 32-bit  N = 2 to 8, 4 to 70 M 1.002-1.007 / .97-.99;  chain  N = 5 and 8
+        // 1.014-1.020 / .98-.99, 16-bit 1.00-1.01 / .98-.99, N = 2 and 4 .99 / .985-.99;  both, 0.3 M, 64 groups 1.00-1.03 / .96-1.00.  (Count form,
+        // 16-bit, stays as it is, 1.004-1.019: so, 4 and 20 M .94-1.00, but 70 M 1.07-1.08.  More groups: .99-1.01 either way.)
+        const bool few = !sparse && num_workers <= kUpTo8 && max_workgroups <= tiles / 2u && (form == kChain || (form == kCount && !half));
+        const int few_groups = few ? kFewGroups : 0;
+        if (!mid_list || (sparse && !(walk && long_list && count16))) return {4u, 0u, few_groups, 0u};
+        if (walk) return {4u, 32768u, few_groups | (!sparse && count16 && (half || max_workgroups <= 512u) ? kLate : 0), kWalkingGroups};
         if (num_workers <= kUpTo8) return {4u, 49152u, 0, 0u};
     }
     if (form == kChainTiny) {
@@ -1040,7 +1047,7 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
         else CDSGD_LAUNCH_COMPRESSED_S(SZ, WAVES, FORM, kGradF32, SPARSE, HOW, WAIT);                          \
     } while (0)
 #define CDSGD_LAUNCH_COMPRESSED(SZ, WAVES, FORM, SPARSE, HOW) CDSGD_LAUNCH_COMPRESSED_W(SZ, WAVES, FORM, SPARSE, HOW, false)
-// (the count form of 9 to 16 workers asks for the words last with 32-bit gradients only: compressed_launch)
+// (the count form asks for the words last, 9 to 16 workers, or first, few groups, with 32-bit gradients only: compressed_launch)
 #define CDSGD_LAUNCH_COMPRESSED_32BIT(SZ, WAVES, FORM, SPARSE, HOW)                                            \
     do {                                                                                                       \
         if (plan->grad_type != kGradF32) return CDSGD_ERR_DEVICE;                                              \
@@ -1067,6 +1074,7 @@ int launch_formal_pass(const PlanTables *plan, long step, int k, float threshold
         else if (shape.waves == 1u && shape.how == kArena) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 1, FORM, false, kArena); \
         else if (shape.waves == 1u && shape.how == 0) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 1, FORM, false, 0);      \
         else if (N <= kUpTo8 && shape.how == kArena) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, false, kArena);  \
+        else if (N <= kUpTo8 && shape.how == kFewGroups) LAUNCH_LATE(kUpTo8, 4, FORM, false, kFewGroups); \
         else if (N <= kUpTo8 && shape.how == 0) CDSGD_LAUNCH_COMPRESSED(kUpTo8, 4, FORM, false, 0);            \
         else if (N <= kUpTo8) return CDSGD_ERR_DEVICE;                                                         \
         else if (shape.how == (kUpTo32Rows | kWrittenOut | kArena) && weights_wait) CDSGD_LAUNCH_COMPRESSED_W(kUpTo32, 4, FORM, false, kWrittenOut | kArena, true); \

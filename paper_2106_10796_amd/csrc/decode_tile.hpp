@@ -405,8 +405,9 @@ __device__ __forceinline__ void tile_put(const unsigned (&w)[kWordsPerWave<SZ>],
     }
 }
 
-// AT_ONCE: chain form up to 16 workers, all rows behind one test.
-template <int SZ, int FORM, int WAVES, bool SPREAD, bool AT_ONCE>
+// READS, chain form up to 16 workers: kOneTest: all rows behind one test;  kAllFirst: all read in front of the tests;  0: as the compiler has them.
+constexpr int kOneTest = 1, kAllFirst = 2;
+template <int SZ, int FORM, int WAVES, bool SPREAD, int READS>
 __device__ __forceinline__ f4 tile_get(f4 own_value, int num_workers, float t, uint8_t *lds, TilePlace<WAVES> at)
 {
     constexpr unsigned kQuads = 64u * WAVES, kBytes = kQuads;
@@ -429,10 +430,10 @@ __device__ __forceinline__ f4 tile_get(f4 own_value, int num_workers, float t, u
         if constexpr (kByBytes<SZ>) {
             // every lane adds up its own quad, a byte of every row: one operation more per worker than by words, no exchange
             agg = f4{0.0f, 0.0f, 0.0f, 0.0f};
-            if constexpr (AT_ONCE) {
+            if constexpr (READS == kOneTest) {
                 // One test and then all rows, their bytes read at once.  With a test for every four rows the compiler puts the reads
                 // behind it as well, or in front of all of them, as it sees fit: a trip to LDS for every four rows.  Decode-and-sum,
-                // t = 0.1, time over that, 1 / 1.6 / 2.2 / 3 / 6 / 16 M elements (in the other kernels the reads are in front):
+                // t = 0.1, time over that, 1 / 1.6 / 2.2 / 3 / 6 / 16 M elements (in the other kernels the reads are in front, of up to 8 workers half of them):
                 //   packed  N = 9 and 12 .89 .95 .95 .94 .96 .99;  13 .92 .95 .97 .97 .99 1.00;  16 .93 .96 .98 .99 .99 1.00;  5 and 8, 2 to 16 M .96-.99
                 //   sparse  3 to 16 M  N = 2 and 4 .98-.99;  8 .97-1.00  (9 to 12, 1 to 16 M .92-1.00, but 13 and 16 from 6 M on 1.01-1.03)
                 const auto add = [&](auto rows) {
@@ -449,6 +450,10 @@ __device__ __forceinline__ f4 tile_get(f4 own_value, int num_workers, float t, u
                 unsigned code[SZ];
 #pragma unroll
                 for (int j = 0; j < SZ; ++j) code[j] = lds[kBytes * (unsigned)j + tid];
+                if constexpr (READS == kAllFirst) {
+#pragma unroll
+                    for (int j = 0; j < SZ; ++j) asm volatile("" : "+v"(code[j]));
+                }
 #pragma unroll
                 for (int j0 = 0; j0 < SZ; j0 += 4)
                     if (j0 < num_workers) {
@@ -482,14 +487,14 @@ __device__ __forceinline__ f4 tile_get(f4 own_value, int num_workers, float t, u
     return agg;
 }
 
-template <int SZ, int FORM, int WAVES, bool TESTS, bool SPREAD>
+template <int SZ, int FORM, int WAVES, bool TESTS, bool SPREAD, int READS>
 __device__ __forceinline__ f4 tile_sums(const unsigned (&w)[kWordsPerWave<SZ>], unsigned own_code, f4 own_value,
                                         int own_at, int num_workers, float t, uint8_t *lds)
 {
     const TilePlace<WAVES> at;
     tile_put<SZ, FORM, WAVES, TESTS>(w, own_code, own_at, num_workers, lds, at);
     group_sync<WAVES>();
-    return tile_get<SZ, FORM, WAVES, SPREAD, false>(own_value, num_workers, t, lds, at);
+    return tile_get<SZ, FORM, WAVES, SPREAD, READS>(own_value, num_workers, t, lds, at);
 }
 
 // ---------------------------------------------------------------------------
@@ -552,7 +557,7 @@ __global__ __launch_bounds__(kTileQuads) void k_decode_sum(float *__restrict__ a
     float *out = agg_out + (size_t)x * (4u * kTileQuads * TILES);
 #pragma unroll
     for (unsigned k = 0; k < TILES; ++k) {
-        const f4 agg = tile_get<SZ, FORM, 4, SPARSE, !SPARSE || SZ == kUpTo4 || SZ == kUpTo8>(f4{0.0f, 0.0f, 0.0f, 0.0f}, num_workers, t, lds + kLds * k, at);
+        const f4 agg = tile_get<SZ, FORM, 4, SPARSE, !SPARSE || SZ == kUpTo4 || SZ == kUpTo8 ? kOneTest : 0>(f4{0.0f, 0.0f, 0.0f, 0.0f}, num_workers, t, lds + kLds * k, at);
         const unsigned qi = kTileQuads * k + tid;
         if (chunk < ext.full_chunks) {
             if (drain) st4p<kStream>(out, qi, agg);

@@ -25,7 +25,8 @@ constexpr bool kLocalFirst = SZ == kUpTo16 && FORM != kCount;
 //   kStreamWords the workers' words are read non-temporally
 //   kArena       the list lies in arenas (ArenaChunk): entry, buffers and stream pointers come in one trip to memory
 //   kSixGroups   no more than six groups to a compute unit
-constexpr int kLate = 1, kWrittenOut = 2, kStreamWords = 4, kArena = 8, kSixGroups = 32;
+//   kFewGroups   few groups walk the list (compressed_launch): the count form asks for the words first, the chain form reads all rows at once
+constexpr int kLate = 1, kWrittenOut = 2, kStreamWords = 4, kArena = 8, kSixGroups = 32, kFewGroups = 64;
 template <int HOW>
 struct ChunkEntry { typedef ChunkRef type; };
 template <>
@@ -40,7 +41,7 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
                                            unsigned rem_bytes, float t, float lr_local, float scale, bool write_local,
                                            uint8_t *lds)
 {
-    constexpr bool LATE = (HOW & kLate) != 0, OUT = (HOW & kWrittenOut) != 0, NT = (HOW & kStreamWords) != 0;
+    constexpr bool LATE = (HOW & kLate) != 0, OUT = (HOW & kWrittenOut) != 0, NT = (HOW & kStreamWords) != 0, FEW = (HOW & kFewGroups) != 0;
     constexpr int kStore = OUT ? kThroughStream : kStream;
     const unsigned tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
@@ -60,6 +61,7 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
     s.tile = tile;
     unsigned words[kWordsPerWave<SZ>];
     if (!LATE) load_words<SZ, WAVES, SPARSE, NT>(words, from, s, wave, tid & 63u);
+    if (FEW && FORM == kCount) __builtin_amdgcn_sched_barrier(0);
     const GradQuad<GT> loaded = load_grad<G, GT>(grad, tid, rem_elems);
     f4 r = ld4g<G>(resid, tid, rem_elems);
     f4 w;
@@ -88,7 +90,7 @@ __device__ __forceinline__ void fused_tile(const TensorDesc &d, const StreamPoin
     for (unsigned c = 0; c < 4; ++c) vl[c] = __builtin_fmaf(-lr_local, g[c], w[c]);
     if (kLocalFirst<SZ, FORM> && write_local) st4g<G, kStore>(wl, tid, rem_elems, vl);
 
-    const f4 agg = tile_sums<SZ, FORM, WAVES, kSlotTests<SZ, SPARSE> || MID, !MID>(words, own, sent, self, num_workers, t, lds);
+    const f4 agg = tile_sums<SZ, FORM, WAVES, kSlotTests<SZ, SPARSE> || MID, !MID, FEW ? kAllFirst : 0>(words, own, sent, self, num_workers, t, lds);
 #pragma unroll
     for (unsigned c = 0; c < 4; ++c) vg[c] = __builtin_fmaf(-scale, agg[c], w[c]);
     if (!kLocalFirst<SZ, FORM> && write_local) st4g<G, kStore>(wl, tid, rem_elems, vl);

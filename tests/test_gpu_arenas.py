@@ -146,3 +146,16 @@ def test_sparse_peers_equal_packed_ones(B, N, sizes, dtype, t):
 def test_sparse_peers_on_either_side_of_six_groups(B, N, tiles, dtype, t):
     for more in (0, 1):
         test_sparse_peers_equal_packed_ones(B, N, [tiles * 1024 - 4096 - 1, 4096 + more], dtype, t)
+
+
+# up to 8 workers, a limit of at most half the list's tiles: a kernel of its own (56 tiles: 14 chunks)
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("N,t", [(1, 0.5), (2, 0.3), (4, 0.5), (4, 0.3), (5, 0.3), (8, 0.5), (8, 0.3)])
+def test_few_groups_walk_the_list(B, N, t, dtype):
+    limited, b, _, _, check = _pair(B, [40 * 1024 - 3, 1, 8192 + 5], N, N // 2, t, dtype)
+    for limit in (1, 3, 28, 29):
+        limited.set_max_workgroups(limit)
+        for plan in (limited, b):
+            plan.step(1, 4, t, 0.4, 0.7)
+            plan.step_global(3, 4, t, 0.7)
+        check("N=%d limit=%d" % (N, limit))

@@ -6,7 +6,7 @@ import re
 from paper_2106_10796_amd import build
 
 COUNT, CHAIN, TINY = 0, 1, 2
-LATE, OUT, NT_WORDS, ARENA, SIX = 1, 2, 4, 8, 32
+LATE, OUT, NT_WORDS, ARENA, SIX, FEW = 1, 2, 4, 8, 32, 64
 TYPES, F32 = (0, 1, 2), (0,)
 ANY = 0
 
@@ -34,6 +34,8 @@ def test_passes_over_a_plan():
     add(ANY, 4, (CHAIN,), TYPES, (0,), (NT_WORDS,))
     add(8, 1, both, TYPES, (0,), (0, ARENA))
     add(8, 4, both, TYPES, (0,), (0, ARENA))
+    add(8, 4, (COUNT,), F32, (0,), (FEW,))
+    add(8, 4, (CHAIN,), TYPES, (0,), (FEW,))
     add(16, 4, both, TYPES, (0,), (0, OUT, ARENA, OUT | ARENA))
     add(16, 4, (CHAIN,), TYPES, (0,), (OUT | LATE, OUT | LATE | ARENA))
     add(16, 4, (COUNT,), F32, (0,), (OUT | LATE, OUT | LATE | ARENA))
